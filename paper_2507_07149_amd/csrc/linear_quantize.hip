@@ -22,9 +22,8 @@ namespace {
 
 constexpr int kLinThreads = 512;             // 8 waves: 4 along m x 2 along n
 constexpr int kBM = 256, kBN = 256, kBK = 64;
-constexpr int kPitch = kBK * 2 + 16;         // bytes per staged row: 16-byte reads of 32 consecutive rows hit distinct banks
-constexpr int kOperandBytes = 256 * kPitch;
-constexpr int kStageBytes = 2 * kOperandBytes;
+constexpr int kRowBytes = kBK * 2;           // bytes of a staged row: one cache line
+constexpr int kOperandBytes = 256 * kRowBytes;
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -93,30 +92,43 @@ __host__ __device__ inline TileIndex tile_of_workgroup(int id, int tiles_m, int 
   return t;
 }
 
-// A thread's share of one step's tiles: four 16-byte pieces of W and four of x (rows 64 apart).
-struct Staged {
-  u32x4 w0, w1, w2, w3, x0, x1, x2, x3;
-};
-__device__ __forceinline__ void fetch(Staged& st, const char* gx, const char* gw, int64_t rows64, int step) {
-  const int64_t k_off = (int64_t)step * (kBK * 2);
-  st.w0 = *reinterpret_cast<const u32x4*>(gw + k_off);
-  st.x0 = *reinterpret_cast<const u32x4*>(gx + k_off);
-  st.w1 = *reinterpret_cast<const u32x4*>(gw + rows64 + k_off);
-  st.x1 = *reinterpret_cast<const u32x4*>(gx + rows64 + k_off);
-  st.w2 = *reinterpret_cast<const u32x4*>(gw + 2 * rows64 + k_off);
-  st.x2 = *reinterpret_cast<const u32x4*>(gx + 2 * rows64 + k_off);
-  st.w3 = *reinterpret_cast<const u32x4*>(gw + 3 * rows64 + k_off);
-  st.x3 = *reinterpret_cast<const u32x4*>(gx + 3 * rows64 + k_off);
+// Main loop.  The product is bound by feeding the compute units: 64 KB of operands per workgroup and step
+// of 64 k, against 2048 cycles of matrix instructions.  What was measured on 32768 x 11008 x 4096 (the
+// product alone, bfloat16; the chip holds about 1.6 GHz under this load):
+//   1105 TFLOP/s  tiles loaded into registers, written to LDS a step later, one barrier per step
+//   1200          loads straight into LDS, ring of four slots of 32 k (rows of 64 bytes)
+//   1230          the same, the loads spread between the matrix instructions (issued in one run behind
+//                 the barrier they hold up the wave while the matrix cores idle)
+//   1340          rows of 128 bytes, whole cache lines, instead of 64
+//   1500          without any loads in the loop (results meaningless: the ceiling of this structure)
+// A step's tile is consumed in four phases, one per 32 rows of W (part nb), and x's rows belong to two parts
+// (mb).  The operands of a phase are read from LDS one phase ahead, x's one step ahead, so that a part of a
+// copy is free again long before its step has ended and the next loads into it start 2 to 3 halves
+// before they are waited for:
+//   half 0 (parts 0, 1) reads W1 W2 of s, x0 of s + 1;  loads x1 W0 of s + 2, W3 of s + 1
+//   half 1 (parts 2, 3) reads W3 of s, W0 x1 of s + 1;  loads W1 W2 of s + 2, x0 of s + 3
+// Every part is overwritten only in a half after the one that read it (the barrier between the halves follows a
+// wait for the reads), and is read only after the barrier behind "all but the last eight loads have
+// landed": the loads of two halves stay in flight, four per wave and half.
+//
+// Rows of 128 bytes are stored unpadded (a load writes 1 KB of consecutive LDS) with the 16-byte piece p
+// of row r at place p ^ (r / 2 mod 8): no bank conflicts in the counters.
+
+// 64 lanes x 16 bytes from memory straight into LDS: lane l reads base + lane_off and writes LDS byte lds_base + 16 l.
+// Written in assembly because the compiler, which cannot tell the parts of the copies apart, would drain
+// all such loads in front of every LDS read; the counted waits of the main loop take that place.  (The load
+// has no register result; M0 holds the LDS address and needs one wait state after its write.)
+__device__ __forceinline__ void load_to_lds(uint32_t lds_base, uint32_t lane_off, const char* base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(lds_base), "v"(lane_off), "s"(base)
+               : "memory");
 }
-__device__ __forceinline__ void stash(const Staged& st, char* base) {
-  *reinterpret_cast<u32x4*>(base) = st.w0;
-  *reinterpret_cast<u32x4*>(base + 64 * kPitch) = st.w1;
-  *reinterpret_cast<u32x4*>(base + 128 * kPitch) = st.w2;
-  *reinterpret_cast<u32x4*>(base + 192 * kPitch) = st.w3;
-  *reinterpret_cast<u32x4*>(base + kOperandBytes) = st.x0;
-  *reinterpret_cast<u32x4*>(base + kOperandBytes + 64 * kPitch) = st.x1;
-  *reinterpret_cast<u32x4*>(base + kOperandBytes + 128 * kPitch) = st.x2;
-  *reinterpret_cast<u32x4*>(base + kOperandBytes + 192 * kPitch) = st.x3;
+__device__ __forceinline__ const char* uniform_pointer(const char* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
 }
 
 template <int DT, int GS_LOG2, bool MIXED, bool QUANT>
@@ -124,7 +136,7 @@ __global__ __launch_bounds__(kLinThreads, 2) void k_linear_quantize_pack(
     const char* __restrict__ x, const char* __restrict__ w, int M, int N, int K, uint32_t seed_lo, uint32_t seed_hi,
     uint32_t uniform_b, const uint8_t* __restrict__ bits, const uint32_t* __restrict__ off, char* __restrict__ y,
     uint32_t* __restrict__ words, float* __restrict__ out_min, float* __restrict__ out_scale) {
-  __shared__ __align__(16) char lds[2 * kStageBytes];
+  __shared__ __align__(1024) char lds[4 * kOperandBytes];      // W of even and odd steps, x of even and odd steps
   const int t = threadIdx.x, lane = t & (kWave - 1), wave = t >> 6;
   const int wm = wave & 3, wn = wave >> 2;
   const int li = lane & 31, lg = lane >> 5;
@@ -139,12 +151,6 @@ __global__ __launch_bounds__(kLinThreads, 2) void k_linear_quantize_pack(
   const int tm = ti.m, tn = ti.n;
   const int64_t m0 = (int64_t)tm * kBM, n0 = (int64_t)tn * kBN;
 
-  // Staging: 2048 16-byte pieces per operand and step of 64 k, four per thread: rows crow + 64 j.
-  const int crow = t >> 3, ccol = t & 7;
-  const char* gx = x + ((m0 + crow) * K + ccol * 8) * 2;
-  const char* gw = w + ((n0 + crow) * K + ccol * 8) * 2;
-  const int64_t rows64 = (int64_t)64 * K * 2;
-  const int stash_off = crow * kPitch + ccol * 16;
   f32x16 acc[2][4];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -153,35 +159,113 @@ __global__ __launch_bounds__(kLinThreads, 2) void k_linear_quantize_pack(
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-  // Step s computes on copy s % 2 of the staged tiles while the registers that hold step s + 1 are
-  // written to the other copy and the loads of step s + 2 are issued: one barrier per step.  Past
-  // the end the last step is fetched and staged again (unused), which keeps the loop free of
-  // branches around the loads.
   const int steps = K / kBK;
-  Staged st;
-  fetch(st, gx, gw, rows64, 0);
-  stash(st, lds + stash_off);
-  fetch(st, gx, gw, rows64, steps > 1 ? 1 : 0);
-  const int a_off = (wn * 128 + li) * kPitch + lg * 16;
-  const int b_off = kOperandBytes + (wm * 64 + li) * kPitch + lg * 16;
-  for (int s = 0; s < steps; ++s) {
-    __syncthreads();                       // copy s % 2 is complete; nobody reads the other copy any more
-    stash(st, lds + ((s + 1) & 1) * kStageBytes + stash_off);
-    fetch(st, gx, gw, rows64, s + 2 < steps ? s + 2 : steps - 1);
-    const char* base = lds + (s & 1) * kStageBytes;
+  const int64_t row_bytes = (int64_t)K * 2;
+  const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)lds);
+  const int uw = __builtin_amdgcn_readfirstlane(wave);
+
+  // What a wave loads: of part nb of W (rows 32 nb ... of either half) eight rows, of part mb of x
+  // (rows 32 mb ... of each quarter) two times eight.
+  const int w_row = (uw >> 2) * 128 + (uw & 3) * 8, x_row = (uw >> 1) * 64 + (uw & 1) * 16;
+  const int l_row = lane >> 3;
+  const uint32_t l_off = (uint32_t)(l_row * row_bytes);
+  const uint32_t piece = (uint32_t)((lane & 7) ^ (l_row >> 1));          // rows 0..7 of sixteen
+  const uint32_t off_even = l_off + (piece << 4), off_odd = l_off + ((piece ^ 4u) << 4);
+  const uint32_t off_w = (uw & 1) ? off_odd : off_even;
+  const char *src_w[4], *src_x[2][2];
 #pragma unroll
-    for (int ks = 0; ks < kBK / 16; ++ks) {
-      u32x4 a[4], b[2];
+  for (int i = 0; i < 4; ++i) src_w[i] = uniform_pointer(w + (n0 + w_row + 32 * i) * row_bytes);
 #pragma unroll
-      for (int nb = 0; nb < 4; ++nb) a[nb] = *reinterpret_cast<const u32x4*>(base + a_off + nb * 32 * kPitch + ks * 32);
+  for (int i = 0; i < 4; ++i) src_x[i >> 1][i & 1] = uniform_pointer(x + (m0 + x_row + 32 * (i >> 1) + 8 * (i & 1)) * row_bytes);
+  const uint32_t dst_w = lds0 + (uint32_t)w_row * kRowBytes, dst_x = lds0 + 2 * kOperandBytes + (uint32_t)x_row * kRowBytes;
+  // Part nb of W of step `s`.  Past the end the last step again (never used): the loop has no branches around loads.
+  auto fetch_w = [&](int nb, int s) {
+    load_to_lds(dst_w + (uint32_t)((s & 1) * kOperandBytes + nb * 32 * kRowBytes), off_w, src_w[nb]);
+    src_w[nb] += s + 1 < steps ? kRowBytes : 0;
+  };
+  auto fetch_x = [&](int mb, int j, int s) {
+    load_to_lds(dst_x + (uint32_t)((s & 1) * kOperandBytes + (mb * 32 + j * 8) * kRowBytes), j ? off_odd : off_even,
+                src_x[mb][j]);
+    src_x[mb][j] += s + 1 < steps ? kRowBytes : 0;
+  };
+
+  // Operand reads: lane li of a block reads the 16-byte piece 2 ks + lg of row li, found at piece ^ (row / 2 mod 8).
+  const char *pa[4], *pb[4];
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb) b[mb] = *reinterpret_cast<const u32x4*>(base + b_off + mb * 32 * kPitch + ks * 32);
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = mfma16<DT>(a[nb], b[mb], acc[mb][nb]);
-    }
+  for (int ks = 0; ks < 4; ++ks) {
+    const int col = ((2 * ks + lg) ^ ((li >> 1) & 7)) << 4;
+    pa[ks] = lds + (wn * 128 + li) * kRowBytes + col;
+    pb[ks] = lds + 2 * kOperandBytes + (wm * 64 + li) * kRowBytes + col;
   }
+  auto read_a = [&](int nb, int ks, int parity) {
+    return *reinterpret_cast<const u32x4*>(pa[ks] + parity * kOperandBytes + nb * 32 * kRowBytes);
+  };
+  auto read_b = [&](int mb, int ks, int parity) {
+    return *reinterpret_cast<const u32x4*>(pb[ks] + parity * kOperandBytes + mb * 32 * kRowBytes);
+  };
+
+  u32x4 a[2][4], b[2][2][4];                 // a[nb % 2][ks], b[step % 2][mb][ks]
+  fetch_x(0, 0, 0); fetch_x(0, 1, 0); fetch_x(1, 0, 0); fetch_x(1, 1, 0); fetch_w(0, 0);
+  fetch_w(1, 0); fetch_w(2, 0); fetch_x(0, 0, 1); fetch_x(0, 1, 1);
+  fetch_x(1, 0, 1); fetch_x(1, 1, 1); fetch_w(0, 1); fetch_w(3, 0);
+  asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    b[0][0][ks] = read_b(0, ks, 0);
+    b[0][1][ks] = read_b(1, ks, 0);
+    a[0][ks] = read_a(0, ks, 0);
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  fetch_w(1, 1); fetch_w(2, 1); fetch_x(0, 0, 2); fetch_x(0, 1, 2);
+  asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+
+  // One step on the copies of parity P; two halves of sixteen matrix instructions, a barrier behind each.
+  auto step = [&](auto parity, int s) {
+    constexpr int P = decltype(parity)::value;
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {                              // k pieces 2h and 2h + 1 of part nb
+        acc[0][nb] = mfma16<DT>(a[nb & 1][2 * h], b[P][0][2 * h], acc[0][nb]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (nb == 0) fetch_x(1, h, s + 2);
+        else if (nb == 1) { if (h == 0) fetch_w(0, s + 2); else fetch_w(3, s + 1); }
+        else if (nb == 2) fetch_w(1 + h, s + 2);
+        else fetch_x(0, h, s + 3);
+        __builtin_amdgcn_sched_barrier(0);
+        a[(nb + 1) & 1][2 * h] = nb < 3 ? read_a(nb + 1, 2 * h, P) : read_a(0, 2 * h, P ^ 1);
+        a[(nb + 1) & 1][2 * h + 1] = nb < 3 ? read_a(nb + 1, 2 * h + 1, P) : read_a(0, 2 * h + 1, P ^ 1);
+        b[P ^ 1][nb >> 1][2 * (nb & 1) + h] = read_b(nb >> 1, 2 * (nb & 1) + h, P ^ 1);
+        acc[1][nb] = mfma16<DT>(a[nb & 1][2 * h], b[P][1][2 * h], acc[1][nb]);
+        acc[0][nb] = mfma16<DT>(a[nb & 1][2 * h + 1], b[P][0][2 * h + 1], acc[0][nb]);
+        acc[1][nb] = mfma16<DT>(a[nb & 1][2 * h + 1], b[P][1][2 * h + 1], acc[1][nb]);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (nb & 1) {
+        asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      }
+    }
+  };
+  int s = 0;
+  for (; s + 1 < steps; s += 2) {
+    step(std::integral_constant<int, 0>{}, s);
+    step(std::integral_constant<int, 1>{}, s + 1);
+  }
+  if (s < steps) step(std::integral_constant<int, 0>{}, s);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
   // ---- epilogue.  Register r of a 32 x 32 block: n = 8*(r/4) + 4*(lane/32) + r%4, m = lane%32. ----
   constexpr int kGs = 1 << GS_LOG2, kBlocksPerGroup = kGs / 32, kGroups = 4 / kBlocksPerGroup;
@@ -215,14 +299,17 @@ __global__ __launch_bounds__(kLinThreads, 2) void k_linear_quantize_pack(
       char* dst = y + (m * N + n_lane + nb * 32) * 2;
       *reinterpret_cast<u32x4*>(dst) = u32x4{yv[0], yv[1], yv[2], yv[3]};
       *reinterpret_cast<u32x4*>(dst + 16) = u32x4{yv[4], yv[5], yv[6], yv[7]};
-      float mn = 0.0f, mx = 0.0f;
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const uint32_t pair = yv[e >> 1];
-        const float v = widen16<DT>((e & 1) ? (pair >> 16) : (pair & 0xFFFFu));
-        xf[nb][e] = v;
-        mn = e == 0 ? v : vmin(mn, v);
-        mx = e == 0 ? v : vmax(mx, v);
+        xf[nb][e] = DT == kBF16 ? u2f((e & 1) ? (pair & 0xFFFF0000u) : (pair << 16))
+                                : widen16<DT>((e & 1) ? (pair >> 16) : (pair & 0xFFFFu));
+      }
+      float mn = vmin(xf[nb][0], xf[nb][1]), mx = vmax(xf[nb][0], xf[nb][1]);
+#pragma unroll
+      for (int e = 2; e < 16; e += 2) {
+        mn = vmin3(mn, xf[nb][e], xf[nb][e + 1]);
+        mx = vmax3(mx, xf[nb][e], xf[nb][e + 1]);
       }
       bmn[nb] = mn;
       bmx[nb] = mx;
@@ -248,7 +335,7 @@ __global__ __launch_bounds__(kLinThreads, 2) void k_linear_quantize_pack(
       }
       const float invs = gs.inv * kScale;
       const bool exact2 = !(invs <= 3.402823466e+38f);          // the factor 256 is then applied to the rounded product
-      const float mult = exact2 ? gs.inv : invs;
+      const bool any_exact2 = __builtin_amdgcn_ballot_w64(exact2) != 0ull;      // rare: a branch of the whole wave
 #pragma unroll
       for (int q = 0; q < kBlocksPerGroup; ++q) {
         const int nb = gi * kBlocksPerGroup + q;
@@ -256,23 +343,27 @@ __global__ __launch_bounds__(kLinThreads, 2) void k_linear_quantize_pack(
         const uint4 rnd4 = philox_block((uint64_t)((m * N + n_lane + nb * 32) >> 4), seed_lo, seed_hi);
         const uint32_t rnd[4] = {rnd4.x, rnd4.y, rnd4.z, rnd4.w};
         uint32_t p[4];
+        auto codes = [&](auto two_products, float mult) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          uint32_t nacc = 0u;
+          for (int c = 0; c < 4; ++c) {
+            uint32_t nacc = 0u;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            float wv = (gs.mn - xf[nb][4 * c + e]) * mult;
-            const float wv2 = wv * kScale;
-            wv = exact2 ? wv2 : wv;
-            const int nc = (round_half_up_to_int(wv) + (int)((rnd[c] >> (8 * e)) & 0xFFu)) >> 8;
-            nacc = (nacc << b) + (uint32_t)nc;
+            for (int e = 0; e < 4; ++e)
+              nacc = (nacc << b) + (uint32_t)neg_code<decltype(two_products)::value>(xf[nb][4 * c + e], gs.mn, mult,
+                                                                                       (rnd[c] >> (8 * e)) & 0xFFu);
+            p[c] = 0u - nacc;                                    // four codes, first element most significant
           }
-          p[c] = 0u - nacc;                                      // four codes, first element most significant
+        };
+        if (any_exact2) {
+          // lanes that do not need it multiply by 256 afterwards too: a power of two, the same product
+          codes(std::true_type{}, gs.inv);
+        } else {
+          codes(std::false_type{}, invs);
         }
         uint32_t* dst = words + woff;
         if (b == 8u) {
-#pragma unroll
-          for (int c = 0; c < 4; ++c) dst[(e0 >> 2) + c] = p[c];
+          typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+          *reinterpret_cast<u32x4_any*>(dst + (e0 >> 2)) = u32x4_any{p[0], p[1], p[2], p[3]};
         } else if (b == 4u) {
           dst[(e0 >> 3)] = (p[0] << 16) | (p[1] & 0xFFFFu);
           dst[(e0 >> 3) + 1] = (p[2] << 16) | (p[3] & 0xFFFFu);

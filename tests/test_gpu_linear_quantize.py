@@ -88,6 +88,30 @@ def test_linear_quantize_pack_shapes(env, shape):
     assert np.array_equal(sc.view(np.uint32), osc.view(np.uint32))
 
 
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5, 6, 7])
+@pytest.mark.parametrize("tiny", [False, True])
+def test_linear_quantize_pack_every_remainder_of_the_step_pipeline(env, steps, tiny):
+    """Steps of 64 along k are fetched up to three ahead and taken in pairs: every count up to beyond the
+    pipeline's depth, odd and even.  Every k and row has its own operand values (a step, row or piece
+    taken twice or left out changes y).  `tiny`: ranges so small that 256 times their reciprocal overflows
+    binary32 in some groups and not in others (the second form of the element map)."""
+    daf, orc = env
+    M, N, K = 256, 512, 64 * steps
+    rng = np.random.default_rng(steps)
+    x, w = _integer_operands(rng, M, N, K, BF16)
+    if tiny:
+        w = (w.float() * torch.from_numpy(2.0 ** rng.integers(-119, -90, (N // 32, 1)).astype(np.float64)).float()
+             .repeat_interleave(32, 0)).to(torch.bfloat16)
+    b = _bits_for(rng, M * N // 32, "mixed")
+    print("case", steps, tiny, flush=True)
+    y, words, mn, sc = _run(daf, x, w, 32, b, 13)
+    oy = orc.linear_forward(to_numpy_bits(x), to_numpy_bits(w), M, K, N, BF16)
+    assert np.array_equal(to_numpy_bits(y).view(oy.dtype).reshape(-1), oy)
+    ow, omn, osc, _ = orc.quantize_pack(oy, BF16, 32, b, 13)
+    assert np.array_equal(words, ow) and np.array_equal(mn.view(np.uint32), omn.view(np.uint32))
+    assert np.array_equal(sc.view(np.uint32), osc.view(np.uint32))
+
+
 @pytest.mark.parametrize("dtype", [F16, BF16])
 def test_linear_quantize_pack_normal_operands(env, dtype):
     daf, orc = env
