@@ -15,11 +15,13 @@
 // such loads make one 8-element MFMA operand.  Rows are padded (stride = 64 bytes mod 256) so
 // that the four rows of a load fall on different banks.
 //
-// Work-group tile: 256 (n) x BK (k) outputs, BK = 256 on 8 waves, or 128 or 64 on 4 waves; 32
-// values of m per step.  A wave owns 64 (n) x 128 (k) (64 x 64 in the narrowest tile): 2 x 4
-// MFMA blocks of 32 x 32, 128 accumulator registers, two waves per SIMD.  The wide n keeps the
-// number of times a value of x is dequantized (once per tile of n) low; the wide k keeps the
-// number of times a row of grad_y is fetched low.  Two copies of the LDS tiles: while the
+// Two kernels.  Outputs of more than 256 rows with enough work (schedule) in a 16-bit format take
+// k_unpack_matmul_wide (unpack_matmul_wide.h), a tile of 512 x 128.  The others, and binary32, take
+// k_unpack_matmul below: a work-group tile of 256 (n) x BK (k) outputs, BK = 128 or 64 on 4 waves, for binary32
+// also 256 on 8 waves; 32 values of m per step (16 in binary32).  A wave owns 64 (n) x 128 (k) (64 x 64 in
+// the narrowest tile): 2 x 4 MFMA blocks of 32 x 32, 128 accumulator registers, two waves per SIMD.  The wide
+// n keeps the number of times a value of x is dequantized (once per tile of n) low; the wide k keeps
+// the number of times a row of grad_y is fetched low.  Two copies of the LDS tiles: while the
 // products read one, the next step's tiles are built in the other, next to the MFMA
 // instructions; one barrier per step.  Global loads run two steps ahead of their use; the
 // per-group constants are fetched once per work-group, six steps ahead, and passed through a
@@ -175,6 +177,38 @@ __device__ __forceinline__ void tile_of_position(uint32_t pos, uint32_t tiles_n,
   }
 }
 
+// What a work-group does.  The first `whole` work-groups take one tile each over all of m and write it
+// to `out`; the tiles after those are each taken by `slices` work-groups, one slice of m each, which write
+// their partial sums to `partial` as compact tiles [slice][tile - whole][256][BK].
+// Consecutive block ids go to different XCDs (each with its own L2).  Every XCD gets a
+// contiguous range of the tile sequence (tile_of_position): the tiles resident on an XCD at
+// one time are then a compact patch.  The steps of m are dealt out to the slices as evenly as whole
+// steps allow.
+struct TileShare {
+  uint32_t tn, tk;
+  bool sliced;
+  int steps, first_step;
+  int64_t partial_tile;
+};
+__device__ __forceinline__ TileShare share_of(uint32_t bid, uint32_t whole, int32_t slices, uint32_t tiles_n,
+                                              uint32_t tiles_k, int all_steps) {
+  TileShare sh;
+  sh.sliced = bid >= whole;
+  const uint32_t count = sh.sliced ? tiles_n * tiles_k - whole : whole;       // tiles of this kind
+  const uint32_t rel = sh.sliced ? bid - whole : bid;
+  const uint32_t slice = sh.sliced ? rel / count : 0u;
+  uint32_t ti = rel - slice * count;
+  const uint32_t xcd = ti & 7u, idx = ti >> 3;
+  const uint32_t base = count / 8u, rem = count & 7u;                         // XCD x owns base (+1 if x < rem) tiles
+  ti = xcd * base + (xcd < rem ? xcd : rem) + idx;
+  tile_of_position(sh.sliced ? whole + ti : ti, tiles_n, tiles_k, sh.tn, sh.tk);
+  const int per = sh.sliced ? all_steps / slices : all_steps, extra = sh.sliced ? all_steps % slices : 0;
+  sh.steps = per + ((int)slice < extra ? 1 : 0);
+  sh.first_step = (int)slice * per + ((int)slice < extra ? (int)slice : extra);
+  sh.partial_tile = (int64_t)slice * count + ti;
+  return sh;
+}
+
 template <int DT, bool MIXED, int BK, bool PARTIAL_N>
 __global__ __launch_bounds__((TileB<BK, (DT == kF32 ? 4 : 2)>::kThreads), (BK > 128 ? 1 : 2)) void k_unpack_matmul(
     const uint32_t* __restrict__ words, const float* __restrict__ mn, const float* __restrict__ scale,
@@ -193,37 +227,14 @@ __global__ __launch_bounds__((TileB<BK, (DT == kF32 ? 4 : 2)>::kThreads), (BK > 
   __shared__ uint4 meta[TB::kMetaRing][TB::kMetaEntries];
 
   const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
-  // The first `whole` work-groups take one tile each over all of m and write it to `out`; the
-  // tiles after those are each taken by `slices` work-groups, one slice of m each, which write
-  // their partial sums to `partial` as compact tiles [slice][tile - whole][256][BK].
-  // Consecutive block ids go to different XCDs (each with its own L2).  Give every XCD a
-  // contiguous range of the tile sequence (tile_of_position): the tiles resident on an XCD at
-  // one time are then a compact patch.
-  const uint32_t n_tiles = (uint32_t)tiles_n * (uint32_t)tiles_k;
-  const uint32_t bid = blockIdx.x;
-  const bool sliced = bid >= whole;
-  const uint32_t count = sliced ? n_tiles - whole : whole;       // tiles of this kind
-  const uint32_t rel = sliced ? bid - whole : bid;
-  const uint32_t slice = sliced ? rel / count : 0u;
-  uint32_t ti = rel - slice * count;
-  {
-    const uint32_t xcd = ti & 7u, idx = ti >> 3;
-    const uint32_t base = count / 8u, rem = count & 7u;          // XCD x owns base (+1 if x < rem) tiles
-    ti = xcd * base + (xcd < rem ? xcd : rem) + idx;
-  }
-  const uint32_t tile = sliced ? whole + ti : ti;
-  uint32_t tn, tk;
-  tile_of_position(tile, (uint32_t)tiles_n, (uint32_t)tiles_k, tn, tk);
-  const int64_t n0 = (int64_t)tn * kBN, k0 = (int64_t)tk * BK;
+  const TileShare share = share_of(blockIdx.x, whole, slices, (uint32_t)tiles_n, (uint32_t)tiles_k, (int)(M / kBM));
+  const int64_t n0 = (int64_t)share.tn * kBN, k0 = (int64_t)share.tk * BK;
   // The last tile of n may reach past the output (N is a multiple of 64, not of 256): the waves
   // whose 64 columns lie outside take part in the loads and the tile construction but run no
   // products and store nothing; the chunks of grad_y outside are read from column 0 instead.
   const uint32_t n_valid = PARTIAL_N ? (uint32_t)((N - n0) < kBN ? (N - n0) : kBN) : (uint32_t)kBN;
-  // The steps of m are dealt out to the slices as evenly as whole steps allow.
-  const int all_steps = (int)(M / kBM);
-  const int per = sliced ? all_steps / slices : all_steps, extra = sliced ? all_steps % slices : 0;
-  const int steps = per + ((int)slice < extra ? 1 : 0);
-  const int64_t m_begin = ((int64_t)slice * per + ((int)slice < extra ? (int)slice : extra)) * kBM;
+  const int steps = share.steps;
+  const int64_t m_begin = (int64_t)share.first_step * kBM;
 
   // Loader roles.  grad_y: thread (cg, rq) owns rows kR*rq .. kR*rq+kR-1 of the step and columns
   // 16 bytes of the 256 columns.  x: thread (co, xr) owns columns 8*co .. 8*co+7 of the BK in row
@@ -491,8 +502,8 @@ __global__ __launch_bounds__((TileB<BK, (DT == kF32 ? 4 : 2)>::kThreads), (BK > 
   if (base < steps) do_step(Index<0>{}, st[1], ad[1], ad[0], base, at);
 
   // ---- epilogue: register r of a 32 x 32 block is row 8*(r/4) + 4*(lane/32) + r%4, column lane%32 ----
-  float* dst = sliced ? partial + ((int64_t)slice * count + ti) * (int64_t)(kBN * BK) : out + n0 * K + k0;
-  const int64_t ld = sliced ? BK : K;
+  float* dst = share.sliced ? partial + share.partial_tile * (int64_t)(kBN * BK) : out + n0 * K + k0;
+  const int64_t ld = share.sliced ? BK : K;
   if (!wave_valid) return;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -506,6 +517,12 @@ __global__ __launch_bounds__((TileB<BK, (DT == kF32 ? 4 : 2)>::kThreads), (BK > 
       }
 }
 
+}  // namespace
+
+#include "unpack_matmul_wide.h"
+
+namespace {
+
 // The sliced tiles: out[tile] = sum over the slices of partial[slice][tile - whole]; one
 // work-group per 256 x 16 strip of a tile (bk4 = BK / 4 float4 per row).  A launch adds n
 // slices that lie `stride` slices apart, starting at slice blockIdx.y * n * stride, and writes
@@ -515,17 +532,17 @@ __global__ __launch_bounds__((TileB<BK, (DT == kF32 ? 4 : 2)>::kThreads), (BK > 
 template <bool TO_OUT>
 __global__ __launch_bounds__(256) void k_sum_slices(float4* __restrict__ partial, uint32_t whole, uint32_t count,
                                                     int32_t slices, int32_t n, int32_t stride, uint32_t tiles_n,
-                                                    int32_t tiles_k,
+                                                    int32_t tiles_k, int32_t bn,
                                                     int32_t bk4, int64_t N, int64_t K, float* __restrict__ out) {
-  const uint32_t strips = (uint32_t)(kBN * bk4) / 256u;           // work-groups per tile
+  const uint32_t strips = (uint32_t)(bn * bk4) / 256u;           // work-groups per tile
   const uint32_t ti = blockIdx.x / strips;
   const uint32_t e = (blockIdx.x - ti * strips) * 256u + threadIdx.x;   // float4 index inside the tile
-  const int64_t tile4 = (int64_t)kBN * bk4;
+  const int64_t tile4 = (int64_t)bn * bk4;
   const uint32_t tile = whole + ti;
   uint32_t tn, tk;
   tile_of_position(tile, tiles_n, (uint32_t)tiles_k, tn, tk);
   const uint32_t row = e / (uint32_t)bk4, col4 = e - row * (uint32_t)bk4;
-  if ((int64_t)tn * kBN + row >= N) return;          // rows of the last tile of n past the output
+  if ((int64_t)tn * bn + row >= N) return;           // rows of the last tile of n past the output
   const int32_t first = (int32_t)blockIdx.y * n * stride;
   float4* p0 = partial + ((int64_t)first * count + ti) * tile4 + e;
   float4 s = *p0;
@@ -534,7 +551,7 @@ __global__ __launch_bounds__(256) void k_sum_slices(float4* __restrict__ partial
     s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
   }
   if (TO_OUT) {
-    float* dst = out + ((int64_t)tn * kBN + row) * K + (int64_t)tk * (bk4 * 4) + 4 * col4;
+    float* dst = out + ((int64_t)tn * bn + row) * K + (int64_t)tk * (bk4 * 4) + 4 * col4;
     *reinterpret_cast<float4*>(dst) = s;
   } else {
     *p0 = s;
@@ -547,17 +564,16 @@ __global__ __launch_bounds__(256) void k_sum_slices(float4* __restrict__ partial
 // step, the binary32 kernel 16); the slicing below counts m in units of 32.
 constexpr int kStepM = 32;
 
-// Width of the tile along k.  Each doubling halves the number of times a row of grad_y is
-// fetched; the 256-column tile (8 waves, one work-group per CU) is used when the output has
-// enough of them to fill the chip without slicing m, else the 128-column one (measured: LLM
-// shape 780 -> 860 TFLOP/s with 256 columns, ViT shape 0.30 against 0.29 ms).
-static int tile_bk(int64_t N, int64_t K) {
-  if (K % 256 == 0 && ((N + kBN - 1) / kBN) * (K / 256) >= 256) return 256;
+// Width of the 256-row tile along k.  Each doubling halves the number of times a row of grad_y is
+// fetched; binary32's 256-column tile (8 waves, one work-group per CU) is used when the output has
+// enough of them to fill the chip without slicing m, else the 128-column one.
+static int tile_bk(int64_t N, int64_t K, int es) {
+  if (es == 4 && K % 256 == 0 && ((N + kBN - 1) / kBN) * (K / 256) >= 256) return 256;
   return K % 128 == 0 ? 128 : 64;
 }
 
 // How the tiles are run.  Work-groups run in rounds of as many as fit on the chip (slots: 1 per
-// CU with the 256-column tile, 2 with the 128-column one, 3 with the 64-column one; 256 CUs).
+// CU with the 512 x 128 and the 256-column tile, 2 with the 128-column one, 3 with the 64-column one; 256 CUs).
 // The tiles of the whole rounds run over all of m; the tiles of a last, partly filled round
 // (all tiles, when there is less than one round) may be cut into `slices` slices of m (2 to 16,
 // more for outputs of a few tiles; of as equal a number of steps as possible) that run as work-groups of their own
@@ -566,20 +582,28 @@ static int tile_bk(int64_t N, int64_t K) {
 // choice by that estimate; the per-step times are measured ones.
 namespace {
 struct Schedule {
-  int bk;
+  int bn, bk;              // the tile; 512 x 128: k_unpack_matmul_wide
   int64_t tiles, whole;    // tiles in all; tiles that run over all of m
   int32_t slices;          // of each other tile (1: there is none)
 };
 Schedule schedule(int64_t M, int64_t N, int64_t K, int es) {   // es: bytes per element (2 or 4)
   Schedule sc;
-  sc.bk = tile_bk(N, K);
-  sc.tiles = ((N + kBN - 1) / kBN) * (K / sc.bk);
-  const int64_t slots = 256 * (sc.bk == 256 ? 1 : sc.bk == 128 ? 2 : 3);
+  // The 512 x 128 tile starts slower (a pipeline four steps deep to fill) and runs faster per step: start and now
+  // in microseconds, bf16, m x n x k: 32768 x 4096 x 11008 3216 / 2654, 8192 x 3072 x 768 72.6 / 60.8,
+  // 8192 x 768 x 768 35.6 / 31.6; below ten steps per compute unit the general kernel is ahead
+  // (4096 x 576 x 768, 6 steps: 22.3 against 24.6, 4096 x 1024 x 1024, 8 steps: equal).  Outputs of 256 and more such
+  // tiles take it for any m: the general kernel has nothing better there (128 x 4096 x 4096: 19.2 / 18.9).
+  const int64_t wide_tiles = ((N + Wide::kBN - 1) / Wide::kBN) * (K / Wide::kBK);
+  const bool wide = es == 2 && N > kBN && K % Wide::kBK == 0 && (wide_tiles >= 256 || wide_tiles * (M / kStepM) >= 10 * 256);
+  sc.bn = wide ? Wide::kBN : kBN;
+  sc.bk = wide ? Wide::kBK : tile_bk(N, K, es);
+  sc.tiles = ((N + sc.bn - 1) / sc.bn) * (K / sc.bk);
+  const int64_t slots = 256 * (wide || sc.bk == 256 ? 1 : sc.bk == 128 ? 2 : 3);
   const int64_t steps = M / kStepM;
   // one work-group over all of m, per 32 values of m: the 16-bit kernels are bound by instruction
   // issue, the binary32 kernel by its MFMAs (128 per wave of 64 cycles each)
-  const double t_all_m = (double)steps * (es == 4 ? 8.0e-6 : sc.bk == 256 ? 1.1e-6 : 1.25e-6);
-  const double tile_bytes = (double)kBN * sc.bk * 4.0;
+  const double t_all_m = (double)steps * (es == 4 ? 8.0e-6 : wide ? 0.95e-6 : 1.25e-6);
+  const double tile_bytes = (double)sc.bn * sc.bk * 4.0;
   sc.whole = sc.tiles;
   sc.slices = 1;
   double best_cost = (double)((sc.tiles + slots - 1) / slots) * t_all_m;
@@ -608,7 +632,7 @@ int64_t daf_unpack_matmul_workspace_size(int64_t M, int64_t N, int64_t K) {
   int64_t bytes = 0;
   for (int es = 2; es <= 4; es += 2) {
     const Schedule sc = schedule(M, N, K, es);
-    const int64_t b = sc.slices > 1 ? (int64_t)sc.slices * (sc.tiles - sc.whole) * kBN * sc.bk * 4 : 0;
+    const int64_t b = sc.slices > 1 ? (int64_t)sc.slices * (sc.tiles - sc.whole) * sc.bn * sc.bk * 4 : 0;
     bytes = b > bytes ? b : bytes;
   }
   return bytes;
@@ -627,7 +651,7 @@ hipError_t daf_launch_unpack_matmul(const daf_plan_t* p, const uint32_t* words, 
   const int64_t M = p->n / K;
   const Schedule sc = schedule(M, N, K, dtype == daf::kF32 ? 4 : 2);
   const int bk = sc.bk;
-  const int32_t tiles_n = (int32_t)((N + kBN - 1) / kBN), tiles_k = (int32_t)(K / bk);
+  const int32_t tiles_n = (int32_t)((N + sc.bn - 1) / sc.bn), tiles_k = (int32_t)(K / bk);
   const int64_t rest = sc.tiles - sc.whole;
   const unsigned blocks = (unsigned)(sc.whole + rest * sc.slices);
   const uint32_t whole = (uint32_t)sc.whole;
@@ -645,7 +669,14 @@ hipError_t daf_launch_unpack_matmul(const daf_plan_t* p, const uint32_t* words, 
   } while (0)
 #define DAF_LAUNCH_BK(DT, MIXED)                                                                                  \
   do {                                                                                                            \
-    if (bk == 256) DAF_LAUNCH(DT, MIXED, 256);                                                                    \
+    if (sc.bn == Wide::kBN) {                                                                                     \
+      if constexpr (DT != daf::kF32)                                                                              \
+        hipLaunchKernelGGL((k_unpack_matmul_wide<DT, MIXED>), dim3(blocks), dim3(Wide::kThreads), 0, stream, words, mn, \
+                           scale, d_bits, p->d_off, (uint32_t)p->uniform_bits, p->group_size, gy, M, N, K, tiles_n, \
+                           tiles_k, whole, slices, out, workspace);                                               \
+    } else if (bk == 256) {                                                                                       \
+      if constexpr (DT == daf::kF32) DAF_LAUNCH(DT, MIXED, 256);                                                  \
+    }                                                                                                             \
     else if (bk == 128) DAF_LAUNCH(DT, MIXED, 128);                                                               \
     else DAF_LAUNCH(DT, MIXED, 64);                                                                               \
   } while (0)
@@ -664,17 +695,17 @@ hipError_t daf_launch_unpack_matmul(const daf_plan_t* p, const uint32_t* words, 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || rest == 0) return e;
   const int32_t bk4 = bk / 4;
-  const unsigned rblocks = (unsigned)(rest * (kBN * bk4 / 256));
+  const unsigned rblocks = (unsigned)(rest * (sc.bn * bk4 / 256));
   float4* part = reinterpret_cast<float4*>(workspace);
   int32_t n = slices, stride = 1;
   if (slices > 16) {                                  // first level: every 16 slices into the first of them
     const unsigned chunks = (unsigned)((slices + 15) / 16);
     hipLaunchKernelGGL(k_sum_slices<false>, dim3(rblocks, chunks), dim3(256), 0, stream, part, whole, (uint32_t)rest,
-                       slices, 16, 1, (uint32_t)tiles_n, tiles_k, bk4, N, K, out);
+                       slices, 16, 1, (uint32_t)tiles_n, tiles_k, (int32_t)sc.bn, bk4, N, K, out);
     n = (int32_t)chunks;
     stride = 16;
   }
   hipLaunchKernelGGL(k_sum_slices<true>, dim3(rblocks, 1), dim3(256), 0, stream, part, whole, (uint32_t)rest, slices, n,
-                     stride, (uint32_t)tiles_n, tiles_k, bk4, N, K, out);
+                     stride, (uint32_t)tiles_n, tiles_k, (int32_t)sc.bn, bk4, N, K, out);
   return hipGetLastError();
 }

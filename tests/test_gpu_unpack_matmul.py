@@ -121,6 +121,40 @@ def test_grad_weight_wide_tile(env, case):
     assert ws == 0
 
 
+# 16-bit formats, 256 or more tiles of 512 x 128, or enough steps: the pipeline of 32 values of m per step is four deep and
+# unrolled by four, so every remainder; N with a last tile of n that is mostly outside the output, groups that do not
+# coincide with the 128 columns of a tile.
+@pytest.mark.parametrize("steps,N,K,gs,bits,dtype", [(4, 2112, 6912, 96, "mixed", BF16), (5, 2112, 6656, 6656, 2, F16),
+                                                     (6, 2560, 6912, 384, "mixed", F16), (7, 2112, 6912, 32, 8, BF16),
+                                                     (8, 2112, 6656, 64, "mixed", BF16), (9, 4160, 3840, 1920, 1, F16),
+                                                     (2561, 320, 128, 32, "mixed", BF16), (1283, 576, 128, 128, 4, F16)])
+def test_grad_weight_512_by_128_tile(env, steps, N, K, gs, bits, dtype):
+    daf, orc = env
+    print("case 512 x 128", steps, N, K, gs, bits, dtype, flush=True)
+    M = 32 * steps
+    g = torch.Generator().manual_seed(steps)
+    x = (torch.randn(M, K, generator=g) * (1 + torch.rand(M, 1, generator=g))).to(torch_dtype(dtype))
+    gy = (torch.randn(M, N, generator=g) * 0.5).to(torch_dtype(dtype))
+    b = _widths(M * K // gs, bits, steps)
+    ow, omn, osc, _ = orc.quantize_pack(to_numpy_bits(x), dtype, gs, b, steps)
+    xh = orc.widen(orc.unpack_dequantize(ow, omn, osc, b, M * K, gs, dtype)[0], dtype).reshape(M, K).astype(np.float64)
+    gd = gy.double().numpy()
+    plan = daf.daf_plan((M, K), gs, torch.from_numpy(b).cuda() if b.size > 1 else int(b[0]))
+    ws = torch.empty(max(daf.daf_unpack_matmul_workspace_bytes(plan, N, K), 16), dtype=torch.uint8, device="cuda:0")
+    out = torch.full((N, K), float("nan"), device="cuda:0")
+    daf.daf_unpack_matmul_grad_weight(plan, torch.from_numpy(ow.view(np.int32)).cuda(), torch.from_numpy(omn).cuda(),
+                                      torch.from_numpy(osc).cuda(), gy.cuda(), out, ws)
+    torch.cuda.synchronize()
+    bound = 2.0 * M * 2.0 ** -24 * (np.abs(gd).T @ np.abs(xh)) + 1e-30
+    assert np.all(np.abs(out.cpu().numpy() - gd.T @ xh) <= bound)
+    plan.destroy()
+
+
+def _widths(G, bits, seed):
+    return (np.random.default_rng(seed).choice([1, 2, 4, 8], G).astype(np.uint8) if bits == "mixed"
+            else np.array([bits], np.uint8))
+
+
 # One tile more than whole rounds of work-groups (256, 512 or 768 per round for the 256-, 128- and
 # 64-column tile): the tiles of the last round are cut into slices of m, the others are not.
 @pytest.mark.timeout(300)
