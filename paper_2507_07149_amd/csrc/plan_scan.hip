@@ -2,8 +2,10 @@
 //
 // The packed buffer concatenates the groups' codes (paper Sec. 3.3 speaks of packing the
 // compressed values together); with a bit width per group the position of group g is the
-// sum of the word counts of all groups before it.  Three small kernels: per-block sums, a
-// single-block scan of those sums, and a per-block rescan that writes the offsets.
+// sum of the word counts of all groups before it.  Up to kOneGroups groups one workgroup does it in one launch;
+// up to kMaxSummedBlocks blocks of 2048 groups, per-block sums and a second launch in which every
+// block adds up the sums before its own and writes its offsets (5.6 M groups: 27 -> 23 us with the launch between
+// the two gone, 197 K: 11.6 -> 9.4); beyond that a single-block scan of the sums comes between them.
 #include "daf_device.h"
 #include "daf_internal.h"
 
@@ -40,7 +42,21 @@ __device__ __forceinline__ void load_widths(const uint8_t* __restrict__ bits, in
   }
 }
 
-// Sum over a block; result valid in thread 0.
+__device__ __forceinline__ void store_widths(uint8_t* __restrict__ plan_bits, int64_t base, int64_t num_groups,
+                                             const uint32_t (&b)[kItems]) {
+  if (base + kItems <= num_groups && (reinterpret_cast<uintptr_t>(plan_bits) & 7u) == 0u) {
+    uint2 v;
+    v.x = b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24);
+    v.y = b[4] | (b[5] << 8) | (b[6] << 16) | (b[7] << 24);
+    *reinterpret_cast<uint2*>(plan_bits + base) = v;
+  } else {
+#pragma unroll
+    for (int i = 0; i < kItems; ++i)
+      if (base + i < num_groups) plan_bits[base + i] = (uint8_t)b[i];
+  }
+}
+
+// Sum over a block, in every thread.
 __device__ __forceinline__ unsigned long long block_sum(unsigned long long v, unsigned long long* lds) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   const int wave = threadIdx.x >> 6;
@@ -74,16 +90,7 @@ __global__ __launch_bounds__(kThreads) void k_plan_block_sums(const uint8_t* __r
       s += group_words(b[i], g, num_groups, n, gs, &bad_here);
     }
   }
-  if (base + kItems <= num_groups && (reinterpret_cast<uintptr_t>(plan_bits) & 7u) == 0u) {
-    uint2 v;
-    v.x = b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24);
-    v.y = b[4] | (b[5] << 8) | (b[6] << 16) | (b[7] << 24);
-    *reinterpret_cast<uint2*>(plan_bits + base) = v;
-  } else {
-#pragma unroll
-    for (int i = 0; i < kItems; ++i)
-      if (base + i < num_groups) plan_bits[base + i] = (uint8_t)b[i];
-  }
+  store_widths(plan_bits, base, num_groups, b);
   const int any_bad = __syncthreads_or(bad);
   const unsigned long long tot = block_sum(s, lds);      // far below 2^63
   if (threadIdx.x == 0) block_sums[blockIdx.x] = tot | (any_bad ? kBadBit : 0ull);
@@ -129,40 +136,16 @@ __global__ __launch_bounds__(kThreads) void k_plan_scan_block_sums(unsigned long
   if (threadIdx.x == kThreads - 1) *total = acc;
 }
 
-// Offsets are kept modulo 2^32 (a plan whose total reaches 2^32 words is rejected from the 64-bit
-// total, and its offsets are never used), so the scan inside a block runs on 32-bit values: a
-// DPP scan inside each wave, the wave totals through LDS.
-__global__ __launch_bounds__(kThreads) void k_plan_write_offsets(const uint8_t* __restrict__ bits,
-                                                                 int64_t num_groups, int64_t n, int32_t gs,
-                                                                 const unsigned long long* __restrict__ block_off,
-                                                                 uint32_t* __restrict__ off) {
-  __shared__ uint32_t wave_tot[kThreads / daf::kWave];
-  const int64_t base = (int64_t)blockIdx.x * kBlockGroups + (int64_t)threadIdx.x * kItems;
-  uint32_t b[kItems], w[kItems];
-  load_widths(bits, base, num_groups, b);
-  uint32_t s = 0;
-  int bad = 0;
-#pragma unroll
-  for (int i = 0; i < kItems; ++i) {
-    const int64_t g = base + i;
-    w[i] = (g < num_groups) ? group_words(b[i], g, num_groups, n, gs, &bad) : 0u;
-    s += w[i];
-  }
-  const int lane = threadIdx.x & (daf::kWave - 1), wave = threadIdx.x >> 6;
-  const uint32_t incl = daf::wave_inclusive_sum(s);
-  if (lane == daf::kWave - 1) wave_tot[wave] = incl;
-  __syncthreads();
-  uint32_t before = 0u;
-#pragma unroll
-  for (int v = 0; v < kThreads / daf::kWave; ++v) before += (v < wave) ? wave_tot[v] : 0u;
-  uint32_t run = (uint32_t)block_off[blockIdx.x] + before + incl - s;   // offset of this thread's first group
+// A thread's kItems consecutive offsets from `run` on; whole runs leave in 16-byte stores.
+__device__ __forceinline__ void store_offsets(uint32_t* __restrict__ off, int64_t base, int64_t num_groups, uint32_t run,
+                                              const uint32_t (&w)[kItems]) {
   uint32_t o[kItems];
 #pragma unroll
   for (int i = 0; i < kItems; ++i) {
     o[i] = run;
     run += w[i];
   }
-  if (base + kItems <= num_groups) {                     // two 16-byte stores
+  if (base + kItems <= num_groups) {
     *reinterpret_cast<uint4*>(off + base) = make_uint4(o[0], o[1], o[2], o[3]);
     *reinterpret_cast<uint4*>(off + base + 4) = make_uint4(o[4], o[5], o[6], o[7]);
   } else {
@@ -172,6 +155,119 @@ __global__ __launch_bounds__(kThreads) void k_plan_write_offsets(const uint8_t* 
   }
 }
 
+// Offsets are kept modulo 2^32 (a plan whose total reaches 2^32 words is rejected from the 64-bit
+// total, and its offsets are never used), so the scan inside a block runs on 32-bit values: a
+// DPP scan inside each wave, the wave totals through LDS.
+// SCANNED: block_sums holds running sums (k_plan_scan_block_sums, which also wrote the total).  Otherwise
+// every block adds up the sums before its own, and the last one writes the total and the flag.
+template <bool SCANNED>
+__global__ __launch_bounds__(kThreads) void k_plan_write_offsets(const uint8_t* __restrict__ bits,
+                                                                 int64_t num_groups, int64_t n, int32_t gs,
+                                                                 const unsigned long long* __restrict__ block_sums,
+                                                                 uint32_t* __restrict__ off,
+                                                                 unsigned long long* __restrict__ total,
+                                                                 int* __restrict__ bad_flag) {
+  __shared__ uint32_t wave_tot[kThreads / daf::kWave];
+  __shared__ unsigned long long lds[4];
+  const int64_t base = (int64_t)blockIdx.x * kBlockGroups + (int64_t)threadIdx.x * kItems;
+  uint32_t b[kItems], w[kItems];
+  load_widths(bits, base, num_groups, b);
+  uint32_t block_off;
+  if (SCANNED) {
+    block_off = (uint32_t)block_sums[blockIdx.x];
+  } else {
+    unsigned long long sum = 0;
+    int bad = 0;
+    for (int64_t i = threadIdx.x; i < (int64_t)blockIdx.x; i += kThreads) {
+      const unsigned long long v = block_sums[i];
+      bad |= (v & kBadBit) ? 1 : 0;
+      sum += v & ~kBadBit;
+    }
+    sum = block_sum(sum, lds);
+    block_off = (uint32_t)sum;
+    if (blockIdx.x == gridDim.x - 1) {
+      const int any_bad = __syncthreads_or(bad);
+      const unsigned long long own = block_sums[blockIdx.x];
+      if (threadIdx.x == 0) {
+        *total = sum + (own & ~kBadBit);
+        *bad_flag = (any_bad || (own & kBadBit)) ? 1 : 0;
+      }
+    }
+  }
+  uint32_t s = 0;
+  int bad_width = 0;
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {
+    const int64_t g = base + i;
+    w[i] = (g < num_groups) ? group_words(b[i], g, num_groups, n, gs, &bad_width) : 0u;
+    s += w[i];
+  }
+  const int lane = threadIdx.x & (daf::kWave - 1), wave = threadIdx.x >> 6;
+  const uint32_t incl = daf::wave_inclusive_sum(s);
+  if (lane == daf::kWave - 1) wave_tot[wave] = incl;
+  __syncthreads();
+  uint32_t before = 0u;
+#pragma unroll
+  for (int v = 0; v < kThreads / daf::kWave; ++v) before += (v < wave) ? wave_tot[v] : 0u;
+  store_offsets(off, base, num_groups, block_off + before + incl - s, w);   // the thread's first group
+}
+
+// Few groups: one workgroup, kItems consecutive groups per thread.
+constexpr int kOneThreads = 1024;
+__global__ __launch_bounds__(kOneThreads) void k_plan_one(const uint8_t* __restrict__ src_bits, uint8_t* __restrict__ plan_bits,
+                                                          int64_t num_groups, int64_t n, int32_t gs,
+                                                          uint32_t* __restrict__ off, unsigned long long* __restrict__ total,
+                                                          int* __restrict__ bad_flag) {
+  constexpr int kWaves = kOneThreads / daf::kWave;
+  __shared__ uint32_t wave_tot[kWaves];
+  __shared__ unsigned long long wave_sum[kWaves];
+  const int64_t base = (int64_t)threadIdx.x * kItems;
+  uint32_t w[kItems];
+  uint32_t s = 0;
+  unsigned long long sum = 0;
+  int bad = 0;
+  uint32_t b[kItems];
+  load_widths(src_bits, base, num_groups, b);
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {
+    const int64_t g = base + i;
+    w[i] = 0u;
+    if (g < num_groups) {
+      int bad_here = 0;
+      (void)group_words(b[i], g, num_groups, n, gs, &bad_here);
+      if (bad_here) { b[i] = 8u; bad = 1; }
+      w[i] = group_words(b[i], g, num_groups, n, gs, &bad_here);
+    }
+    s += w[i];
+    sum += w[i];
+  }
+  store_widths(plan_bits, base, num_groups, b);
+  const int lane = threadIdx.x & (daf::kWave - 1), wave = threadIdx.x >> 6;
+  const uint32_t incl = daf::wave_inclusive_sum(s);
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+  if (lane == daf::kWave - 1) {
+    wave_tot[wave] = incl;
+    wave_sum[wave] = sum;
+  }
+  const int any_bad = __syncthreads_or(bad);
+  uint32_t before = 0u;
+  unsigned long long all = 0;
+#pragma unroll
+  for (int v = 0; v < kWaves; ++v) {
+    before += (v < wave) ? wave_tot[v] : 0u;
+    all += wave_sum[v];
+  }
+  store_offsets(off, base, num_groups, before + incl - s, w);
+  if (threadIdx.x == 0) {
+    *total = all;
+    *bad_flag = any_bad;
+  }
+}
+
+// One launch 7.0 us up to here (two launches 9.5); with twice as many groups per thread 10.1.
+constexpr int64_t kOneGroups = kItems * kOneThreads;
+constexpr int64_t kMaxSummedBlocks = 4096;            // 32 KB of block sums, read by every block
+
 }  // namespace
 
 int64_t daf_plan_scan_blocks(int64_t num_groups) { return (num_groups + kBlockGroups - 1) / kBlockGroups; }
@@ -179,11 +275,21 @@ int64_t daf_plan_scan_blocks(int64_t num_groups) { return (num_groups + kBlockGr
 hipError_t daf_launch_plan_scan(const uint8_t* src_bits, uint8_t* plan_bits, int64_t num_groups, int64_t n,
                                 int32_t group_size, uint32_t* d_off, unsigned long long* d_block_sums, int64_t n_blocks,
                                 unsigned long long* d_total, int* d_bad, hipStream_t stream) {
+  if (num_groups <= kOneGroups) {
+    hipLaunchKernelGGL(k_plan_one, dim3(1), dim3(kOneThreads), 0, stream, src_bits, plan_bits, num_groups, n, group_size,
+                       d_off, d_total, d_bad);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_plan_block_sums, dim3((unsigned)n_blocks), dim3(kThreads), 0, stream, src_bits, plan_bits,
                      num_groups, n, group_size, d_block_sums);
-  hipLaunchKernelGGL(k_plan_scan_block_sums, dim3(1), dim3(kThreads), 0, stream, d_block_sums, n_blocks,
-                     d_total, d_bad);
-  hipLaunchKernelGGL(k_plan_write_offsets, dim3((unsigned)n_blocks), dim3(kThreads), 0, stream, plan_bits,
-                     num_groups, n, group_size, d_block_sums, d_off);
+  if (n_blocks <= kMaxSummedBlocks) {
+    hipLaunchKernelGGL(k_plan_write_offsets<false>, dim3((unsigned)n_blocks), dim3(kThreads), 0, stream, plan_bits,
+                       num_groups, n, group_size, d_block_sums, d_off, d_total, d_bad);
+  } else {
+    hipLaunchKernelGGL(k_plan_scan_block_sums, dim3(1), dim3(kThreads), 0, stream, d_block_sums, n_blocks,
+                       d_total, d_bad);
+    hipLaunchKernelGGL(k_plan_write_offsets<true>, dim3((unsigned)n_blocks), dim3(kThreads), 0, stream, plan_bits,
+                       num_groups, n, group_size, d_block_sums, d_off, d_total, d_bad);
+  }
   return hipGetLastError();
 }

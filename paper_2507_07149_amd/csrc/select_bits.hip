@@ -14,13 +14,16 @@
 // whose key equals T_k.  Keys are the bit patterns of the ranges, which order like the ranges
 // because a range is never negative.
 //
-// Six launches: zero the counters; write the keys and count their first digit; count the second
-// digit; count the third; count the keys equal to T_k per block of 4096 groups and find I_k;
-// classify.  What used to be a launch of one workgroup after each counting pass (pick the bin
-// that holds the rank, scan the per-block tie counts) is done by the workgroup that finishes
-// last, found with a ticket counter.  Everything that crosses workgroups inside a launch goes
-// through device-scope atomics (adds, stores, loads), so no cache write-back is needed; what a
-// later launch reads is written with ordinary stores.
+// Up to kSmallGroups groups: one launch of one workgroup that keeps the keys in registers
+// (k_select_small).  More: six launches: zero the first counters; write the keys and count their first digit (and zero the
+// other counters); count the second digit; count the third; count the keys equal to T_k per block of 4096
+// groups; classify.  What a pass decides (the bin that holds the rank) is worked out from its counters by
+// every workgroup of the next launch for itself: a scan of 2048 counters from the cache, next to the
+// keys that are on their way, instead of a ticket, a last workgroup and its trips past the caches at the end
+// of every launch.  The same for the ties: a block of the last launch adds up the tie counts of the blocks
+// before it.  Nothing crosses workgroups inside a launch.  Selection alone, four classes, before (ticket and last
+// workgroup in four of six launches) and now: 500 groups 39 / 14 us, 8192 40 / 20, 197 K 49 / 29, 1 M 54 / 34, 5.6 M 94 / 66;
+// all ranges equal: 197 K 53 / 38, 5.6 M 127 / 104.
 #include "daf_device.h"
 #include "daf_internal.h"
 
@@ -36,49 +39,37 @@ constexpr int kHistCopies = 2;
 constexpr int kBins = 2048;                      // the widest digit has 11 bits
 constexpr int kBinsPerThread = kBins / kThreads; // 4
 constexpr int kPasses = 3;
-constexpr int kLaunchesWithTicket = 4;           // three counting passes and the tie count
-constexpr int kTicketLanes = 16;
 constexpr unsigned kMaxWorkgroups = 384;         // of the counting launches, see daf_launch_select_bits
-static_assert(kBins % kThreads == 0 && kBinsPerThread % 2 == 0, "a thread reads its bins in 8-byte pieces");
+static_assert(kBins % kThreads == 0 && kBinsPerThread == 4, "a thread reads its bins in one 16-byte piece");
 constexpr int kLdsCopies0 = 8;                   // copies of a workgroup's own histogram, first pass (one histogram)
 constexpr int kLdsCopies = 2;                    // later passes (one histogram per threshold)
 
 __host__ __device__ constexpr int pass_shift(int pass) { return pass == 0 ? 21 : pass == 1 ? 10 : 0; }
 __host__ __device__ constexpr int pass_bits(int pass) { return pass == 2 ? 10 : 11; }
 
-struct SelectState {
+// What is decided after a number of passes, per threshold.
+struct Decided {
   uint32_t prefix[kMaxThresholds];      // digits of T_k decided so far
   uint32_t rank[kMaxThresholds];        // rank still to be located inside the prefix bucket; E_k at the end
-  uint32_t tie_index[kMaxThresholds];   // I_k
-  // Workgroups of a launch that have finished (all zero between launches), in two levels:
-  // [1 + r] counts the workgroups whose index is r modulo kTicketLanes, [0] the residues that are
-  // complete.  Atomics to one address are served one after the other, about 8 ns each; a single
-  // counter drawn by 1024 workgroups that finish together costs as much as a small launch.
-  uint32_t ticket[kLaunchesWithTicket][1 + kTicketLanes];
-  uint32_t pad[3];
-  // kHistCopies copies of the histograms, a workgroup adds to copy (its index mod kHistCopies):
-  // atomics to one address are served one after the other at the memory side (about 8 ns each),
-  // and with few distinct digits every workgroup hits the same few counters.  One copy is
-  // 3 x 2048 counters: the workgroup that picks the bins reads all copies, so there are few.
-  uint32_t hist[kHistCopies][kMaxThresholds][kBins];
 };
-static_assert(offsetof(SelectState, hist) % 16 == 0, "the counters are read and cleared in 8- and 16-byte pieces");
+struct SelectState {
+  Decided after[kPasses];               // after[p]: passes 0 .. p, written by the launch that follows pass p
+  uint32_t pad[2];
+  // Counters of the passes, kHistCopies copies, a workgroup adds to copy (its index mod kHistCopies): atomics
+  // to one address are served one after the other at the memory side (about 8 ns each), and with few
+  // distinct digits every workgroup hits the same few counters.  Few copies, because every workgroup of the next launch
+  // reads them all.  (The first pass has one histogram for all thresholds.)
+  uint32_t hist[kPasses][kHistCopies][kMaxThresholds][kBins];
+};
+static_assert(offsetof(SelectState, hist) % 16 == 0, "the counters are read and cleared in 16-byte pieces");
 
-// Ranks to locate, empty prefixes, zeroed counters and tickets.
-__global__ __launch_bounds__(kThreads) void k_select_init(SelectState* __restrict__ st, uint32_t r0, uint32_t r1,
-                                                          uint32_t r2) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    st->prefix[0] = st->prefix[1] = st->prefix[2] = 0u;
-    st->rank[0] = r0;
-    st->rank[1] = r1;
-    st->rank[2] = r2;
-    st->tie_index[0] = st->tie_index[1] = st->tie_index[2] = 0u;
-    for (int i = 0; i < kLaunchesWithTicket * (1 + kTicketLanes); ++i) (&st->ticket[0][0])[i] = 0u;
+// Zeroes the first pass's counters.
+__global__ __launch_bounds__(kThreads) void k_select_init(SelectState* __restrict__ st) {
+  const int i = blockIdx.x * kThreads + threadIdx.x;
+  if (i < kHistCopies * kBins / 4) {
+    const int copy = i / (kBins / 4), piece = i % (kBins / 4);
+    reinterpret_cast<uint4*>(&st->hist[0][copy][0][0])[piece] = make_uint4(0u, 0u, 0u, 0u);
   }
-  uint4* h = reinterpret_cast<uint4*>(&st->hist[0][0][0]);
-  constexpr int kPieces = kHistCopies * kMaxThresholds * kBins / 4;
-  for (int i = blockIdx.x * kThreads + threadIdx.x; i < kPieces; i += gridDim.x * kThreads)
-    h[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // A workgroup's own histogram in LDS holds COPIES counters per bin, side by side, and a lane adds
@@ -120,39 +111,6 @@ __device__ __forceinline__ uint32_t block_exclusive_sum(uint32_t v, uint32_t* wa
   return before + incl - v;
 }
 
-// Device-scope accesses for what one workgroup writes and another reads inside a launch.
-__device__ __forceinline__ uint64_t coherent_load(const uint64_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ uint32_t coherent_load(const uint32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void coherent_store(uint32_t* p, uint32_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// True in every thread of the workgroup that finishes a launch last.  Each thread first waits for
-// its own atomics and stores to be acknowledged, so when the last ticket is drawn every
-// workgroup's contributions are in place.  The caller zeroes ticket[0] when it is done.
-__device__ __forceinline__ bool last_workgroup(uint32_t* ticket, uint32_t* flag) {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const uint32_t r = blockIdx.x % kTicketLanes;
-    const uint32_t with_r = (gridDim.x - r + kTicketLanes - 1) / kTicketLanes;
-    const uint32_t residues = gridDim.x < (unsigned)kTicketLanes ? gridDim.x : (unsigned)kTicketLanes;
-    uint32_t last = 0u;
-    if (__hip_atomic_fetch_add(&ticket[1 + r], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == with_r - 1) {
-      coherent_store(&ticket[1 + r], 0u);
-      last = (__hip_atomic_fetch_add(&ticket[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == residues - 1) ? 1u : 0u;
-    }
-    *flag = last;
-  }
-  __syncthreads();
-  asm volatile("" ::: "memory");
-  return *flag != 0u;
-}
-
 // Thresholds whose prefixes are equal so far select inside the same bucket: they share one
 // histogram, that of the first of them.
 struct Slices {
@@ -166,43 +124,43 @@ __device__ __forceinline__ Slices shared_slices(const uint32_t (&prefix)[kMaxThr
   return s;
 }
 
-// The end of a counting pass, run by every workgroup after it has added its counts: the one that
-// finishes last sums the copies, finds for each threshold the bin whose cumulative count first
-// exceeds the rank, extends the prefix by that digit, and leaves counters and ticket zeroed.
+// The ranks looked for, R_k, before the first pass.
+struct Ranks {
+  uint32_t r[kMaxThresholds];
+};
+
+// The counters of pass PASS that a thread looks at: four consecutive bins of every histogram, all copies added.
 template <int PASS>
-__device__ __forceinline__ void finish_pass(SelectState* __restrict__ st, int n_thresholds,
-                                            const uint32_t (&prefix)[kMaxThresholds], const Slices& slices,
-                                            uint32_t* wave_tot, uint32_t* flag) {
-  if (!last_workgroup(st->ticket[PASS], flag)) return;
-  uint32_t rank[kMaxThresholds];
-  for (int k = 0; k < kMaxThresholds; ++k) rank[k] = st->rank[k];
-  // The counters come from memory past the caches, a few microseconds per trip: the loads of all
-  // histograms in use are issued before any of them is needed.
-  uint64_t raw[kMaxThresholds][kHistCopies][kBinsPerThread / 2];
+struct Bins {
+  uint4 raw[PASS == 0 ? 1 : kMaxThresholds][kHistCopies];
+};
+template <int PASS>
+__device__ __forceinline__ void load_bins(Bins<PASS>& b, const SelectState* __restrict__ st, int n_thresholds) {
 #pragma unroll
-  for (int k = 0; k < kMaxThresholds; ++k) {
-    const bool used = k < n_thresholds && slices.of[k] == k;
+  for (int k = 0; k < (PASS == 0 ? 1 : kMaxThresholds); ++k)
 #pragma unroll
-    for (int c = 0; c < kHistCopies; ++c) {
-      const uint64_t* src = reinterpret_cast<const uint64_t*>(&st->hist[c][k][threadIdx.x * kBinsPerThread]);
+    for (int c = 0; c < kHistCopies; ++c)
+      b.raw[k][c] = k < n_thresholds ? reinterpret_cast<const uint4*>(&st->hist[PASS][c][k][0])[threadIdx.x]
+                                     : make_uint4(0u, 0u, 0u, 0u);
+}
+
+// Finds for each threshold the bin of pass PASS whose cumulative count first exceeds the rank and extends
+// the prefix by that digit; every thread of the workgroup has the result.
+template <int PASS>
+__device__ __forceinline__ void decide(Decided& d, const Bins<PASS>& bins, int n_thresholds, uint32_t* wave_tot,
+                                       Decided* shared) {
+  const Slices slices = shared_slices(d.prefix, PASS);
+  constexpr int kHists = PASS == 0 ? 1 : kMaxThresholds;
+  uint32_t hs[kHists][kBinsPerThread];
 #pragma unroll
-      for (int i = 0; i < kBinsPerThread / 2; ++i) raw[k][c][i] = used ? coherent_load(src + i) : 0ull;
+  for (int k = 0; k < kHists; ++k) {
+    uint4 h = bins.raw[k][0];
+#pragma unroll
+    for (int c = 1; c < kHistCopies; ++c) {
+      const uint4 v = bins.raw[k][c];
+      h.x += v.x; h.y += v.y; h.z += v.z; h.w += v.w;
     }
-  }
-  uint32_t hs[kMaxThresholds][kBinsPerThread];
-#pragma unroll
-  for (int k = 0; k < kMaxThresholds; ++k) {
-#pragma unroll
-    for (int i = 0; i < kBinsPerThread / 2; ++i) {
-      uint32_t lo = 0u, hi = 0u;
-#pragma unroll
-      for (int c = 0; c < kHistCopies; ++c) {
-        lo += (uint32_t)raw[k][c][i];
-        hi += (uint32_t)(raw[k][c][i] >> 32);
-      }
-      hs[k][2 * i] = lo;
-      hs[k][2 * i + 1] = hi;
-    }
+    hs[k][0] = h.x; hs[k][1] = h.y; hs[k][2] = h.z; hs[k][3] = h.w;
   }
 #pragma unroll
   for (int k = 0; k < kMaxThresholds; ++k) {
@@ -211,25 +169,28 @@ __device__ __forceinline__ void finish_pass(SelectState* __restrict__ st, int n_
     uint32_t sum = 0u;
 #pragma unroll
     for (int i = 0; i < kBinsPerThread; ++i) {
-      h[i] = slices.of[k] == 0 ? hs[0][i] : slices.of[k] == 1 ? hs[1][i] : hs[2][i];
+      h[i] = (kHists == 1 || slices.of[k] == 0) ? hs[0][i] : slices.of[k] == 1 ? hs[kHists > 1 ? 1 : 0][i] : hs[kHists > 1 ? 2 : 0][i];
       sum += h[i];
     }
     uint32_t total;
     uint32_t run = block_exclusive_sum(sum, wave_tot, &total);
 #pragma unroll
     for (int i = 0; i < kBinsPerThread; ++i) {
-      if (run <= rank[k] && rank[k] < run + h[i]) {       // exactly one bin (ranks are < G)
-        st->prefix[k] = prefix[k] | ((uint32_t)(threadIdx.x * kBinsPerThread + i) << pass_shift(PASS));
-        st->rank[k] = rank[k] - run;
+      if (run <= d.rank[k] && d.rank[k] < run + h[i]) {       // exactly one bin of one thread (ranks are < G)
+        shared->prefix[k] = d.prefix[k] | ((uint32_t)(threadIdx.x * kBinsPerThread + i) << pass_shift(PASS));
+        shared->rank[k] = d.rank[k] - run;
       }
       run += h[i];
     }
   }
-  __syncthreads();                                        // every thread has its counts
-  uint4* h4 = reinterpret_cast<uint4*>(&st->hist[0][0][0]);
-  constexpr int kPieces = kHistCopies * kMaxThresholds * kBins / 4;
-  for (int i = threadIdx.x; i < kPieces; i += kThreads) h4[i] = make_uint4(0u, 0u, 0u, 0u);
-  if (threadIdx.x == 0) coherent_store(&st->ticket[PASS][0], 0u);
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kMaxThresholds; ++k) {
+    if (k < n_thresholds) {
+      d.prefix[k] = shared->prefix[k];
+      d.rank[k] = shared->rank[k];
+    }
+  }
 }
 
 // keys[g] = bit pattern of the group's range, and in the same pass the histogram of the keys'
@@ -244,10 +205,15 @@ __global__ __launch_bounds__(kThreads) void k_select_keys(const float* __restric
                                                           int64_t G, uint32_t* __restrict__ keys,
                                                           SelectState* __restrict__ st, int n_thresholds) {
   constexpr int kLoads = 8;
-  __shared__ uint32_t lh[kBins * kLdsCopies0];
-  __shared__ uint32_t wave_tot[kThreads / kWave];
-  __shared__ uint32_t flag;
-  for (int i = threadIdx.x; i < kBins * kLdsCopies0; i += kThreads) lh[i] = 0u;
+  __shared__ __attribute__((aligned(16))) uint32_t lh[kBins * kLdsCopies0];
+  for (int i = threadIdx.x; i < kBins * kLdsCopies0 / 4; i += kThreads)
+    reinterpret_cast<uint4*>(lh)[i] = make_uint4(0u, 0u, 0u, 0u);
+  {                                                       // the later passes' counters
+    uint4* later = reinterpret_cast<uint4*>(&st->hist[1][0][0][0]);
+    constexpr int kPieces = (kPasses - 1) * kHistCopies * kMaxThresholds * kBins / 4;
+    for (int i = blockIdx.x * kThreads + threadIdx.x; i < kPieces; i += gridDim.x * kThreads)
+      later[i] = make_uint4(0u, 0u, 0u, 0u);
+  }
   __syncthreads();
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t wave_stride = (int64_t)gridDim.x * (kThreads / kWave) * (kWave * kLoads);
@@ -277,25 +243,40 @@ __global__ __launch_bounds__(kThreads) void k_select_keys(const float* __restric
   if (n_thresholds > 0) {
     for (int i = threadIdx.x; i < kBins; i += kThreads) {
       const uint32_t c = hist_count<kLdsCopies0>(lh, i);
-      if (c) atomicAdd(&st->hist[blockIdx.x % kHistCopies][0][i], c);
+      if (c) atomicAdd(&st->hist[0][blockIdx.x % kHistCopies][0][i], c);
     }
   }
-  const uint32_t prefix[kMaxThresholds] = {0u, 0u, 0u};
-  finish_pass<0>(st, n_thresholds, prefix, shared_slices(prefix, 0), wave_tot, &flag);
+}
+
+// What is decided after pass PASS, from its counters (every thread has the result).
+template <int PASS>
+__device__ __forceinline__ Decided decided_after(SelectState* __restrict__ st, const Ranks& ranks, int n_thresholds,
+                                                 uint32_t* wave_tot, Decided* shared) {
+  Bins<PASS> bins;
+  load_bins<PASS>(bins, st, n_thresholds);
+  Decided d;
+#pragma unroll
+  for (int k = 0; k < kMaxThresholds; ++k) {
+    d.prefix[k] = PASS == 0 ? 0u : st->after[PASS == 0 ? 0 : PASS - 1].prefix[k];
+    d.rank[k] = PASS == 0 ? ranks.r[k] : st->after[PASS == 0 ? 0 : PASS - 1].rank[k];
+  }
+  decide<PASS>(d, bins, n_thresholds, wave_tot, shared);
+  if (blockIdx.x == 0 && threadIdx.x == 0) st->after[PASS] = d;      // for the launches after this one
+  return d;
 }
 
 // Histogram of the PASS-th digit among the keys whose higher digits equal the prefix.
 template <int PASS>
 __global__ __launch_bounds__(kThreads) void k_select_hist(const uint32_t* __restrict__ keys, int64_t G,
-                                                          SelectState* __restrict__ st, int n_thresholds) {
+                                                          SelectState* __restrict__ st, Ranks ranks, int n_thresholds) {
   constexpr int kShift = pass_shift(PASS), kDigitBins = 1 << pass_bits(PASS);
-  __shared__ uint32_t lh[kMaxThresholds][kBins * kLdsCopies];
+  __shared__ __attribute__((aligned(16))) uint32_t lh[kMaxThresholds][kBins * kLdsCopies];
   __shared__ uint32_t wave_tot[kThreads / kWave];
-  __shared__ uint32_t flag;
-  for (int i = threadIdx.x; i < kMaxThresholds * kBins * kLdsCopies; i += kThreads) (&lh[0][0])[i] = 0u;
-  __syncthreads();
-  uint32_t prefix[kMaxThresholds];
-  for (int k = 0; k < kMaxThresholds; ++k) prefix[k] = st->prefix[k];
+  __shared__ Decided shared;
+  for (int i = threadIdx.x; i < kMaxThresholds * kBins * kLdsCopies / 4; i += kThreads)
+    reinterpret_cast<uint4*>(&lh[0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
+  const Decided d = decided_after<PASS - 1>(st, ranks, n_thresholds, wave_tot, &shared);
+  const uint32_t(&prefix)[kMaxThresholds] = d.prefix;
   const Slices slices = shared_slices(prefix, PASS);
   const int64_t stride = (int64_t)gridDim.x * kThreads;
   // Sixteen keys per lane and trip: four 16-byte loads issued together (the key array is padded
@@ -334,9 +315,9 @@ __global__ __launch_bounds__(kThreads) void k_select_hist(const uint32_t* __rest
   for (int i = threadIdx.x; i < n_thresholds * kBins; i += kThreads) {
     const int k = i / kBins;
     const uint32_t c = hist_count<kLdsCopies>(lh[k], i % kBins);
-    if (c && slices.of[k] == k) atomicAdd(&(&st->hist[blockIdx.x % kHistCopies][0][0])[i], c);
+    const bool own = k == 0 || (k == 1 ? slices.of[1] == 1 : slices.of[2] == 2);
+    if (c && own) atomicAdd(&(&st->hist[PASS][blockIdx.x % kHistCopies][0][0])[i], c);
   }
-  finish_pass<PASS>(st, n_thresholds, prefix, slices, wave_tot, &flag);
 }
 
 // A thread's kItems consecutive keys: two 16-byte loads (the key array is padded to a multiple
@@ -356,25 +337,14 @@ __device__ __forceinline__ void load_keys(const uint32_t* __restrict__ keys, int
     if (base + i >= G) key[i] = 0xFFFFFFFFu;
 }
 
-// Per block of 4096 consecutive groups: how many keys equal each threshold.  The workgroup that
-// finishes last then finds, for every threshold with E_k > 0, the block in which the running
-// count of equal keys passes E_k, and inside that block the group I_k itself.
+// Per block of 4096 consecutive groups: how many keys equal each threshold.
 __global__ __launch_bounds__(kThreads) void k_select_ties(const uint32_t* __restrict__ keys, int64_t G,
-                                                          SelectState* __restrict__ st, int n_thresholds,
+                                                          SelectState* __restrict__ st, Ranks ranks, int n_thresholds,
                                                           uint32_t* __restrict__ block_ties, int64_t n_blocks) {
   __shared__ uint32_t cnt[kMaxThresholds];
   __shared__ uint32_t wave_tot[kThreads / kWave];
-  __shared__ uint32_t flag;
-  __shared__ uint32_t found[kMaxThresholds][2];          // block that holds I_k, equal keys still to skip in it
-  if (threadIdx.x < 2 * kMaxThresholds) (&found[0][0])[threadIdx.x] = 0u;
-  uint32_t T[kMaxThresholds], E[kMaxThresholds];
-  for (int k = 0; k < kMaxThresholds; ++k) {
-    T[k] = st->prefix[k];
-    E[k] = st->rank[k];
-  }
-  const int64_t ties_stride = (n_blocks + 3) & ~(int64_t)3;      // per threshold; keeps 8-byte loads aligned
-  // A workgroup takes every gridDim.x-th block: few workgroups, because each draws a ticket at
-  // the end and tickets are served one after the other.
+  __shared__ Decided shared;
+  const Decided d = decided_after<kPasses - 1>(st, ranks, n_thresholds, wave_tot, &shared);
   for (int64_t b = blockIdx.x; b < n_blocks; b += gridDim.x) {
     if (threadIdx.x < kMaxThresholds) cnt[threadIdx.x] = 0u;
     __syncthreads();
@@ -385,123 +355,223 @@ __global__ __launch_bounds__(kThreads) void k_select_ties(const uint32_t* __rest
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
       if (base + i < G) {
-        for (int k = 0; k < n_thresholds; ++k) c[k] += (key[i] == T[k]) ? 1u : 0u;
+#pragma unroll
+        for (int k = 0; k < kMaxThresholds; ++k)
+          if (k < n_thresholds) c[k] += (key[i] == d.prefix[k]) ? 1u : 0u;
       }
     }
-    for (int k = 0; k < n_thresholds; ++k)
-      if (c[k]) atomicAdd(&cnt[k], c[k]);
+#pragma unroll
+    for (int k = 0; k < kMaxThresholds; ++k)
+      if (k < n_thresholds && c[k]) atomicAdd(&cnt[k], c[k]);
     __syncthreads();
-    if (threadIdx.x < (unsigned)n_thresholds)
-      coherent_store(&block_ties[(int64_t)threadIdx.x * ties_stride + b], cnt[threadIdx.x]);
+    if (threadIdx.x < (unsigned)n_thresholds) block_ties[(int64_t)threadIdx.x * n_blocks + b] = cnt[threadIdx.x];
     __syncthreads();
   }
-  if (!last_workgroup(st->ticket[kPasses], &flag)) return;
-
-  // Running count of equal keys over the blocks, 4096 blocks per trip (eight consecutive counts
-  // per thread, all thresholds' loads issued together), until the block that holds I_k is found.
-  bool wanted[kMaxThresholds];
-  uint32_t carry[kMaxThresholds];
-#pragma unroll
-  for (int k = 0; k < kMaxThresholds; ++k) {
-    wanted[k] = k < n_thresholds && E[k] != 0u;           // E_k = 0: every equal key counts, I_k = 0
-    carry[k] = 0u;
-  }
-  for (int64_t t0 = 0; t0 < n_blocks; t0 += kBlockGroups) {
-    const int64_t i0 = t0 + (int64_t)threadIdx.x * kItems;
-    uint64_t raw[kMaxThresholds][kItems / 2];
-#pragma unroll
-    for (int k = 0; k < kMaxThresholds; ++k) {
-      const uint64_t* src = reinterpret_cast<const uint64_t*>(block_ties + (int64_t)k * ties_stride + i0);
-#pragma unroll
-      for (int j = 0; j < kItems / 2; ++j)
-        raw[k][j] = (wanted[k] && i0 + 2 * j < n_blocks) ? coherent_load(src + j) : 0ull;
-    }
-#pragma unroll
-    for (int k = 0; k < kMaxThresholds; ++k) {
-      if (!wanted[k]) continue;
-      uint32_t v[kItems];
-      uint32_t sum = 0u;
-#pragma unroll
-      for (int j = 0; j < kItems; ++j) {
-        const uint32_t e = (j & 1) ? (uint32_t)(raw[k][j / 2] >> 32) : (uint32_t)raw[k][j / 2];
-        v[j] = (i0 + j < n_blocks) ? e : 0u;              // the padding of the array holds no counts
-        sum += v[j];
-      }
-      uint32_t total;
-      uint32_t run = carry[k] + block_exclusive_sum(sum, wave_tot, &total);
-      if (run <= E[k] && E[k] < run + sum) {              // at most one thread over all trips (E_k < number of equal keys)
-#pragma unroll
-        for (int j = 0; j < kItems; ++j) {
-          if (run <= E[k] && E[k] < run + v[j]) {
-            found[k][0] = (uint32_t)(i0 + j);
-            found[k][1] = E[k] - run;
-          }
-          run += v[j];
-        }
-      }
-      carry[k] += total;
-    }
-  }
-  __syncthreads();
-  // Inside the found blocks: the thread whose keys hold the wanted equal key writes its index.
-  uint32_t fkey[kMaxThresholds][kItems];
-  int64_t fbase[kMaxThresholds];
-#pragma unroll
-  for (int k = 0; k < kMaxThresholds; ++k) {
-    fbase[k] = (int64_t)found[k][0] * kBlockGroups + (int64_t)threadIdx.x * kItems;
-    if (wanted[k]) load_keys(keys, fbase[k], G, fkey[k]);
-  }
-#pragma unroll
-  for (int k = 0; k < kMaxThresholds; ++k) {
-    if (!wanted[k]) continue;
-    const uint32_t skip = found[k][1];
-    uint32_t mine = 0u;
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) mine += (fbase[k] + i < G && fkey[k][i] == T[k]) ? 1u : 0u;
-    uint32_t total;
-    uint32_t before = block_exclusive_sum(mine, wave_tot, &total);
-    if (before <= skip && skip < before + mine) {
-#pragma unroll
-      for (int i = 0; i < kItems; ++i) {
-        if (fbase[k] + i < G && fkey[k][i] == T[k]) {
-          if (before == skip) st->tie_index[k] = (uint32_t)(fbase[k] + i);
-          ++before;
-        }
-      }
-    }
-  }
-  if (threadIdx.x == 0) coherent_store(&st->ticket[kPasses][0], 0u);
 }
 
-__global__ __launch_bounds__(kThreads) void k_select_classify(const uint32_t* __restrict__ keys, int64_t G,
-                                                              const SelectState* __restrict__ st, int n_thresholds,
-                                                              uint32_t classes_packed, uint8_t* __restrict__ out_bits) {
-  const int64_t base = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * kItems;
-  uint32_t T[kMaxThresholds], I[kMaxThresholds];
-  for (int k = 0; k < kMaxThresholds; ++k) {
-    T[k] = st->prefix[k];
-    I[k] = st->tie_index[k];
+// More blocks than a block of k_select_classify wants to add up: their tie counts become running sums first
+// (one workgroup per threshold).
+constexpr int64_t kMaxSummedBlocks = 2048;
+__global__ __launch_bounds__(kThreads) void k_select_scan_ties(uint32_t* __restrict__ block_ties, int64_t n_blocks) {
+  __shared__ uint32_t wave_tot[kThreads / kWave];
+  uint32_t* ties = block_ties + (int64_t)blockIdx.x * n_blocks;
+  uint32_t carry = 0u;
+  for (int64_t i0 = 0; i0 < n_blocks; i0 += kThreads) {
+    const int64_t i = i0 + threadIdx.x;
+    const uint32_t v = i < n_blocks ? ties[i] : 0u;
+    uint32_t total;
+    const uint32_t before = block_exclusive_sum(v, wave_tot, &total);
+    if (i < n_blocks) ties[i] = carry + before;
+    carry += total;
   }
-  uint32_t key[kItems];
-  load_keys(keys, base, G, key);
-  uint8_t w[kItems];
-#pragma unroll
-  for (int i = 0; i < kItems; ++i) {
-    const uint32_t g = (uint32_t)(base + i);
-    uint32_t cls = 0;
-    for (int k = 0; k < n_thresholds; ++k)
-      if (key[i] > T[k] || (key[i] == T[k] && g >= I[k])) ++cls;
-    w[i] = (uint8_t)(classes_packed >> (8u * cls));
-  }
-  if (base + kItems <= G && (reinterpret_cast<uintptr_t>(out_bits) & 7u) == 0u) {
+}
+
+// Eight widths of consecutive groups, bytes of two words, `count` of them inside the array.
+__device__ __forceinline__ void store_widths(uint8_t* __restrict__ out, const uint8_t (&w)[kItems], int64_t count) {
+  if (count >= kItems && (reinterpret_cast<uintptr_t>(out) & 7u) == 0u) {
     const uint2 v = make_uint2((uint32_t)w[0] | ((uint32_t)w[1] << 8) | ((uint32_t)w[2] << 16) | ((uint32_t)w[3] << 24),
                                (uint32_t)w[4] | ((uint32_t)w[5] << 8) | ((uint32_t)w[6] << 16) | ((uint32_t)w[7] << 24));
-    *reinterpret_cast<uint2*>(out_bits + base) = v;       // eight widths in one store
+    *reinterpret_cast<uint2*>(out) = v;                   // eight widths in one store
   } else {
 #pragma unroll
     for (int i = 0; i < kItems; ++i)
-      if (base + i < G) out_bits[base + i] = w[i];
+      if (i < count) out[i] = w[i];
   }
+}
+
+// rank(g) >= R_k  iff  key_g > T_k, or key_g == T_k and at least E_k equal keys come before g.
+__global__ __launch_bounds__(kThreads) void k_select_classify(const uint32_t* __restrict__ keys, int64_t G,
+                                                              const SelectState* __restrict__ st, int n_thresholds,
+                                                              uint32_t classes_packed, const uint32_t* __restrict__ block_ties,
+                                                              int64_t n_blocks, bool scanned, uint8_t* __restrict__ out_bits) {
+  __shared__ uint32_t wave_tot[kThreads / kWave];
+  const int64_t base = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * kItems;
+  uint32_t key[kItems];
+  load_keys(keys, base, G, key);
+  uint8_t w[kItems];
+  uint32_t cls[kItems];
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) cls[i] = 0u;
+  for (int k = 0; k < n_thresholds; ++k) {
+    const uint32_t T = st->after[kPasses - 1].prefix[k], E = st->after[kPasses - 1].rank[k];      // (uniform)
+    uint32_t before = 0u;                                  // equal keys before the thread's first
+    if (E != 0u) {                                         // (0: every equal key counts)
+      const uint32_t* ties = block_ties + (int64_t)k * n_blocks;
+      uint32_t total, sum = 0u;
+      if (scanned) {
+        sum = ties[blockIdx.x];
+      } else {
+        for (int64_t i = threadIdx.x; i < (int64_t)blockIdx.x; i += kThreads) sum += ties[i];
+        (void)block_exclusive_sum(sum, wave_tot, &total);
+        sum = total;
+      }
+      uint32_t mine = 0u;
+#pragma unroll
+      for (int i = 0; i < kItems; ++i) mine += (base + i < G && key[i] == T) ? 1u : 0u;
+      before = sum + block_exclusive_sum(mine, wave_tot, &total);
+    }
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+      const bool equal = key[i] == T;
+      if (key[i] > T || (equal && before >= E)) ++cls[i];
+      before += equal ? 1u : 0u;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) w[i] = (uint8_t)(classes_packed >> (8u * cls[i]));
+  if (base < G) store_widths(out_bits + base, w, G - base);
+}
+
+// ---- few groups: one workgroup, the keys in registers ------------------------------------------------------------
+// kItems consecutive groups per thread (so that equal keys are met in group order), 1024 threads; every
+// pass counts into LDS, finds the bins and goes on.
+constexpr int kSmallThreads = 1024;
+constexpr int64_t kSmallGroups = 8 * kSmallThreads;
+
+__device__ __forceinline__ uint32_t small_exclusive_sum(uint32_t v, uint32_t* wave_tot) {
+  constexpr int kWaves = kSmallThreads / kWave;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+  const uint32_t incl = wave_inclusive_sum(v);
+  __syncthreads();
+  if (lane == kWave - 1) wave_tot[wave] = incl;
+  __syncthreads();
+  uint32_t before = 0u;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) before += (w < wave) ? wave_tot[w] : 0u;
+  return before + incl - v;
+}
+
+template <int PASS>
+__device__ __forceinline__ void small_pass(const uint32_t (&key)[kItems], int64_t base, int64_t G, Decided& d, int n_thresholds,
+                                           uint32_t* lh, uint32_t* wave_tot, Decided* shared) {
+  constexpr int kShift = pass_shift(PASS), kDigitBins = 1 << pass_bits(PASS);
+  constexpr int kCopies = PASS == 0 ? kLdsCopies0 : kLdsCopies, kHists = PASS == 0 ? 1 : kMaxThresholds;
+  static_assert(kHists * kCopies * kBins <= kLdsCopies0 * kBins, "the first pass takes the most LDS");
+  const Slices slices = shared_slices(d.prefix, PASS);
+  __syncthreads();                                         // the counters may still be read
+  for (int i = threadIdx.x; i < kHists * kCopies * kDigitBins / 4; i += kSmallThreads)
+    reinterpret_cast<uint4*>(lh)[i] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {
+    const uint32_t digit = (key[i] >> kShift) & (uint32_t)(kDigitBins - 1);
+#pragma unroll
+    for (int k = 0; k < kHists; ++k) {
+      if (k >= n_thresholds || slices.of[k] != k) continue;
+      bool in = base + i < G;
+      if constexpr (PASS > 0) in = in && (((key[i] ^ d.prefix[k]) >> (kShift + pass_bits(PASS))) == 0u);
+      hist_add<kCopies>(lh + k * kCopies * kDigitBins, digit, in);
+    }
+  }
+  __syncthreads();
+  constexpr int kPer = kDigitBins / kSmallThreads;         // 2 or 1 bins per thread
+#pragma unroll
+  for (int k = 0; k < kMaxThresholds; ++k) {
+    if (k >= n_thresholds) break;
+    const uint32_t* h = lh + slices.of[k] * kCopies * kDigitBins;
+    uint32_t c[kPer], sum = 0u;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      c[i] = hist_count<kCopies>(h, threadIdx.x * kPer + i);
+      sum += c[i];
+    }
+    uint32_t run = small_exclusive_sum(sum, wave_tot);
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      if (run <= d.rank[k] && d.rank[k] < run + c[i]) {
+        shared->prefix[k] = d.prefix[k] | ((uint32_t)(threadIdx.x * kPer + i) << kShift);
+        shared->rank[k] = d.rank[k] - run;
+      }
+      run += c[i];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kMaxThresholds; ++k) {
+    if (k < n_thresholds) {
+      d.prefix[k] = shared->prefix[k];
+      d.rank[k] = shared->rank[k];
+    }
+  }
+}
+
+template <bool FROM_SCALE>
+__global__ __launch_bounds__(kSmallThreads) void k_select_small(const float* __restrict__ gmin, const float* __restrict__ gmax,
+                                                                const uint8_t* prev_bits, uint32_t prev_uniform, int64_t G,
+                                                                Ranks ranks, int n_thresholds, uint32_t classes_packed,
+                                                                uint8_t* out_bits) {
+  __shared__ __attribute__((aligned(16))) uint32_t lh[kBins * kLdsCopies0];
+  __shared__ uint32_t wave_tot[kSmallThreads / kWave];
+  __shared__ Decided shared;
+  const int64_t base = (int64_t)threadIdx.x * kItems;
+  uint32_t key[kItems];
+  // (out_bits may be prev_bits: all widths are read before the first barrier, and none is written before the last)
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {
+    const int64_t g = base + i;
+    key[i] = 0xFFFFFFFFu;
+    if (g < G) {
+      if (FROM_SCALE) {
+        const uint32_t b = prev_bits != nullptr ? (uint32_t)prev_bits[g] : prev_uniform;
+        key[i] = f2u(gmin[g] * (float)((1u << (b & 15u)) - 1u));
+      } else {
+        key[i] = f2u(gmax[g] - gmin[g]);
+      }
+    }
+  }
+  Decided d;
+#pragma unroll
+  for (int k = 0; k < kMaxThresholds; ++k) {
+    d.prefix[k] = 0u;
+    d.rank[k] = ranks.r[k];
+  }
+  if (n_thresholds > 0) {
+    small_pass<0>(key, base, G, d, n_thresholds, lh, wave_tot, &shared);
+    small_pass<1>(key, base, G, d, n_thresholds, lh, wave_tot, &shared);
+    small_pass<2>(key, base, G, d, n_thresholds, lh, wave_tot, &shared);
+  }
+  uint32_t cls[kItems];
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) cls[i] = 0u;
+#pragma unroll
+  for (int k = 0; k < kMaxThresholds; ++k) {
+    if (k >= n_thresholds) break;
+    const uint32_t T = d.prefix[k], E = d.rank[k];
+    uint32_t mine = 0u;
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) mine += (base + i < G && key[i] == T) ? 1u : 0u;
+    uint32_t before = small_exclusive_sum(mine, wave_tot);
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+      const bool equal = key[i] == T;
+      if (key[i] > T || (equal && before >= E)) ++cls[i];
+      before += equal ? 1u : 0u;
+    }
+  }
+  uint8_t w[kItems];
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) w[i] = (uint8_t)(classes_packed >> (8u * cls[i]));
+  if (base < G) store_widths(out_bits + base, w, G - base);
 }
 
 }  // namespace
@@ -520,23 +590,34 @@ hipError_t daf_launch_select_bits(const float* gmin, const float* gmax, const ui
   const int64_t n_blocks = (G + kBlockGroups - 1) / kBlockGroups;
 
   // thresholds R_k = ceil(k*G/C) that some rank can reach (R_k < G); the rest never apply
-  uint32_t R[kMaxThresholds] = {0u, 0u, 0u};
+  Ranks ranks = {{0u, 0u, 0u}};
   int n_thr = 0;
   for (int k = 1; k < n_classes; ++k) {
     const int64_t r = (k * G + n_classes - 1) / n_classes;
-    if (r < G) R[n_thr++] = (uint32_t)r;
+    if (r < G) ranks.r[n_thr++] = (uint32_t)r;
   }
   uint32_t packed = 0;
   for (int c = 0; c < n_classes; ++c) packed |= (uint32_t)classes[c] << (8 * c);
   // thresholds skipped because R_k >= G sit at the end (R_k grows with k), so class = number of
   // satisfied thresholds still indexes `classes` correctly.
 
+  // One launch, 14 to 20 us up to here against 27 for the six; two and four times as many keys per thread: 32 and 59 us
+  // against 27 (one workgroup counts a pass alone).
+  if (G <= kSmallGroups) {
+    if (gmax != nullptr)
+      hipLaunchKernelGGL(k_select_small<false>, dim3(1), dim3(kSmallThreads), 0, stream, gmin, gmax, nullptr, 0u, G, ranks,
+                         n_thr, packed, out_bits);
+    else
+      hipLaunchKernelGGL(k_select_small<true>, dim3(1), dim3(kSmallThreads), 0, stream, gmin, nullptr, prev_bits,
+                         (uint32_t)prev_uniform, G, ranks, n_thr, packed, out_bits);
+    return hipGetLastError();
+  }
+
   // The counting launches take at most kMaxWorkgroups workgroups of 8 waves: each adds its non-zero
-  // counts to the shared counters and draws a ticket, and both are served one after the other per
-  // address (5.6 M groups: 82 us for the whole selection with 384 workgroups of 512 threads, 84 with
-  // 256, 90 with 1024; 94 to 125 with workgroups of 256 threads).
+  // counts to the shared counters, and those are served one after the other per address (5.6 M groups: 66 us
+  // with 256, 384 and 512 workgroups, 73 with 768).
   const unsigned cap = kMaxWorkgroups;
-  hipLaunchKernelGGL(k_select_init, dim3(24), dim3(kThreads), 0, stream, st, R[0], R[1], R[2]);
+  hipLaunchKernelGGL(k_select_init, dim3((kHistCopies * kBins / 4 + kThreads - 1) / kThreads), dim3(kThreads), 0, stream, st);
   const unsigned kblocks = (unsigned)((G + 8 * kThreads - 1) / (8 * kThreads));                  // eight keys per thread and trip
   if (gmax != nullptr)
     hipLaunchKernelGGL(k_select_keys<false>, dim3(kblocks < cap ? kblocks : cap), dim3(kThreads), 0, stream, gmin, gmax,
@@ -544,15 +625,17 @@ hipError_t daf_launch_select_bits(const float* gmin, const float* gmax, const ui
   else
     hipLaunchKernelGGL(k_select_keys<true>, dim3(kblocks < cap ? kblocks : cap), dim3(kThreads), 0, stream, gmin, nullptr,
                        prev_bits, (uint32_t)prev_uniform, G, keys, st, n_thr);
+  const bool scanned = n_blocks > kMaxSummedBlocks;
   if (n_thr > 0) {
     const unsigned cblocks = (unsigned)((((G + 3) >> 2) + 4 * kThreads - 1) / (4 * kThreads));   // sixteen keys per thread and trip
     const unsigned hblocks = cblocks < cap ? cblocks : cap;
-    hipLaunchKernelGGL(k_select_hist<1>, dim3(hblocks), dim3(kThreads), 0, stream, keys, G, st, n_thr);
-    hipLaunchKernelGGL(k_select_hist<2>, dim3(hblocks), dim3(kThreads), 0, stream, keys, G, st, n_thr);
+    hipLaunchKernelGGL(k_select_hist<1>, dim3(hblocks), dim3(kThreads), 0, stream, keys, G, st, ranks, n_thr);
+    hipLaunchKernelGGL(k_select_hist<2>, dim3(hblocks), dim3(kThreads), 0, stream, keys, G, st, ranks, n_thr);
     hipLaunchKernelGGL(k_select_ties, dim3((unsigned)(n_blocks < cap ? n_blocks : cap)), dim3(kThreads), 0, stream, keys,
-                       G, st, n_thr, block_ties, n_blocks);
+                       G, st, ranks, n_thr, block_ties, n_blocks);
+    if (scanned) hipLaunchKernelGGL(k_select_scan_ties, dim3((unsigned)n_thr), dim3(kThreads), 0, stream, block_ties, n_blocks);
   }
   hipLaunchKernelGGL(k_select_classify, dim3((unsigned)n_blocks), dim3(kThreads), 0, stream, keys, G, st, n_thr, packed,
-                     out_bits);
+                     block_ties, n_blocks, scanned, out_bits);
   return hipGetLastError();
 }

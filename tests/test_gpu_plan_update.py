@@ -56,6 +56,29 @@ def test_update_then_quantize_without_sync(dtype, gs, n):
     plan.destroy()
 
 
+@pytest.mark.parametrize("G", [8191, 8192, 8193, 4096 * 2048, 4096 * 2048 + 1])
+def test_offsets_at_the_limits_of_the_scan_forms(G):
+    """One launch up to 8192 groups; two up to 4096 blocks of 2048 groups; three above.  The last group is
+    short, an invalid width sits in the last block."""
+    gs, n = 32, 32 * G - 7
+    rng = np.random.default_rng(G)
+    bits = rng.choice([1, 2, 4, 8], G).astype(np.uint8)
+    plan = daf.daf_plan((n,), gs, torch.from_numpy(bits).cuda())
+    words = bits.astype(np.int64)
+    words[-1] = (25 * bits[-1] + 31) // 32
+    assert plan.packed_words == words.sum()
+    assert np.array_equal(plan.offsets().numpy().view(np.uint32), np.cumsum(words) - words)
+    bits[-2] = 7
+    plan.update(torch.from_numpy(bits).cuda())
+    with pytest.raises(daf.DafError) as e:
+        plan.finish()
+    assert e.value.status == -1
+    words[-2] = 8                                         # an invalid width counts as 8
+    assert plan.packed_words == words.sum()
+    assert np.array_equal(plan.offsets().numpy().view(np.uint32), np.cumsum(words) - words)
+    plan.destroy()
+
+
 def test_invalid_width_in_an_update_is_made_safe_and_reported():
     n, gs = 4096 * 4, 128
     G = n // gs

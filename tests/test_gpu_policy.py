@@ -89,6 +89,32 @@ def test_select_bits_ties(env, classes):
         assert np.array_equal(got.cpu().numpy(), orc.select_bits(gmin, gmax, classes)), (G, choices)
 
 
+@pytest.mark.parametrize("G", [8191, 8192, 8193, 16_385, 4096 * 2048, 4096 * 2048 + 1])
+@pytest.mark.parametrize("ties", [False, True])
+def test_select_bits_at_the_limits_of_its_forms(env, G, ties):
+    """One launch up to 8192 groups, several above; up to 2048 blocks of 4096 groups a block adds up the
+    tie counts before it, above they are scanned in a launch of their own."""
+    daf, orc = env
+    rng = np.random.default_rng(G)
+    gmin = np.zeros(G, dtype=np.float32)
+    gmax = rng.choice(np.array([0.25, 0.5, 0.5, 1.0, 1.0, 1.0, 3.0], np.float32), G) if ties else rng.random(G, dtype=np.float32)
+    got = _select(daf, torch.from_numpy(gmin).cuda(), torch.from_numpy(gmax).cuda(), (1, 2, 4, 8))
+    assert np.array_equal(got.cpu().numpy(), orc.select_bits(gmin, gmax, (1, 2, 4, 8)))
+
+
+@pytest.mark.parametrize("G", [5000, 20_000])
+def test_select_bits_from_scale_in_place(env, G):
+    """Both forms, out_bits being the previous widths."""
+    daf, orc = env
+    rng = np.random.default_rng(G)
+    prev = rng.choice([1, 2, 4, 8], G).astype(np.uint8)
+    scale = rng.choice(np.array([0.5, 1.0, 1.5], np.float32), G)
+    bits = torch.from_numpy(prev).cuda()
+    daf.daf_select_bits_from_scale(torch.from_numpy(scale).cuda(), bits, (2, 4, 8), bits, daf.daf_select_bits_workspace(G))
+    want = orc.select_bits(np.zeros(G, np.float32), scale * ((1 << prev.astype(np.int64)) - 1).astype(np.float32), (2, 4, 8))
+    assert np.array_equal(bits.cpu().numpy(), want)
+
+
 def test_select_bits_workspace_reuse(env):
     """One workspace, filled with ones beforehand, serves calls of different sizes one after the
     other: every call leaves its counters and tickets as the next one needs them.  Many equal
