@@ -145,21 +145,22 @@ __device__ __forceinline__ void store_chunk(u32x4* out, int64_t c, u32x4 o, bool
 // arithmetic + stores) so that all loads of one phase are in flight together: with per-group
 // widths the word address depends on two earlier loads, and a chunk-by-chunk loop would pay
 // that latency once per chunk.
-template <int DT, bool MIXED, bool RELU_BWD>
+// THREADS threads take K chunks each: a workgroup, or (list calls, the chunks after a tensor's last whole tile) a wave.
+template <int DT, bool MIXED, bool RELU_BWD, int THREADS = kThreads, int K = chunks_per_thread(MIXED)>
 __device__ __forceinline__ void unpack_dequantize_block(
     int64_t block, const uint32_t* __restrict__ words, const float* __restrict__ mn, const float* __restrict__ scale,
     const uint8_t* __restrict__ bits, const uint32_t* __restrict__ off, int32_t uniform_bits,
     int64_t n_chunks, int32_t gs, int32_t gs_shift, u32x4* out, const u32x4* grad, bool cached, int64_t chunk0 = 0) {
   constexpr int kEpl = ElemTraits<DT>::kPerLoad;
-  constexpr int K = chunks_per_thread(MIXED);
-  const int64_t base = chunk0 + block * (kThreads * K) + threadIdx.x;   // chunk0: the first chunk this launch covers
+  // chunk0: the first chunk this launch covers
+  const int64_t base = chunk0 + block * (THREADS * K) + (THREADS == kThreads ? threadIdx.x : threadIdx.x & (THREADS - 1));
 
   int64_t g[K];
   uint32_t b[K], woff[K], bitpos[K];
   float m[K], s[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    int64_t c = base + (int64_t)k * kThreads;
+    int64_t c = base + (int64_t)k * THREADS;
     c = (c < n_chunks) ? c : n_chunks - 1;                         // clamp: loads stay in bounds
     const int64_t e0 = c * kEpl;                                   // first element of the chunk
     g[k] = (gs_shift >= 0) ? (e0 >> gs_shift) : (e0 / gs);
@@ -179,7 +180,7 @@ __device__ __forceinline__ void unpack_dequantize_block(
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     if (RELU_BWD) {                                                // the gradient chunk at the output's place
-      int64_t c = base + (int64_t)k * kThreads;
+      int64_t c = base + (int64_t)k * THREADS;
       c = (c < n_chunks) ? c : n_chunks - 1;
       gq[k] = __builtin_nontemporal_load(&grad[c]);
     }
@@ -191,7 +192,7 @@ __device__ __forceinline__ void unpack_dequantize_block(
   }
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    const int64_t c = base + (int64_t)k * kThreads;
+    const int64_t c = base + (int64_t)k * THREADS;
     u32x4 o = dequantize_chunk<DT>(w0[k], w1[k], bitpos[k], b[k], m[k], s[k]);
     if (RELU_BWD) {
       o = (u32x4){keep_where_positive<DT>(o.x, gq[k].x), keep_where_positive<DT>(o.y, gq[k].y),
@@ -376,14 +377,16 @@ __global__ __launch_bounds__(kThreads) DAF_TILE_WAVES void k_unpack_dequantize_t
                                                   cached != 0);
 }
 
-// ---- tiles for group sizes that are not a power of two -------------------------------------
+// ---- tiles for the other group sizes ----------------------------------------------------------
 // The same tile, but groups start anywhere in it (the first and the last may continue in the
 // neighbouring tiles): lane l holds the constants of group g_first + l, a chunk finds its group
 // by dividing its element index by the group size (a multiply-high with a rounded-up
-// reciprocal, exact for the few thousand values that occur), and with one width for all groups
+// reciprocal, exact for the few thousand values that occur; groups longer than 32768 elements touch a
+// tile two at a time, and a comparison finds them), and with one width for all groups
 // the packed words do not depend on the group size at all: element e sits at bit e * B of the
-// stream.  With per-group widths the run starts at the word of the tile's first element inside
-// its group and may be one word longer than the tile's bits.
+// stream.  With per-group widths the run starts at the tile's first element (tiles and groups start at
+// multiples of 32 elements, so that is a whole word) and is at most as long as the tile's bits.
+// Long groups took the chunk kernel before: one group for a 51 M-element binary32 tensor, 2 bits: 41.3 -> 36 us.
 template <int DT, int B>
 struct alignas(16) TileLdsAny {
   static constexpr int kWords = TileLds<DT, B, kTileChunksPerLane>::kWords + (B ? 0 : kWave);
@@ -410,6 +413,7 @@ __device__ __forceinline__ void unpack_dequantize_tile_any_body(
   const int64_t g_first = e_tile0 / gs;                          // once per wave
   const uint32_t rem0 = (uint32_t)(e_tile0 - g_first * gs);      // the tile starts this far into its first group
   const int groups = (int)((rem0 + (uint32_t)kElems - 1u) / (uint32_t)gs) + 1;   // at most 64: checked by the launcher
+  auto group_of = [&](uint32_t e) { return gs_magic ? __umulhi(e, gs_magic) : (e >= (uint32_t)gs ? 1u : 0u); };
 
   TileGroup mine;
   mine.mn = 0.0f; mine.scale = 0.0f; mine.b = B ? (uint32_t)B : 1u; mine.woff = 0u;
@@ -435,14 +439,15 @@ __device__ __forceinline__ void unpack_dequantize_tile_any_body(
   } else {
     const uint32_t b_first = (uint32_t)__builtin_amdgcn_readlane((int)mine.b, 0);
     const uint32_t off_first = (uint32_t)__builtin_amdgcn_readlane((int)my_off, 0);
-    const uint32_t first_word = off_first + ((rem0 * b_first) >> 5);
+    const uint32_t first_word = off_first + (uint32_t)(((uint64_t)rem0 * b_first) >> 5);
     const uint32_t e_last = rem0 + (uint32_t)(kElems - kEpl);                     // the tile's last chunk
-    const int gl_last = __builtin_amdgcn_readfirstlane((int)__umulhi(e_last, gs_magic));
+    const int gl_last = __builtin_amdgcn_readfirstlane((int)group_of(e_last));
     const uint32_t b_last = (uint32_t)__builtin_amdgcn_readlane((int)mine.b, gl_last);
     const uint32_t off_last = (uint32_t)__builtin_amdgcn_readlane((int)my_off, gl_last);
-    const uint32_t bit_end = (e_last - (uint32_t)gl_last * (uint32_t)gs + (uint32_t)kEpl) * b_last;
-    const uint32_t tile_words = off_last + ((bit_end + 31u) >> 5) - first_word;   // <= kMaxWords
-    mine.woff = my_off - first_word;                    // modulo 2^32: the first group may start before the run
+    // bits up to the end of the last chunk, from the start of its group or, in the tile's first group, of the run
+    const uint32_t bit_end = (gl_last == 0 ? (uint32_t)kElems : e_last - (uint32_t)gl_last * (uint32_t)gs + (uint32_t)kEpl) * b_last;
+    const uint32_t tile_words = (gl_last == 0 ? 0u : off_last - first_word) + ((bit_end + 31u) >> 5);   // <= kMaxWords
+    mine.woff = lane == 0 ? 0u : my_off - first_word;   // the first group's place is the start of the run
 #pragma unroll
     for (int j = 0; j < kWordLoads; ++j) {
       const uint32_t i = (uint32_t)(j * kWave + lane);
@@ -459,12 +464,12 @@ __device__ __forceinline__ void unpack_dequantize_tile_any_body(
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const uint32_t e0 = (uint32_t)(u * kWave + lane) * kEpl;     // first element of chunk u*64 + lane of the tile
-    const uint32_t gl = __umulhi(rem0 + e0, gs_magic);           // = (rem0 + e0) / gs
+    const uint32_t gl = group_of(rem0 + e0);                     // = (rem0 + e0) / gs
     g[u] = lds.group[gl];
     const uint32_t b = kMixed ? g[u].b : (uint32_t)B;
     uint32_t widx;
     if (kMixed) {
-      bit[u] = (rem0 + e0 - gl * (uint32_t)gs) * b;              // bit position inside the group
+      bit[u] = (gl == 0u ? e0 : rem0 + e0 - gl * (uint32_t)gs) * b;   // bit position inside the run (first group), inside the group
       widx = g[u].woff + (bit[u] >> 5);
     } else {
       bit[u] = e0 * b;                                           // bit position inside the tile's run
@@ -507,15 +512,28 @@ __global__ __launch_bounds__(kThreads) DAF_TILE_WAVES void k_unpack_dequantize_t
                                                    grad, cached != 0);
 }
 
-// Whole tiles of a plan whose group size is not a power of two on that path (0: does not fit).
+// Whole tiles of a plan whose groups are not whole parts of a tile on that path (0: does not fit).
+// (binary32 with 8 bits for every group stays with the chunk kernel: 0.76-0.78 of the memory rate
+// there against 0.70-0.74 through tiles, measured on 2^27 elements with groups of 96 ... 11008)
 template <int DT>
 int64_t any_tile_path_tiles(const daf_plan_t* p, uint32_t* magic) {
   constexpr int kElems = kTileChunks * ElemTraits<DT>::kPerLoad;
   const int64_t gs = p->group_size;
-  if ((gs & (gs - 1)) == 0 || gs < 64 || gs > 32768 || gs % 32 != 0) return 0;
+  if (DT == kF32 && p->uniform_bits == 8) return 0;
+  if (gs < 64 || gs % 32 != 0 || ((gs & (gs - 1)) == 0 && gs <= kElems)) return 0;
+  if (gs > 32768 || (gs & (gs - 1)) == 0) {
+    // Long groups: one of a tile's two round trips is shorter than the chunk kernel's three (a quantize and a dequantize call,
+    // chunk kernel / tiles: binary16, 16384 per group, four widths, 33 M elements 38.3 / 35.8 us, 246 M 215 / 210;
+    // one group, 2 bits, 33 M 44.7 / 42.9, 246 M 282 / 272), except where many words a lane stream as well without
+    // tiles: binary32 beyond 67 M elements (197 M, 2 bits: 410 / 418; 33 M: 79.5 / 76.8), 4 bits of a 16-bit format there
+    // (291 / 304; 33 M: 46.9 / 45.4), and 1 bit below it (39.6 / 41.0; 246 M: 269 / 258).
+    const bool small = p->n <= (int64_t)1 << 26;
+    if (DT == kF32 || p->uniform_bits == 4) { if (!small) return 0; }
+    else if (p->uniform_bits == 1 && small) return 0;
+  }
   if ((gs - 1 + kElems - 1) / gs + 1 > kWave) return 0;           // groups that touch one tile
   if (p->num_groups >= ((int64_t)1 << 31)) return 0;
-  *magic = (uint32_t)((((uint64_t)1 << 32) + (uint64_t)gs - 1) / (uint64_t)gs);
+  *magic = gs > 32768 ? 0u : (uint32_t)((((uint64_t)1 << 32) + (uint64_t)gs - 1) / (uint64_t)gs);
   return p->n / kElems;
 }
 
@@ -528,7 +546,8 @@ struct TileBatchEntry {
   const uint32_t* off;
   u32x4* out;
   int64_t tile_end;                                 // tiles of this and all earlier entries
-  int32_t gs_log2;
+  int64_t n_chunks;                                 // the entry's last tile may reach past them
+  int32_t gs, gs_log2;
   int32_t cached;                                   // the plan's output store policy
 };
 constexpr int kMaxTileBatch = kBatchSlots;
@@ -538,6 +557,15 @@ struct TileBatch {
   int32_t n;
 };
 
+// The chunks of an entry after its last whole tile, one wave, the chunk kernel's way: they ride along instead of having a
+// launch of their own per list or per tensor (24 ragged binary16 tensors of 58 MB: 73 -> 40 us with groups of 128).
+template <int DT, int B>
+__device__ __forceinline__ void left_over_chunks(const TileBatchEntry& e, int64_t tile, int32_t gs_shift) {
+  unpack_dequantize_block<DT, B == 0, false, kWave, kTileChunksPerLane>(0, e.words, e.mn, e.scale, e.bits, e.off, B,
+                                                                        e.n_chunks, e.gs, gs_shift, e.out, nullptr,
+                                                                        e.cached != 0, tile * kTileChunks);
+}
+
 template <int DT, int B>
 __global__ __launch_bounds__(kThreads) DAF_TILE_WAVES void k_unpack_dequantize_tile_batch(const TileBatch batch) {
   const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -545,8 +573,39 @@ __global__ __launch_bounds__(kThreads) DAF_TILE_WAVES void k_unpack_dequantize_t
   const int t = batch_entry_of(batch.ends, (uint32_t)gtile);
   if (t >= batch.n) return;                          // past the last tile (the grid is whole workgroups)
   const TileBatchEntry e = batch.e[t];               // by value: one scalar load of the whole descriptor
-  unpack_dequantize_tile_body<DT, B, false>(gtile - (t ? batch.e[t - 1].tile_end : 0), wave_in_block, e.words, e.mn,
-                                            e.scale, e.bits, e.off, e.gs_log2, e.out, nullptr, e.cached != 0);
+  const int64_t tile = gtile - (t ? batch.e[t - 1].tile_end : 0);
+  if ((tile + 1) * kTileChunks > e.n_chunks)
+    left_over_chunks<DT, B>(e, tile, e.gs_log2);
+  else
+    unpack_dequantize_tile_body<DT, B, false>(tile, wave_in_block, e.words, e.mn, e.scale, e.bits, e.off, e.gs_log2, e.out,
+                                              nullptr, e.cached != 0);
+}
+
+struct AnyTileBatchEntry {
+  TileBatchEntry t;                                 // (its gs_log2 is not used)
+  int64_t num_groups;
+  uint32_t magic;
+};
+struct AnyTileBatch {
+  uint32_t ends[kBatchSlots];
+  AnyTileBatchEntry e[kMaxTileBatch];
+  int32_t n;
+};
+static_assert(sizeof(AnyTileBatch) <= 4096, "kernel arguments");
+
+template <int DT, int B>
+__global__ __launch_bounds__(kThreads) DAF_TILE_WAVES void k_unpack_dequantize_tile_any_batch(const AnyTileBatch batch) {
+  const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t gtile = (int64_t)blockIdx.x * kWavesPerBlock + wave_in_block;
+  const int t = batch_entry_of(batch.ends, (uint32_t)gtile);
+  if (t >= batch.n) return;                          // past the last tile (the grid is whole workgroups)
+  const AnyTileBatchEntry e = batch.e[t];
+  const int64_t tile = gtile - (t ? batch.e[t - 1].t.tile_end : 0);
+  if ((tile + 1) * kTileChunks > e.t.n_chunks)
+    left_over_chunks<DT, B>(e.t, tile, -1);
+  else
+    unpack_dequantize_tile_any_body<DT, B, false>(tile, wave_in_block, e.t.words, e.t.mn, e.t.scale, e.t.bits, e.t.off,
+                                                  e.t.gs, e.magic, e.num_groups, e.t.out, nullptr, e.t.cached != 0);
 }
 
 // Whole tiles of a plan on the tile path (0: the plan's group size does not fit it).
@@ -579,6 +638,7 @@ struct Batch {
   BatchEntry e[kMaxBatch];
   int32_t n;
 };
+static_assert(sizeof(Batch) <= 4096, "kernel arguments");
 
 template <int DT, bool MIXED>
 __global__ __launch_bounds__(kThreads) void k_unpack_dequantize_chunk_batch(const Batch batch) {
@@ -626,10 +686,7 @@ hipError_t launch_dtype(const daf_plan_t* p, const uint32_t* words, const float*
   int32_t gs_log2 = 0;
   const int64_t n_tiles = tile_path_tiles<DT>(p, &gs_log2);
   uint32_t magic = 0;
-  // (binary32 with 8 bits for every group stays with the chunk kernel: 0.76-0.78 of the memory rate
-  // there against 0.70-0.74 through tiles, measured on 2^27 elements with groups of 96 ... 11008)
-  const int64_t any_tiles =
-      (n_tiles == 0 && !(DT == kF32 && p->uniform_bits == 8)) ? any_tile_path_tiles<DT>(p, &magic) : 0;
+  const int64_t any_tiles = n_tiles == 0 ? any_tile_path_tiles<DT>(p, &magic) : 0;
   if (any_tiles > 0) {
     const bool left = any_tiles * kTileChunks * kEpl < p->n;
     const unsigned blocks = (unsigned)((any_tiles + kWavesPerBlock - 1) / kWavesPerBlock) + (left ? 1u : 0u);
@@ -648,6 +705,30 @@ hipError_t launch_dtype(const daf_plan_t* p, const uint32_t* words, const float*
     }
 #undef DAF_LAUNCH
     return hipGetLastError();
+  }
+  if constexpr (kEpl == 8) {
+    // Groups of 32 elements of a 16-bit format, one width: more than 64 in a whole tile, a tile of half the size holds 64
+    // (quantize and dequantize, chunk kernel / half tiles: 33 M elements, 2 bits 34.1 / 31.0 us, 246 M 213 / 197, 8 bits
+    // 254 / 243; with per-group widths 134 M 132 / 135: the chunk kernel stays).
+    constexpr int kHalf = kTileChunksPerLane / 2;
+    const int64_t half_tiles = n_tiles == 0 && p->uniform_bits ? tile_path_tiles<DT>(p, &gs_log2, kHalf) : 0;
+    if (half_tiles > 0) {
+      const bool left = half_tiles * kWave * kHalf * kEpl < p->n;
+      const unsigned blocks = (unsigned)((half_tiles + kWavesPerBlock - 1) / kWavesPerBlock) + (left ? 1u : 0u);
+#define DAF_LAUNCH(BITS)                                                                                              \
+  hipLaunchKernelGGL((k_unpack_dequantize_tile<DT, BITS, RELU_BWD, kHalf>), dim3(blocks), dim3(kThreads), 0, stream, \
+                     words, mn, scale, d_bits, p->d_off, half_tiles, p->group_size, gs_log2,                         \
+                     static_cast<u32x4*>(out_x), static_cast<const u32x4*>(grad), p->output_cached, p->n / kEpl, p->n)
+      switch (p->uniform_bits) {
+        case 1: DAF_LAUNCH(1); break;
+        case 2: DAF_LAUNCH(2); break;
+        case 4: DAF_LAUNCH(4); break;
+        case 8: DAF_LAUNCH(8); break;
+        default: return hipErrorInvalidValue;
+      }
+#undef DAF_LAUNCH
+      return hipGetLastError();
+    }
   }
   if (n_tiles == 0) return launch_chunks<DT, RELU_BWD>(p, words, mn, scale, d_bits, out_x, grad, 0, stream);
   // A small tensor with per-group widths takes tiles of twice the size: every wave pays two
@@ -687,18 +768,65 @@ hipError_t launch_dtype(const daf_plan_t* p, const uint32_t* words, const float*
   return hipGetLastError();
 }
 
-// Same results as one daf_launch_unpack_dequantize per item.  Consecutive items of the same
-// width kind (one width for all groups, or per-group widths) share a launch for their whole
-// chunks (at most kMaxBatch per launch); the few elements after an item's last whole chunk are
-// launched as before.
+// Launches the tiles of a list and forgets them.
+template <int DT>
+hipError_t launch_tiles(TileBatch& b, int bits, hipStream_t stream) {
+  hipError_t err = hipSuccess;
+  if (b.n > 0) {
+    const unsigned blocks = (unsigned)((b.e[b.n - 1].tile_end + kWavesPerBlock - 1) / kWavesPerBlock);
+#define DAF_LAUNCH(BITS) hipLaunchKernelGGL((k_unpack_dequantize_tile_batch<DT, BITS>), dim3(blocks), dim3(kThreads), 0, stream, b)
+    switch (bits) {
+      case 0: DAF_LAUNCH(0); break;
+      case 1: DAF_LAUNCH(1); break;
+      case 2: DAF_LAUNCH(2); break;
+      case 4: DAF_LAUNCH(4); break;
+      case 8: DAF_LAUNCH(8); break;
+      default: return hipErrorInvalidValue;
+    }
+#undef DAF_LAUNCH
+    err = hipGetLastError();
+  }
+  return err;
+}
+template <int DT>
+hipError_t launch_tiles(AnyTileBatch& b, int bits, hipStream_t stream) {
+  hipError_t err = hipSuccess;
+  if (b.n > 0) {
+    const unsigned blocks = (unsigned)((b.e[b.n - 1].t.tile_end + kWavesPerBlock - 1) / kWavesPerBlock);
+#define DAF_LAUNCH(BITS) hipLaunchKernelGGL((k_unpack_dequantize_tile_any_batch<DT, BITS>), dim3(blocks), dim3(kThreads), 0, stream, b)
+    switch (bits) {
+      case 0: DAF_LAUNCH(0); break;
+      case 1: DAF_LAUNCH(1); break;
+      case 2: DAF_LAUNCH(2); break;
+      case 4: DAF_LAUNCH(4); break;
+      case 8:
+        if constexpr (DT != kF32) DAF_LAUNCH(8);       // (binary32 with 8 bits for every group: the chunk kernel)
+        else return hipErrorInvalidValue;
+        break;
+      default: return hipErrorInvalidValue;
+    }
+#undef DAF_LAUNCH
+    err = hipGetLastError();
+  }
+  return err;
+}
+inline TileBatchEntry& tile_entry(TileBatch& b, int i) { return b.e[i]; }
+inline TileBatchEntry& tile_entry(AnyTileBatch& b, int i) { return b.e[i].t; }
+
+// Same results as one daf_launch_unpack_dequantize per item.  Consecutive items of the same kind (kernel; width, or
+// per-group widths) share a launch (at most kBatchSlots per launch); the few elements after an item's last
+// whole chunk have a launch of their own.
 template <int DT>
 hipError_t launch_items(const daf_dequantize_item_t* items, int32_t n_items, hipStream_t stream) {
   constexpr int kEpl = ElemTraits<DT>::kPerLoad;
-  Batch batch;
-  batch.n = 0;
-  for (int i = 0; i < kBatchSlots; ++i) batch.ends[i] = 0xFFFFFFFFu;
-  bool cur_mixed = false;
   hipError_t err = hipSuccess;
+  auto clear = [](auto& b) {
+    b.n = 0;
+    for (int i = 0; i < kBatchSlots; ++i) b.ends[i] = 0xFFFFFFFFu;
+  };
+  Batch batch;
+  clear(batch);
+  bool cur_mixed = false;
   auto flush = [&]() {
     if (batch.n > 0 && err == hipSuccess) {
       const unsigned blocks = (unsigned)batch.e[batch.n - 1].block_end;
@@ -708,31 +836,16 @@ hipError_t launch_items(const daf_dequantize_item_t* items, int32_t n_items, hip
         hipLaunchKernelGGL((k_unpack_dequantize_chunk_batch<DT, false>), dim3(blocks), dim3(kThreads), 0, stream, batch);
       err = hipGetLastError();
     }
-    batch.n = 0;
-    for (int i = 0; i < kBatchSlots; ++i) batch.ends[i] = 0xFFFFFFFFu;
+    clear(batch);
   };
-  TileBatch tbatch;                    // items on the tile path (group size a power of two)
-  tbatch.n = 0;
-  for (int i = 0; i < kBatchSlots; ++i) tbatch.ends[i] = 0xFFFFFFFFu;
-  int tcur_bits = -1;
-  auto tflush = [&]() {
-    if (tbatch.n > 0 && err == hipSuccess) {
-      const unsigned blocks = (unsigned)((tbatch.e[tbatch.n - 1].tile_end + kWavesPerBlock - 1) / kWavesPerBlock);
-#define DAF_LAUNCH(BITS) \
-  hipLaunchKernelGGL((k_unpack_dequantize_tile_batch<DT, BITS>), dim3(blocks), dim3(kThreads), 0, stream, tbatch)
-      switch (tcur_bits) {
-        case 0: DAF_LAUNCH(0); break;
-        case 1: DAF_LAUNCH(1); break;
-        case 2: DAF_LAUNCH(2); break;
-        case 4: DAF_LAUNCH(4); break;
-        case 8: DAF_LAUNCH(8); break;
-        default: err = hipErrorInvalidValue; break;
-      }
-#undef DAF_LAUNCH
-      if (err == hipSuccess) err = hipGetLastError();
-    }
-    tbatch.n = 0;
-    for (int i = 0; i < kBatchSlots; ++i) tbatch.ends[i] = 0xFFFFFFFFu;
+  TileBatch tbatch;                    // items whose groups are whole parts of a tile
+  AnyTileBatch abatch;                 // items of the other group sizes
+  clear(tbatch);
+  clear(abatch);
+  int tcur_bits = -1, acur_bits = -1;
+  auto tflush = [&](auto& b, int bits) {
+    if (err == hipSuccess) err = launch_tiles<DT>(b, bits, stream);
+    clear(b);
   };
   for (int32_t i = 0; i < n_items && err == hipSuccess; ++i) {
     const daf_dequantize_item_t& it = items[i];
@@ -741,30 +854,35 @@ hipError_t launch_items(const daf_dequantize_item_t* items, int32_t n_items, hip
     const int64_t n_chunks = p->n / kEpl;
     const bool mixed = p->uniform_bits == 0;
     int32_t gs_log2 = 0;
-    const int64_t n_tiles = tile_path_tiles<DT>(p, &gs_log2);
-    if (n_tiles > 0) {
-      if (tbatch.n == kMaxTileBatch || (tbatch.n > 0 && p->uniform_bits != tcur_bits) ||
-          (tbatch.n > 0 && tbatch.e[tbatch.n - 1].tile_end + n_tiles > 0x7fffffff))
-        tflush();
-      tcur_bits = p->uniform_bits;
-      TileBatchEntry& e = tbatch.e[tbatch.n];
+    uint32_t magic = 0;
+    auto add_tiles = [&](auto& b, int& cur_bits) {
+      const int64_t n_tiles = (n_chunks + kTileChunks - 1) / kTileChunks;      // the last one may be short
+      if (b.n == kMaxTileBatch || (b.n > 0 && p->uniform_bits != cur_bits) ||
+          (b.n > 0 && tile_entry(b, b.n - 1).tile_end + n_tiles > 0x7fffffff))
+        tflush(b, cur_bits);
+      cur_bits = p->uniform_bits;
+      TileBatchEntry& e = tile_entry(b, b.n);
       e.words = it.words;
       e.mn = it.min;
       e.scale = it.scale;
       e.bits = mixed ? d_bits : nullptr;
       e.off = mixed ? p->d_off : nullptr;
       e.out = static_cast<u32x4*>(it.out_x);
-      e.tile_end = (tbatch.n ? tbatch.e[tbatch.n - 1].tile_end : 0) + n_tiles;
-      tbatch.ends[tbatch.n] = (uint32_t)e.tile_end;
+      e.tile_end = (b.n ? tile_entry(b, b.n - 1).tile_end : 0) + n_tiles;
+      b.ends[b.n] = (uint32_t)e.tile_end;
+      e.n_chunks = n_chunks;
+      e.gs = p->group_size;
       e.gs_log2 = gs_log2;
       e.cached = p->output_cached;
-      ++tbatch.n;
-      if (n_tiles * kTileChunks * kEpl < p->n)          // chunks and elements after the last whole tile
-        err = launch_chunks<DT, false>(p, it.words, it.min, it.scale, d_bits, it.out_x, nullptr,
-                                       n_tiles * kTileChunks, stream);
-      continue;
-    }
-    if (n_chunks > 0) {
+      return b.n++;
+    };
+    if (tile_path_tiles<DT>(p, &gs_log2) > 0) {
+      add_tiles(tbatch, tcur_bits);
+    } else if (any_tile_path_tiles<DT>(p, &magic) > 0) {
+      const int at = add_tiles(abatch, acur_bits);
+      abatch.e[at].num_groups = p->num_groups;
+      abatch.e[at].magic = magic;
+    } else if (n_chunks > 0) {
       const int64_t per_block = (int64_t)kThreads * chunks_per_thread(mixed);
       const int64_t blocks = (n_chunks + per_block - 1) / per_block;
       if (batch.n == kMaxBatch || (batch.n > 0 && mixed != cur_mixed) ||
@@ -795,7 +913,8 @@ hipError_t launch_items(const daf_dequantize_item_t* items, int32_t n_items, hip
     }
   }
   flush();
-  tflush();
+  tflush(tbatch, tcur_bits);
+  tflush(abatch, acur_bits);
   return err;
 }
 

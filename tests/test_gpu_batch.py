@@ -141,3 +141,37 @@ def test_batch_argument_errors(env):
     lib = daf.load_library()
     assert lib.daf_quantize_pack_batch(None, 1, 0, None) == -1
     assert lib.daf_unpack_dequantize_batch(None, 0, 0, None) == -1
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("bits", [1, 2, 4, 8, "mixed"])
+def test_long_groups_and_groups_of_32_dequantize_through_tiles(env, dtype, bits):
+    """Groups longer than a tile: a tile inside one group, a group boundary in a tile's first, middle or last chunk,
+    a last group of one element, one group for the tensor; groups of 32 elements; tensors that end inside a
+    tile.  Each as a call of its own and all in one list call."""
+    daf, orc = env
+    cases = [(8192 * 3, 8192), (8192 * 2 + 4096 + 1, 8192), (40000 * 3 + 8, 40000), (36896 * 4 + 1000, 36896),
+             (65536 + 96 + 4096, 65536 + 96), (4096 * 9 + 77, 4096 * 10), (131072 + 1, 131072), (2048 * 5, 32), (2048 * 4 + 40, 32)]
+    _roundtrip(daf, orc, dtype, [(n, gs, bits) for n, gs in cases])
+    for n, gs in cases:
+        print("case", dtype, bits, n, gs, flush=True)
+        _roundtrip(daf, orc, dtype, [(n, gs, bits)])
+        g = torch.Generator().manual_seed(n)
+        x = torch.randn(n, generator=g).to(torch_dtype(dtype))
+        G = -(-n // gs)
+        b = (np.random.default_rng(n).choice([1, 2, 4, 8], G).astype(np.uint8) if bits == "mixed" else np.array([bits], np.uint8))
+        ow, omn, osc, _ = orc.quantize_pack(to_numpy_bits(x), dtype, gs, b, 3)
+        plan = daf.daf_plan((n,), gs, torch.from_numpy(b).cuda() if b.size > 1 else int(b[0]))
+        out = torch.full_like(x, 7.0, device="cuda:0")
+        daf.daf_unpack_dequantize(plan, torch.from_numpy(ow.view(np.int32)).cuda(), torch.from_numpy(omn).cuda(),
+                                  torch.from_numpy(osc).cuda(), out)
+        want, _ = orc.unpack_dequantize(ow, omn, osc, b, n, gs, dtype)
+        assert np.array_equal(to_numpy_bits(out.cpu()), want)
+        plan.destroy()
+
+
+def test_list_of_more_tensors_than_a_launch_takes(env):
+    """Forty ragged tensors: two launches per kind, every tensor's short last tile in one of them."""
+    daf, orc = env
+    _roundtrip(daf, orc, F16, [(4096 * (i % 3) + 8 * i + 8, 64, "mixed") for i in range(40)])
+    _roundtrip(daf, orc, F32, [(2048 * (i % 3) + 4 * i + 5, 96, 2) for i in range(40)])
