@@ -319,6 +319,34 @@ __device__ __forceinline__ void seg_sum2(float& a, float& b) {
 }
 #undef DAF_SUM2
 
+// The same for six values (three sums of two loads): an instruction reads the register written six
+// instructions earlier, no wait states between the steps.
+#define DAF_SUM6(CTRL)                                                       \
+  "v_add_f32_dpp %0, %0, %0 " CTRL "\n" "v_add_f32_dpp %1, %1, %1 " CTRL "\n" \
+  "v_add_f32_dpp %2, %2, %2 " CTRL "\n" "v_add_f32_dpp %3, %3, %3 " CTRL "\n" \
+  "v_add_f32_dpp %4, %4, %4 " CTRL "\n" "v_add_f32_dpp %5, %5, %5 " CTRL "\n"
+#define DAF_SUM6_ASM(BODY) \
+  asm("s_nop 4\n" BODY "s_nop 1\n" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]))
+template <int LPG_LOG2>
+__device__ __forceinline__ void seg_sum6(float (&a)[3], float (&b)[3]) {
+  static_assert(LPG_LOG2 >= 2 && LPG_LOG2 <= 6, "run length 4..64 lanes");
+  if constexpr (LPG_LOG2 == 2) {
+    DAF_SUM6_ASM(DAF_SUM6(DAF_DPP_X1) DAF_SUM6(DAF_DPP_X2));
+  } else if constexpr (LPG_LOG2 == 3) {
+    DAF_SUM6_ASM(DAF_SUM6(DAF_DPP_X1) DAF_SUM6(DAF_DPP_X2) DAF_SUM6(DAF_DPP_HM));
+  } else if constexpr (LPG_LOG2 == 4) {
+    DAF_SUM6_ASM(DAF_SUM6(DAF_DPP_X1) DAF_SUM6(DAF_DPP_X2) DAF_SUM6(DAF_DPP_HM) DAF_SUM6(DAF_DPP_M));
+  } else if constexpr (LPG_LOG2 == 5) {
+    DAF_SUM6_ASM(DAF_SUM6(DAF_DPP_X1) DAF_SUM6(DAF_DPP_X2) DAF_SUM6(DAF_DPP_HM) DAF_SUM6(DAF_DPP_M)
+                 DAF_SUM6(DAF_DPP_B15));
+  } else {
+    DAF_SUM6_ASM(DAF_SUM6(DAF_DPP_X1) DAF_SUM6(DAF_DPP_X2) DAF_SUM6(DAF_DPP_HM) DAF_SUM6(DAF_DPP_M)
+                 DAF_SUM6(DAF_DPP_B15) DAF_SUM6(DAF_DPP_B31));
+  }
+}
+#undef DAF_SUM6_ASM
+#undef DAF_SUM6
+
 // Inclusive prefix sum over the 64 lanes of a wave.
 __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
 #define DAF_SCAN(CTRL, MASK) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, MASK, 0xF, false)

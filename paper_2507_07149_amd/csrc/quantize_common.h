@@ -62,6 +62,19 @@ __device__ __forceinline__ uint32_t sr_variance_term(int t) {
   return T * (256u - T);
 }
 
+// The sum of sr_variance_term over four elements, as 256 * sum(T) - sum(T^2): the low bytes of the four t are
+// brought together and two dot products do the rest, 5 instructions instead of 16.  (The term is the same for
+// T and 256 - T, so the byte of t itself will do, and 0 stands for 256.)  The metrics variant of the tile kernel is
+// bound by vector instructions alone; with this and sums over the lanes two loads at a time it takes 25
+// per bfloat16 element instead of 28: 360 M elements, groups of 64, 245 -> 233 us, 90 M binary32 elements 116 -> 103 us.
+__device__ __forceinline__ void sr_variance_sums(const int (&t)[4], uint32_t& sum, uint32_t& sum_sq) {
+  const uint32_t lo = __builtin_amdgcn_perm((uint32_t)t[1], (uint32_t)t[0], 0x0C0C0400u);
+  const uint32_t hi = __builtin_amdgcn_perm((uint32_t)t[3], (uint32_t)t[2], 0x04000C0Cu);
+  const uint32_t bytes = lo | hi;
+  sum = __builtin_amdgcn_udot4(bytes, 0x01010101u, sum, false);
+  sum_sq = __builtin_amdgcn_udot4(bytes, bytes, sum_sq, false);
+}
+
 // max(x, +0) on the raw bits of one 32-bit word (one binary32 value or two 16-bit values):
 // a value whose sign bit is set (negative, or -0) is a negative integer and becomes +0, any
 // other value is kept; for finite inputs that is x > 0 ? x : +0 exactly.

@@ -90,30 +90,30 @@ __device__ __forceinline__ void quantize_chunk(const float (&xf)[ElemTraits<DT>:
   constexpr int kEpl = ElemTraits<DT>::kPerLoad;
   uint32_t nacc[2] = {0u, 0u};
   float e2 = 0.0f, m2 = 0.0f;
-  uint32_t v2 = 0u;
+  uint32_t t_sum = 0u, t_sq = 0u;
 #pragma unroll
   for (int q = 0; q < kEpl / 4; ++q) {
     const uint32_t rw = rnd[q];                 // the random bytes of four consecutive elements
+    int rt[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const float xv = xf[q * 4 + e];
-      int rt;
-      const int nc = neg_code<EXACT2>(xv, mn, invs, (rw >> (8 * e)) & 0xFFu, METRICS ? &rt : nullptr);
+      const int nc = neg_code<EXACT2>(xv, mn, invs, (rw >> (8 * e)) & 0xFFu, METRICS ? &rt[e] : nullptr);
       nacc[q] = (nacc[q] << b) + (uint32_t)nc;
       if (METRICS) {
         const float d = xv - __builtin_fmaf((float)(-nc), scale, mn);
         e2 = __builtin_fmaf(d, d, e2);
         m2 = __builtin_fmaf(xv, xv, m2);
-        v2 += sr_variance_term(rt);
       }
     }
+    if (METRICS) sr_variance_sums(rt, t_sum, t_sq);
   }
   nacc0 = nacc[0];
   nacc1 = nacc[1];
   if (METRICS) {
     *err = e2;
     *mag = m2;
-    *var = (float)v2;
+    *var = (float)(256u * t_sum - t_sq);
   }
 }
 
@@ -423,7 +423,7 @@ __device__ __forceinline__ void quantize_pack_tile_body(
         lds.info[lane] = gi;
         if (METRICS) lds.gscale[lane] = s.scale;
       }
-      if (METRICS) {
+      if (METRICS && S::kLoadsPerGroup > 1) {
         wave_lds_sync();                       // every lane has read its (min, max) pairs
         lds.stat[lane] = make_float2(0.0f, 0.0f);
         lds.gvar[lane] = 0.0f;
@@ -451,6 +451,7 @@ __device__ __forceinline__ void quantize_pack_tile_body(
     //    groups whose reciprocal times 256 overflows is rare.)
     auto quantize_tile = [&](auto exact2) {
       constexpr bool kExact2 = decltype(exact2)::value;
+      [[maybe_unused]] float metric_sums[2][3];  // error, magnitude, variance of the last two loads
 #pragma unroll
       for (int u = 0; u < S::kLoads; ++u) {
         const int grp = (u * S::kGpl + (lane >> S::kLaneLog2)) / S::kLoadsPerGroup;
@@ -473,14 +474,25 @@ __device__ __forceinline__ void quantize_pack_tile_body(
         uint32_t n0, n1;
         if constexpr (METRICS) {
           const float g_scale = lds.gscale[grp];
-          float err, mag, var, unused = 0.0f;
-          quantize_chunk<DT, kExact2, true>(xf[u], g_mn, g_invs, b, rnd[u], n0, n1, g_scale, &err, &mag, &var);
-          seg_sum2<S::kLaneLog2>(err, mag);      // over the group's lanes of this load
-          seg_sum2<S::kLaneLog2>(var, unused);
-          if (lane_in_run == (uint32_t)S::kLpg - 1u) {
-            const float2 acc = lds.stat[grp];    // the group's earlier loads (same lane, in order)
-            lds.stat[grp] = make_float2(acc.x + err, acc.y + mag);
-            lds.gvar[grp] += var;
+          float* sums = metric_sums[u & 1];
+          quantize_chunk<DT, kExact2, true>(xf[u], g_mn, g_invs, b, rnd[u], n0, n1, g_scale, &sums[0], &sums[1], &sums[2]);
+          if (u & 1) {                           // over the group's lanes, two loads at a time
+            seg_sum6<S::kLaneLog2>(metric_sums[0], metric_sums[1]);
+            if (lane_in_run == (uint32_t)S::kLpg - 1u) {
+#pragma unroll
+              for (int h = 0; h < 2; ++h) {
+                const int gh = ((u - 1 + h) * S::kGpl + (lane >> S::kLaneLog2)) / S::kLoadsPerGroup;
+                const float* r = metric_sums[h];
+                if (S::kLoadsPerGroup == 1) {
+                  lds.stat[gh] = make_float2(r[0], r[1]);
+                  lds.gvar[gh] = r[2];
+                } else {
+                  const float2 acc = lds.stat[gh];    // the group's earlier loads (same lane, in order)
+                  lds.stat[gh] = make_float2(acc.x + r[0], acc.y + r[1]);
+                  lds.gvar[gh] += r[2];
+                }
+              }
+            }
           }
         } else if constexpr (kPairs16) {
           quantize_chunk_f16<kExact2>(raw[u], g_mn, g_invs, b, rnd[u], n0, n1);
