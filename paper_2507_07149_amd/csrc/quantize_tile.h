@@ -260,6 +260,34 @@ __device__ __forceinline__ void stage_chunk(uint8_t* stage8, uint32_t addr, uint
   }
 }
 
+// The (min, max) of n <= kMaxFold pairs, by all kThreads threads of a workgroup; every thread has the result.
+constexpr int kFoldPerThread = 8, kMaxFold = kFoldPerThread * kThreads;
+__device__ __forceinline__ float2 fold_pairs(const float2* __restrict__ pairs, int n) {
+  __shared__ float2 wave_pair[kWavesPerBlock];
+  float2 p[kFoldPerThread];
+#pragma unroll
+  for (int j = 0; j < kFoldPerThread; ++j) {
+    const int i = j * kThreads + (int)threadIdx.x;
+    p[j] = pairs[i < n ? i : n - 1];
+  }
+  float mn = vmin3(p[0].x, p[1].x, p[2].x), mn2 = p[3].x, mx = vmax3(p[0].y, p[1].y, p[2].y), mx2 = p[3].y;
+#pragma unroll
+  for (int j = 4; j < kFoldPerThread; j += 2) {
+    mn = vmin(mn, p[j].x); mx = vmax(mx, p[j].y);
+    mn2 = vmin(mn2, p[j + 1].x); mx2 = vmax(mx2, p[j + 1].y);
+  }
+  seg_minmax_x2<6>(mn, mx, mn2, mx2);
+  if ((threadIdx.x & (kWave - 1)) == kWave - 1) wave_pair[threadIdx.x >> 6] = make_float2(vmin(mn, mn2), vmax(mx, mx2));
+  __syncthreads();
+  float2 r = wave_pair[0];
+#pragma unroll
+  for (int w = 1; w < kWavesPerBlock; ++w) {
+    r.x = vmin(r.x, wave_pair[w].x);
+    r.y = vmax(r.y, wave_pair[w].y);
+  }
+  return r;
+}
+
 // B = 1, 2, 4, 8: every group has that width (offsets are computed).  B = 0: per-group widths
 // from `bits`, offsets from `off`.
 // One tile per wave; the hardware schedules the waves.  (A looping variant in which a wave
@@ -278,14 +306,19 @@ __device__ __forceinline__ void stage_chunk(uint8_t* stage8, uint32_t addr, uint
 // RELU = true: x holds z; every element becomes max(z, +0) right after the load, the result is
 // written to out_y in the same layout (out_y may be x itself: a lane only overwrites chunks it
 // has already loaded), and everything else sees y.
-template <int DT, int LPG_LOG2, int B, bool EXT = false, bool METRICS = false, bool RELU = false, int DIV = 1>
+//
+// FOLD (with EXT, one group for the tensor): ext_stat holds n_ext (min, max) pairs that every workgroup reduces for
+// itself, behind the tile's loads; all its waves take part (fold_pairs has a barrier).
+template <int DT, int LPG_LOG2, int B, bool EXT = false, bool METRICS = false, bool RELU = false, int DIV = 1,
+          bool FOLD = false>
 __device__ __forceinline__ void quantize_pack_tile_body(
     typename std::conditional<RELU, const u32x4*, const u32x4* __restrict__>::type x, int64_t tile, int wave_in_block,
     const uint8_t* __restrict__ bits, const uint32_t* __restrict__ off, uint32_t seed_lo, uint32_t seed_hi,
     uint32_t* __restrict__ words, float* __restrict__ out_min, float* __restrict__ out_scale,
     const float2* __restrict__ ext_stat, int64_t tiles_per_group, float* __restrict__ out_metrics,
-    u32x4* out_y) {
+    u32x4* out_y, int n_ext = 0) {
   using S = TileShape<DT, LPG_LOG2, DIV>;
+  static_assert(!FOLD || EXT, "pairs are folded for external statistics");
   static_assert(!EXT || S::kGroups == 1, "external statistics: the tile is part of one group");
   static_assert(!(EXT && METRICS), "metrics are not computed for groups longer than a tile");
   static_assert(!(RELU && (EXT || METRICS)), "the fused max(z, 0) exists for the plain tile kernel only");
@@ -368,7 +401,9 @@ __device__ __forceinline__ void quantize_pack_tile_body(
     uint32_t tile_words;
     {
       float2 st;
-      if constexpr (EXT) {
+      if constexpr (FOLD) {
+        st = fold_pairs(ext_stat, n_ext);
+      } else if constexpr (EXT) {
         st = ext_stat[g0];
       } else if constexpr (kPairs16) {
         uint32_t pk = f2u(lds.stat[(lane & (S::kGroups - 1)) * S::kLoadsPerGroup].x);

@@ -17,14 +17,14 @@ namespace {
 
 constexpr int kBigTile = 4096;   // elements per tile in every max-shape instantiation
 
+// The (min, max) of one tile, or of the elements after the last whole one (tile == n_full_tiles), complete in the wave's last
+// lane.  False: there is no such tile.
 template <int DT>
-__global__ __launch_bounds__(kThreads) void k_tile_minmax(const void* __restrict__ x, int64_t n_full_tiles,
-                                                          int64_t n, float2* __restrict__ partial) {
+__device__ __forceinline__ bool tile_pair(const void* __restrict__ x, int64_t tile, int64_t n_full_tiles, int64_t n, float& mn,
+                                          float& mx) {
   constexpr int kEpl = ElemTraits<DT>::kPerLoad;
   constexpr int kLoads = kBigTile / (kWave * kEpl);
   const int lane = threadIdx.x & (kWave - 1);
-  const int64_t tile = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-  float mn, mx;
   if (tile < n_full_tiles) {
     const u32x4* chunks = static_cast<const u32x4*>(x) + tile * (kLoads * kWave);
     u32x4 v[kLoads];
@@ -60,9 +60,46 @@ __global__ __launch_bounds__(kThreads) void k_tile_minmax(const void* __restrict
     float mn2 = mn, mx2 = mx;
     seg_minmax_x2<6>(mn, mx, mn2, mx2);
   } else {
-    return;
+    return false;
   }
-  if (lane == kWave - 1) partial[tile] = make_float2(mn, mx);
+  return true;
+}
+
+template <int DT>
+__global__ __launch_bounds__(kThreads) void k_tile_minmax(const void* __restrict__ x, int64_t n_full_tiles,
+                                                          int64_t n, float2* __restrict__ partial) {
+  const int64_t tile = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+  float mn, mx;
+  if (tile_pair<DT>(x, tile, n_full_tiles, n, mn, mx) && (threadIdx.x & (kWave - 1)) == kWave - 1)
+    partial[tile] = make_float2(mn, mx);
+}
+
+// One group for the tensor, up to kMaxFold * 8 tiles: a workgroup of 8 waves leaves one pair, so that there are few
+// enough for every workgroup of the quantize pass to reduce them itself (FOLD), and the launch between the two passes and
+// the one for the elements after the last whole tile are gone.  Quantize and dequantize, 2 bits, before / now:
+// binary16 2.3 M elements 21.2 / 14.9 us, 67 M 93 / 77; binary32 31 M 74.0 / 67.9, 51 M 115.4 / 110.1, 67 M 152 / 139.
+// (16 waves: binary32 51 M 115.2, too few of them fit a compute unit; the other sizes within 1 us.)
+constexpr int kFoldThreads = 512, kFoldTiles = kFoldThreads / kWave;
+template <int DT>
+__global__ __launch_bounds__(kFoldThreads) void k_block_minmax(const void* __restrict__ x, int64_t n_full_tiles, int64_t n,
+                                                               float2* __restrict__ partial) {
+  __shared__ float2 wave_pair[kFoldTiles];
+  const int wave = threadIdx.x >> 6;
+  const int64_t first = (int64_t)blockIdx.x * kFoldTiles;
+  const int64_t all = n_full_tiles + (n_full_tiles * kBigTile < n ? 1 : 0);
+  float mn, mx;
+  // (waves past the last tile take it again)
+  (void)tile_pair<DT>(x, first + wave < all ? first + wave : all - 1, n_full_tiles, n, mn, mx);
+  if ((threadIdx.x & (kWave - 1)) == kWave - 1) wave_pair[wave] = make_float2(mn, mx);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float2 r = wave_pair[0];
+    for (int w = 1; w < kFoldTiles; ++w) {
+      r.x = vmin(r.x, wave_pair[w].x);
+      r.y = vmax(r.y, wave_pair[w].y);
+    }
+    partial[blockIdx.x] = r;
+  }
 }
 
 // One workgroup per group: reduce the group's tile pairs (up to N/4096 of them when the whole
@@ -107,15 +144,14 @@ __global__ __launch_bounds__(kReduceThreads) void k_group_reduce(const float2* _
 // The elements after the last full tile, [e_begin, n): all in group g, whose (min, max) is
 // known.  One workgroup, one packed word per thread and iteration.
 template <int DT>
-__global__ __launch_bounds__(kThreads) void k_quantize_pack_tail_ext(
+__device__ __forceinline__ void quantize_pack_tail_ext(
     const void* __restrict__ x, int64_t e_begin, int64_t n, int64_t g, int64_t group_begin,
     const uint8_t* __restrict__ bits, const uint32_t* __restrict__ off, int32_t uniform_bits,
-    const float2* __restrict__ ext_stat, uint32_t seed_lo, uint32_t seed_hi, uint32_t* __restrict__ words,
+    const float2 st, uint32_t seed_lo, uint32_t seed_hi, uint32_t* __restrict__ words,
     float* __restrict__ out_min, float* __restrict__ out_scale) {
   const uint32_t b = uniform_bits ? (uint32_t)uniform_bits : (uint32_t)bits[g];
   const uint32_t group_off = uniform_bits ? (uint32_t)((group_begin * uniform_bits) >> 5) : off[g];
   const uint32_t word_base = group_off + (uint32_t)(((e_begin - group_begin) * b) >> 5);
-  const float2 st = ext_stat[g];
   const GroupScale s = group_scale(st.x, st.y, b);
   if (threadIdx.x == 0 && e_begin == group_begin) {
     out_min[g] = s.mn;
@@ -148,6 +184,39 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack_tail_ext(
 }
 
 template <int DT>
+__global__ __launch_bounds__(kThreads) void k_quantize_pack_tail_ext(
+    const void* __restrict__ x, int64_t e_begin, int64_t n, int64_t g, int64_t group_begin,
+    const uint8_t* __restrict__ bits, const uint32_t* __restrict__ off, int32_t uniform_bits,
+    const float2* __restrict__ ext_stat, uint32_t seed_lo, uint32_t seed_hi, uint32_t* __restrict__ words,
+    float* __restrict__ out_min, float* __restrict__ out_scale) {
+  quantize_pack_tail_ext<DT>(x, e_begin, n, g, group_begin, bits, off, uniform_bits, ext_stat[g], seed_lo, seed_hi, words,
+                             out_min, out_scale);
+}
+
+// The quantize pass of a tensor that is one group, from the pairs k_block_minmax left (one width: a plan with
+// one group has no per-group widths).  When elements are left after the last whole tile the grid has one
+// more workgroup, the first, which takes them.
+template <int DT, int LPG_LOG2, int B>
+__global__ __launch_bounds__(kThreads) void k_quantize_pack_fold(const void* __restrict__ x, int64_t n_tiles, int64_t n,
+                                                                 const float2* __restrict__ pairs, int n_pairs,
+                                                                 uint32_t seed_lo, uint32_t seed_hi,
+                                                                 uint32_t* __restrict__ words, float* __restrict__ out_min,
+                                                                 float* __restrict__ out_scale) {
+  const unsigned tail = n_tiles * kBigTile < n ? 1u : 0u;
+  if (blockIdx.x < tail) {
+    quantize_pack_tail_ext<DT>(x, n_tiles * kBigTile, n, 0, 0, nullptr, nullptr, B, fold_pairs(pairs, n_pairs), seed_lo,
+                               seed_hi, words, out_min, out_scale);
+    return;
+  }
+  const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // waves past the last tile take it again and write the same words: every wave is needed at fold_pairs' barrier
+  const int64_t tile = min((int64_t)(blockIdx.x - tail) * kWavesPerBlock + wave_in_block, n_tiles - 1);
+  quantize_pack_tile_body<DT, LPG_LOG2, B, true, false, false, 1, true>(
+      static_cast<const u32x4*>(x), tile, wave_in_block, nullptr, nullptr, seed_lo, seed_hi, words, out_min, out_scale, pairs,
+      n_tiles, nullptr, nullptr, n_pairs);
+}
+
+template <int DT>
 hipError_t launch_big(const daf_plan_t* p, const void* x, uint32_t seed_lo, uint32_t seed_hi, uint32_t* out_words,
                       float* out_min, float* out_scale, void* scratch, hipStream_t stream) {
   constexpr int kMaxLog2 = (DT == kF32) ? 10 : 9;                // the shape whose tile is one group
@@ -158,6 +227,25 @@ hipError_t launch_big(const daf_plan_t* p, const void* x, uint32_t seed_lo, uint
   const int64_t tpg = (p->num_groups == 1) ? n_partials : p->group_size / kBigTile;
   float2* partial = reinterpret_cast<float2*>(scratch);        // every entry read below is written first
   float2* stat = partial + n_partials;
+
+  const int64_t n_pairs = (n_partials + kFoldTiles - 1) / kFoldTiles;
+  if (p->num_groups == 1 && p->uniform_bits && n_full_tiles > 0 && n_pairs <= kMaxFold) {
+    hipLaunchKernelGGL((k_block_minmax<DT>), dim3((unsigned)n_pairs), dim3(kFoldThreads), 0, stream, x, n_full_tiles, p->n,
+                       partial);
+    const unsigned blocks = (unsigned)((n_full_tiles + kWavesPerBlock - 1) / kWavesPerBlock) + (tail ? 1u : 0u);
+#define DAF_LAUNCH(BITS)                                                                                            \
+  hipLaunchKernelGGL((k_quantize_pack_fold<DT, kMaxLog2, BITS>), dim3(blocks), dim3(kThreads), 0, stream, x,        \
+                     n_full_tiles, p->n, partial, (int)n_pairs, seed_lo, seed_hi, out_words, out_min, out_scale)
+    switch (p->uniform_bits) {
+      case 1: DAF_LAUNCH(1); break;
+      case 2: DAF_LAUNCH(2); break;
+      case 4: DAF_LAUNCH(4); break;
+      case 8: DAF_LAUNCH(8); break;
+      default: return hipErrorInvalidValue;
+    }
+#undef DAF_LAUNCH
+    return hipGetLastError();
+  }
 
   const unsigned blocks1 = (unsigned)((n_partials + kWavesPerBlock - 1) / kWavesPerBlock);
   hipLaunchKernelGGL((k_tile_minmax<DT>), dim3(blocks1), dim3(kThreads), 0, stream, x, n_full_tiles, p->n, partial);

@@ -175,3 +175,42 @@ def test_list_of_more_tensors_than_a_launch_takes(env):
     daf, orc = env
     _roundtrip(daf, orc, F16, [(4096 * (i % 3) + 8 * i + 8, 64, "mixed") for i in range(40)])
     _roundtrip(daf, orc, F32, [(2048 * (i % 3) + 4 * i + 5, 96, 2) for i in range(40)])
+
+
+def _per_tensor(daf, orc, dtype, bits, n):
+    g = torch.Generator().manual_seed(n)
+    x = (torch.randn(n, generator=g) * 3).to(torch_dtype(dtype))
+    x[n // 2] = -41.0
+    x[-1] = 57.0                                           # the last element holds the maximum: the tail counts
+    gs = -(-n // 32) * 32
+    b = np.array([bits], np.uint8)
+    plan = daf.daf_plan((n,), gs, bits)
+    words = torch.full((plan.packed_words,), -1, dtype=torch.int32, device="cuda:0")
+    mn, sc = torch.full((1,), float("nan"), device="cuda:0"), torch.full((1,), float("nan"), device="cuda:0")
+    xd = x.cuda()
+    ow, omn, osc, _ = orc.quantize_pack(to_numpy_bits(x), dtype, gs, b, 77)
+    for call in (daf.daf_quantize_pack, daf.daf_quantize_pack_static):
+        words.fill_(-1)
+        call(plan, xd, 77, words, mn, sc)
+        torch.cuda.synchronize()
+        assert np.array_equal(words.cpu().numpy().view(np.uint32), ow), n
+        assert np.array_equal(mn.cpu().numpy().view(np.uint32), omn.view(np.uint32))
+        assert np.array_equal(sc.cpu().numpy().view(np.uint32), osc.view(np.uint32))
+    plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("bits", [1, 2, 4, 8])
+def test_one_group_per_tensor_at_tile_and_workgroup_edges(env, dtype, bits):
+    """Around one tile, four tiles (a workgroup of the quantize pass) and eight (one of the statistics pass)."""
+    daf, orc = env
+    print("case per tensor", dtype, bits, flush=True)
+    for n in (31, 4095, 4096, 4097, 4096 * 3 + 4095, 4096 * 4, 4096 * 5 + 33, 4096 * 8 - 1, 4096 * 8, 4096 * 9 + 2, 4096 * 33 + 4000):
+        _per_tensor(daf, orc, dtype, bits, n)
+
+
+@pytest.mark.parametrize("n", [2048 * 8 * 4096, 2048 * 8 * 4096 + 1])
+def test_one_group_per_tensor_at_the_limit_of_the_folded_reduction(env, n):
+    daf, orc = env
+    print("case per tensor limit", n, flush=True)
+    _per_tensor(daf, orc, BF16, 2, n)
