@@ -443,4 +443,21 @@ __device__ __forceinline__ float chunk_elem(const uint4& raw, int e) {
   return widen16<DT == kF32 ? kF16 : DT>((e & 1) ? (d >> 16) : (d & 0xFFFFu));
 }
 
+// 64 lanes x 16 bytes from memory straight into LDS: lane l reads base + lane_off, LDS byte lds_base + 16 l is
+// written.  In assembly because the compiler would drain every such load in front of the next LDS read; the
+// kernels count their loads and wait for them themselves.  (No register result; one wait state behind the write of M0.)
+__device__ __forceinline__ void load_to_lds(uint32_t lds_base, uint32_t lane_off, const char* base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(lds_base), "v"(lane_off), "s"(base)
+               : "memory");
+}
+// A pointer that is the same in all lanes, in scalar registers.
+__device__ __forceinline__ const char* uniform_pointer(const char* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
+}
+
 }  // namespace daf

@@ -114,23 +114,6 @@ __host__ __device__ inline TileIndex tile_of_workgroup(int id, int tiles_m, int 
 // Rows of 128 bytes are stored unpadded (a load writes 1 KB of consecutive LDS) with the 16-byte piece p
 // of row r at place p ^ (r / 2 mod 8): no bank conflicts in the counters.
 
-// 64 lanes x 16 bytes from memory straight into LDS: lane l reads base + lane_off and writes LDS byte lds_base + 16 l.
-// Written in assembly because the compiler, which cannot tell the parts of the copies apart, would drain
-// all such loads in front of every LDS read; the counted waits of the main loop take that place.  (The load
-// has no register result; M0 holds the LDS address and needs one wait state after its write.)
-__device__ __forceinline__ void load_to_lds(uint32_t lds_base, uint32_t lane_off, const char* base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :
-               : "s"(lds_base), "v"(lane_off), "s"(base)
-               : "memory");
-}
-__device__ __forceinline__ const char* uniform_pointer(const char* p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-  return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
-}
-
 template <int DT, int GS_LOG2, bool MIXED, bool QUANT>
 __global__ __launch_bounds__(kLinThreads, 2) void k_linear_quantize_pack(
     const char* __restrict__ x, const char* __restrict__ w, int M, int N, int K, uint32_t seed_lo, uint32_t seed_hi,

@@ -35,22 +35,6 @@ struct Wide {
   static_assert(kEntries * 4 == kThreads, "a thread carries one of the four constants of one group");
 };
 
-// 64 lanes x 16 bytes from memory straight into LDS: lane l reads base + lane_off, LDS byte lds_base + 16 l is
-// written.  In assembly because the compiler would drain every such load in front of the next LDS read; the
-// counted wait at the end of a step takes that place.  (No register result; one wait state behind the write of M0.)
-__device__ __forceinline__ void load_to_lds(uint32_t lds_base, uint32_t lane_off, const char* base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :
-               : "s"(lds_base), "v"(lane_off), "s"(base)
-               : "memory");
-}
-__device__ __forceinline__ const char* uniform_pointer(const char* p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-  return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
-}
-
 template <int DT, bool MIXED>
 __global__ __launch_bounds__(Wide::kThreads, 2) void k_unpack_matmul_wide(
     const uint32_t* __restrict__ words, const float* __restrict__ mn, const float* __restrict__ scale,
