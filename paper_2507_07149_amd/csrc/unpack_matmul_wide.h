@@ -35,6 +35,13 @@ struct Wide {
   static_assert(kEntries * 4 == kThreads, "a thread carries one of the four constants of one group");
 };
 
+// load_at for the loads that the wait at the end of a step counts: a relaxed atomic load (an ordinary load instruction
+// at this scope) is never left out, doubled or moved past another load, whether its result is used or not.  Aligned.
+__device__ __forceinline__ uint32_t counted_load(const void* uniform_base, uint32_t byte_off) {
+  const char* base = static_cast<const char*>(uniform_base);
+  return __hip_atomic_load(reinterpret_cast<const uint32_t*>(base + byte_off), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+
 template <int DT, bool MIXED>
 __global__ __launch_bounds__(Wide::kThreads, 2) void k_unpack_matmul_wide(
     const uint32_t* __restrict__ words, const float* __restrict__ mn, const float* __restrict__ scale,
@@ -85,28 +92,28 @@ __global__ __launch_bounds__(Wide::kThreads, 2) void k_unpack_matmul_wide(
   const uint32_t x_store = W::kXAt + xr * (uint32_t)W::kXRow + ((16u * co) ^ (64u * (xr & 3u)));
 
   // Group constants, {min, scale, word offset, width} per group: a thread carries one of the four of one group, which
-  // one depends on its wave only.  No branch: the array is chosen by pointer.  Four widths are read at a time
-  // (the group count is a multiple of 32) and the right one is picked when it is stored.  With one width for all
-  // groups the upper four waves carry what the lower four do.
+  // one depends on its wave only.  No branch: the array is chosen by pointer.  A width is read with the aligned
+  // word that holds it (a step's first group is a multiple of 32) and picked out when it is stored.  With one width for
+  // all groups the upper four waves carry what the lower four do.
   const uint32_t field = MIXED ? uw >> 1 : (uw >> 1) & 1u;
   const uint32_t e = t & 127u, m_row = e / (uint32_t)W::kGroupsPerRow;
   const uint32_t m_j = min(e % (uint32_t)W::kGroupsPerRow, n_groups - 1u);   // (entries past the tile's groups hold the last one again)
   const uint32_t m_goff = m_row * gpr + g_first + m_j;                       // relative to the step's first group
   const bool is_width = field == 3u;
+  const uint32_t skew = (uint32_t)reinterpret_cast<uintptr_t>(bits) & 3u;    // (the caller's array may start anywhere)
   const char* const meta_src = field == 0u   ? reinterpret_cast<const char*>(mn)
                                : field == 1u ? reinterpret_cast<const char*>(scale)
                                : field == 2u ? reinterpret_cast<const char*>(off)
-                                             : reinterpret_cast<const char*>(bits);
+                                             : reinterpret_cast<const char*>(bits) - skew;
   const int meta_log2 = is_width ? 0 : 2;
-  const uint32_t meta_off = is_width ? m_goff & ~3u : 4u * m_goff;
-  const uint32_t meta_shift = is_width ? 8u * (m_goff & 3u) : 0u, meta_mask = is_width ? 0xFFu : ~0u;
+  const uint32_t meta_off = is_width ? (m_goff + skew) & ~3u : 4u * m_goff;
+  const uint32_t meta_shift = is_width ? 8u * ((m_goff + skew) & 3u) : 0u, meta_mask = is_width ? 0xFFu : ~0u;
   const uint32_t meta_dst = W::kMetaAt + 16u * e + 4u * field;
   const int64_t g_begin = m_begin * (int64_t)gpr, g_stride = W::kBM * (int64_t)gpr;
   int64_t gu = g_begin;                                                      // first group of the step whose constants are requested next
   int meta_q = 0;
   auto meta_load = [&](uint32_t& v) __attribute__((always_inline)) {
-    typedef uint32_t any_u32 __attribute__((aligned(1)));
-    v = load_at<any_u32>(meta_src + (gu << meta_log2), opaque(meta_off));
+    v = counted_load(meta_src + (gu << meta_log2), opaque(meta_off));
     gu += ++meta_q < steps ? g_stride : 0;
   };
   auto meta_store = [&](uint32_t v, int q) __attribute__((always_inline)) {
@@ -130,8 +137,8 @@ __global__ __launch_bounds__(Wide::kThreads, 2) void k_unpack_matmul_wide(
   struct Codes { uint32_t wa, wb, b; };
   auto fetch_codes = [&](Codes& c, const Group& g) __attribute__((always_inline)) {
     const uint32_t w0 = g.off + (__umul24(in_group, g.b) >> 5);
-    c.wa = load_at<uint32_t>(words, 4u * w0);
-    c.wb = load_at<uint32_t>(words, 4u * (w0 + (g.b >> 3)));
+    c.wa = counted_load(words, 4u * w0);
+    c.wb = counted_load(words, 4u * (w0 + (g.b >> 3)));
     c.b = g.b;
   };
   auto read_scale = [&](int q) __attribute__((always_inline)) {              // {min, scale}
@@ -244,8 +251,11 @@ __global__ __launch_bounds__(Wide::kThreads, 2) void k_unpack_matmul_wide(
   // ---- step s: products of step s; step s + 2 of x is built; requested: grad_y of s + 3, words of s + 5, group
   // constants of s + 10.  Those of s + 6 enter the ring in the place of s + 2, whose minimum and scale are already in
   // registers; minimum and scale of s + 3 are read from it, and behind the barrier offset and width of s + 6.
+  // LAST: one of the (at most three) steps after the last whole four: everything it needs has been requested, so it requests
+  // nothing more and its wait counts nothing.
   uint32_t x_cur = 0u, x_next = W::kXBytes, x_build = 2 * W::kXBytes;
-  auto do_step = [&](Codes& c, Codes& c_fill, Group& g, uint32_t& v, int s) __attribute__((always_inline)) {
+  auto do_step = [&](auto last, Codes& c, Codes& c_fill, Group& g, uint32_t& v, int s) __attribute__((always_inline)) {
+    constexpr bool LAST = decltype(last)::value != 0;
     const uint32_t gy_copy[2] = {(uint32_t)((s + 1) & (W::kGyCopies - 1)) * W::kGyBytes,      // [half that is read]
                                  (uint32_t)(s & (W::kGyCopies - 1)) * W::kGyBytes};
     const uint32_t x_copy[2] = {x_next, x_cur};
@@ -262,22 +272,25 @@ __global__ __launch_bounds__(Wide::kThreads, 2) void k_unpack_matmul_wide(
         asm volatile("" : "+v"(h.v[slot - 2]));     // here, not where it is stored
       }
       if (slot == 10) end_build(h, x_build);
-      if (slot == 4) fetch_codes(c_fill, g);        // words of s + 5
       if (slot == 1) ms_next = read_scale(s + 3);
-      if (slot == 6) {
+      if (!LAST && slot == 4) fetch_codes(c_fill, g);        // words of s + 5
+      if (!LAST && slot == 6) {
         meta_store(v, s + 6);
-        meta_load(v);                               // constants of s + 10
+        meta_load(v);                                        // constants of s + 10
       }
-      if (slot >= 11 && slot < 15) load_gy(s + 3, slot - 11);
+      if (!LAST && slot >= 11 && slot < 15) load_gy(s + 3, slot - 11);
       __builtin_amdgcn_sched_barrier(0);
     }
     // grad_y of s + 2 has landed when at most the loads behind it are in flight: two words and a constant of s, four
-    // rows of grad_y of s + 3
-    asm volatile("s_waitcnt vmcnt(7) lgkmcnt(0)" ::: "memory");
+    // rows of grad_y of s + 3.  (All seven are loads that the compiler may not drop: counted_load, load_to_lds.)
+    if (LAST)
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(7) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    fetch_group(g, s + 6);
+    if (!LAST) fetch_group(g, s + 6);
     ms = ms_next;
     const uint32_t free_copy = x_cur;
     x_cur = x_next;
@@ -286,14 +299,14 @@ __global__ __launch_bounds__(Wide::kThreads, 2) void k_unpack_matmul_wide(
   };
   int s = 0;
   for (; s + 4 <= steps; s += 4) {
-    do_step(codes[0], codes[3], group, mv[0], s);
-    do_step(codes[1], codes[0], group, mv[1], s + 1);
-    do_step(codes[2], codes[1], group, mv[2], s + 2);
-    do_step(codes[3], codes[2], group, mv[3], s + 3);
+    do_step(Index<0>{}, codes[0], codes[3], group, mv[0], s);
+    do_step(Index<0>{}, codes[1], codes[0], group, mv[1], s + 1);
+    do_step(Index<0>{}, codes[2], codes[1], group, mv[2], s + 2);
+    do_step(Index<0>{}, codes[3], codes[2], group, mv[3], s + 3);
   }
-  if (s < steps) do_step(codes[0], codes[3], group, mv[0], s);
-  if (s + 1 < steps) do_step(codes[1], codes[0], group, mv[1], s + 1);
-  if (s + 2 < steps) do_step(codes[2], codes[1], group, mv[2], s + 2);
+  if (s < steps) do_step(Index<1>{}, codes[0], codes[3], group, mv[0], s);
+  if (s + 1 < steps) do_step(Index<1>{}, codes[1], codes[0], group, mv[1], s + 1);
+  if (s + 2 < steps) do_step(Index<1>{}, codes[2], codes[1], group, mv[2], s + 2);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may arrive in LDS after the work-group has ended
 
   // ---- epilogue: register r of a 32 x 32 block is row 8*(r/4) + 4*(lane/32) + r%4, column lane%32 ----

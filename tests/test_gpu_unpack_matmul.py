@@ -150,6 +150,64 @@ def test_grad_weight_512_by_128_tile(env, steps, N, K, gs, bits, dtype):
     plan.destroy()
 
 
+# The same kernel where a wave's loads are furthest from its neighbours': many work-groups, grad_y from memory, and a number
+# of steps that leaves three after the last whole four (32768 x 3072 x 768: slices of 146 and 147 steps; 352 x 4096 x 4096:
+# 256 tiles, not sliced, 11 steps), with one width, whose steps have the fewest waits of their own, and with several.
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("M,N,K,gs,bits,dtype", [(32768, 3072, 768, 128, 2, F16), (32768, 3072, 768, 128, "mixed", F16),
+                                                 (32768, 3072, 768, 64, 4, BF16), (352, 4096, 4096, 64, 8, F16),
+                                                 (352, 4096, 4096, 128, 1, BF16)])
+def test_grad_weight_512_by_128_tile_three_steps_left(env, M, N, K, gs, bits, dtype):
+    daf, orc = env
+    print("case three steps left", M, N, K, gs, bits, dtype, flush=True)
+    g = torch.Generator().manual_seed(M + K)
+    x = torch.randn(M, K, generator=g).to(torch_dtype(dtype))
+    gy = (torch.randn(M, N, generator=g) * 0.5).to(torch_dtype(dtype))
+    b = _widths(M * K // gs, bits, M)
+    ow, omn, osc, _ = orc.quantize_pack(to_numpy_bits(x), dtype, gs, b, M)
+    xh = orc.widen(orc.unpack_dequantize(ow, omn, osc, b, M * K, gs, dtype)[0], dtype).reshape(M, K).astype(np.float64)
+    plan = daf.daf_plan((M, K), gs, torch.from_numpy(b).cuda() if b.size > 1 else int(b[0]))
+    ws = torch.empty(max(daf.daf_unpack_matmul_workspace_bytes(plan, N, K), 16), dtype=torch.uint8, device="cuda:0")
+    words, mn, sc, gyd = torch.from_numpy(ow.view(np.int32)).cuda(), torch.from_numpy(omn).cuda(), torch.from_numpy(osc).cuda(), gy.cuda()
+    outs = [torch.full((N, K), float("nan"), device="cuda:0") for _ in range(3)]
+    for out in outs:
+        daf.daf_unpack_matmul_grad_weight(plan, words, mn, sc, gyd, out, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    gd = gy.double().numpy()
+    want, mag = gd.T @ xh, np.abs(gd).T @ np.abs(xh)
+    assert np.all(np.abs(outs[0].cpu().numpy() - want) <= 2.0 * M * 2.0 ** -24 * mag + 1e-30)
+    plan.destroy()
+
+
+@pytest.mark.parametrize("start", [1, 2, 3])
+def test_grad_weight_512_by_128_tile_widths_at_any_address(env, start):
+    """The widths may be handed in at any byte address: the same result as with the plan's own copy."""
+    daf, orc = env
+    M, N, K, gs = 160, 4096, 4096, 96 if start == 2 else 32
+    K = 3840 if gs == 96 else K                                               # (groups end with the rows)
+    N = 4608 if gs == 96 else N
+    print("case widths at", start, flush=True)
+    g = torch.Generator().manual_seed(start)
+    x = torch.randn(M * K, generator=g).to(torch.bfloat16).cuda()
+    gy = torch.randn(M, N, generator=g).to(torch.bfloat16).cuda()
+    G = M * K // gs
+    store = torch.zeros(G + start + 4, dtype=torch.uint8, device="cuda:0")
+    bits = store[start: start + G]
+    bits.copy_(torch.from_numpy(_widths(G, "mixed", start)))
+    plan = daf.daf_plan((M, K), gs, bits.clone())
+    words = torch.zeros(plan.packed_words, dtype=torch.int32, device="cuda:0")
+    mn, sc = torch.empty(G, device="cuda:0"), torch.empty(G, device="cuda:0")
+    daf.daf_quantize_pack(plan, x, 5, words, mn, sc)
+    ws = torch.empty(max(daf.daf_unpack_matmul_workspace_bytes(plan, N, K), 16), dtype=torch.uint8, device="cuda:0")
+    own, given = torch.empty(N, K, device="cuda:0"), torch.empty(N, K, device="cuda:0")
+    daf.daf_unpack_matmul_grad_weight(plan, words, mn, sc, gy, own, ws)
+    daf.daf_unpack_matmul_grad_weight(plan, words, mn, sc, gy, given, ws, bits=bits)
+    torch.cuda.synchronize()
+    assert torch.equal(own, given) and bool(own.abs().sum() > 0)
+    plan.destroy()
+
+
 def _widths(G, bits, seed):
     return (np.random.default_rng(seed).choice([1, 2, 4, 8], G).astype(np.uint8) if bits == "mixed"
             else np.array([bits], np.uint8))
