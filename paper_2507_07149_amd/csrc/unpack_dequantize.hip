@@ -394,7 +394,10 @@ struct alignas(16) TileLdsAny {
   TileGroup group[kWave];
 };
 
-template <int DT, int B, bool RELU_BWD>
+// LONG: groups of more than 32768 elements.  Kernels of their own: with the choice made by every chunk the others
+// paid for it (groups of 768, 199 M elements, quantize and dequantize: binary16, 4 bits 183.2 us, apart 174.3; binary32,
+// 2 bits 290.6 and 281.1).
+template <int DT, int B, bool RELU_BWD, bool LONG>
 __device__ __forceinline__ void unpack_dequantize_tile_any_body(
     int64_t tile, int wave_in_block, const uint32_t* __restrict__ words, const float* __restrict__ mn,
     const float* __restrict__ scale, const uint8_t* __restrict__ bits, const uint32_t* __restrict__ off, int32_t gs,
@@ -413,7 +416,7 @@ __device__ __forceinline__ void unpack_dequantize_tile_any_body(
   const int64_t g_first = e_tile0 / gs;                          // once per wave
   const uint32_t rem0 = (uint32_t)(e_tile0 - g_first * gs);      // the tile starts this far into its first group
   const int groups = (int)((rem0 + (uint32_t)kElems - 1u) / (uint32_t)gs) + 1;   // at most 64: checked by the launcher
-  auto group_of = [&](uint32_t e) { return gs_magic ? __umulhi(e, gs_magic) : (e >= (uint32_t)gs ? 1u : 0u); };
+  auto group_of = [&](uint32_t e) { return LONG ? (e >= (uint32_t)gs ? 1u : 0u) : __umulhi(e, gs_magic); };
 
   TileGroup mine;
   mine.mn = 0.0f; mine.scale = 0.0f; mine.b = B ? (uint32_t)B : 1u; mine.woff = 0u;
@@ -439,15 +442,17 @@ __device__ __forceinline__ void unpack_dequantize_tile_any_body(
   } else {
     const uint32_t b_first = (uint32_t)__builtin_amdgcn_readlane((int)mine.b, 0);
     const uint32_t off_first = (uint32_t)__builtin_amdgcn_readlane((int)my_off, 0);
-    const uint32_t first_word = off_first + (uint32_t)(((uint64_t)rem0 * b_first) >> 5);
+    const uint32_t first_word = off_first + (LONG ? (uint32_t)(((uint64_t)rem0 * b_first) >> 5) : (rem0 * b_first) >> 5);
     const uint32_t e_last = rem0 + (uint32_t)(kElems - kEpl);                     // the tile's last chunk
     const int gl_last = __builtin_amdgcn_readfirstlane((int)group_of(e_last));
     const uint32_t b_last = (uint32_t)__builtin_amdgcn_readlane((int)mine.b, gl_last);
     const uint32_t off_last = (uint32_t)__builtin_amdgcn_readlane((int)my_off, gl_last);
-    // bits up to the end of the last chunk, from the start of its group or, in the tile's first group, of the run
-    const uint32_t bit_end = (gl_last == 0 ? (uint32_t)kElems : e_last - (uint32_t)gl_last * (uint32_t)gs + (uint32_t)kEpl) * b_last;
-    const uint32_t tile_words = (gl_last == 0 ? 0u : off_last - first_word) + ((bit_end + 31u) >> 5);   // <= kMaxWords
-    mine.woff = lane == 0 ? 0u : my_off - first_word;   // the first group's place is the start of the run
+    // Bits up to the end of the last chunk, from the start of its group; modulo 2^32 the first group may start before the
+    // run.  A long first group's bits do not fit 32 bits: its places count from the start of the run.
+    const bool from_run = LONG && gl_last == 0;
+    const uint32_t bit_end = (from_run ? (uint32_t)kElems : e_last - (uint32_t)gl_last * (uint32_t)gs + (uint32_t)kEpl) * b_last;
+    const uint32_t tile_words = (from_run ? 0u : off_last - first_word) + ((bit_end + 31u) >> 5);   // <= kMaxWords
+    mine.woff = LONG && lane == 0 ? 0u : my_off - first_word;
 #pragma unroll
     for (int j = 0; j < kWordLoads; ++j) {
       const uint32_t i = (uint32_t)(j * kWave + lane);
@@ -469,7 +474,7 @@ __device__ __forceinline__ void unpack_dequantize_tile_any_body(
     const uint32_t b = kMixed ? g[u].b : (uint32_t)B;
     uint32_t widx;
     if (kMixed) {
-      bit[u] = (gl == 0u ? e0 : rem0 + e0 - gl * (uint32_t)gs) * b;   // bit position inside the run (first group), inside the group
+      bit[u] = (LONG && gl == 0u ? e0 : rem0 + e0 - gl * (uint32_t)gs) * b;   // bit position inside the group (the run)
       widx = g[u].woff + (bit[u] >> 5);
     } else {
       bit[u] = e0 * b;                                           // bit position inside the tile's run
@@ -490,7 +495,7 @@ __device__ __forceinline__ void unpack_dequantize_tile_any_body(
   }
 }
 
-template <int DT, int B, bool RELU_BWD>
+template <int DT, int B, bool RELU_BWD, bool LONG>
 __global__ __launch_bounds__(kThreads) DAF_TILE_WAVES void k_unpack_dequantize_tile_any(
     const uint32_t* __restrict__ words, const float* __restrict__ mn, const float* __restrict__ scale,
     const uint8_t* __restrict__ bits, const uint32_t* __restrict__ off, int64_t n_tiles, int32_t gs, uint32_t gs_magic,
@@ -508,7 +513,7 @@ __global__ __launch_bounds__(kThreads) DAF_TILE_WAVES void k_unpack_dequantize_t
   const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t tile = (int64_t)(blockIdx.x - (left ? 1u : 0u)) * kWavesPerBlock + wave_in_block;
   if (tile >= n_tiles) return;
-  unpack_dequantize_tile_any_body<DT, B, RELU_BWD>(tile, wave_in_block, words, mn, scale, bits, off, gs, gs_magic, G, out,
+  unpack_dequantize_tile_any_body<DT, B, RELU_BWD, LONG>(tile, wave_in_block, words, mn, scale, bits, off, gs, gs_magic, G, out,
                                                    grad, cached != 0);
 }
 
@@ -593,7 +598,7 @@ struct AnyTileBatch {
 };
 static_assert(sizeof(AnyTileBatch) <= 4096, "kernel arguments");
 
-template <int DT, int B>
+template <int DT, int B, bool LONG>
 __global__ __launch_bounds__(kThreads) DAF_TILE_WAVES void k_unpack_dequantize_tile_any_batch(const AnyTileBatch batch) {
   const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t gtile = (int64_t)blockIdx.x * kWavesPerBlock + wave_in_block;
@@ -604,7 +609,7 @@ __global__ __launch_bounds__(kThreads) DAF_TILE_WAVES void k_unpack_dequantize_t
   if ((tile + 1) * kTileChunks > e.t.n_chunks)
     left_over_chunks<DT, B>(e.t, tile, -1);
   else
-    unpack_dequantize_tile_any_body<DT, B, false>(tile, wave_in_block, e.t.words, e.t.mn, e.t.scale, e.t.bits, e.t.off,
+    unpack_dequantize_tile_any_body<DT, B, false, LONG>(tile, wave_in_block, e.t.words, e.t.mn, e.t.scale, e.t.bits, e.t.off,
                                                   e.t.gs, e.magic, e.num_groups, e.t.out, nullptr, e.t.cached != 0);
 }
 
@@ -690,11 +695,14 @@ hipError_t launch_dtype(const daf_plan_t* p, const uint32_t* words, const float*
   if (any_tiles > 0) {
     const bool left = any_tiles * kTileChunks * kEpl < p->n;
     const unsigned blocks = (unsigned)((any_tiles + kWavesPerBlock - 1) / kWavesPerBlock) + (left ? 1u : 0u);
-#define DAF_LAUNCH(BITS)                                                                                          \
-  hipLaunchKernelGGL((k_unpack_dequantize_tile_any<DT, BITS, RELU_BWD>), dim3(blocks), dim3(kThreads), 0, stream,  \
-                     words, mn, scale, d_bits, p->d_off, any_tiles, p->group_size, magic, p->num_groups,          \
+#define DAF_LAUNCH_L(BITS, LONG)                                                                                  \
+  hipLaunchKernelGGL((k_unpack_dequantize_tile_any<DT, BITS, RELU_BWD, LONG>), dim3(blocks), dim3(kThreads), 0,    \
+                     stream, words, mn, scale, d_bits, p->d_off, any_tiles, p->group_size, magic, p->num_groups,  \
                      static_cast<u32x4*>(out_x), static_cast<const u32x4*>(grad), p->output_cached, p->n / kEpl,  \
                      p->n)
+#define DAF_LAUNCH(BITS)                 \
+  if (magic) DAF_LAUNCH_L(BITS, false);  \
+  else DAF_LAUNCH_L(BITS, true)
     switch (p->uniform_bits) {
       case 0: DAF_LAUNCH(0); break;
       case 1: DAF_LAUNCH(1); break;
@@ -704,6 +712,7 @@ hipError_t launch_dtype(const daf_plan_t* p, const uint32_t* words, const float*
       default: return hipErrorInvalidValue;
     }
 #undef DAF_LAUNCH
+#undef DAF_LAUNCH_L
     return hipGetLastError();
   }
   if constexpr (kEpl == 8) {
@@ -793,19 +802,24 @@ hipError_t launch_tiles(AnyTileBatch& b, int bits, hipStream_t stream) {
   hipError_t err = hipSuccess;
   if (b.n > 0) {
     const unsigned blocks = (unsigned)((b.e[b.n - 1].t.tile_end + kWavesPerBlock - 1) / kWavesPerBlock);
-#define DAF_LAUNCH(BITS) hipLaunchKernelGGL((k_unpack_dequantize_tile_any_batch<DT, BITS>), dim3(blocks), dim3(kThreads), 0, stream, b)
+#define DAF_LAUNCH_L(BITS, LONG) \
+  hipLaunchKernelGGL((k_unpack_dequantize_tile_any_batch<DT, BITS, LONG>), dim3(blocks), dim3(kThreads), 0, stream, b)
+#define DAF_LAUNCH(BITS)                           \
+  if (b.e[0].magic) DAF_LAUNCH_L(BITS, false);     \
+  else DAF_LAUNCH_L(BITS, true)
     switch (bits) {
       case 0: DAF_LAUNCH(0); break;
       case 1: DAF_LAUNCH(1); break;
       case 2: DAF_LAUNCH(2); break;
       case 4: DAF_LAUNCH(4); break;
       case 8:
-        if constexpr (DT != kF32) DAF_LAUNCH(8);       // (binary32 with 8 bits for every group: the chunk kernel)
+        if constexpr (DT != kF32) { DAF_LAUNCH(8); }   // (binary32 with 8 bits for every group: the chunk kernel)
         else return hipErrorInvalidValue;
         break;
       default: return hipErrorInvalidValue;
     }
 #undef DAF_LAUNCH
+#undef DAF_LAUNCH_L
     err = hipGetLastError();
   }
   return err;
@@ -879,6 +893,7 @@ hipError_t launch_items(const daf_dequantize_item_t* items, int32_t n_items, hip
     if (tile_path_tiles<DT>(p, &gs_log2) > 0) {
       add_tiles(tbatch, tcur_bits);
     } else if (any_tile_path_tiles<DT>(p, &magic) > 0) {
+      if (abatch.n > 0 && (abatch.e[0].magic != 0u) != (magic != 0u)) tflush(abatch, acur_bits);     // (two kernels)
       const int at = add_tiles(abatch, acur_bits);
       abatch.e[at].num_groups = p->num_groups;
       abatch.e[at].magic = magic;
