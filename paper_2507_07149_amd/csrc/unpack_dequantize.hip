@@ -239,6 +239,8 @@ __global__ __launch_bounds__(kThreads) void k_unpack_dequantize_chunk(
 // shorter than one word per lane.
 constexpr int kTileChunksPerLane = 8;
 constexpr int kTileChunks = kWave * kTileChunksPerLane;           // 512
+constexpr int kTileChunksLog2 = 9;
+static_assert(kTileChunks == 1 << kTileChunksLog2, "whole tiles are counted by a shift");
 constexpr int kWavesPerBlock = kThreads / kWave;
 
 struct alignas(16) TileGroup {   // what a chunk needs to know about its group
@@ -284,7 +286,9 @@ __device__ __forceinline__ void unpack_dequantize_tile_body(
     mine.scale = scale[g0 + lane];
     if (kMixed) mine.b = bits[g0 + lane];
   }
-  if (kMixed) tile_base = off[g0];
+  // (readfirstlane: in the kernel for ragged lists the compiler would keep the value in a vector register and wait for
+  // every load of words before it issued the next: 35 M binary16 elements, four widths: 48 us instead of 42)
+  if (kMixed) tile_base = (uint32_t)__builtin_amdgcn_readfirstlane((int)off[g0]);
   else tile_base = (uint32_t)tile * (uint32_t)(kElems / 32 * B);
   u32x4 gq[RELU_BWD ? U : 1];
   if (RELU_BWD) {
@@ -550,8 +554,8 @@ struct TileBatchEntry {
   const uint8_t* bits;
   const uint32_t* off;
   u32x4* out;
-  int64_t tile_end;                                 // tiles of this and all earlier entries
-  int64_t n_chunks;                                 // the entry's last tile may reach past them
+  int64_t tile_end;                                 // waves of this and all earlier entries
+  int64_t n_chunks;
   int32_t gs, gs_log2;
   int32_t cached;                                   // the plan's output store policy
 };
@@ -562,16 +566,23 @@ struct TileBatch {
   int32_t n;
 };
 
-// The chunks of an entry after its last whole tile, one wave, the chunk kernel's way: they ride along instead of having a
-// launch of their own per list or per tensor (24 ragged binary16 tensors of 58 MB: 73 -> 40 us with groups of 128).
+// The chunks of an entry after its last whole tile, the chunk kernel's way: they ride along instead of having a launch of
+// their own per list or per tensor (24 ragged binary16 tensors of 58 MB: 73 -> 40 us with groups of 128).  Two chunks per
+// lane, up to four waves: eight on one wave take a third more registers than a tile does.
+constexpr int kLeftChunksPerLane = 2, kLeftChunks = kWave * kLeftChunksPerLane;
+__host__ __device__ inline int64_t waves_of_entry(int64_t n_chunks) {
+  return n_chunks / kTileChunks + (n_chunks % kTileChunks + kLeftChunks - 1) / kLeftChunks;
+}
 template <int DT, int B>
-__device__ __forceinline__ void left_over_chunks(const TileBatchEntry& e, int64_t tile, int32_t gs_shift) {
-  unpack_dequantize_block<DT, B == 0, false, kWave, kTileChunksPerLane>(0, e.words, e.mn, e.scale, e.bits, e.off, B,
-                                                                        e.n_chunks, e.gs, gs_shift, e.out, nullptr,
-                                                                        e.cached != 0, tile * kTileChunks);
+__device__ __forceinline__ void left_over_chunks(const TileBatchEntry& e, int64_t wave, int64_t whole_tiles, int32_t gs_shift) {
+  unpack_dequantize_block<DT, B == 0, false, kWave, kLeftChunksPerLane>(
+      wave - whole_tiles, e.words, e.mn, e.scale, e.bits, e.off, B, e.n_chunks, e.gs, gs_shift, e.out, nullptr,
+      e.cached != 0, whole_tiles * kTileChunks);
 }
 
-template <int DT, int B>
+// RAGGED: some entry has chunks after its last whole tile.  A list without any has a kernel without that code, which
+// costs the tiles 1 to 2 us per launch (17 bfloat16 tensors, 35 M elements, four widths: 21.3 us with it, 18.7 without).
+template <int DT, int B, bool RAGGED>
 __global__ __launch_bounds__(kThreads) DAF_TILE_WAVES void k_unpack_dequantize_tile_batch(const TileBatch batch) {
   const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t gtile = (int64_t)blockIdx.x * kWavesPerBlock + wave_in_block;
@@ -579,11 +590,15 @@ __global__ __launch_bounds__(kThreads) DAF_TILE_WAVES void k_unpack_dequantize_t
   if (t >= batch.n) return;                          // past the last tile (the grid is whole workgroups)
   const TileBatchEntry e = batch.e[t];               // by value: one scalar load of the whole descriptor
   const int64_t tile = gtile - (t ? batch.e[t - 1].tile_end : 0);
-  if ((tile + 1) * kTileChunks > e.n_chunks)
-    left_over_chunks<DT, B>(e, tile, e.gs_log2);
-  else
-    unpack_dequantize_tile_body<DT, B, false>(tile, wave_in_block, e.words, e.mn, e.scale, e.bits, e.off, e.gs_log2, e.out,
-                                              nullptr, e.cached != 0);
+  if constexpr (RAGGED) {
+    const int64_t whole = e.n_chunks >> kTileChunksLog2;
+    if (tile >= whole) {
+      left_over_chunks<DT, B>(e, tile, whole, e.gs_log2);
+      return;
+    }
+  }
+  unpack_dequantize_tile_body<DT, B, false>(tile, wave_in_block, e.words, e.mn, e.scale, e.bits, e.off, e.gs_log2, e.out,
+                                            nullptr, e.cached != 0);
 }
 
 struct AnyTileBatchEntry {
@@ -606,8 +621,9 @@ __global__ __launch_bounds__(kThreads) DAF_TILE_WAVES void k_unpack_dequantize_t
   if (t >= batch.n) return;                          // past the last tile (the grid is whole workgroups)
   const AnyTileBatchEntry e = batch.e[t];
   const int64_t tile = gtile - (t ? batch.e[t - 1].t.tile_end : 0);
-  if ((tile + 1) * kTileChunks > e.t.n_chunks)
-    left_over_chunks<DT, B>(e.t, tile, -1);
+  const int64_t whole = e.t.n_chunks >> kTileChunksLog2;
+  if (tile >= whole)
+    left_over_chunks<DT, B>(e.t, tile, whole, -1);
   else
     unpack_dequantize_tile_any_body<DT, B, false, LONG>(tile, wave_in_block, e.t.words, e.t.mn, e.t.scale, e.t.bits, e.t.off,
                                                   e.t.gs, e.magic, e.num_groups, e.t.out, nullptr, e.t.cached != 0);
@@ -783,7 +799,13 @@ hipError_t launch_tiles(TileBatch& b, int bits, hipStream_t stream) {
   hipError_t err = hipSuccess;
   if (b.n > 0) {
     const unsigned blocks = (unsigned)((b.e[b.n - 1].tile_end + kWavesPerBlock - 1) / kWavesPerBlock);
-#define DAF_LAUNCH(BITS) hipLaunchKernelGGL((k_unpack_dequantize_tile_batch<DT, BITS>), dim3(blocks), dim3(kThreads), 0, stream, b)
+    bool ragged = false;
+    for (int i = 0; i < b.n; ++i) ragged |= b.e[i].n_chunks % kTileChunks != 0;
+#define DAF_LAUNCH_R(BITS, RAGGED) \
+  hipLaunchKernelGGL((k_unpack_dequantize_tile_batch<DT, BITS, RAGGED>), dim3(blocks), dim3(kThreads), 0, stream, b)
+#define DAF_LAUNCH(BITS)                     \
+  if (ragged) DAF_LAUNCH_R(BITS, true);      \
+  else DAF_LAUNCH_R(BITS, false)
     switch (bits) {
       case 0: DAF_LAUNCH(0); break;
       case 1: DAF_LAUNCH(1); break;
@@ -793,6 +815,7 @@ hipError_t launch_tiles(TileBatch& b, int bits, hipStream_t stream) {
       default: return hipErrorInvalidValue;
     }
 #undef DAF_LAUNCH
+#undef DAF_LAUNCH_R
     err = hipGetLastError();
   }
   return err;
@@ -870,7 +893,7 @@ hipError_t launch_items(const daf_dequantize_item_t* items, int32_t n_items, hip
     int32_t gs_log2 = 0;
     uint32_t magic = 0;
     auto add_tiles = [&](auto& b, int& cur_bits) {
-      const int64_t n_tiles = (n_chunks + kTileChunks - 1) / kTileChunks;      // the last one may be short
+      const int64_t n_tiles = waves_of_entry(n_chunks);
       if (b.n == kMaxTileBatch || (b.n > 0 && p->uniform_bits != cur_bits) ||
           (b.n > 0 && tile_entry(b, b.n - 1).tile_end + n_tiles > 0x7fffffff))
         tflush(b, cur_bits);

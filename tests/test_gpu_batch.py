@@ -170,6 +170,20 @@ def test_long_groups_and_groups_of_32_dequantize_through_tiles(env, dtype, bits)
         plan.destroy()
 
 
+@pytest.mark.parametrize("dtype", [F32, F16])
+@pytest.mark.parametrize("bits", [2, 8, "mixed"])
+@pytest.mark.parametrize("gs", [128, 96])
+def test_list_left_over_chunks(env, dtype, bits, gs):
+    """A tensor's chunks after its last whole tile of 512 go to waves of 128: none, one, and the edges of a wave and of a tile
+    in one list, with and without elements after the last chunk; then a list without any left over."""
+    daf, orc = env
+    epl = 4 if dtype == F32 else 8
+    print("case left over", dtype, bits, gs, flush=True)
+    left = [0, 1, 63, 127, 128, 129, 255, 256, 257, 384, 385, 511]
+    _roundtrip(daf, orc, dtype, [((512 * (1 + i % 3) + c) * epl + (i % 2) * 3, gs, bits) for i, c in enumerate(left)])
+    _roundtrip(daf, orc, dtype, [(512 * k * epl, gs, bits) for k in (1, 2, 7)])
+
+
 def test_list_of_more_tensors_than_a_launch_takes(env):
     """Forty ragged tensors: two launches per kind, every tensor's short last tile in one of them."""
     daf, orc = env
