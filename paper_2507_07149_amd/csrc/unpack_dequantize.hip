@@ -525,20 +525,25 @@ __global__ __launch_bounds__(kThreads) DAF_TILE_WAVES void k_unpack_dequantize_t
 // (binary32 with 8 bits for every group stays with the chunk kernel: 0.76-0.78 of the memory rate
 // there against 0.70-0.74 through tiles, measured on 2^27 elements with groups of 96 ... 11008)
 template <int DT>
-int64_t any_tile_path_tiles(const daf_plan_t* p, uint32_t* magic) {
+int64_t any_tile_path_tiles(const daf_plan_t* p, bool relu_bwd, uint32_t* magic) {
   constexpr int kElems = kTileChunks * ElemTraits<DT>::kPerLoad;
   const int64_t gs = p->group_size;
   if (DT == kF32 && p->uniform_bits == 8) return 0;
   if (gs < 64 || gs % 32 != 0 || ((gs & (gs - 1)) == 0 && gs <= kElems)) return 0;
   if (gs > 32768 || (gs & (gs - 1)) == 0) {
-    // Long groups: one of a tile's two round trips is shorter than the chunk kernel's three (a quantize and a dequantize call,
-    // chunk kernel / tiles: binary16, 16384 per group, four widths, 33 M elements 38.3 / 35.8 us, 246 M 215 / 210;
-    // one group, 2 bits, 33 M 44.7 / 42.9, 246 M 282 / 272), except where many words a lane stream as well without
-    // tiles: binary32 beyond 67 M elements (197 M, 2 bits: 410 / 418; 33 M: 79.5 / 76.8), 4 bits of a 16-bit format there
-    // (291 / 304; 33 M: 46.9 / 45.4), and 1 bit below it (39.6 / 41.0; 246 M: 269 / 258).
+    // Long groups.  A tile makes two round trips to memory where the chunk kernel makes three (a quantize and a dequantize
+    // call on three tensors in turn, chunk kernel / tiles; binary16, groups of 40000: 2 bits, 34.6 M elements 45.6 / 41.6 us,
+    // 75 M 85.1 / 80.7; four widths 53.6 / 50.4 and 101 / 96.9; 8 bits, groups of 65536, 50.2 / 49.4, 199 M 228.7 / 227.4),
+    // except where many words a lane stream as well without tiles: binary32 beyond 67 M elements (2 bits, 197 M 410 / 418; just
+    // below the limit 114.6 / 111.5, four widths 137.1 / 130.8), 4 bits of a 16-bit format there (246 M 291 / 304; just below
+    // 78.0 / 78.1, 34.6 M 46.0 / 43.9), and 1 bit below it (34.6 M 39.6 / 41.0; 75 M 81.3 / 76.1).
     const bool small = p->n <= (int64_t)1 << 26;
     if (DT == kF32 || p->uniform_bits == 4) { if (!small) return 0; }
     else if (p->uniform_bits == 1 && small) return 0;
+    // With a gradient to read beside it the chunk kernel's shorter waves stream better, but for small tensors (the call alone,
+    // groups of 8192, four widths: binary16, 16.8 M elements 14.5 / 14.0 us, 21 M 17.2 / 19.1, 66 M 45.8 / 50.2;
+    // binary32, 8.4 M 13.6 / 12.2, 12.6 M 19.5 / 19.8, 66 M 86.1 / 91.0; binary16, 2 bits 13.6 / 12.9, 16.6 / 17.3, 44.7 / 47.3).
+    if (relu_bwd && p->n > (int64_t)1 << (DT == kF32 ? 23 : 24)) return 0;
   }
   if ((gs - 1 + kElems - 1) / gs + 1 > kWave) return 0;           // groups that touch one tile
   if (p->num_groups >= ((int64_t)1 << 31)) return 0;
@@ -707,7 +712,7 @@ hipError_t launch_dtype(const daf_plan_t* p, const uint32_t* words, const float*
   int32_t gs_log2 = 0;
   const int64_t n_tiles = tile_path_tiles<DT>(p, &gs_log2);
   uint32_t magic = 0;
-  const int64_t any_tiles = n_tiles == 0 ? any_tile_path_tiles<DT>(p, &magic) : 0;
+  const int64_t any_tiles = n_tiles == 0 ? any_tile_path_tiles<DT>(p, RELU_BWD, &magic) : 0;
   if (any_tiles > 0) {
     const bool left = any_tiles * kTileChunks * kEpl < p->n;
     const unsigned blocks = (unsigned)((any_tiles + kWavesPerBlock - 1) / kWavesPerBlock) + (left ? 1u : 0u);
@@ -915,7 +920,7 @@ hipError_t launch_items(const daf_dequantize_item_t* items, int32_t n_items, hip
     };
     if (tile_path_tiles<DT>(p, &gs_log2) > 0) {
       add_tiles(tbatch, tcur_bits);
-    } else if (any_tile_path_tiles<DT>(p, &magic) > 0) {
+    } else if (any_tile_path_tiles<DT>(p, false, &magic) > 0) {
       if (abatch.n > 0 && (abatch.e[0].magic != 0u) != (magic != 0u)) tflush(abatch, acur_bits);     // (two kernels)
       const int at = add_tiles(abatch, acur_bits);
       abatch.e[at].num_groups = p->num_groups;

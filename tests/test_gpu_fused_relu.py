@@ -111,11 +111,46 @@ def test_fused_relu_argument_errors(env):
 
 # ---- consumer side: backward of max(z, 0) straight from the packed words --------------------
 
+# groups longer than 32768 elements: a tile finds its group by a comparison
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("bits", [2, "mixed"])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_unpack_relu_backward_long_groups(env, dtype, bits, in_place):
+    _relu_backward_case(env, dtype, 40000, bits, in_place)
+
+
+@pytest.mark.parametrize("dtype,bits", [(F16, 2), (BF16, "mixed"), (F32, 4), (F32, "mixed")])
+def test_unpack_relu_backward_long_groups_either_side_of_the_limit(env, dtype, bits):
+    """Tensors up to 2^24 elements (2^23 in binary32) go through tiles, larger ones chunk by chunk: both against the threshold
+    on the values daf_unpack_dequantize writes."""
+    daf, _ = env
+    limit = 1 << (23 if dtype == F32 else 24)
+    for n in (limit, limit + 4099):
+        print("case limit", dtype, bits, n, flush=True)
+        y = torch.relu(torch.randn(n, device="cuda:0")).to(torch_dtype(dtype))
+        gy = torch.randn(n, device="cuda:0").to(torch_dtype(dtype))
+        G = -(-n // 8192)
+        b = torch.from_numpy(np.random.default_rng(1).choice([1, 2, 4, 8], G).astype(np.uint8)).cuda() if bits == "mixed" else bits
+        plan = daf.daf_plan((n,), 8192, b)
+        words = torch.empty(plan.packed_words, dtype=torch.int32, device="cuda:0")
+        mn, sc = torch.empty(G, device="cuda:0"), torch.empty(G, device="cuda:0")
+        daf.daf_quantize_pack(plan, y, 3, words, mn, sc)
+        xh, gz = torch.empty_like(y), torch.full_like(y, 5.0)
+        daf.daf_unpack_dequantize(plan, words, mn, sc, xh)
+        daf.daf_unpack_relu_backward(plan, words, mn, sc, gy, gz)
+        assert torch.equal(gz, torch.where(xh > 0, gy, torch.zeros_like(gy)))
+        plan.destroy()
+
+
 @pytest.mark.parametrize("dtype", [F32, F16, BF16])
 @pytest.mark.parametrize("gs", [32, 64, 96, 256, 4096, 8192])
 @pytest.mark.parametrize("bits", [1, 2, 4, 8, "mixed"])
 @pytest.mark.parametrize("in_place", [False, True])
 def test_unpack_relu_backward_matrix(env, dtype, gs, bits, in_place):
+    _relu_backward_case(env, dtype, gs, bits, in_place)
+
+
+def _relu_backward_case(env, dtype, gs, bits, in_place):
     daf, orc = env
     n = 256 * 8 * 8 * 2 + 5 * gs + 13               # two blocks of chunks, whole groups, a ragged tail
     G = (n + gs - 1) // gs
