@@ -739,9 +739,11 @@ hipError_t launch_dtype(const daf_plan_t* p, const uint32_t* words, const float*
   if constexpr (kEpl == 8) {
     // Groups of 32 elements of a 16-bit format, one width: more than 64 in a whole tile, a tile of half the size holds 64
     // (quantize and dequantize, chunk kernel / half tiles: 33 M elements, 2 bits 34.1 / 31.0 us, 246 M 213 / 197, 8 bits
-    // 254 / 243; with per-group widths 134 M 132 / 135: the chunk kernel stays).
+    // 254 / 243; with per-group widths 134 M 132 / 135: the chunk kernel stays).  The relu backward, alone: 34.6 M,
+    // 2 bits 26.0 / 26.7, 4 bits 26.9 / 28.0, 105 M 73.4 / 76.3, 199 M 151 / 142, 2 bits 139 / 133: from 2^27 elements on.
     constexpr int kHalf = kTileChunksPerLane / 2;
-    const int64_t half_tiles = n_tiles == 0 && p->uniform_bits ? tile_path_tiles<DT>(p, &gs_log2, kHalf) : 0;
+    const bool pays = p->uniform_bits && (!RELU_BWD || p->n >= (int64_t)1 << 27);
+    const int64_t half_tiles = n_tiles == 0 && pays ? tile_path_tiles<DT>(p, &gs_log2, kHalf) : 0;
     if (half_tiles > 0) {
       const bool left = half_tiles * kWave * kHalf * kEpl < p->n;
       const unsigned blocks = (unsigned)((half_tiles + kWavesPerBlock - 1) / kWavesPerBlock) + (left ? 1u : 0u);

@@ -142,6 +142,25 @@ def test_unpack_relu_backward_long_groups_either_side_of_the_limit(env, dtype, b
         plan.destroy()
 
 
+@pytest.mark.parametrize("dtype,bits", [(F16, 1), (F16, 8), (BF16, 2), (BF16, 4)])
+def test_unpack_relu_backward_groups_of_32_through_half_tiles(env, dtype, bits):
+    """From 2^27 elements on: against the threshold on the values daf_unpack_dequantize writes, with a ragged end."""
+    daf, _ = env
+    n = (1 << 27) + 2048 + 77
+    print("case half tiles", dtype, bits, n, flush=True)
+    y = torch.relu(torch.randn(n, device="cuda:0")).to(torch_dtype(dtype))
+    gy = torch.randn(n, device="cuda:0").to(torch_dtype(dtype))
+    plan = daf.daf_plan((n,), 32, bits)
+    words = torch.empty(plan.packed_words, dtype=torch.int32, device="cuda:0")
+    mn, sc = torch.empty(plan.num_groups, device="cuda:0"), torch.empty(plan.num_groups, device="cuda:0")
+    daf.daf_quantize_pack(plan, y, 3, words, mn, sc)
+    xh, gz = torch.empty_like(y), torch.full_like(y, 5.0)
+    daf.daf_unpack_dequantize(plan, words, mn, sc, xh)
+    daf.daf_unpack_relu_backward(plan, words, mn, sc, gy, gz)
+    assert torch.equal(gz, torch.where(xh > 0, gy, torch.zeros_like(gy)))
+    plan.destroy()
+
+
 @pytest.mark.parametrize("dtype", [F32, F16, BF16])
 @pytest.mark.parametrize("gs", [32, 64, 96, 256, 4096, 8192])
 @pytest.mark.parametrize("bits", [1, 2, 4, 8, "mixed"])
