@@ -524,13 +524,21 @@ __global__ __launch_bounds__(kThreads) DAF_TILE_WAVES void k_unpack_dequantize_t
 // Whole tiles of a plan whose groups are not whole parts of a tile on that path (0: does not fit).
 // (binary32 with 8 bits for every group stays with the chunk kernel: 0.76-0.78 of the memory rate
 // there against 0.70-0.74 through tiles, measured on 2^27 elements with groups of 96 ... 11008)
+// list_elems: elements of all tensors of a list call, 0 for a call on one tensor.
 template <int DT>
-int64_t any_tile_path_tiles(const daf_plan_t* p, bool relu_bwd, uint32_t* magic) {
+int64_t any_tile_path_tiles(const daf_plan_t* p, bool relu_bwd, int64_t list_elems, uint32_t* magic) {
   constexpr int kElems = kTileChunks * ElemTraits<DT>::kPerLoad;
   const int64_t gs = p->group_size;
   if (DT == kF32 && p->uniform_bits == 8) return 0;
   if (gs < 64 || gs % 32 != 0 || ((gs & (gs - 1)) == 0 && gs <= kElems)) return 0;
-  if (gs > 32768 || (gs & (gs - 1)) == 0) {
+  const bool is_long = gs > 32768 || (gs & (gs - 1)) == 0;
+  // binary32 with 1 bit writes 32 times what it reads: the chunk kernel's plain stream is ahead beyond about 42 M elements, in
+  // lists whatever the group size (groups of 768, chunk / tiles: 37 M 66.2 / 64.7 us, 49 M 75.1 / 75.9, 89 M 127.8 / 134.1,
+  // 147 M 210 / 225) and with long groups (40000: 34.6 M 64.7 / 63.9, 52 M 93.7 / 95.0, 67 M 112.6 / 116.1).
+  if (DT == kF32 && p->uniform_bits == 1 && (is_long || list_elems > 0) &&
+      (list_elems > p->n ? list_elems : p->n) > (int64_t)5 << 23)
+    return 0;
+  if (is_long) {
     // Long groups.  A tile makes two round trips to memory where the chunk kernel makes three (a quantize and a dequantize
     // call on three tensors in turn, chunk kernel / tiles; binary16, groups of 40000: 2 bits, 34.6 M elements 45.6 / 41.6 us,
     // 75 M 85.1 / 80.7; four widths 53.6 / 50.4 and 101 / 96.9; 8 bits, groups of 65536, 50.2 / 49.4, 199 M 228.7 / 227.4),
@@ -712,7 +720,7 @@ hipError_t launch_dtype(const daf_plan_t* p, const uint32_t* words, const float*
   int32_t gs_log2 = 0;
   const int64_t n_tiles = tile_path_tiles<DT>(p, &gs_log2);
   uint32_t magic = 0;
-  const int64_t any_tiles = n_tiles == 0 ? any_tile_path_tiles<DT>(p, RELU_BWD, &magic) : 0;
+  const int64_t any_tiles = n_tiles == 0 ? any_tile_path_tiles<DT>(p, RELU_BWD, 0, &magic) : 0;
   if (any_tiles > 0) {
     const bool left = any_tiles * kTileChunks * kEpl < p->n;
     const unsigned blocks = (unsigned)((any_tiles + kWavesPerBlock - 1) / kWavesPerBlock) + (left ? 1u : 0u);
@@ -887,6 +895,8 @@ hipError_t launch_items(const daf_dequantize_item_t* items, int32_t n_items, hip
   clear(tbatch);
   clear(abatch);
   int tcur_bits = -1, acur_bits = -1;
+  int64_t list_elems = 0;
+  for (int32_t i = 0; i < n_items; ++i) list_elems += items[i].plan->n;
   auto tflush = [&](auto& b, int bits) {
     if (err == hipSuccess) err = launch_tiles<DT>(b, bits, stream);
     clear(b);
@@ -922,7 +932,7 @@ hipError_t launch_items(const daf_dequantize_item_t* items, int32_t n_items, hip
     };
     if (tile_path_tiles<DT>(p, &gs_log2) > 0) {
       add_tiles(tbatch, tcur_bits);
-    } else if (any_tile_path_tiles<DT>(p, false, &magic) > 0) {
+    } else if (any_tile_path_tiles<DT>(p, false, list_elems, &magic) > 0) {
       if (abatch.n > 0 && (abatch.e[0].magic != 0u) != (magic != 0u)) tflush(abatch, acur_bits);     // (two kernels)
       const int at = add_tiles(abatch, acur_bits);
       abatch.e[at].num_groups = p->num_groups;

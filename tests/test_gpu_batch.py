@@ -170,6 +170,54 @@ def test_long_groups_and_groups_of_32_dequantize_through_tiles(env, dtype, bits)
         plan.destroy()
 
 
+def _xhat_one_bit(words, mn, scale, n, gs, dtype):
+    """xhat of a tensor of 1-bit codes: the first code of a word in its most significant bit.  With codes 0 and 1
+    fma(code, scale, min) is min + scale rounded once."""
+    shift = torch.arange(31, -1, -1, device="cuda:0", dtype=torch.int32)
+    lo, hi = mn.to(torch_dtype(dtype)), (mn.double() + scale.double()).float().to(torch_dtype(dtype))
+    code = ((words[:, None] >> shift) & 1).bool().view(-1)[:n]
+    g = torch.arange(n, device="cuda:0") // gs if mn.numel() > 1 else None
+    return torch.where(code, hi if g is None else hi[g], lo if g is None else lo[g])
+
+
+@pytest.mark.parametrize("dtype,n,gs", [(F16, (1 << 26) + 4096 + 77, 0), (BF16, (1 << 26) + 9, 40000), (F16, (1 << 26), 8192),
+                                        (F32, 5 << 23, 40000), (F32, (5 << 23) + 2048 + 5, 0)])
+def test_one_bit_long_groups_either_side_of_the_limit(env, dtype, n, gs):
+    """1 bit: a 16-bit format takes tiles beyond 2^26 elements only, binary32 up to 5 * 2^23 only."""
+    daf, _ = env
+    print("case one bit", dtype, n, gs, flush=True)
+    gs = gs or -(-n // 32) * 32
+    x = torch.randn(n, device="cuda:0").to(torch_dtype(dtype))
+    plan = daf.daf_plan((n,), gs, 1)
+    words = torch.empty(plan.packed_words, dtype=torch.int32, device="cuda:0")
+    mn, sc = torch.empty(plan.num_groups, device="cuda:0"), torch.empty(plan.num_groups, device="cuda:0")
+    out = torch.full_like(x, 9.0)
+    daf.daf_quantize_pack(plan, x, 3, words, mn, sc)
+    daf.daf_unpack_dequantize(plan, words, mn, sc, out)
+    assert torch.equal(out, _xhat_one_bit(words, mn, sc, n, gs, dtype))
+    plan.destroy()
+
+
+@pytest.mark.parametrize("sizes", [(9 << 20, 5 << 22, 11 << 20), ((9 << 20) + 7, 5 << 22, (11 << 20) + 12000)])
+def test_one_bit_lists_either_side_of_the_limit(env, sizes):
+    """binary32 with 1 bit: a list takes tiles up to 5 * 2^23 elements in all."""
+    daf, _ = env
+    print("case one bit list", sizes, sum(sizes) - (5 << 23), flush=True)
+    items, outs = [], []
+    for i, n in enumerate(sizes):
+        x = torch.randn(n, device="cuda:0")
+        plan = daf.daf_plan((n,), 768, 1)
+        words = torch.empty(plan.packed_words, dtype=torch.int32, device="cuda:0")
+        mn, sc = torch.empty(plan.num_groups, device="cuda:0"), torch.empty(plan.num_groups, device="cuda:0")
+        daf.daf_quantize_pack(plan, x, i, words, mn, sc)
+        outs.append(torch.full_like(x, 9.0))
+        items.append((plan, words, mn, sc, outs[-1], None))
+    daf.daf_unpack_dequantize_batch(items)
+    for (plan, words, mn, sc, out, _), n in zip(items, sizes):
+        assert torch.equal(out, _xhat_one_bit(words, mn, sc, n, 768, F32))
+        plan.destroy()
+
+
 @pytest.mark.parametrize("dtype", [F32, F16])
 @pytest.mark.parametrize("bits", [2, 8, "mixed"])
 @pytest.mark.parametrize("gs", [128, 96])
