@@ -1,13 +1,15 @@
 // Backward-pass side: unpack the codes (the extraction rule of Algorithm 2, for the group's
 // own width) and dequantize them to the original precision, xhat = fma(code, scale, min)
-// (inverse of Eq. 1; paper Sec. 2.2).  Two kernels:
+// (inverse of Eq. 1; paper Sec. 2.2).  Four kernels (the first three also in a form for lists of tensors):
 //
-//   k_unpack_dequantize_tile   group sizes that are a power of two (64 or fewer groups per tile).  One
+//   k_unpack_dequantize_tile   groups that are whole parts of a tile (a power of two, 64 or fewer per tile).  One
 //                              wave owns a tile of 512 output chunks of 16 bytes: it fetches the
 //                              tile's min, scale, widths and its contiguous run of packed words
 //                              with coalesced loads into wave-private LDS (one round trip to
 //                              memory; two with per-group widths, whose word offsets come from an
 //                              in-tile prefix sum), then produces the chunks from LDS.
+//   k_unpack_dequantize_tile_any  the same for the other group sizes from 64 elements on, where it pays
+//                              (any_tile_path_tiles): groups start anywhere in a tile or are longer than it.
 //   k_unpack_dequantize_chunk  any group size.  A thread produces 16 bytes of output at a time
 //                              (4 fp32 or 8 16-bit elements).  Such a chunk never straddles a
 //                              group and its bits never straddle a word pair, so it needs one
@@ -16,7 +18,7 @@
 //   k_unpack_dequantize_tail   the fewer than 8 elements after the last whole chunk (list calls; a
 //                              single-tensor call gives them to one more workgroup of the main launch).
 //
-// RELU_BWD = true turns both into the backward of y = max(z, 0) whose output y was the saved
+// RELU_BWD = true turns them into the backward of y = max(z, 0) whose output y was the saved
 // activation: instead of xhat the kernels write grad_z = (xhat > 0) ? grad_y : +0, with xhat
 // rounded to the element format first, so the result is what a threshold on the materialised
 // xhat would give, and xhat itself never reaches memory.
@@ -206,10 +208,7 @@ template <int DT, bool MIXED, bool RELU_BWD>
 __global__ __launch_bounds__(kThreads) void k_unpack_dequantize_chunk(
     const uint32_t* __restrict__ words, const float* __restrict__ mn, const float* __restrict__ scale,
     const uint8_t* __restrict__ bits, const uint32_t* __restrict__ off, int32_t uniform_bits,
-    int64_t n_chunks, int32_t gs, int32_t gs_shift, u32x4* out, const u32x4* grad, int cached, int64_t n,
-    int64_t chunk0) {
-  // Covers the chunks chunk0 .. n_chunks - 1 (chunk0 > 0: the chunks that the tile kernel of a
-  // list call left over).
+    int64_t n_chunks, int32_t gs, int32_t gs_shift, u32x4* out, const u32x4* grad, int cached, int64_t n) {
   // When elements are left after the last whole chunk (fewer than 8) the grid has one more
   // workgroup, the first, whose first wave takes them: no launch of their own.
   const unsigned first_chunk_block = n > n_chunks * ElemTraits<DT>::kPerLoad ? 1u : 0u;
@@ -220,13 +219,13 @@ __global__ __launch_bounds__(kThreads) void k_unpack_dequantize_chunk(
     return;
   }
   unpack_dequantize_block<DT, MIXED, RELU_BWD>((int64_t)(blockIdx.x - first_chunk_block), words, mn, scale, bits, off,
-                                               uniform_bits, n_chunks, gs, gs_shift, out, grad, cached != 0, chunk0);
+                                               uniform_bits, n_chunks, gs, gs_shift, out, grad, cached != 0);
 }
 
 // ------------------------------------------------------------------------------------------
 // Tile path: one wave per tile of 512 output chunks (2048 binary32 or 4096 16-bit elements).
 // ------------------------------------------------------------------------------------------
-// The chunk kernel below fetches widths, offsets, min, scale and words chunk by chunk: small
+// The chunk kernel above fetches widths, offsets, min, scale and words chunk by chunk: small
 // loads that depend on each other, which a backward pass (whose packed input comes from HBM, not
 // from a cache) pays in full.  Here the wave reads everything its tile needs with coalesced loads
 // issued together: min, scale (and width) of the tile's groups, one offset, and the tile's words,
@@ -257,7 +256,8 @@ struct alignas(16) TileLds {
   TileGroup group[kWave];
 };
 
-// U = 16-byte chunks per lane: 8; 16 for small tensors with per-group widths (see launch_dtype).
+// U = 16-byte chunks per lane: 8; 16 for small tensors with per-group widths, 4 for 16-bit groups of 32 elements (see
+// launch_dtype).
 template <int DT, int B, bool RELU_BWD, int U = kTileChunksPerLane>
 __device__ __forceinline__ void unpack_dequantize_tile_body(
     int64_t tile, int wave_in_block, const uint32_t* __restrict__ words, const float* __restrict__ mn,
@@ -684,25 +684,25 @@ __global__ __launch_bounds__(kThreads) void k_unpack_dequantize_chunk_batch(cons
                                             e.cached != 0);
 }
 
-// The chunks chunk0 .. of a tensor (and the elements after its last whole chunk) through the chunk kernel.
+// All chunks of a tensor (and the elements after its last whole chunk) through the chunk kernel.
 template <int DT, bool RELU_BWD>
 hipError_t launch_chunks(const daf_plan_t* p, const uint32_t* words, const float* mn, const float* scale,
-                         const uint8_t* d_bits, void* out_x, const void* grad, int64_t chunk0, hipStream_t stream) {
+                         const uint8_t* d_bits, void* out_x, const void* grad, hipStream_t stream) {
   constexpr int kEpl = ElemTraits<DT>::kPerLoad;
   const int64_t n_chunks = p->n / kEpl;                 // a chunk never straddles a group (32 | group size)
   int32_t gs_shift = -1;
   if ((p->group_size & (p->group_size - 1)) == 0) gs_shift = __builtin_ctz((unsigned)p->group_size);
-  if (n_chunks > chunk0) {
+  if (n_chunks > 0) {
     const int64_t per_block = (int64_t)kThreads * chunks_per_thread(p->uniform_bits == 0);
-    const unsigned blocks = (unsigned)((n_chunks - chunk0 + per_block - 1) / per_block) + (n_chunks * kEpl < p->n ? 1u : 0u);
+    const unsigned blocks = (unsigned)((n_chunks + per_block - 1) / per_block) + (n_chunks * kEpl < p->n ? 1u : 0u);
     if (p->uniform_bits)
       hipLaunchKernelGGL((k_unpack_dequantize_chunk<DT, false, RELU_BWD>), dim3(blocks), dim3(kThreads), 0, stream,
                          words, mn, scale, nullptr, nullptr, p->uniform_bits, n_chunks, p->group_size, gs_shift,
-                         static_cast<u32x4*>(out_x), static_cast<const u32x4*>(grad), p->output_cached, p->n, chunk0);
+                         static_cast<u32x4*>(out_x), static_cast<const u32x4*>(grad), p->output_cached, p->n);
     else
       hipLaunchKernelGGL((k_unpack_dequantize_chunk<DT, true, RELU_BWD>), dim3(blocks), dim3(kThreads), 0, stream,
                          words, mn, scale, d_bits, p->d_off, 0, n_chunks, p->group_size, gs_shift,
-                         static_cast<u32x4*>(out_x), static_cast<const u32x4*>(grad), p->output_cached, p->n, chunk0);
+                         static_cast<u32x4*>(out_x), static_cast<const u32x4*>(grad), p->output_cached, p->n);
     return hipGetLastError();                            // the elements after the last chunk rode along
   }
   if (n_chunks * kEpl < p->n) {
@@ -770,7 +770,7 @@ hipError_t launch_dtype(const daf_plan_t* p, const uint32_t* words, const float*
       return hipGetLastError();
     }
   }
-  if (n_tiles == 0) return launch_chunks<DT, RELU_BWD>(p, words, mn, scale, d_bits, out_x, grad, 0, stream);
+  if (n_tiles == 0) return launch_chunks<DT, RELU_BWD>(p, words, mn, scale, d_bits, out_x, grad, stream);
   // A small tensor with per-group widths takes tiles of twice the size: every wave pays two
   // round trips to memory (widths, then words) before it can store anything, and with few
   // waves per SIMD to overlap them fewer, longer waves come out ahead (a 50 MB binary16 tensor:
