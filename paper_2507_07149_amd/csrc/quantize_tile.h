@@ -321,6 +321,7 @@ __device__ __forceinline__ void quantize_pack_tile_body(
   static_assert(!FOLD || EXT, "pairs are folded for external statistics");
   static_assert(!EXT || S::kGroups == 1, "external statistics: the tile is part of one group");
   static_assert(!(EXT && METRICS), "metrics are not computed for groups longer than a tile");
+  static_assert(!METRICS || S::kLoads % 2 == 0, "the metrics' sums over the lanes are taken two loads at a time");
   static_assert(!(RELU && (EXT || METRICS)), "the fused max(z, 0) exists for the plain tile kernel only");
   constexpr int kEpl = S::kEpl;
   constexpr bool kMixed = (B == 0);
