@@ -108,11 +108,17 @@ def dtype_id(dtype: torch.dtype) -> int:
     return _DTYPE_ID[dtype]
 
 
+# The current stream's handle without the Stream object that torch.cuda.current_stream() builds around it (2.8 us of a
+# call whose launch takes 4).  Private names of torch: where it lacks one, the public call is made.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_handle(stream) -> Optional[int]:
     if stream is None:
-        # the current stream of the current device, without the Stream object that torch.cuda.current_stream()
-        # builds around it (2.8 us of a call whose launch takes 4)
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+        if _raw_stream is None or _current_device is None:
+            return torch.cuda.current_stream().cuda_stream or None
+        return _raw_stream(_current_device()) or None
     return stream.cuda_stream or None
 
 

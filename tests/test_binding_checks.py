@@ -108,3 +108,19 @@ def test_linear_tile_map_visits_every_tile_once():
         L.daf_linear_tile_of_workgroup(8 * s + 3, tiles_m, tiles_n, ctypes.byref(tm), ctypes.byref(tn))
         rows.add(tm.value); cols.add(tn.value)
     assert len(rows) <= 4 and len(cols) <= 9
+
+
+@pytest.mark.parametrize("missing", ["_raw_stream", "_current_device"])
+def test_current_stream_without_the_private_functions(monkeypatch, missing):
+    """A torch that lacks the private stream functions: the handle comes from torch.cuda.current_stream()."""
+    from paper_2507_07149_amd import binding
+
+    class Stream:
+        cuda_stream = 0x1234
+
+    monkeypatch.setattr(binding, "_raw_stream", lambda device: 100 + device)
+    monkeypatch.setattr(binding, "_current_device", lambda: 3)
+    assert binding._stream_handle(None) == 103 and binding._stream_handle(Stream) == 0x1234
+    monkeypatch.setattr(binding, missing, None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    assert binding._stream_handle(None) == 0x1234
