@@ -468,6 +468,16 @@ int daf_unpack_matmul_grad_weight(const daf_plan_t* plan, const uint32_t* words,
                                   const uint8_t* bits, const void* grad_y, int64_t N, int64_t K, daf_dtype_t dtype,
                                   float* out_grad_w, void* workspace, void* stream);
 
+/* How daf_unpack_matmul_grad_weight runs a shape: a host computation, for tuning and tests.  The output is cut into
+ * tiles of tile_n x tile_k (512 x 128 is a kernel of its own); the first whole_tiles run over all of m, each of the others
+ * in `slices` slices of m whose partial sums are added afterwards.
+ * Errors: DAF_EINVAL, DAF_EUNSUPPORTED as daf_unpack_matmul_grad_weight for the same shape. */
+typedef struct {
+  int32_t tile_n, tile_k, slices;
+  int64_t tiles, whole_tiles;
+} daf_matmul_schedule_t;
+int daf_unpack_matmul_schedule(const daf_plan_t* plan, int64_t N, int64_t K, daf_dtype_t dtype, daf_matmul_schedule_t* out);
+
 int64_t daf_select_bits_workspace_bytes(int64_t num_groups);
 int daf_select_bits(const float* group_min, const float* group_max, int64_t num_groups,
                     const uint8_t* classes, int32_t n_classes, uint8_t* out_bits,

@@ -79,6 +79,8 @@ def load_library():
     L.daf_linear_tile_of_workgroup.restype = c.c_int
     L.daf_unpack_relu_backward.argtypes = [vp, vp, vp, vp, vp, vp, vp, c.c_int, vp]
     L.daf_unpack_relu_backward.restype = c.c_int
+    L.daf_unpack_matmul_schedule.argtypes = [vp, i64, i64, c.c_int, vp]
+    L.daf_unpack_matmul_schedule.restype = c.c_int
     L.daf_unpack_matmul_workspace_bytes.argtypes = [vp, i64, i64]
     L.daf_unpack_matmul_workspace_bytes.restype = i64
     L.daf_unpack_matmul_grad_weight.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, c.c_int, vp, vp, vp]
@@ -417,6 +419,20 @@ def daf_unpack_relu_backward(plan: Plan, words: torch.Tensor, mn: torch.Tensor, 
 
 def daf_unpack_matmul_workspace_bytes(plan: Plan, N: int, K: int) -> int:
     return int(load_library().daf_unpack_matmul_workspace_bytes(plan.handle, N, K))
+
+
+class _MatmulSchedule(ctypes.Structure):
+    _fields_ = [("tile_n", ctypes.c_int32), ("tile_k", ctypes.c_int32), ("slices", ctypes.c_int32),
+                ("tiles", ctypes.c_int64), ("whole_tiles", ctypes.c_int64)]
+
+
+def daf_unpack_matmul_schedule(plan: Plan, N: int, K: int, dtype: torch.dtype) -> dict:
+    """How daf_unpack_matmul_grad_weight runs this shape: tile_n, tile_k, slices, tiles, whole_tiles."""
+    s = _MatmulSchedule()
+    rc = load_library().daf_unpack_matmul_schedule(plan.handle, N, K, _DTYPE_ID[dtype], ctypes.byref(s))
+    if rc != 0:
+        raise DafError(rc, "daf_unpack_matmul_schedule")
+    return {name: getattr(s, name) for name, _ in s._fields_}
 
 
 def daf_unpack_matmul_grad_weight(plan: Plan, words: torch.Tensor, mn: torch.Tensor, scale: torch.Tensor,

@@ -423,6 +423,15 @@ int64_t daf_unpack_matmul_workspace_bytes(const daf_plan_t* plan, int64_t N, int
   return daf_unpack_matmul_workspace_size(M, N, K);
 }
 
+int daf_unpack_matmul_schedule(const daf_plan_t* plan, int64_t N, int64_t K, daf_dtype_t dtype, daf_matmul_schedule_t* out) {
+  if (plan == nullptr || out == nullptr || N <= 0 || K <= 0 || plan->n % K != 0) return DAF_EINVAL;
+  if (dtype != DAF_F32 && dtype != DAF_F16 && dtype != DAF_BF16) return DAF_EUNSUPPORTED;
+  const int64_t M = plan->n / K;
+  if (!daf_unpack_matmul_shape_ok(M, N, K, plan->group_size)) return DAF_EUNSUPPORTED;
+  daf_unpack_matmul_schedule_of(M, N, K, (int)dtype, out);
+  return DAF_OK;
+}
+
 int daf_unpack_matmul_grad_weight(const daf_plan_t* plan, const uint32_t* words, const float* min, const float* scale,
                                   const uint8_t* bits, const void* grad_y, int64_t N, int64_t K, daf_dtype_t dtype,
                                   float* out_grad_w, void* workspace, void* stream) {

@@ -17,8 +17,8 @@
 //
 // Two kernels.  Outputs of more than 256 rows with enough work (schedule) in a 16-bit format take
 // k_unpack_matmul_wide (unpack_matmul_wide.h), a tile of 512 x 128.  The others, and binary32, take
-// k_unpack_matmul below: a work-group tile of 256 (n) x BK (k) outputs, BK = 128 or 64 on 4 waves, for binary32
-// also 256 on 8 waves; 32 values of m per step (16 in binary32).  A wave owns 64 (n) x 128 (k) (64 x 64 in
+// k_unpack_matmul below: a work-group tile of 256 (n) x BK (k) outputs, BK = 256 on 8 waves, or 128 or 64 on 4 waves;
+// 32 values of m per step (16 in binary32).  A wave owns 64 (n) x 128 (k) (64 x 64 in
 // the narrowest tile): 2 x 4 MFMA blocks of 32 x 32, 128 accumulator registers, two waves per SIMD.  The wide
 // n keeps the number of times a value of x is dequantized (once per tile of n) low; the wide k keeps
 // the number of times a row of grad_y is fetched low.  Two copies of the LDS tiles: while the
@@ -565,10 +565,11 @@ __global__ __launch_bounds__(256) void k_sum_slices(float4* __restrict__ partial
 constexpr int kStepM = 32;
 
 // Width of the 256-row tile along k.  Each doubling halves the number of times a row of grad_y is
-// fetched; binary32's 256-column tile (8 waves, one work-group per CU) is used when the output has
-// enough of them to fill the chip without slicing m, else the 128-column one.
-static int tile_bk(int64_t N, int64_t K, int es) {
-  if (es == 4 && K % 256 == 0 && ((N + kBN - 1) / kBN) * (K / 256) >= 256) return 256;
+// fetched; the 256-column tile (8 waves, one work-group per CU) is used when the output has
+// enough of them to fill the chip without slicing m, else the 128-column one (16-bit formats that do not take the
+// 512 x 128 tile: 2048 x 256 x 65536, 256 / 128 columns 77.0 / 82.2 us, 4096 x 128 x 65536 111 / 125).
+static int tile_bk(int64_t N, int64_t K) {
+  if (K % 256 == 0 && ((N + kBN - 1) / kBN) * (K / 256) >= 256) return 256;
   return K % 128 == 0 ? 128 : 64;
 }
 
@@ -585,28 +586,20 @@ struct Schedule {
   int bn, bk;              // the tile; 512 x 128: k_unpack_matmul_wide
   int64_t tiles, whole;    // tiles in all; tiles that run over all of m
   int32_t slices;          // of each other tile (1: there is none)
+  double seconds;          // the estimate, with the two steps that it takes to start a round
 };
-Schedule schedule(int64_t M, int64_t N, int64_t K, int es) {   // es: bytes per element (2 or 4)
+Schedule schedule_tile(int64_t M, int64_t N, int64_t K, int bn, int bk, int64_t slots, double t_step) {
   Schedule sc;
-  // The 512 x 128 tile starts slower (a pipeline four steps deep to fill) and runs faster per step: start and now
-  // in microseconds, bf16, m x n x k: 32768 x 4096 x 11008 3216 / 2654, 8192 x 3072 x 768 72.6 / 60.8,
-  // 8192 x 768 x 768 35.6 / 31.6; below ten steps per compute unit the general kernel is ahead
-  // (4096 x 576 x 768, 6 steps: 22.3 against 24.6, 4096 x 1024 x 1024, 8 steps: equal).  Outputs of 256 and more such
-  // tiles take it for any m: the general kernel has nothing better there (128 x 4096 x 4096: 19.2 / 18.9).
-  const int64_t wide_tiles = ((N + Wide::kBN - 1) / Wide::kBN) * (K / Wide::kBK);
-  const bool wide = es == 2 && N > kBN && K % Wide::kBK == 0 && (wide_tiles >= 256 || wide_tiles * (M / kStepM) >= 10 * 256);
-  sc.bn = wide ? Wide::kBN : kBN;
-  sc.bk = wide ? Wide::kBK : tile_bk(N, K, es);
-  sc.tiles = ((N + sc.bn - 1) / sc.bn) * (K / sc.bk);
-  const int64_t slots = 256 * (wide || sc.bk == 256 ? 1 : sc.bk == 128 ? 2 : 3);
+  sc.bn = bn;
+  sc.bk = bk;
+  sc.tiles = ((N + bn - 1) / bn) * (K / bk);
   const int64_t steps = M / kStepM;
-  // one work-group over all of m, per 32 values of m: the 16-bit kernels are bound by instruction
-  // issue, the binary32 kernel by its MFMAs (128 per wave of 64 cycles each)
-  const double t_all_m = (double)steps * (es == 4 ? 8.0e-6 : wide ? 0.95e-6 : 1.25e-6);
-  const double tile_bytes = (double)sc.bn * sc.bk * 4.0;
+  const double t_all_m = (double)steps * t_step, start = 2.0 * t_step;
+  const double tile_bytes = (double)bn * bk * 4.0;
   sc.whole = sc.tiles;
   sc.slices = 1;
   double best_cost = (double)((sc.tiles + slots - 1) / slots) * t_all_m;
+  sc.seconds = best_cost + (double)((sc.tiles + slots - 1) / slots) * start;
   const int64_t whole = sc.tiles / slots * slots, rest = sc.tiles - whole;
   if (rest == 0) return sc;
   // (at most 16 slices, or, for outputs of a few tiles only, as many as fill the chip once)
@@ -614,15 +607,36 @@ Schedule schedule(int64_t M, int64_t N, int64_t K, int es) {   // es: bytes per 
   for (int32_t s = 2; s <= max_slices && steps >= 4 * s; ++s) {
     if ((double)s * rest * tile_bytes > 256.0 * 1048576.0) break;
     const double longest = (double)((steps + s - 1) / s) / (double)steps;      // share of m of the longest slice
-    const double cost = (double)(whole / slots) * t_all_m + (double)((rest * s + slots - 1) / slots) * t_all_m * longest +
-                        (2 * s + 1) * rest * tile_bytes / 4.0e12;
+    const double rounds = (double)((rest * s + slots - 1) / slots);
+    const double cost = (double)(whole / slots) * t_all_m + rounds * t_all_m * longest + (2 * s + 1) * rest * tile_bytes / 4.0e12;
     if (cost < best_cost * 0.98) {                   // (a clear gain only)
       best_cost = cost;
       sc.whole = whole;
       sc.slices = s;
+      sc.seconds = cost + ((double)(whole / slots) + rounds) * start;
     }
   }
   return sc;
+}
+Schedule schedule(int64_t M, int64_t N, int64_t K, int es) {   // es: bytes per element (2 or 4)
+  // Per work-group and 32 values of m: the 16-bit kernels are bound by instruction issue, the binary32 kernel by its MFMAs
+  // (128 per wave of 64 cycles each).
+  const int bk = tile_bk(N, K);
+  const Schedule general = schedule_tile(M, N, K, kBN, bk, 256 * (bk == 256 ? 1 : bk == 128 ? 2 : 3),
+                                         es == 4 ? 8.0e-6 : bk == 256 ? 1.1e-6 : 1.25e-6);
+  // The 512 x 128 tile starts slower (a pipeline four steps deep to fill) and runs faster per step: general kernel and
+  // 512 x 128 in microseconds, bf16, m x n x k: 32768 x 4096 x 11008 3044 / 2495, 8192 x 3136 x 768 67.8 / 61.2;
+  // below ten steps per compute unit the general kernel is ahead (4096 x 576 x 768, 6 steps: 22.3 / 24.6,
+  // 4096 x 1024 x 1024, 8 steps: equal).  Outputs of 256 and more such tiles take it for any m (128 x 4096 x 4096: 19.2 / 18.9).
+  const int64_t wide_tiles = ((N + Wide::kBN - 1) / Wide::kBN) * (K / Wide::kBK);
+  const bool fits = es == 2 && N > kBN && K % Wide::kBK == 0 && (wide_tiles >= 256 || wide_tiles * (M / kStepM) >= 10 * 256);
+  if (!fits) return general;
+  // Where the last of few tiles of n is mostly outside the output, or a last round is nearly empty, the estimates decide
+  // (32768 x 576 x 4352 235 / 270, 8192 x 768 x 4352 79.6 / 83.2, 512 x 1088 x 11008 27.0 / 34.0).  Near each other the
+  // 512 x 128 tile; over 240 shapes the choice costs 0.2 % against the faster kernel of each, 9 % at
+  // most (32768 x 1344 x 768: 102 / 112).
+  const Schedule wide = schedule_tile(M, N, K, Wide::kBN, Wide::kBK, 256, 0.95e-6);
+  return wide.seconds * 0.97 <= general.seconds ? wide : general;
 }
 }  // namespace
 
@@ -636,6 +650,15 @@ int64_t daf_unpack_matmul_workspace_size(int64_t M, int64_t N, int64_t K) {
     bytes = b > bytes ? b : bytes;
   }
   return bytes;
+}
+
+void daf_unpack_matmul_schedule_of(int64_t M, int64_t N, int64_t K, int dtype, daf_matmul_schedule_t* out) {
+  const Schedule sc = schedule(M, N, K, dtype == daf::kF32 ? 4 : 2);
+  out->tile_n = sc.bn;
+  out->tile_k = sc.bk;
+  out->slices = sc.slices;
+  out->tiles = sc.tiles;
+  out->whole_tiles = sc.whole;
 }
 
 bool daf_unpack_matmul_shape_ok(int64_t M, int64_t N, int64_t K, int32_t gs) {
@@ -674,9 +697,7 @@ hipError_t daf_launch_unpack_matmul(const daf_plan_t* p, const uint32_t* words, 
         hipLaunchKernelGGL((k_unpack_matmul_wide<DT, MIXED>), dim3(blocks), dim3(Wide::kThreads), 0, stream, words, mn, \
                            scale, d_bits, p->d_off, (uint32_t)p->uniform_bits, p->group_size, gy, M, N, K, tiles_n, \
                            tiles_k, whole, slices, out, workspace);                                               \
-    } else if (bk == 256) {                                                                                       \
-      if constexpr (DT == daf::kF32) DAF_LAUNCH(DT, MIXED, 256);                                                  \
-    }                                                                                                             \
+    } else if (bk == 256) DAF_LAUNCH(DT, MIXED, 256);                                                             \
     else if (bk == 128) DAF_LAUNCH(DT, MIXED, 128);                                                               \
     else DAF_LAUNCH(DT, MIXED, 64);                                                                               \
   } while (0)

@@ -123,3 +123,29 @@ def test_quantize_route_of_uniform_plans(lib, n, gs, dtype, want):
     assert lib.daf_plan_quantize_route(p, dtype) == want
     assert lib.daf_plan_quantize_route(p, 7) == -2 and lib.daf_plan_quantize_route(None, 0) == -1
     lib.daf_plan_destroy(p)
+
+
+# m, n, k, element format -> tile of the weight gradient: 512 x 128 only where it is not slower than the general kernel
+@pytest.mark.parametrize("m,n,k,dtype,tile", [
+    (32768, 4096, 11008, 2, (512, 128)), (32768, 3072, 768, 1, (512, 128)), (128, 4096, 4096, 2, (512, 128)),
+    (8192, 832, 4352, 1, (512, 128)), (32768, 320, 768, 2, (512, 128)),
+    # the last tile of n mostly outside the output, a last round that is nearly empty
+    (32768, 576, 4352, 2, (256, 128)), (32768, 768, 4352, 1, (256, 128)), (8192, 576, 4352, 1, (256, 128)),
+    (512, 1088, 11008, 2, (256, 128)),
+    # one tile of n: never; enough of them for the wider general tile
+    (4096, 256, 4096, 2, (256, 128)), (2048, 256, 65536, 1, (256, 256)), (4096, 128, 65536, 2, (256, 256)),
+    (4096, 4096, 4096, 0, (256, 256)), (256, 256, 192, 2, (256, 64)), (512, 1024, 1024, 1, (256, 128))])
+def test_weight_gradient_tile(lib, m, n, k, dtype, tile):
+    import paper_2507_07149_amd as daf
+    import torch
+    plan = daf.daf_plan((m, k), 64, 4)
+    s = daf.daf_unpack_matmul_schedule(plan, n, k, (torch.float32, torch.float16, torch.bfloat16)[dtype])
+    assert (s["tile_n"], s["tile_k"]) == tile
+    assert s["tiles"] == -(-n // tile[0]) * (k // tile[1]) and 0 <= s["whole_tiles"] <= s["tiles"]
+    assert (s["slices"] > 1) == (s["whole_tiles"] < s["tiles"])
+    if s["slices"] > 1:
+        need = s["slices"] * (s["tiles"] - s["whole_tiles"]) * tile[0] * tile[1] * 4
+        assert need <= daf.daf_unpack_matmul_workspace_bytes(plan, n, k)
+    with pytest.raises(daf.DafError):
+        daf.daf_unpack_matmul_schedule(plan, n + 1, k, torch.float16)
+    plan.destroy()

@@ -84,7 +84,7 @@ def test_grad_weight_groups_that_are_rows_or_not_a_power_of_two(env, case):
 
 @pytest.mark.parametrize("case", [(256, 64, 256, 64, "mixed", BF16), (128, 320, 384, 32, 2, F16), (512, 192, 128, 128, "mixed", F32),
                                   (8192, 64, 256, 64, 4, F32), (2048, 448, 192, 64, "mixed", BF16),
-                                  (32, 4160, 4096, 64, "mixed", BF16)])       # the last: 256-column tile, 17 tiles of n
+                                  (32, 4160, 4096, 64, "mixed", BF16)])       # the last: 512 x 128 tile, 9 tiles of n
 def test_grad_weight_n_not_a_multiple_of_256(env, case):
     daf, orc = env
     M, N, K, gs, bits, dtype = case
@@ -104,11 +104,11 @@ def test_grad_weight_tall_and_skinny(env):
 def test_grad_weight_without_split_needs_no_workspace(env):
     daf, orc = env
     print("case no split", flush=True)
-    ws = _case(daf, orc, 64, 4096, 4096, 256, 4, BF16, 3)              # 512 tiles: one slice of m
+    ws = _case(daf, orc, 64, 4096, 4096, 256, 4, BF16, 3)              # 256 tiles of 512 x 128: one slice of m
     assert ws == 0
 
 
-# 256 or more 256 x 256 tiles: the 256-column tile (8 waves per work-group)
+# 256 or more 256 x 256 tiles: 8 waves per work-group, the 256-column tile in binary32, 512 x 128 in the 16-bit formats
 @pytest.mark.parametrize("case", [(32, 4096, 4096, 64, "mixed", BF16), (96, 4096, 4096, 128, "mixed", F16),
                                   (64, 8192, 2048, 32, "mixed", BF16), (64, 2048, 8192, 256, 8, F16),
                                   (32, 4096, 4096, 64, 1, BF16), (64, 4096, 4096, 64, "mixed", F32),
@@ -124,13 +124,27 @@ def test_grad_weight_wide_tile(env, case):
 # 16-bit formats, 256 or more tiles of 512 x 128, or enough steps: the pipeline of 32 values of m per step is four deep and
 # unrolled by four, so every remainder; N with a last tile of n that is mostly outside the output, groups that do not
 # coincide with the 128 columns of a tile.
-@pytest.mark.parametrize("steps,N,K,gs,bits,dtype", [(4, 2112, 6912, 96, "mixed", BF16), (5, 2112, 6656, 6656, 2, F16),
-                                                     (6, 2560, 6912, 384, "mixed", F16), (7, 2112, 6912, 32, 8, BF16),
-                                                     (8, 2112, 6656, 64, "mixed", BF16), (9, 4160, 3840, 1920, 1, F16),
+@pytest.mark.parametrize("steps,N,K,gs,bits,dtype", [(4, 2368, 6912, 96, "mixed", BF16), (5, 3648, 4096, 4096, 2, F16),
+                                                     (6, 2560, 6912, 384, "mixed", F16), (7, 3648, 4096, 32, 8, BF16),
+                                                     (8, 3648, 4096, 64, "mixed", BF16), (9, 3648, 4096, 2048, 1, F16),
                                                      (2561, 320, 128, 32, "mixed", BF16), (1283, 576, 128, 128, 4, F16)])
 def test_grad_weight_512_by_128_tile(env, steps, N, K, gs, bits, dtype):
+    _steps_case(env, steps, N, K, gs, bits, dtype, 512, 128)
+
+
+# The general kernel in the 16-bit formats: a few tiles of 512 x 128 more than a round of work-groups holds (the general
+# kernel's tiles are one round), one tile of n with 128 columns of k, the last of them in slices of m, and with 256.
+@pytest.mark.parametrize("steps,N,K,gs,bits,dtype,bk", [(4, 2112, 6912, 96, "mixed", BF16, 128), (5, 2112, 6656, 6656, 2, F16, 128),
+                                                        (7, 2112, 6912, 32, 8, BF16, 128), (9, 4160, 3840, 1920, 1, F16, 128),
+                                                        (16, 256, 128 * 513, 64, "mixed", BF16, 128), (16, 192, 128 * 513, 384, 2, F16, 128),
+                                                        (3, 256, 65536, 128, "mixed", F16, 256), (2, 128, 65536, 32, 4, BF16, 256)])
+def test_grad_weight_general_kernel(env, steps, N, K, gs, bits, dtype, bk):
+    _steps_case(env, steps, N, K, gs, bits, dtype, 256, bk)
+
+
+def _steps_case(env, steps, N, K, gs, bits, dtype, bn, bk):
     daf, orc = env
-    print("case 512 x 128", steps, N, K, gs, bits, dtype, flush=True)
+    print("case", bn, bk, steps, N, K, gs, bits, dtype, flush=True)
     M = 32 * steps
     g = torch.Generator().manual_seed(steps)
     x = (torch.randn(M, K, generator=g) * (1 + torch.rand(M, 1, generator=g))).to(torch_dtype(dtype))
@@ -140,6 +154,9 @@ def test_grad_weight_512_by_128_tile(env, steps, N, K, gs, bits, dtype):
     xh = orc.widen(orc.unpack_dequantize(ow, omn, osc, b, M * K, gs, dtype)[0], dtype).reshape(M, K).astype(np.float64)
     gd = gy.double().numpy()
     plan = daf.daf_plan((M, K), gs, torch.from_numpy(b).cuda() if b.size > 1 else int(b[0]))
+    how = daf.daf_unpack_matmul_schedule(plan, N, K, torch_dtype(dtype))
+    assert (how["tile_n"], how["tile_k"]) == (bn, bk)
+    assert (K != 128 * 513) or (how["slices"] > 1 and how["whole_tiles"] == 512)
     ws = torch.empty(max(daf.daf_unpack_matmul_workspace_bytes(plan, N, K), 16), dtype=torch.uint8, device="cuda:0")
     out = torch.full((N, K), float("nan"), device="cuda:0")
     daf.daf_unpack_matmul_grad_weight(plan, torch.from_numpy(ow.view(np.int32)).cuda(), torch.from_numpy(omn).cuda(),
@@ -213,8 +230,9 @@ def _widths(G, bits, seed):
             else np.array([bits], np.uint8))
 
 
-# One tile more than whole rounds of work-groups (256, 512 or 768 per round for the 256-, 128- and
-# 64-column tile): the tiles of the last round are cut into slices of m, the others are not.
+# A few tiles more than whole rounds of work-groups (256 per round for the 512 x 128 and the 256 x 256 tile, 512 for 256 x 128,
+# 768 for 256 x 64): the tiles of the last round are cut into slices of m, the others are not.  The 16-bit cases with bk of
+# 256 and 128 take the 512 x 128 tile, the binary32 ones the tile of 256 x bk (which the workspace is sized by).
 @pytest.mark.timeout(300)
 @pytest.mark.parametrize("K,bk,bits,dtype", [(4352, 256, "mixed", BF16), (4224, 128, "mixed", F16), (3136, 64, 4, BF16),
                                              (4352, 256, "mixed", F32), (4224, 128, 2, F32), (3136, 64, "mixed", F32)])
@@ -222,6 +240,11 @@ def test_grad_weight_sliced_last_round(env, K, bk, bits, dtype):
     daf, orc = env
     M, N = 4096, 4096
     print("case sliced last round", K, bk, bits, dtype, flush=True)
+    plan = daf.daf_plan((M, K), 64, 4)
+    how = daf.daf_unpack_matmul_schedule(plan, N, K, torch_dtype(dtype))
+    plan.destroy()
+    assert (how["tile_n"], how["tile_k"]) == ((512, 128) if dtype != F32 and bk > 64 else (256, bk))
+    assert how["slices"] > 1 and 0 < how["whole_tiles"] < how["tiles"]
     ws = _case(daf, orc, M, N, K, 64, bits, dtype, 17)
     tile_bytes = 256 * bk * 4
     assert ws > 0 and ws % (16 * tile_bytes) == 0 and ws <= 64 * 16 * tile_bytes     # 16 tiles, each in a few slices
@@ -255,7 +278,7 @@ def test_identity_gradient_returns_xhat_bit_for_bit(env, dtype, bits, K):
 
 @pytest.mark.parametrize("dtype,bits", [(BF16, "mixed"), (F16, "mixed"), (BF16, 8), (F16, 2), (F32, "mixed"), (F32, 4)])
 def test_identity_gradient_wide_tile(env, dtype, bits):
-    _identity_case(env, dtype, bits, 4096, 4096)                               # 256 tiles of 256 x 256
+    _identity_case(env, dtype, bits, 4096, 4096)                               # 256 tiles of 512 x 128 (binary32: 256 x 256)
 
 
 def _identity_case(env, dtype, bits, M, K):
@@ -295,7 +318,7 @@ def _identity_case(env, dtype, bits, M, K):
 @pytest.mark.parametrize("cfg,N", [(5, 4096), (3, 3072)])
 def test_grad_weight_at_benchmark_size_sampled(env, cfg, N):
     """The shapes bench.py --fused-matmul times (the LLM MLP activation with per-group widths
-    {2,4,8} on the 256-column tile; the ViT activation with {1,2,4,8}, m in slices): sampled
+    {2,4,8}; the ViT activation with {1,2,4,8}, m in slices): sampled
     outputs against the oracle, which quantizes and dequantizes only the groups those outputs
     read, one group at a time; and every output against the plain dequantize kernel's xhat
     multiplied by the library in binary32 (a property that holds at any size)."""
