@@ -467,9 +467,8 @@ def main():
         flops = 2.0 * M * N * K
         peak = 157.3 if x.dtype == torch.float32 else 2500.0   # dense MFMA, binary32 / 16-bit formats
         ach = flops / (t_fused * 1e-3) / 1e12
-        wide_tiles = -(-N // 512) * (K // 128)
-        wide = x.element_size() == 2 and N > 256 and K % 128 == 0 and (wide_tiles >= 256 or wide_tiles * (M // 32) >= 2560)
-        kernel = "k_unpack_matmul_wide" if wide else "k_unpack_matmul"
+        tile_n = daf.daf_unpack_matmul_schedule(plan, N, K, x.dtype)["tile_n"]
+        kernel = "k_unpack_matmul_wide" if tile_n == 512 else "k_unpack_matmul"
         print(json.dumps({"metric": "weight gradient from the packed activation, TFLOP/s", "value": round(ach, 1),
                           "unit": "TFLOP/s", "n_gpus": 1, "steps": reps, "data": "synthetic", "higher_is_better": True,
                           "dtype": "f32" if args.f32 else {0: "f32", 1: "f16", 2: "bf16"}[w.dtype],
@@ -883,27 +882,13 @@ def measure(cfg, args, daf, torch, np, dev, headline):
     qk_ms, dk_ms = qk["median"], dk["median"]
     alg = sum(algorithmic_bytes(w, p.packed_words) for w, p in zip(workloads, plans))
     alg_q = alg + sum(w.numel * w.x.element_size() for w in workloads if two_reads(w))
-    gs0 = workloads[0].group_size
-    q_kernel_name = ("k_quantize_pack_fold" if two_reads(workloads[0]) and workloads[0].bits.size == 1 and
-                     gs0 >= workloads[0].numel and workloads[0].numel <= 1 << 26 and not batched else
-                     "k_quantize_pack_tile" if gs0 & (gs0 - 1) == 0 and gs0 <= 4096 or two_reads(workloads[0])
-                     else "k_quantize_pack_units" if gs0 <= 4096 else "k_quantize_pack_long")
+    q_route = plans[0].quantize_route(workloads[0].x.dtype)
+    q_kernel_name = "statistics, then k_quantize_pack_*" if q_route == "two_pass" else f"k_quantize_pack_{q_route}"
+    d_route = plans[0].dequantize_route(workloads[0].x.dtype, list_elements=sum(w.numel for w in workloads) if batched else 0)
+    d_kernel_name = f"k_unpack_dequantize_{d_route}"
     if batched:
         q_kernel_name += "_batch"
-    pow2 = gs0 > 0 and gs0 & (gs0 - 1) == 0
-    fp32 = workloads[0].x.dtype == torch.float32
-    one_width = int(workloads[0].bits[0]) if workloads[0].bits.size == 1 else 0
-    small = workloads[0].numel <= 1 << 26
-    if pow2 and gs0 <= 4096:
-        d_kernel_name = "k_unpack_dequantize_tile"
-    elif gs0 < 64 or fp32 and one_width == 8:
-        d_kernel_name = "k_unpack_dequantize_chunk"
-    elif (pow2 or gs0 > 32768) and ((fp32 or one_width == 4) and not small or
-                                    not fp32 and one_width == 1 and small):
-        d_kernel_name = "k_unpack_dequantize_chunk"
-    else:
-        d_kernel_name = "k_unpack_dequantize_tile_any"
-    d_kernel_name += "_batch" if batched else ""
+        d_kernel_name += "_batch"
 
     traffic = QUOTED_TRAFFIC.get(cfg) if args.group_size is None else None
 

@@ -135,6 +135,20 @@ typedef enum {
 } daf_route_t;
 int daf_plan_quantize_route(const daf_plan_t* plan, daf_dtype_t dtype);
 
+/* The same for the calls that unpack: daf_unpack_dequantize, daf_unpack_relu_backward (relu_backward = 1) and
+ * daf_unpack_dequantize_batch (list_elements = the elements of all tensors of the list, else 0).
+ *   DAF_DEQUANTIZE_TILE      groups that are whole parts of a wave's tile
+ *   DAF_DEQUANTIZE_TILE_ANY  tiles in which groups start anywhere, or that lie inside a group
+ *   DAF_DEQUANTIZE_CHUNK     16 bytes of output at a time
+ * Returns the route (>= 0), DAF_EINVAL for a NULL plan, a negative list_elements or both kinds of call at once,
+ * DAF_EUNSUPPORTED for an unknown dtype. */
+typedef enum {
+  DAF_DEQUANTIZE_TILE = 0,
+  DAF_DEQUANTIZE_TILE_ANY = 1,
+  DAF_DEQUANTIZE_CHUNK = 2
+} daf_dequantize_route_t;
+int daf_plan_dequantize_route(const daf_plan_t* plan, daf_dtype_t dtype, int relu_backward, int64_t list_elements);
+
 /* Copies the G group word offsets to HOST memory (synchronous; for inspection and tests).
  * Works for uniform plans too (offsets are then computed, not stored). */
 int daf_plan_copy_offsets(const daf_plan_t* plan, uint32_t* out_off);

@@ -55,6 +55,8 @@ def load_library():
     L.daf_plan_copy_offsets.restype = c.c_int
     L.daf_plan_quantize_route.argtypes = [vp, c.c_int]
     L.daf_plan_quantize_route.restype = c.c_int
+    L.daf_plan_dequantize_route.argtypes = [vp, c.c_int, c.c_int, i64]
+    L.daf_plan_dequantize_route.restype = c.c_int
     L.daf_plan_set_output_cached.argtypes = [vp, c.c_int]
     L.daf_plan_set_output_cached.restype = c.c_int
     L.daf_plan_destroy.argtypes = [vp]
@@ -238,6 +240,15 @@ class Plan:
         if rc < 0:
             raise DafError(rc, "daf_plan_quantize_route")
         return Plan.ROUTES[rc]
+
+    DEQUANTIZE_ROUTES = ("tile", "tile_any", "chunk")
+
+    def dequantize_route(self, dtype: torch.dtype, relu_backward: bool = False, list_elements: int = 0) -> str:
+        """`list_elements`: the elements of all tensors of a list call; 0 for a call on this tensor alone."""
+        rc = load_library().daf_plan_dequantize_route(self.handle, _DTYPE_ID[dtype], int(relu_backward), list_elements)
+        if rc < 0:
+            raise DafError(rc, "daf_plan_dequantize_route")
+        return Plan.DEQUANTIZE_ROUTES[rc]
 
     def set_output_cached(self, cached: bool) -> None:
         rc = load_library().daf_plan_set_output_cached(self.handle, 1 if cached else 0)

@@ -236,6 +236,12 @@ int daf_plan_quantize_route(const daf_plan_t* plan, daf_dtype_t dtype) {
   return daf_quantize_route(plan, (int)dtype);
 }
 
+int daf_plan_dequantize_route(const daf_plan_t* plan, daf_dtype_t dtype, int relu_backward, int64_t list_elements) {
+  if (plan == nullptr || list_elements < 0 || (relu_backward && list_elements > 0)) return DAF_EINVAL;
+  if (dtype != DAF_F32 && dtype != DAF_F16 && dtype != DAF_BF16) return DAF_EUNSUPPORTED;
+  return daf_dequantize_route(plan, (int)dtype, relu_backward != 0, list_elements);
+}
+
 int daf_plan_copy_offsets(const daf_plan_t* plan, uint32_t* out_off) {
   if (plan == nullptr || out_off == nullptr) return DAF_EINVAL;
   if (plan->uniform_bits) {

@@ -65,6 +65,7 @@ hipError_t daf_launch_unpack_matmul(const daf_plan_t* p, const uint32_t* words, 
 // One call for several tensors of one dtype (daf_quantize_item_t / daf_dequantize_item_t: daf.h).
 hipError_t daf_launch_quantize_pack_batch(const daf_quantize_item_t* items, int32_t n_items, int dtype,
                                           hipStream_t stream);
+int daf_dequantize_route(const daf_plan_t* p, int dtype, bool relu_bwd, int64_t list_elems);   // a daf_dequantize_route_t
 hipError_t daf_launch_unpack_dequantize_batch(const daf_dequantize_item_t* items, int32_t n_items, int dtype,
                                               hipStream_t stream);
 

@@ -257,7 +257,7 @@ struct alignas(16) TileLds {
 };
 
 // U = 16-byte chunks per lane: 8; 16 for small tensors with per-group widths, 4 for 16-bit groups of 32 elements (see
-// launch_dtype).
+// route_of).
 template <int DT, int B, bool RELU_BWD, int U = kTileChunksPerLane>
 __device__ __forceinline__ void unpack_dequantize_tile_body(
     int64_t tile, int wave_in_block, const uint32_t* __restrict__ words, const float* __restrict__ mn,
@@ -713,24 +713,63 @@ hipError_t launch_chunks(const daf_plan_t* p, const uint32_t* words, const float
   return hipSuccess;
 }
 
+// Which kernel a call takes, and with what.  list_elems as above.
+struct Route {
+  daf_dequantize_route_t kind;
+  int64_t tiles;                 // whole tiles
+  int chunks_per_lane;           // of a tile
+  int32_t gs_log2;               // TILE
+  uint32_t magic;                // TILE_ANY
+};
+template <int DT>
+Route route_of(const daf_plan_t* p, bool relu_bwd, int64_t list_elems) {
+  Route r = {DAF_DEQUANTIZE_TILE, 0, kTileChunksPerLane, 0, 0u};
+  r.tiles = tile_path_tiles<DT>(p, &r.gs_log2);
+  if (r.tiles > 0) {
+    // A small tensor with per-group widths takes tiles of twice the size: every wave pays two
+    // round trips to memory (widths, then words) before it can store anything, and with few
+    // waves per SIMD to overlap them fewer, longer waves come out ahead (a 50 MB binary16 tensor:
+    // 14.5 -> 12.5 us; the 721 MB bfloat16 one prefers the smaller tile, 157 against 164 us).
+    if (list_elems == 0 && p->uniform_bits == 0 && r.tiles <= 8192) {
+      int32_t log2_big = 0;
+      const int64_t big_tiles = tile_path_tiles<DT>(p, &log2_big, 2 * kTileChunksPerLane);
+      if (big_tiles > 0) return {DAF_DEQUANTIZE_TILE, big_tiles, 2 * kTileChunksPerLane, log2_big, 0u};
+    }
+    return r;
+  }
+  r.tiles = any_tile_path_tiles<DT>(p, relu_bwd, list_elems, &r.magic);
+  if (r.tiles > 0) {
+    r.kind = DAF_DEQUANTIZE_TILE_ANY;
+    return r;
+  }
+  // Groups of 32 elements of a 16-bit format, one width: more than 64 in a whole tile, a tile of half the size holds 64
+  // (quantize and dequantize, chunk kernel / half tiles: 33 M elements, 2 bits 34.1 / 31.0 us, 246 M 213 / 197, 8 bits
+  // 254 / 243; with per-group widths 134 M 132 / 135: the chunk kernel stays).  The relu backward, alone: 34.6 M,
+  // 2 bits 26.0 / 26.7, 4 bits 26.9 / 28.0, 105 M 73.4 / 76.3, 199 M 151 / 142, 2 bits 139 / 133: from 2^27 elements on.
+  if (DT != kF32 && list_elems == 0 && p->uniform_bits && (!relu_bwd || p->n >= (int64_t)1 << 27)) {
+    r.tiles = tile_path_tiles<DT>(p, &r.gs_log2, kTileChunksPerLane / 2);
+    r.chunks_per_lane = kTileChunksPerLane / 2;
+    if (r.tiles > 0) return r;
+  }
+  return {DAF_DEQUANTIZE_CHUNK, 0, 0, 0, 0u};
+}
+
 template <int DT, bool RELU_BWD>
 hipError_t launch_dtype(const daf_plan_t* p, const uint32_t* words, const float* mn, const float* scale,
                         const uint8_t* d_bits, void* out_x, const void* grad, hipStream_t stream) {
   constexpr int kEpl = ElemTraits<DT>::kPerLoad;
-  int32_t gs_log2 = 0;
-  const int64_t n_tiles = tile_path_tiles<DT>(p, &gs_log2);
-  uint32_t magic = 0;
-  const int64_t any_tiles = n_tiles == 0 ? any_tile_path_tiles<DT>(p, RELU_BWD, 0, &magic) : 0;
-  if (any_tiles > 0) {
-    const bool left = any_tiles * kTileChunks * kEpl < p->n;
-    const unsigned blocks = (unsigned)((any_tiles + kWavesPerBlock - 1) / kWavesPerBlock) + (left ? 1u : 0u);
+  const Route r = route_of<DT>(p, RELU_BWD, 0);
+  if (r.kind == DAF_DEQUANTIZE_CHUNK) return launch_chunks<DT, RELU_BWD>(p, words, mn, scale, d_bits, out_x, grad, stream);
+  const bool left = r.tiles * kWave * r.chunks_per_lane * kEpl < p->n;
+  const unsigned blocks = (unsigned)((r.tiles + kWavesPerBlock - 1) / kWavesPerBlock) + (left ? 1u : 0u);
+  if (r.kind == DAF_DEQUANTIZE_TILE_ANY) {
 #define DAF_LAUNCH_L(BITS, LONG)                                                                                  \
   hipLaunchKernelGGL((k_unpack_dequantize_tile_any<DT, BITS, RELU_BWD, LONG>), dim3(blocks), dim3(kThreads), 0,    \
-                     stream, words, mn, scale, d_bits, p->d_off, any_tiles, p->group_size, magic, p->num_groups,  \
+                     stream, words, mn, scale, d_bits, p->d_off, r.tiles, p->group_size, r.magic, p->num_groups,  \
                      static_cast<u32x4*>(out_x), static_cast<const u32x4*>(grad), p->output_cached, p->n / kEpl,  \
                      p->n)
-#define DAF_LAUNCH(BITS)                 \
-  if (magic) DAF_LAUNCH_L(BITS, false);  \
+#define DAF_LAUNCH(BITS)                   \
+  if (r.magic) DAF_LAUNCH_L(BITS, false);  \
   else DAF_LAUNCH_L(BITS, true)
     switch (p->uniform_bits) {
       case 0: DAF_LAUNCH(0); break;
@@ -744,67 +783,36 @@ hipError_t launch_dtype(const daf_plan_t* p, const uint32_t* words, const float*
 #undef DAF_LAUNCH_L
     return hipGetLastError();
   }
-  if constexpr (kEpl == 8) {
-    // Groups of 32 elements of a 16-bit format, one width: more than 64 in a whole tile, a tile of half the size holds 64
-    // (quantize and dequantize, chunk kernel / half tiles: 33 M elements, 2 bits 34.1 / 31.0 us, 246 M 213 / 197, 8 bits
-    // 254 / 243; with per-group widths 134 M 132 / 135: the chunk kernel stays).  The relu backward, alone: 34.6 M,
-    // 2 bits 26.0 / 26.7, 4 bits 26.9 / 28.0, 105 M 73.4 / 76.3, 199 M 151 / 142, 2 bits 139 / 133: from 2^27 elements on.
-    constexpr int kHalf = kTileChunksPerLane / 2;
-    const bool pays = p->uniform_bits && (!RELU_BWD || p->n >= (int64_t)1 << 27);
-    const int64_t half_tiles = n_tiles == 0 && pays ? tile_path_tiles<DT>(p, &gs_log2, kHalf) : 0;
-    if (half_tiles > 0) {
-      const bool left = half_tiles * kWave * kHalf * kEpl < p->n;
-      const unsigned blocks = (unsigned)((half_tiles + kWavesPerBlock - 1) / kWavesPerBlock) + (left ? 1u : 0u);
-#define DAF_LAUNCH(BITS)                                                                                              \
-  hipLaunchKernelGGL((k_unpack_dequantize_tile<DT, BITS, RELU_BWD, kHalf>), dim3(blocks), dim3(kThreads), 0, stream, \
-                     words, mn, scale, d_bits, p->d_off, half_tiles, p->group_size, gs_log2,                         \
+#define DAF_LAUNCH_U(BITS, U)                                                                                   \
+  hipLaunchKernelGGL((k_unpack_dequantize_tile<DT, BITS, RELU_BWD, U>), dim3(blocks), dim3(kThreads), 0, stream, \
+                     words, mn, scale, d_bits, p->d_off, r.tiles, p->group_size, r.gs_log2,                     \
                      static_cast<u32x4*>(out_x), static_cast<const u32x4*>(grad), p->output_cached, p->n / kEpl, p->n)
+  if (r.chunks_per_lane == 2 * kTileChunksPerLane) {
+    DAF_LAUNCH_U(0, 2 * kTileChunksPerLane);             // (per-group widths only)
+    return hipGetLastError();
+  }
+  if (r.chunks_per_lane < kTileChunksPerLane) {
+    if constexpr (kEpl == 8) {
       switch (p->uniform_bits) {
-        case 1: DAF_LAUNCH(1); break;
-        case 2: DAF_LAUNCH(2); break;
-        case 4: DAF_LAUNCH(4); break;
-        case 8: DAF_LAUNCH(8); break;
+        case 1: DAF_LAUNCH_U(1, kTileChunksPerLane / 2); break;
+        case 2: DAF_LAUNCH_U(2, kTileChunksPerLane / 2); break;
+        case 4: DAF_LAUNCH_U(4, kTileChunksPerLane / 2); break;
+        case 8: DAF_LAUNCH_U(8, kTileChunksPerLane / 2); break;
         default: return hipErrorInvalidValue;
       }
-#undef DAF_LAUNCH
       return hipGetLastError();
     }
+    return hipErrorInvalidValue;
   }
-  if (n_tiles == 0) return launch_chunks<DT, RELU_BWD>(p, words, mn, scale, d_bits, out_x, grad, stream);
-  // A small tensor with per-group widths takes tiles of twice the size: every wave pays two
-  // round trips to memory (widths, then words) before it can store anything, and with few
-  // waves per SIMD to overlap them fewer, longer waves come out ahead (a 50 MB binary16 tensor:
-  // 14.5 -> 12.5 us; the 721 MB bfloat16 one prefers the smaller tile, 157 against 164 us).
-  if (p->uniform_bits == 0 && n_tiles <= 8192) {
-    int32_t log2_big = 0;
-    const int64_t big_tiles = tile_path_tiles<DT>(p, &log2_big, 2 * kTileChunksPerLane);
-    if (big_tiles > 0) {
-      constexpr int kBig = 2 * kTileChunks;
-      const bool left = big_tiles * kBig * kEpl < p->n;
-      const unsigned blocks = (unsigned)((big_tiles + kWavesPerBlock - 1) / kWavesPerBlock) + (left ? 1u : 0u);
-      hipLaunchKernelGGL((k_unpack_dequantize_tile<DT, 0, RELU_BWD, 2 * kTileChunksPerLane>), dim3(blocks), dim3(kThreads),
-                         0, stream, words, mn, scale, d_bits, p->d_off, big_tiles, p->group_size, log2_big,
-                         static_cast<u32x4*>(out_x), static_cast<const u32x4*>(grad), p->output_cached, p->n / kEpl,
-                         p->n);
-      return hipGetLastError();
-    }
-  }
-  const bool left = n_tiles * kTileChunks * kEpl < p->n;
-  const unsigned blocks = (unsigned)((n_tiles + kWavesPerBlock - 1) / kWavesPerBlock) + (left ? 1u : 0u);
-#define DAF_LAUNCH(BITS)                                                                                      \
-  hipLaunchKernelGGL((k_unpack_dequantize_tile<DT, BITS, RELU_BWD>), dim3(blocks), dim3(kThreads), 0, stream,  \
-                     words, mn, scale, d_bits, p->d_off, n_tiles, p->group_size, gs_log2,                     \
-                     static_cast<u32x4*>(out_x), static_cast<const u32x4*>(grad), p->output_cached,           \
-                     p->n / kEpl, p->n)
   switch (p->uniform_bits) {
-    case 0: DAF_LAUNCH(0); break;
-    case 1: DAF_LAUNCH(1); break;
-    case 2: DAF_LAUNCH(2); break;
-    case 4: DAF_LAUNCH(4); break;
-    case 8: DAF_LAUNCH(8); break;
+    case 0: DAF_LAUNCH_U(0, kTileChunksPerLane); break;
+    case 1: DAF_LAUNCH_U(1, kTileChunksPerLane); break;
+    case 2: DAF_LAUNCH_U(2, kTileChunksPerLane); break;
+    case 4: DAF_LAUNCH_U(4, kTileChunksPerLane); break;
+    case 8: DAF_LAUNCH_U(8, kTileChunksPerLane); break;
     default: return hipErrorInvalidValue;
   }
-#undef DAF_LAUNCH
+#undef DAF_LAUNCH_U
   return hipGetLastError();
 }
 
@@ -907,8 +915,7 @@ hipError_t launch_items(const daf_dequantize_item_t* items, int32_t n_items, hip
     const uint8_t* d_bits = it.bits ? it.bits : p->d_bits;
     const int64_t n_chunks = p->n / kEpl;
     const bool mixed = p->uniform_bits == 0;
-    int32_t gs_log2 = 0;
-    uint32_t magic = 0;
+    const Route r = route_of<DT>(p, false, list_elems);
     auto add_tiles = [&](auto& b, int& cur_bits) {
       const int64_t n_tiles = waves_of_entry(n_chunks);
       if (b.n == kMaxTileBatch || (b.n > 0 && p->uniform_bits != cur_bits) ||
@@ -926,17 +933,17 @@ hipError_t launch_items(const daf_dequantize_item_t* items, int32_t n_items, hip
       b.ends[b.n] = (uint32_t)e.tile_end;
       e.n_chunks = n_chunks;
       e.gs = p->group_size;
-      e.gs_log2 = gs_log2;
+      e.gs_log2 = r.gs_log2;
       e.cached = p->output_cached;
       return b.n++;
     };
-    if (tile_path_tiles<DT>(p, &gs_log2) > 0) {
+    if (r.kind == DAF_DEQUANTIZE_TILE) {
       add_tiles(tbatch, tcur_bits);
-    } else if (any_tile_path_tiles<DT>(p, false, list_elems, &magic) > 0) {
-      if (abatch.n > 0 && (abatch.e[0].magic != 0u) != (magic != 0u)) tflush(abatch, acur_bits);     // (two kernels)
+    } else if (r.kind == DAF_DEQUANTIZE_TILE_ANY) {
+      if (abatch.n > 0 && (abatch.e[0].magic != 0u) != (r.magic != 0u)) tflush(abatch, acur_bits);   // (two kernels)
       const int at = add_tiles(abatch, acur_bits);
       abatch.e[at].num_groups = p->num_groups;
-      abatch.e[at].magic = magic;
+      abatch.e[at].magic = r.magic;
     } else if (n_chunks > 0) {
       const int64_t per_block = (int64_t)kThreads * chunks_per_thread(mixed);
       const int64_t blocks = (n_chunks + per_block - 1) / per_block;
@@ -974,6 +981,15 @@ hipError_t launch_items(const daf_dequantize_item_t* items, int32_t n_items, hip
 }
 
 }  // namespace
+
+int daf_dequantize_route(const daf_plan_t* p, int dtype, bool relu_bwd, int64_t list_elems) {
+  switch (dtype) {
+    case daf::kF32:  return route_of<daf::kF32>(p, relu_bwd, list_elems).kind;
+    case daf::kF16:  return route_of<daf::kF16>(p, relu_bwd, list_elems).kind;
+    case daf::kBF16: return route_of<daf::kBF16>(p, relu_bwd, list_elems).kind;
+    default: return DAF_EUNSUPPORTED;
+  }
+}
 
 hipError_t daf_launch_unpack_dequantize_batch(const daf_dequantize_item_t* items, int32_t n_items, int dtype,
                                               hipStream_t stream) {

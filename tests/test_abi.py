@@ -149,3 +149,30 @@ def test_weight_gradient_tile(lib, m, n, k, dtype, tile):
     with pytest.raises(daf.DafError):
         daf.daf_unpack_matmul_schedule(plan, n + 1, k, torch.float16)
     plan.destroy()
+
+
+# n, group size, width, element format, (relu backward, elements of the list) -> route; plans that need no device
+@pytest.mark.parametrize("n,gs,b,dtype,call,want", [
+    (1 << 20, 64, 2, 0, (0, 0), 0), (1 << 20, 2048, 8, 0, (0, 0), 0), (1 << 20, 4096, 2, 1, (1, 0), 0),
+    # 4096 elements are two tiles in binary32
+    (1 << 20, 4096, 2, 0, (0, 0), 1), (1 << 20, 4096, 8, 0, (0, 0), 2), ((1 << 26) + 4096, 4096, 2, 0, (0, 0), 2),
+    # groups of 32: 64 to a tile in binary32, half tiles in a 16-bit call on one tensor
+    (1 << 20, 32, 2, 0, (0, 0), 0), (1 << 20, 32, 2, 1, (0, 0), 0), (1 << 20, 32, 2, 1, (0, 1 << 20), 2),
+    (1 << 20, 32, 2, 2, (1, 0), 2), (1 << 27, 32, 2, 2, (1, 0), 0),
+    # not a power of two
+    (768 * 4000, 768, 4, 1, (0, 0), 1), (768 * 4000, 768, 8, 0, (0, 0), 2), (96 * 40000, 96, 1, 0, (1, 0), 1),
+    (768 * 4000, 768, 1, 0, (0, 5 << 23), 1), (768 * 4000, 768, 1, 0, (0, (5 << 23) + 1), 2), (768 * 70000, 768, 1, 0, (0, 0), 1),
+    # longer than a tile
+    (40000 * 1677, 40000, 2, 1, (0, 0), 1), (40000 * 1677, 40000, 1, 1, (0, 0), 2), (40000 * 1678, 40000, 1, 1, (0, 0), 1),
+    (40000 * 1677, 40000, 4, 2, (0, 0), 1), (40000 * 1678, 40000, 4, 2, (0, 0), 2), (40000 * 1678, 40000, 8, 2, (0, 0), 1),
+    (40000 * 1677, 40000, 2, 0, (0, 0), 1), (40000 * 1678, 40000, 2, 0, (0, 0), 2),
+    (40000 * 419, 40000, 2, 1, (1, 0), 1), (40000 * 420, 40000, 2, 1, (1, 0), 2), (40000 * 209, 40000, 2, 0, (1, 0), 1),
+    (40000 * 210, 40000, 2, 0, (1, 0), 2), (40000 * 1048, 40000, 1, 0, (0, 0), 1), (40000 * 1049, 40000, 1, 0, (0, 0), 2),
+    (100, 64, 2, 1, (0, 0), 2)])
+def test_dequantize_route_of_uniform_plans(lib, n, gs, b, dtype, call, want):
+    rc, p = _plan(lib, (n,), gs, [b])
+    assert rc == 0
+    assert lib.daf_plan_dequantize_route(p, dtype, *call) == want
+    assert lib.daf_plan_dequantize_route(p, 7, 0, 0) == -2 and lib.daf_plan_dequantize_route(None, 0, 0, 0) == -1
+    assert lib.daf_plan_dequantize_route(p, dtype, 1, 5) == -1 and lib.daf_plan_dequantize_route(p, dtype, 0, -1) == -1
+    lib.daf_plan_destroy(p)
