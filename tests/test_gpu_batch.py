@@ -148,7 +148,9 @@ def test_batch_argument_errors(env):
 def test_long_groups_and_groups_of_32_dequantize_through_tiles(env, dtype, bits):
     """Groups longer than a tile: a tile inside one group, a group boundary in a tile's first, middle or last chunk,
     a last group of one element, one group for the tensor; groups of 32 elements; tensors that end inside a
-    tile.  Each as a call of its own and all in one list call."""
+    tile.  Each as a call of its own and all in one list call.  By rule the chunk kernel still takes: binary32 with 8
+    bits; 1 bit in a 16-bit format up to 2^26 elements (the tile route has a test of its own below); 16-bit groups of 32
+    with several widths or in a list."""
     daf, orc = env
     cases = [(8192 * 3, 8192), (8192 * 2 + 4096 + 1, 8192), (40000 * 3 + 8, 40000), (36896 * 4 + 1000, 36896),
              (65536 + 96 + 4096, 65536 + 96), (4096 * 9 + 77, 4096 * 10), (131072 + 1, 131072), (2048 * 5, 32), (2048 * 4 + 40, 32)]
@@ -162,6 +164,11 @@ def test_long_groups_and_groups_of_32_dequantize_through_tiles(env, dtype, bits)
         b = (np.random.default_rng(n).choice([1, 2, 4, 8], G).astype(np.uint8) if bits == "mixed" else np.array([bits], np.uint8))
         ow, omn, osc, _ = orc.quantize_pack(to_numpy_bits(x), dtype, gs, b, 3)
         plan = daf.daf_plan((n,), gs, torch.from_numpy(b).cuda() if b.size > 1 else int(b[0]))
+        if gs == 32:
+            route = "chunk" if dtype != F32 and b.size > 1 else "tile"
+        else:                                                    # (every other group size here is longer than a tile)
+            route = "chunk" if b.size == 1 and b[0] == (8 if dtype == F32 else 1) else "tile_any"
+        assert plan.dequantize_route(torch_dtype(dtype)) == route
         out = torch.full_like(x, 7.0, device="cuda:0")
         daf.daf_unpack_dequantize(plan, torch.from_numpy(ow.view(np.int32)).cuda(), torch.from_numpy(omn).cuda(),
                                   torch.from_numpy(osc).cuda(), out)

@@ -117,14 +117,15 @@ def test_select_bits_from_scale_in_place(env, G):
 
 def test_select_bits_workspace_reuse(env):
     """One workspace, filled with ones beforehand, serves calls of different sizes one after the
-    other: every call leaves its counters and tickets as the next one needs them.  Many equal
+    other: a call zeroes the counters it uses at its own start and leaves them as they are.  (Up to 8192
+    groups the workspace is not touched: 8193 and 12289 are the small calls between large ones.)  Many equal
     ranges spread over many blocks put the thresholds in the middle of runs of ties."""
     daf, orc = env
     rng = np.random.default_rng(11)
     G_max = 700_001
     ws = daf.daf_select_bits_workspace(G_max)
     ws.fill_(1)
-    for G in (G_max, 4099, 250_000, 1, G_max):
+    for G in (G_max, 8193, 250_000, 12_289, 4099, 8193, 1, G_max):
         gmin = np.zeros(G, dtype=np.float32)
         gmax = rng.choice([0.25, 0.5, 0.5, 0.5, 1.0, 1.0, 1.0, 1.0, 3.0], G).astype(np.float32)
         out = torch.full((G,), 255, dtype=torch.uint8, device="cuda:0")
