@@ -450,7 +450,7 @@ __device__ __forceinline__ void load_to_lds(uint32_t lds_base, uint32_t lane_off
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :
                : "s"(lds_base), "v"(lane_off), "s"(base)
-               : "memory");
+               : "memory", "m0");
 }
 // A pointer that is the same in all lanes, in scalar registers.
 __device__ __forceinline__ const char* uniform_pointer(const char* p) {
