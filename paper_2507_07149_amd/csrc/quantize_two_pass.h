@@ -78,7 +78,9 @@ __global__ __launch_bounds__(kThreads) void k_tile_minmax(const void* __restrict
 // enough for every workgroup of the quantize pass to reduce them itself (FOLD), and the launch between the two passes and
 // the one for the elements after the last whole tile are gone.  Quantize and dequantize, 2 bits, before / now:
 // binary16 2.3 M elements 21.2 / 14.9 us, 67 M 93 / 77; binary32 31 M 74.0 / 67.9, 51 M 115.4 / 110.1, 67 M 152 / 139.
-// (16 waves: binary32 51 M 115.2, too few of them fit a compute unit; the other sizes within 1 us.)
+// (16 waves: binary32 51 M 115.2, too few of them fit a compute unit; the other sizes within 1 us.)  Quantize alone at the other
+// widths, binary16: 1 bit 4.2 M 11.4 / 8.6, 34.6 M 28.1 / 28.4, 66 M 48.0 / 47.0; 8 bits 11.5 / 8.8, 32.1 / 32.9, 56.5 / 56.1;
+// binary32: 1 bit 16.8 M 26.9 / 26.1, 66 M 90.4 / 86.2; 8 bits 28.9 / 27.2, 100.4 / 95.0.
 constexpr int kFoldThreads = 512, kFoldTiles = kFoldThreads / kWave;
 template <int DT>
 __global__ __launch_bounds__(kFoldThreads) void k_block_minmax(const void* __restrict__ x, int64_t n_full_tiles, int64_t n,
