@@ -1,5 +1,5 @@
 // Route "group": one wave (or workgroup) per group with element loads: whatever the other routes
-// leave over (groups after the last whole tile, the tensor's short last group).
+// leave over (the tensor's short last group after long ones, tensors shorter than a group, sizes of no other route).
 #pragma once
 #include "quantize_common.h"
 

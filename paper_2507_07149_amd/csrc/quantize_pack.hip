@@ -15,8 +15,8 @@
 //   two passes             longer groups and per-tensor statistics (k_tile_minmax,
 //                          k_group_reduce, then k_quantize_pack_tile with the group's pair).
 //   k_quantize_pack_group  one wave (or workgroup) per group, element loads: whatever the others
-//                          leave, i.e. the groups after the last full tile and the short last
-//                          group.
+//                          leave, i.e. the short last group after long ones, and sizes beyond 65536.
+// (tile and units: the tile in which the tensor ends is a short one of the same kind, short_tile_load.)
 //
 // Rounding arithmetic.  With mn, L = 2^b-1 and inv = L/range of the group, an element maps to
 // v = (x-mn)*inv and is rounded up iff r + 1/2 < frac(v)*256 for its random byte r, i.e. iff
@@ -101,34 +101,32 @@ __global__ __launch_bounds__(kThreads) void k_group_minmax_group(const void* __r
 }
 
 template <int DT, int LPG_LOG2>
-__global__ __launch_bounds__(kThreads) void k_group_minmax_tile(const u32x4* __restrict__ x, int64_t n_tiles,
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_group_minmax_tile(const u32x4* __restrict__ x, int64_t n_tiles,
                                                                 float* __restrict__ out_min,
-                                                                float* __restrict__ out_max, int64_t n_elems,
-                                                                int64_t left_begin, int64_t left_end) {
+                                                                float* __restrict__ out_max, int short_len) {
   using S = TileShape<DT, LPG_LOG2>;
   __shared__ float2 stat_all[kWavesPerBlock][kWave];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // groups left over after the last whole tile: one more workgroup, the first of the grid
-  const unsigned first_tile_block = left_end > left_begin ? 1u : 0u;
-  if (blockIdx.x < first_tile_block) {
-    group_minmax_group_body<DT>(x, n_elems, S::kGroupSize, left_begin, left_end, out_min, out_max, wave_in_block,
-                                kWavesPerBlock);
-    return;
-  }
-  const int64_t tile = (int64_t)(blockIdx.x - first_tile_block) * kWavesPerBlock + wave_in_block;
-  if (tile >= n_tiles) return;
+  const int64_t tile = (int64_t)blockIdx.x * kWavesPerBlock + wave_in_block;
+  int groups = S::kGroups;
   float2* stat = stat_all[wave_in_block];
   uint4 raw[S::kLoads];
+  if (tile < n_tiles) {
 #pragma unroll
-  for (int u = 0; u < S::kLoads; ++u) {
-    const u32x4 v = __builtin_nontemporal_load(&x[tile * (S::kLoads * kWave) + u * kWave + lane]);
-    raw[u] = make_uint4(v.x, v.y, v.z, v.w);
+    for (int u = 0; u < S::kLoads; ++u) {
+      const u32x4 v = __builtin_nontemporal_load(&x[tile * (S::kLoads * kWave) + u * kWave + lane]);
+      raw[u] = make_uint4(v.x, v.y, v.z, v.w);
+    }
+  } else {                             // the tile in which the tensor ends
+    if (tile > n_tiles || short_len == 0) return;
+    short_tile_load<DT>(&x[tile * (S::kLoads * kWave)], short_len, lane, raw);
+    groups = (short_len + S::kGroupSize - 1) / S::kGroupSize;
   }
   float xf[S::kLoads][S::kEpl];
   tile_minmax<DT, LPG_LOG2>(raw, xf, stat, lane);
   wave_lds_sync();
-  if (lane < S::kGroups) {
+  if (lane < groups) {
     float2 st = stat[lane * S::kLoadsPerGroup];
 #pragma unroll
     for (int j = 1; j < S::kLoadsPerGroup; ++j) {
@@ -156,26 +154,19 @@ template <int DT>
 __global__ __launch_bounds__(kThreads) void k_group_minmax_units(const u32x4* __restrict__ x, int64_t n_tiles, int32_t m,
                                                                  int32_t k_full, int32_t k_last, int32_t part_log2,
                                                                  float* __restrict__ out_min,
-                                                                 float* __restrict__ out_max, int64_t n_elems,
-                                                                 int64_t left_begin, int64_t left_end) {
+                                                                 float* __restrict__ out_max, int short_len) {
   using S = UnitShape<DT>;
   __shared__ float2 ustat_all[kWavesPerBlock][S::kUnits];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // the tensor's short last group: one more workgroup, the first of the grid
-  const unsigned first_tile_block = left_end > left_begin ? 1u : 0u;
-  if (blockIdx.x < first_tile_block) {
-    group_minmax_group_body<DT>(x, n_elems, m * 32, left_begin, left_end, out_min, out_max, wave_in_block,
-                                kWavesPerBlock);
-    return;
-  }
-  const int64_t tile = (int64_t)(blockIdx.x - first_tile_block) * kWavesPerBlock + wave_in_block;
+  const int64_t tile = (int64_t)blockIdx.x * kWavesPerBlock + wave_in_block;
   if (tile >= n_tiles) return;
   const int k = (tile == n_tiles - 1) ? k_last : k_full;
   const uint32_t n_chunks = ((uint32_t)(k * m)) << S::kLanesLog2;
   const int64_t chunk0 = tile * (int64_t)(((uint32_t)(k_full * m)) << S::kLanesLog2);
   uint4 raw[S::kLoads];
-  unit_tile_load<DT>(x, chunk0, n_chunks, lane, raw);
+  if (short_len > 0 && tile == n_tiles - 1) short_tile_load<DT>(&x[chunk0], short_len, lane, raw);
+  else unit_tile_load<DT>(x, chunk0, n_chunks, lane, raw);
   float xf[S::kLoads][S::kEpl];
   const float2 st = unit_tile_stats<DT>(raw, xf, ustat_all[wave_in_block], k, m, part_log2, lane);
   if (lane < k) {
@@ -212,12 +203,12 @@ hipError_t launch_group_minmax(const daf_plan_t* p, const void* x, float* out_mi
   case (1 << LOG2):                                                                                             \
     if constexpr (TileShape<DT, LOG2>::kValid) {                                                                \
       const int64_t n_tiles = full_groups / TileShape<DT, LOG2>::kGroups;                                       \
-      const int64_t left = n_tiles * TileShape<DT, LOG2>::kGroups;                                              \
-      if (n_tiles > 0) {                                                                                        \
-        hipLaunchKernelGGL((k_group_minmax_tile<DT, LOG2>), dim3((unsigned)((n_tiles + kWavesPerBlock - 1) /    \
-                           kWavesPerBlock) + (left < p->num_groups ? 1u : 0u)), dim3(kThreads), 0, stream,      \
-                           static_cast<const u32x4*>(x), n_tiles, out_min, out_max, p->n, left, p->num_groups); \
-        fast_groups = p->num_groups;        /* the leftover groups ride in the same launch */                   \
+      const int short_len = (int)(p->n - n_tiles * TileShape<DT, LOG2>::kElems);                                \
+      if (full_groups > 0) {                                                                                    \
+        hipLaunchKernelGGL((k_group_minmax_tile<DT, LOG2>), dim3((unsigned)((n_tiles + (short_len > 0) +        \
+                           kWavesPerBlock - 1) / kWavesPerBlock)), dim3(kThreads), 0, stream,                   \
+                           static_cast<const u32x4*>(x), n_tiles, out_min, out_max, short_len);                 \
+        fast_groups = p->num_groups;        /* the tile in which the tensor ends included */                    \
       }                                                                                                         \
     }                                                                                                           \
     break;
@@ -232,11 +223,10 @@ hipError_t launch_group_minmax(const daf_plan_t* p, const void* x, float* out_mi
   }
   UnitGeometry ug;
   if (fast_groups == 0 && unit_geometry(p, &ug)) {
-    hipLaunchKernelGGL((k_group_minmax_units<DT>), dim3((unsigned)((ug.n_tiles + kWavesPerBlock - 1) / kWavesPerBlock) +
-                       (ug.full_groups < p->num_groups ? 1u : 0u)), dim3(kThreads), 0, stream,
-                       static_cast<const u32x4*>(x), ug.n_tiles, ug.m, ug.k, ug.k_last, ug.part_log2, out_min, out_max,
-                       p->n, ug.full_groups, p->num_groups);
-    fast_groups = p->num_groups;            // the short last group rides in the same launch
+    hipLaunchKernelGGL((k_group_minmax_units<DT>), dim3((unsigned)((ug.n_tiles + kWavesPerBlock - 1) / kWavesPerBlock)),
+                       dim3(kThreads), 0, stream, static_cast<const u32x4*>(x), ug.n_tiles, ug.m, ug.k, ug.k_last,
+                       ug.part_log2, out_min, out_max, ug.short_len);
+    fast_groups = p->num_groups;            // the short last group included
   }
   const int64_t rest = p->num_groups - fast_groups;
   if (rest > 0) {
@@ -248,12 +238,13 @@ hipError_t launch_group_minmax(const daf_plan_t* p, const void* x, float* out_mi
   return hipGetLastError();
 }
 
-// Tiles per tensor on the fast path (0 if the plan is not eligible) and the groups they cover.
+// Whether the plan takes the fast path; its whole tiles, and the elements of the tile in which the tensor ends (0 if
+// that is a whole one).  A tensor shorter than one group goes the general way.
 template <int DT>
-bool tile_geometry(const daf_plan_t* p, int* lpg_log2, int64_t* n_tiles, int64_t* fast_groups) {
+bool tile_geometry(const daf_plan_t* p, int* lpg_log2, int64_t* n_tiles, int* short_len) {
   constexpr int kEpl = ElemTraits<DT>::kPerLoad;
   *n_tiles = 0;
-  *fast_groups = 0;
+  *short_len = 0;
   if (p->d_big_scratch != nullptr) return false;
   const int32_t lpg = p->group_size / kEpl;
   if (p->group_size % kEpl != 0 || lpg < 4 || (lpg & (lpg - 1)) != 0) return false;
@@ -264,8 +255,8 @@ bool tile_geometry(const daf_plan_t* p, int* lpg_log2, int64_t* n_tiles, int64_t
     if constexpr (QTile<DT, LOG2>::kValid) {                             \
       *lpg_log2 = LOG2;                                                  \
       *n_tiles = full_groups / QTile<DT, LOG2>::kGroups;                 \
-      *fast_groups = *n_tiles * QTile<DT, LOG2>::kGroups;                \
-      ok = *n_tiles > 0;                                                 \
+      *short_len = (int)(p->n - *n_tiles * QTile<DT, LOG2>::kElems);     \
+      ok = full_groups > 0;                                              \
     }                                                                    \
     break;
   switch (lpg) {
@@ -280,12 +271,12 @@ bool tile_geometry(const daf_plan_t* p, int* lpg_log2, int64_t* n_tiles, int64_t
 // Which kernels a plan's quantize call uses for its whole groups (the values of daf_route_t).
 template <int DT>
 int quantize_route(const daf_plan_t* p) {
-  int log2 = 0;
-  int64_t n_tiles = 0, fast_groups = 0;
+  int log2 = 0, short_len = 0;
+  int64_t n_tiles = 0;
   UnitGeometry ug;
   if (long_applies(p)) return 2;
   if (p->d_big_scratch != nullptr) return 3;
-  if (tile_geometry<DT>(p, &log2, &n_tiles, &fast_groups)) return 0;
+  if (tile_geometry<DT>(p, &log2, &n_tiles, &short_len)) return 0;
   if (unit_geometry(p, &ug)) return 1;
   return 4;
 }
@@ -310,7 +301,7 @@ hipError_t launch_dtype(const daf_plan_t* p, const void* x, uint64_t seed, uint3
                           big_scratch ? big_scratch : p->d_big_scratch, stream);
   }
 
-  // fast path: groups of 4 .. 1024 chunks (a power of two, at most one tile), whole tiles only
+  // fast path: groups of 4 .. 1024 chunks (a power of two, at most one tile)
   const int32_t lpg = p->group_size / kEpl;
   if (route == 0) {
     int64_t n_tiles = 0;
@@ -319,10 +310,9 @@ hipError_t launch_dtype(const daf_plan_t* p, const void* x, uint64_t seed, uint3
   case (1 << LOG2):                                                                                      \
     if constexpr (QTile<DT, LOG2>::kValid) {                                                             \
       n_tiles = full_groups / QTile<DT, LOG2>::kGroups;                                                  \
-      fast_groups = p->num_groups;          /* the leftover groups ride in the same launch */            \
-      if (n_tiles > 0) e = launch_tile<DT, LOG2, METRICS, RELU>(p, x, n_tiles, seed_lo, seed_hi, out_words, \
-                                                                out_min, out_scale, out_metrics, out_y,  \
-                                                                stream);                                 \
+      fast_groups = p->num_groups;          /* the tile in which the tensor ends included */             \
+      e = launch_tile<DT, LOG2, METRICS, RELU>(p, x, n_tiles, seed_lo, seed_hi, out_words, out_min,      \
+                                               out_scale, out_metrics, out_y, stream);                   \
     }                                                                                                    \
     break;
     switch (lpg) {
@@ -366,8 +356,14 @@ template <int DT, int LPG_LOG2>
 hipError_t launch_batch_bits(const Batch& batch, int32_t uniform_bits, hipStream_t stream) {
   const int64_t tiles = batch.e[batch.n - 1].tile_end;
   const unsigned blocks = (unsigned)((tiles + kWavesPerBlock - 1) / kWavesPerBlock);
-#define DAF_LAUNCH(BITS) \
-  hipLaunchKernelGGL((k_quantize_pack_tile_batch<DT, LPG_LOG2, BITS>), dim3(blocks), dim3(kThreads), 0, stream, batch)
+  bool any_short = false;
+  for (int i = 0; i < batch.n; ++i) any_short = any_short || batch.e[i].short_len > 0;
+#define DAF_LAUNCH(BITS)                                                                                                  \
+  do {                                                                                                                    \
+    auto kernel = any_short ? k_quantize_pack_tile_batch<DT, LPG_LOG2, BITS, true>                                        \
+                            : k_quantize_pack_tile_batch<DT, LPG_LOG2, BITS, false>;                                      \
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), 0, stream, batch);                                           \
+  } while (0)
   switch (uniform_bits) {
     case 0: DAF_LAUNCH(0); break;
     case 1: DAF_LAUNCH(1); break;
@@ -396,9 +392,8 @@ hipError_t launch_batch(const Batch& batch, int lpg_log2, int32_t uniform_bits, 
 }
 
 // Same results as one daf_launch_quantize_pack per item.  Consecutive items whose plans share
-// group size and width kind go into one launch for their whole tiles (at most kMaxBatch per
-// launch); the groups after an item's last whole tile, and items the fast path does not cover,
-// are launched as before.
+// group size and width kind go into one launch (at most kMaxBatch per launch); the short last groups of
+// items with long groups share launches of their own, items the fast path does not cover have one each.
 template <int DT>
 hipError_t launch_items(const daf_quantize_item_t* items, int32_t n_items, hipStream_t stream) {
   Batch batch;
@@ -424,7 +419,7 @@ hipError_t launch_items(const daf_quantize_item_t* items, int32_t n_items, hipSt
     }
     gb.n = 0;
   };
-  // the groups [g_begin, num_groups) of an item, to be quantized group by group
+  // the short last group of an item with long groups: the groups [g_begin, num_groups), group by group
   auto leftovers = [&](const daf_quantize_item_t& it, int64_t g_begin) {
     const daf_plan_t* p = it.plan;
     if (g_begin >= p->num_groups || err != hipSuccess) return;
@@ -472,8 +467,13 @@ hipError_t launch_items(const daf_quantize_item_t* items, int32_t n_items, hipSt
   auto uflush = [&]() {
     if (ubatch.n > 0 && err == hipSuccess) {
       const unsigned blocks = (unsigned)((ubatch.e[ubatch.n - 1].tile_end + kWavesPerBlock - 1) / kWavesPerBlock);
-#define DAF_LAUNCH(BITS) \
-  hipLaunchKernelGGL((k_quantize_pack_units_batch<DT, BITS>), dim3(blocks), dim3(kThreads), 0, stream, ubatch)
+      bool any_short = false;
+      for (int j = 0; j < ubatch.n; ++j) any_short = any_short || ubatch.e[j].short_len > 0;
+#define DAF_LAUNCH(BITS)                                                                                                  \
+  do {                                                                                                                    \
+    auto kernel = any_short ? k_quantize_pack_units_batch<DT, BITS, true> : k_quantize_pack_units_batch<DT, BITS, false>; \
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), 0, stream, ubatch);                                          \
+  } while (0)
       switch (ucur_bits) {
         case 0: DAF_LAUNCH(0); break;
         case 1: DAF_LAUNCH(1); break;
@@ -490,8 +490,8 @@ hipError_t launch_items(const daf_quantize_item_t* items, int32_t n_items, hipSt
   for (int32_t i = 0; i < n_items && err == hipSuccess; ++i) {
     const daf_quantize_item_t& it = items[i];
     const daf_plan_t* p = it.plan;
-    int log2 = 0;
-    int64_t n_tiles = 0, fast_groups = 0;
+    int log2 = 0, short_len = 0;
+    int64_t n_tiles = 0;
     if (long_applies(p)) {
       const int32_t m = p->group_size / 32;
       const int32_t n_waves = (m + 127) / 128;
@@ -539,18 +539,19 @@ hipError_t launch_items(const daf_quantize_item_t* items, int32_t n_items, hipSt
       e.k_last = ug.k_last;
       e.part_log2 = ug.part_log2;
       e.magic = (65536u + (uint32_t)ug.m - 1u) / (uint32_t)ug.m;
+      e.short_len = ug.short_len;
       ++ubatch.n;
-      leftovers(it, ug.full_groups);                                    // the short last group
       continue;
     }
-    if (!tile_geometry<DT>(p, &log2, &n_tiles, &fast_groups)) {
+    if (!tile_geometry<DT>(p, &log2, &n_tiles, &short_len)) {
       flush();
       if (err == hipSuccess)
         err = launch_dtype<DT, false>(p, it.x, it.seed, it.out_words, it.out_min, it.out_scale, nullptr, nullptr, stream);
       continue;
     }
+    const int64_t tiles = n_tiles + (short_len > 0);
     if (batch.n == kMaxBatch || (batch.n > 0 && (p->group_size != cur_gs || p->uniform_bits != cur_bits)) ||
-        (batch.n > 0 && batch.e[batch.n - 1].tile_end + n_tiles > 0x7fffffff))
+        (batch.n > 0 && batch.e[batch.n - 1].tile_end + tiles > 0x7fffffff))
       flush();
     cur_log2 = log2;
     cur_gs = p->group_size;
@@ -562,12 +563,12 @@ hipError_t launch_items(const daf_quantize_item_t* items, int32_t n_items, hipSt
     e.words = it.out_words;
     e.mn = it.out_min;
     e.sc = it.out_scale;
-    e.tile_end = (batch.n ? batch.e[batch.n - 1].tile_end : 0) + n_tiles;
+    e.tile_end = (int32_t)((batch.n ? batch.e[batch.n - 1].tile_end : 0) + tiles);
+    e.short_len = short_len;
     batch.ends[batch.n] = (uint32_t)e.tile_end;
     e.seed_lo = (uint32_t)it.seed;
     e.seed_hi = (uint32_t)(it.seed >> 32);
     ++batch.n;
-    leftovers(it, fast_groups);                                         // groups after the last whole tile
   }
   flush();
   uflush();

@@ -75,6 +75,71 @@ struct alignas(16) WaveLds {
   float gvar[kWave];                    // sum of T*(256-T) per group (metrics variant)
 };
 
+// ---- the tile in which a tensor ends ---------------------------------------------------------
+// A tensor rarely ends with a whole tile.  What is left, whole groups and at last a short one, is one more tile whose
+// chunks past the end hold copies of the tensor's last element: they leave the short group's minimum and maximum as
+// they are, and their codes are set to 0, which is what a packed word holds behind its last element.  The groups
+// used to go one by one through quantize_pack_group_body in a workgroup of their own, up to 63 chains of
+// dependent loads of ~3 us each behind four waves: 6774528 bfloat16 elements, groups of 64, three widths, both directions
+// 52.7 us, now 13.4.
+constexpr int kMaxEpl = 8;
+// `len` elements, 1 <= len < LOADS * kWave * kEpl, from `chunks` on; chunk u * kWave + lane goes to raw[u].
+template <int DT, int LOADS>
+__device__ __forceinline__ void short_tile_load(const u32x4* chunks, int len, int lane, uint4 (&raw)[LOADS]) {
+  constexpr int kEpl = ElemTraits<DT>::kPerLoad;
+  const int whole = len / kEpl, last = len - 1;
+  // every load is issued before any is used, the elements one by one behind the chunks
+  u32x4 v[LOADS];
+#pragma unroll
+  for (int u = 0; u < LOADS; ++u) v[u] = u32x4{0u, 0u, 0u, 0u};
+  if (whole > 0) {
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) {
+      const int c = u * kWave + lane;
+      v[u] = __builtin_nontemporal_load(&chunks[c < whole ? c : whole - 1]);
+    }
+  }
+  uint32_t elem[kEpl], edge[4], end;                 // the chunk the tensor ends in; a dword behind it
+#pragma unroll
+  for (int e = 0; e < kEpl; ++e) {
+    const int i = whole * kEpl + e < len ? whole * kEpl + e : last;
+    elem[e] = DT == kF32 ? reinterpret_cast<const uint32_t*>(chunks)[i] : reinterpret_cast<const uint16_t*>(chunks)[i];
+  }
+  end = elem[kEpl - 1];                              // fewer than kEpl are left: the last element
+  if (DT != kF32) end |= end << 16;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    edge[e] = DT == kF32 ? elem[e] : elem[(2 * e) % kEpl] | (elem[(2 * e + 1) % kEpl] << 16);
+#pragma unroll
+  for (int u = 0; u < LOADS; ++u) {
+    const int c = u * kWave + lane;
+    raw[u] = c < whole    ? make_uint4(v[u].x, v[u].y, v[u].z, v[u].w)
+             : c == whole ? make_uint4(edge[0], edge[1], edge[2], edge[3])
+                          : make_uint4(end, end, end, end);
+  }
+}
+// The first `len` elements of such a tile to `chunks`.
+template <int DT, int LOADS>
+__device__ __forceinline__ void short_tile_store(u32x4* chunks, int len, int lane, const uint4 (&raw)[LOADS]) {
+  constexpr int kEpl = ElemTraits<DT>::kPerLoad;
+  const int whole = len / kEpl, rest = len % kEpl;
+#pragma unroll
+  for (int u = 0; u < LOADS; ++u) {
+    const int c = u * kWave + lane;
+    if (c < whole) {
+      chunks[c] = u32x4{raw[u].x, raw[u].y, raw[u].z, raw[u].w};
+    } else if (c == whole) {
+      const uint32_t w[4] = {raw[u].x, raw[u].y, raw[u].z, raw[u].w};
+#pragma unroll
+      for (int e = 0; e < kEpl; ++e) {
+        if (e >= rest) continue;
+        if (DT == kF32) reinterpret_cast<uint32_t*>(chunks)[c * kEpl + e] = w[e % 4];
+        else reinterpret_cast<uint16_t*>(chunks)[c * kEpl + e] = (uint16_t)(w[e / 2] >> (16 * (e & 1)));
+      }
+    }
+  }
+}
+
 // Codes of one 16-byte chunk, accumulated most significant first and NEGATED (the element map
 // yields -code): nacc0 = -(elements 0..3), nacc1 = -(elements 4..7) (16-bit inputs only).
 //
@@ -82,11 +147,14 @@ struct alignas(16) WaveLds {
 // quantization error and tensor magnitude): err += (x - xhat)^2 with xhat = fma(code, scale, mn)
 // as the dequantizer computes it, mag += x^2, both in binary32; var = sum of T*(256-T), the
 // variance of the stochastic rounding in units of scale^2 / 65536 (exact integer).
+//
+// Elements from `valid` on (the tensor ends in this chunk or before it) count as code 0 and for no sum.
 template <int DT, bool EXACT2, bool METRICS = false>
 __device__ __forceinline__ void quantize_chunk(const float (&xf)[ElemTraits<DT>::kPerLoad], float mn,
                                                float invs, uint32_t b, const uint32_t* rnd,
                                                uint32_t& nacc0, uint32_t& nacc1, float scale = 0.0f,
-                                               float* err = nullptr, float* mag = nullptr, float* var = nullptr) {
+                                               float* err = nullptr, float* mag = nullptr, float* var = nullptr,
+                                               int valid = kMaxEpl) {
   constexpr int kEpl = ElemTraits<DT>::kPerLoad;
   uint32_t nacc[2] = {0u, 0u};
   float e2 = 0.0f, m2 = 0.0f;
@@ -98,9 +166,12 @@ __device__ __forceinline__ void quantize_chunk(const float (&xf)[ElemTraits<DT>:
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const float xv = xf[q * 4 + e];
-      const int nc = neg_code<EXACT2>(xv, mn, invs, (rw >> (8 * e)) & 0xFFu, METRICS ? &rt[e] : nullptr);
+      int nc = neg_code<EXACT2>(xv, mn, invs, (rw >> (8 * e)) & 0xFFu, METRICS ? &rt[e] : nullptr);
+      const bool in = q * 4 + e < valid;
+      nc = in ? nc : 0;
       nacc[q] = (nacc[q] << b) + (uint32_t)nc;
-      if (METRICS) {
+      if (METRICS && !in) rt[e] = 0;
+      if (METRICS && in) {
         const float d = xv - __builtin_fmaf((float)(-nc), scale, mn);
         e2 = __builtin_fmaf(d, d, e2);
         m2 = __builtin_fmaf(xv, xv, m2);
@@ -121,7 +192,8 @@ __device__ __forceinline__ void quantize_chunk(const float (&xf)[ElemTraits<DT>:
 // one mixed-precision fma per element (the widening conversion disappears into it).
 template <bool EXACT2>
 __device__ __forceinline__ void quantize_chunk_f16(const uint4& raw, float mn, float invs, uint32_t b,
-                                                   const uint32_t* rnd, uint32_t& nacc0, uint32_t& nacc1) {
+                                                   const uint32_t* rnd, uint32_t& nacc0, uint32_t& nacc1,
+                                                   int valid = kMaxEpl) {
   const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
   uint32_t nacc[2] = {0u, 0u};
 #pragma unroll
@@ -131,7 +203,8 @@ __device__ __forceinline__ void quantize_chunk_f16(const uint4& raw, float mn, f
     for (int e = 0; e < 4; ++e) {
       const uint32_t pair = w[q * 2 + (e >> 1)];
       const float d = (e & 1) ? min_minus_half<1>(pair, mn) : min_minus_half<0>(pair, mn);
-      nacc[q] = (nacc[q] << b) + (uint32_t)neg_code_of_difference<EXACT2>(d, invs, (rw >> (8 * e)) & 0xFFu);
+      const int nc = neg_code_of_difference<EXACT2>(d, invs, (rw >> (8 * e)) & 0xFFu);
+      nacc[q] = (nacc[q] << b) + (uint32_t)(q * 4 + e < valid ? nc : 0);
     }
   }
   nacc0 = nacc[0];
@@ -307,39 +380,55 @@ __device__ __forceinline__ float2 fold_pairs(const float2* __restrict__ pairs, i
 // written to out_y in the same layout (out_y may be x itself: a lane only overwrites chunks it
 // has already loaded), and everything else sees y.
 //
+// SHORT: the tile in which the tensor ends; it holds `len` elements (short_tile_load).
+//
 // FOLD (with EXT, one group for the tensor): ext_stat holds n_ext (min, max) pairs that every workgroup reduces for
 // itself, behind the tile's loads; all its waves take part (fold_pairs has a barrier).
+// (The LDS of a workgroup: one place for a kernel's whole and short tiles.)
+template <int DT, int LPG_LOG2, int DIV>
+__device__ __forceinline__ WaveLds<DT, LPG_LOG2, DIV>* tile_lds() {
+  __shared__ WaveLds<DT, LPG_LOG2, DIV> all[kWavesPerBlock];
+  return all;
+}
+
 template <int DT, int LPG_LOG2, int B, bool EXT = false, bool METRICS = false, bool RELU = false, int DIV = 1,
-          bool FOLD = false>
+          bool FOLD = false, bool SHORT = false>
 __device__ __forceinline__ void quantize_pack_tile_body(
     typename std::conditional<RELU, const u32x4*, const u32x4* __restrict__>::type x, int64_t tile, int wave_in_block,
     const uint8_t* __restrict__ bits, const uint32_t* __restrict__ off, uint32_t seed_lo, uint32_t seed_hi,
     uint32_t* __restrict__ words, float* __restrict__ out_min, float* __restrict__ out_scale,
     const float2* __restrict__ ext_stat, int64_t tiles_per_group, float* __restrict__ out_metrics,
-    u32x4* out_y, int n_ext = 0) {
+    u32x4* out_y, int n_ext = 0, int len = 0) {
   using S = TileShape<DT, LPG_LOG2, DIV>;
   static_assert(!FOLD || EXT, "pairs are folded for external statistics");
   static_assert(!EXT || S::kGroups == 1, "external statistics: the tile is part of one group");
   static_assert(!(EXT && METRICS), "metrics are not computed for groups longer than a tile");
   static_assert(!METRICS || S::kLoads % 2 == 0, "the metrics' sums over the lanes are taken two loads at a time");
   static_assert(!(RELU && (EXT || METRICS)), "the fused max(z, 0) exists for the plain tile kernel only");
+  static_assert(!(SHORT && EXT), "a short tile holds whole groups and the tensor's last");
   constexpr int kEpl = S::kEpl;
   constexpr bool kMixed = (B == 0);
   constexpr uint32_t kGroupWords32 = S::kGroupSize / 32;      // words per group and bit of width
-  __shared__ WaveLds<DT, LPG_LOG2, DIV> lds_all[kWavesPerBlock];
 
   const int lane = threadIdx.x & (kWave - 1);
-  WaveLds<DT, LPG_LOG2, DIV>& lds = lds_all[wave_in_block];
+  WaveLds<DT, LPG_LOG2, DIV>& lds = tile_lds<DT, LPG_LOG2, DIV>()[wave_in_block];
   const uint32_t lane_in_run = (uint32_t)(lane & (S::kLpg - 1));
   // LDS byte address of the staging area (16-byte aligned, so the byte swizzles commute with it)
   const uint32_t stage_base = (uint32_t)reinterpret_cast<uintptr_t>(lds.stage);
+  // groups of the tile, and the length of the last one
+  const int n_groups = SHORT ? (len + S::kGroupSize - 1) / S::kGroupSize : S::kGroups;
+  const uint32_t last_len = SHORT ? (uint32_t)(len - (n_groups - 1) * S::kGroupSize) : (uint32_t)S::kGroupSize;
 
   // 1. all global loads of the tile, issued up front
   uint4 raw[S::kLoads];
+  if constexpr (SHORT) {
+    short_tile_load<DT>(&x[tile * (S::kLoads * kWave)], len, lane, raw);
+  } else {
 #pragma unroll
-  for (int u = 0; u < S::kLoads; ++u) {
-    const u32x4 v = __builtin_nontemporal_load(&x[tile * (S::kLoads * kWave) + u * kWave + lane]);
-    raw[u] = make_uint4(v.x, v.y, v.z, v.w);
+    for (int u = 0; u < S::kLoads; ++u) {
+      const u32x4 v = __builtin_nontemporal_load(&x[tile * (S::kLoads * kWave) + u * kWave + lane]);
+      raw[u] = make_uint4(v.x, v.y, v.z, v.w);
+    }
   }
   if constexpr (RELU) {
 #pragma unroll
@@ -347,8 +436,9 @@ __device__ __forceinline__ void quantize_pack_tile_body(
       raw[u] = make_uint4(relu_bits<DT>(raw[u].x), relu_bits<DT>(raw[u].y), relu_bits<DT>(raw[u].z),
                           relu_bits<DT>(raw[u].w));
       const u32x4 y = {raw[u].x, raw[u].y, raw[u].z, raw[u].w};
-      out_y[tile * (S::kLoads * kWave) + u * kWave + lane] = y;    // the next layer reads it soon: cached store
+      if (!SHORT) out_y[tile * (S::kLoads * kWave) + u * kWave + lane] = y;    // the next layer reads it soon: cached store
     }
+    if constexpr (SHORT) short_tile_store<DT>(&out_y[tile * (S::kLoads * kWave)], len, lane, raw);
   }
 
   {
@@ -359,7 +449,7 @@ __device__ __forceinline__ void quantize_pack_tile_body(
     uint32_t my_b = (uint32_t)B;
     uint32_t tile_base;
     if (kMixed) {
-      my_b = (lane < S::kGroups) ? (uint32_t)bits[g0 + lane] : 1u;
+      my_b = (lane < n_groups) ? (uint32_t)bits[g0 + lane] : 1u;
       tile_base = off[g0];
       if (EXT) tile_base += tile_in_group * (kGroupWords32 * (uint32_t)__builtin_amdgcn_readfirstlane((int)my_b));
     } else {
@@ -424,7 +514,8 @@ __device__ __forceinline__ void quantize_pack_tile_body(
       }
       const GroupScale s = group_scale(st.x, st.y, my_b);
       const float invs = s.inv * kScale;
-      need_exact2 = __builtin_amdgcn_ballot_w64(!(invs <= 3.402823466e+38f) && lane < S::kGroups) != 0ull;
+      // (the variant with two multiplications is right for every group: short tiles have it alone)
+      need_exact2 = SHORT || __builtin_amdgcn_ballot_w64(!(invs <= 3.402823466e+38f) && lane < S::kGroups) != 0ull;
       uint32_t woff;
       if (kMixed) {
         const uint32_t w = (lane < S::kGroups) ? kGroupWords32 * my_b : 0u;
@@ -435,8 +526,11 @@ __device__ __forceinline__ void quantize_pack_tile_body(
         tile_words = S::kGroups * kGroupWords32 * B;
         woff = (uint32_t)lane * (kGroupWords32 * B);
       }
+      // (a short tile's run is laid out in LDS as if all its groups were there and whole; what leaves ends early)
+      if constexpr (SHORT)
+        tile_words = (uint32_t)__builtin_amdgcn_readlane((int)(woff + ((last_len * my_b + 31u) >> 5)), n_groups - 1);
       if (lane < S::kGroups) {
-        if (!EXT || tile_in_group == 0u) {
+        if ((!EXT || tile_in_group == 0u) && (!SHORT || lane < n_groups)) {
           if (kMixed) {
             // Streaming stores: with many packed words per tile (wide codes) plain stores
             // of these two small runs slowed the whole kernel down measurably; with the
@@ -508,10 +602,12 @@ __device__ __forceinline__ void quantize_pack_tile_body(
           addr = (stage_base + head * 4u + (uint32_t)grp * (kGroupWords32 * B * 4u) + ((lig * kLaneBits) >> 3)) ^ kSwz;
         }
         uint32_t n0, n1;
+        const int valid = SHORT ? len - (u * kWave + lane) * kEpl : kMaxEpl;   // elements from here to the end
         if constexpr (METRICS) {
           const float g_scale = lds.gscale[grp];
           float* sums = metric_sums[u & 1];
-          quantize_chunk<DT, kExact2, true>(xf[u], g_mn, g_invs, b, rnd[u], n0, n1, g_scale, &sums[0], &sums[1], &sums[2]);
+          quantize_chunk<DT, kExact2, true>(xf[u], g_mn, g_invs, b, rnd[u], n0, n1, g_scale, &sums[0], &sums[1], &sums[2],
+                                            valid);
           if (u & 1) {                           // over the group's lanes, two loads at a time
             seg_sum6<S::kLaneLog2>(metric_sums[0], metric_sums[1]);
             if (lane_in_run == (uint32_t)S::kLpg - 1u) {
@@ -531,9 +627,9 @@ __device__ __forceinline__ void quantize_pack_tile_body(
             }
           }
         } else if constexpr (kPairs16) {
-          quantize_chunk_f16<kExact2>(raw[u], g_mn, g_invs, b, rnd[u], n0, n1);
+          quantize_chunk_f16<kExact2>(raw[u], g_mn, g_invs, b, rnd[u], n0, n1, valid);
         } else {
-          quantize_chunk<DT, kExact2>(xf[u], g_mn, g_invs, b, rnd[u], n0, n1);
+          quantize_chunk<DT, kExact2>(xf[u], g_mn, g_invs, b, rnd[u], n0, n1, 0.0f, nullptr, nullptr, nullptr, valid);
         }
         stage_chunk_at<kEpl>(addr, b, n0, n1, lane);
       }
@@ -554,10 +650,12 @@ __device__ __forceinline__ void quantize_pack_tile_body(
         __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(&lds.stage[w0]), reinterpret_cast<u32x4*>(dst + w0));
       // the up to three words before the first and after the last whole piece: lanes 0..3 and 4..7
       const uint32_t w = (lane < 4) ? (uint32_t)lane : full_end + (uint32_t)lane - 4u;
-      if (lane < 8 && ((lane < 4) ? (w >= head && w < full_begin) : (w < span)))
+      // (the run of a short tile may end before its first whole piece begins)
+      if (lane < 8 && ((lane < 4) ? (w >= head && w < full_begin && (!SHORT || w < span))
+                                  : (w < span && (!SHORT || w >= full_begin))))
         __builtin_nontemporal_store(lds.stage[w], dst + w);
     }
-    if (METRICS && lane < S::kGroups) {
+    if (METRICS && lane < n_groups) {
       const float sc = lds.gscale[lane];
       float* m = out_metrics + 3 * (g0 + lane);
       m[0] = lds.stat[lane].x;
@@ -567,30 +665,44 @@ __device__ __forceinline__ void quantize_pack_tile_body(
   }
 }
 
+// Waves per SIMD of the tile kernel.  At least: as many as the whole tiles' registers allow; the short tile's code shall
+// not cost a wave (metrics: 128 registers instead of 131 and so 4 waves instead of 3, 361 M bfloat16 elements 233 -> 206 us).
+// At most: more waves than these scatter the streams of a binary32 tensor (both directions, 47 M elements, 2 bits, 4 / 5 / 6 / 8
+// waves: 70.3 / 69.1 / 67.1 / 68.0 us; 92 M, 8 bits: 158.5 / 157.0 / 159.7 / 160.9).
+template <int DT, int LPG_LOG2, bool METRICS>
+constexpr int tile_min_waves() {
+  if (DT == kF32) return LPG_LOG2 == 10 ? 4 : 1;
+  if (METRICS) return LPG_LOG2 == 2 ? 5 : 4;
+  return DT == kF16 ? (LPG_LOG2 == 2 ? 8 : 6) : (LPG_LOG2 == 2 ? 7 : 4);
+}
+template <int DT, int B, bool METRICS>
+constexpr int tile_max_waves() {
+  return DT != kF32 || METRICS ? 8 : B == 8 ? 5 : 6;
+}
+
 template <int DT, int LPG_LOG2, int B, bool EXT = false, bool METRICS = false, bool RELU = false, int DIV = 1>
-__global__ __launch_bounds__(kThreads) void k_quantize_pack_tile(
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(EXT ? 1 : tile_min_waves<DT, LPG_LOG2, METRICS>(), EXT ? 8 : tile_max_waves<DT, B, METRICS>())))
+void k_quantize_pack_tile(
     typename std::conditional<RELU, const u32x4*, const u32x4* __restrict__>::type x, int64_t n_tiles,
     const uint8_t* __restrict__ bits, const uint32_t* __restrict__ off, uint32_t seed_lo, uint32_t seed_hi,
     uint32_t* __restrict__ words, float* __restrict__ out_min, float* __restrict__ out_scale,
     const float2* __restrict__ ext_stat, int64_t tiles_per_group, float* __restrict__ out_metrics,
-    u32x4* out_y, int64_t n_elems, int64_t left_begin, int64_t left_end) {
+    u32x4* out_y, int short_len) {
   const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // When groups are left over after the last whole tile (left_begin .. left_end - 1, the tensor's
-  // short last group among them) the grid has one more workgroup, the first, which quantizes
-  // them the general way: no launch of their own, and they run while the tiles stream.
-  const unsigned first_tile_block = (!EXT && left_end > left_begin) ? 1u : 0u;
+  // The tile in which the tensor ends takes longer than a whole one and goes first, in a workgroup of its own: as the
+  // grid's last wave it was the launch's end, and as the first of all it moved the others' tiles by one.
+  const unsigned first_block = short_len > 0 ? 1u : 0u;
   if constexpr (!EXT) {
-    if (blockIdx.x < first_tile_block) {
-      constexpr bool kCoop = !METRICS && TileShape<DT, LPG_LOG2>::kGroupSize >= 1024;
-      quantize_pack_group_body<DT, METRICS, RELU, kCoop>(x, n_elems, TileShape<DT, LPG_LOG2>::kGroupSize, left_begin,
-                                                         left_end, bits, off, B, seed_lo, seed_hi, words, out_min,
-                                                         out_scale, out_metrics, out_y,
-                                                         kCoop ? (int64_t)0 : (int64_t)wave_in_block,
-                                                         kCoop ? (int64_t)1 : (int64_t)kWavesPerBlock);
+    if (blockIdx.x < first_block) {
+      if (wave_in_block > 0) return;
+      quantize_pack_tile_body<DT, LPG_LOG2, B, false, METRICS, RELU, DIV, false, true>(
+          x, n_tiles, wave_in_block, bits, off, seed_lo, seed_hi, words, out_min, out_scale, nullptr, (int64_t)1, out_metrics,
+          out_y, 0, short_len);
       return;
     }
   }
-  const int64_t tile = (int64_t)(blockIdx.x - first_tile_block) * kWavesPerBlock + wave_in_block;
+  const int64_t tile = (int64_t)(blockIdx.x - first_block) * kWavesPerBlock + wave_in_block;
   if (tile >= n_tiles) return;
   quantize_pack_tile_body<DT, LPG_LOG2, B, EXT, METRICS, RELU, DIV>(x, tile, wave_in_block, bits, off, seed_lo, seed_hi,
                                                                     words, out_min, out_scale, ext_stat,
@@ -609,9 +721,11 @@ struct BatchEntry {
   uint32_t* words;
   float* mn;
   float* sc;
-  int64_t tile_end;                                 // tiles of this and all earlier entries
+  int32_t tile_end;                                 // tiles of this and all earlier entries
+  int32_t short_len;                                // elements of the last of them where it is a short one, else 0
   uint32_t seed_lo, seed_hi;
 };
+static_assert(sizeof(BatchEntry) == 64, "a descriptor is one cache line");
 struct Batch {
   uint32_t ends[kBatchSlots];                       // e[t].tile_end, 0xFFFFFFFF beyond n
   BatchEntry e[kMaxBatch];
@@ -623,7 +737,8 @@ struct Batch {
 };
 static_assert(kMaxBatch <= kBatchSlots, "one cumulative count per entry");
 
-template <int DT, int LPG_LOG2, int B>
+// SHORT: some tensors of the list end inside a tile.  Lists of whole tiles have the kernel without that code.
+template <int DT, int LPG_LOG2, int B, bool SHORT>
 __global__ __launch_bounds__(kThreads) void k_quantize_pack_tile_batch(const Batch batch) {
   const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t gtile = (int64_t)blockIdx.x * kWavesPerBlock + wave_in_block;
@@ -631,6 +746,14 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack_tile_batch(const Bat
   if (t >= batch.n) return;                          // past the last tile (the grid is whole workgroups)
   const BatchEntry& e = batch.e[t];
   const int64_t tile = gtile - (t ? batch.e[t - 1].tile_end : 0);
+  if constexpr (SHORT) {
+    if (e.short_len > 0 && gtile == e.tile_end - 1) {
+      quantize_pack_tile_body<DT, LPG_LOG2, B, false, false, false, tile_div<DT, LPG_LOG2>(), false, true>(
+          static_cast<const u32x4*>(e.x), tile, wave_in_block, e.bits, e.off, e.seed_lo, e.seed_hi, e.words, e.mn, e.sc,
+          nullptr, (int64_t)1, nullptr, nullptr, 0, e.short_len);
+      return;
+    }
+  }
   quantize_pack_tile_body<DT, LPG_LOG2, B, false, false, false, tile_div<DT, LPG_LOG2>()>(
       static_cast<const u32x4*>(e.x), tile, wave_in_block, e.bits, e.off, e.seed_lo, e.seed_hi, e.words, e.mn, e.sc,
       nullptr, (int64_t)1, nullptr, nullptr);
@@ -641,15 +764,14 @@ hipError_t launch_tile(const daf_plan_t* p, const void* x, int64_t n_tiles, uint
                        uint32_t* out_words, float* out_min, float* out_scale, float* out_metrics, void* out_y,
                        hipStream_t stream) {
   using S = QTile<DT, LPG_LOG2>;
-  const int64_t left = n_tiles * S::kGroups;                         // first group after the whole tiles
+  const int short_len = (int)(p->n - n_tiles * S::kElems);            // elements after the whole tiles
 #define DAF_LAUNCH(BITS)                                                                                   \
   do {                                                                                                     \
     auto kernel = k_quantize_pack_tile<DT, LPG_LOG2, BITS, false, METRICS, RELU, tile_div<DT, LPG_LOG2>()>; \
-    const unsigned blocks = (unsigned)((n_tiles + kWavesPerBlock - 1) / kWavesPerBlock) + (left < p->num_groups ? 1u : 0u); \
+    const unsigned blocks = (unsigned)((n_tiles + kWavesPerBlock - 1) / kWavesPerBlock) + (short_len > 0);   \
     hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), 0, stream, static_cast<const u32x4*>(x),      \
                        n_tiles, p->d_bits, p->d_off, seed_lo, seed_hi, out_words, out_min, out_scale,      \
-                       nullptr, (int64_t)1, out_metrics, static_cast<u32x4*>(out_y), p->n, left,           \
-                       p->num_groups);                                                                     \
+                       nullptr, (int64_t)1, out_metrics, static_cast<u32x4*>(out_y), short_len);           \
   } while (0)
   switch (p->uniform_bits) {
     case 0: DAF_LAUNCH(0); break;

@@ -258,7 +258,7 @@ hipError_t launch_big(const daf_plan_t* p, const void* x, uint32_t seed_lo, uint
 #define DAF_LAUNCH(BITS)                                                                                      \
   hipLaunchKernelGGL((k_quantize_pack_tile<DT, kMaxLog2, BITS, true>), dim3(blocks), dim3(kThreads), 0, stream, \
                      static_cast<const u32x4*>(x), n_full_tiles, p->d_bits, p->d_off, seed_lo, seed_hi,       \
-                     out_words, out_min, out_scale, stat, tpg, nullptr, nullptr, (int64_t)0, (int64_t)0, (int64_t)0)
+                     out_words, out_min, out_scale, stat, tpg, nullptr, nullptr, 0)
     switch (p->uniform_bits) {
       case 0: DAF_LAUNCH(0); break;
       case 1: DAF_LAUNCH(1); break;
