@@ -117,8 +117,8 @@ int32_t daf_plan_group_size(const daf_plan_t* plan);
 int32_t daf_plan_uniform_bits(const daf_plan_t* plan);   /* the shared width, or 0 for per-group widths */
 
 /* Which kernels daf_quantize_pack (and its fused variants) use for the whole groups of this plan
- * when the tensor has the given element format; the groups after the last whole tile and the
- * tensor's short last group always go one by one.  A host computation, for tuning and tests.
+ * when the tensor has the given element format (TILE and UNITS: the tensor's short last group included).
+ * A host computation, for tuning and tests.
  *   DAF_ROUTE_TILE      group size a power of two up to 4096: one wave per 4096-element tile
  *   DAF_ROUTE_UNITS     other group sizes up to 4096: one wave per run of whole groups
  *   DAF_ROUTE_LONG      4128 ... 65536 elements: one workgroup per group
@@ -431,6 +431,10 @@ int daf_linear_quantize_pack(const daf_plan_t* plan, const void* x, const void* 
  * the kernel uses, so that tests without a GPU can check that it visits every tile once.
  * Returns DAF_EINVAL for an id outside [0, tiles_m * tiles_n) or a null pointer. */
 int daf_linear_tile_of_workgroup(int32_t id, int32_t tiles_m, int32_t tiles_n, int32_t* tile_m, int32_t* tile_n);
+/* The same for the smaller tiles that outputs of few 256 x 256 tiles are cut into, and into how many each of those is cut
+ * for a product of these sizes (1: not at all; 2, 4, 8 or 16).  Host computations, for tuning and tests. */
+int daf_linear_few_tile_of_workgroup(int32_t id, int32_t tiles_m, int32_t tiles_n, int32_t* tile_m, int32_t* tile_n);
+int daf_linear_tiles_per_256(int64_t M, int64_t N, int64_t K);
 
 /* ---- consumer fusion for an element-wise consumer -------------------------------------------
  *

@@ -16,7 +16,7 @@
 // together).  Minimum and maximum of a group are then a reduction inside a lane plus one
 // exchange with the lane 32 away.  The element map, the random bytes and the word layout are
 // those of daf_quantize_pack, so words, min and scale equal daf_quantize_pack(y) bit for bit.
-#include "quantize_common.h"
+#include "linear_few_tiles.h"
 
 namespace {
 
@@ -25,51 +25,8 @@ constexpr int kBM = 256, kBN = 256, kBK = 64;
 constexpr int kRowBytes = kBK * 2;           // bytes of a staged row: one cache line
 constexpr int kOperandBytes = 256 * kRowBytes;
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-
-template <int DT>
-__device__ __forceinline__ f32x16 mfma16(const u32x4& a, const u32x4& b, f32x16 c) {
-  if constexpr (DT == kBF16) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
-                                                   0, 0);
-  } else {
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0,
-                                                  0);
-  }
-}
-
-// Two binary32 values rounded (nearest even) to the 16-bit format, low half first.
-template <int DT>
-__device__ __forceinline__ uint32_t round_pair(float lo, float hi) {
-  if constexpr (DT == kBF16) {
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    const f32x2 v = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-  } else {
-    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-    const f16x2 v = {(_Float16)lo, (_Float16)hi};
-    return __builtin_bit_cast(uint32_t, v);
-  }
-}
-
-// The value held by the lane 32 away.
-__device__ __forceinline__ uint32_t other_half(uint32_t v) {
-  const u32x2 r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return (threadIdx.x & 32) ? r.x : r.y;
-}
-__device__ __forceinline__ float both_halves_min(float v) { return vmin(v, u2f(other_half(f2u(v)))); }
-__device__ __forceinline__ float both_halves_max(float v) { return vmax(v, u2f(other_half(f2u(v)))); }
-
 // blockIdx -> tile.  Whole rounds of 256 workgroups: the s-th workgroup of die d in round r takes
-// position 256 r + 32 d + s; the rest keep their index.  Position -> tile: panels of kPanel tile
-// rows, column by column inside a panel (the last panel may be lower).  Both maps are bijections.
-struct TileIndex {
-  int m, n;
-};
+// position 256 r + 32 d + s; the rest keep their index.  A bijection, as tile_of_position is.
 __host__ __device__ inline TileIndex tile_of_workgroup(int id, int tiles_m, int tiles_n) {
   constexpr int kDies = 8, kPerDie = 32, kPanel = 4;
   const int total = tiles_m * tiles_n;
@@ -78,18 +35,7 @@ __host__ __device__ inline TileIndex tile_of_workgroup(int id, int tiles_m, int 
     const int die = id % kDies, seq = id / kDies;
     pos = (seq / kPerDie) * (kDies * kPerDie) + die * kPerDie + seq % kPerDie;
   }
-  const int full = tiles_m / kPanel * kPanel;            // tile rows in whole panels
-  TileIndex t;
-  if (pos < full * tiles_n) {
-    const int panel = pos / (kPanel * tiles_n), in = pos % (kPanel * tiles_n);
-    t.m = panel * kPanel + in % kPanel;
-    t.n = in / kPanel;
-  } else {
-    const int rows = tiles_m - full, in = pos - full * tiles_n;
-    t.m = full + in % rows;
-    t.n = in / rows;
-  }
-  return t;
+  return tile_of_position(pos, tiles_m, tiles_n, kPanel);
 }
 
 // Main loop.  The product is bound by feeding the compute units: 64 KB of operands per workgroup and step
@@ -250,7 +196,7 @@ __global__ __launch_bounds__(kLinThreads, 2) void k_linear_quantize_pack(
   if (s < steps) step(std::integral_constant<int, 0>{}, s);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
-  // ---- epilogue.  Register r of a 32 x 32 block: n = 8*(r/4) + 4*(lane/32) + r%4, m = lane%32. ----
+  // ---- epilogue, by blocks of 32 x 32 (linear_common.h) ----
   constexpr int kGs = 1 << GS_LOG2, kBlocksPerGroup = kGs / 32, kGroups = 4 / kBlocksPerGroup;
 #pragma unroll
   for (int mb = 0; mb < 2; ++mb) {
@@ -260,42 +206,12 @@ __global__ __launch_bounds__(kLinThreads, 2) void k_linear_quantize_pack(
     float bmn[4], bmx[4];
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb) {
-      uint32_t d[4][2];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        d[j][0] = round_pair<DT>(acc[mb][nb][4 * j], acc[mb][nb][4 * j + 1]);
-        d[j][1] = round_pair<DT>(acc[mb][nb][4 * j + 2], acc[mb][nb][4 * j + 3]);
-      }
-      // Lower half-wave: runs j = 0..3 are n 0-3, 8-11, 16-19, 24-27; upper: 4-7, 12-15, 20-23, 28-31.
-      // Swapping the upper half of run 0 with the lower half of run 2 (and 1 with 3) leaves n 0-15
-      // in the lower half-wave and n 16-31 in the upper one.
       uint32_t yv[8];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const u32x2 r02 = __builtin_amdgcn_permlane32_swap(d[0][h], d[2][h], false, false);
-        const u32x2 r13 = __builtin_amdgcn_permlane32_swap(d[1][h], d[3][h], false, false);
-        yv[h] = r02.x;
-        yv[2 + h] = r02.y;
-        yv[4 + h] = r13.x;
-        yv[6 + h] = r13.y;
-      }
+      block_row<DT>(acc[mb][nb], yv);
       char* dst = y + (m * N + n_lane + nb * 32) * 2;
       *reinterpret_cast<u32x4*>(dst) = u32x4{yv[0], yv[1], yv[2], yv[3]};
       *reinterpret_cast<u32x4*>(dst + 16) = u32x4{yv[4], yv[5], yv[6], yv[7]};
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const uint32_t pair = yv[e >> 1];
-        xf[nb][e] = DT == kBF16 ? u2f((e & 1) ? (pair & 0xFFFF0000u) : (pair << 16))
-                                : widen16<DT>((e & 1) ? (pair >> 16) : (pair & 0xFFFFu));
-      }
-      float mn = vmin(xf[nb][0], xf[nb][1]), mx = vmax(xf[nb][0], xf[nb][1]);
-#pragma unroll
-      for (int e = 2; e < 16; e += 2) {
-        mn = vmin3(mn, xf[nb][e], xf[nb][e + 1]);
-        mx = vmax3(mx, xf[nb][e], xf[nb][e + 1]);
-      }
-      bmn[nb] = mn;
-      bmx[nb] = mx;
+      widen_row<DT>(yv, xf[nb], bmn[nb], bmx[nb]);
     }
     if (!QUANT) continue;                                        // the product alone
 #pragma unroll
@@ -316,68 +232,82 @@ __global__ __launch_bounds__(kLinThreads, 2) void k_linear_quantize_pack(
         out_min[g] = gs.mn;
         out_scale[g] = gs.scale;
       }
-      const float invs = gs.inv * kScale;
-      const bool exact2 = !(invs <= 3.402823466e+38f);          // the factor 256 is then applied to the rounded product
-      const bool any_exact2 = __builtin_amdgcn_ballot_w64(exact2) != 0ull;      // rare: a branch of the whole wave
+      const LinearGroup group = linear_group(gs, b, words + woff);
 #pragma unroll
       for (int q = 0; q < kBlocksPerGroup; ++q) {
         const int nb = gi * kBlocksPerGroup + q;
-        const uint32_t e0 = (uint32_t)(q * 32 + lg * 16);       // first of the lane's 16 elements, counted inside the group
-        const uint4 rnd4 = philox_block((uint64_t)((m * N + n_lane + nb * 32) >> 4), seed_lo, seed_hi);
-        const uint32_t rnd[4] = {rnd4.x, rnd4.y, rnd4.z, rnd4.w};
-        uint32_t p[4];
-        auto codes = [&](auto two_products, float mult) {
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            uint32_t nacc = 0u;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              nacc = (nacc << b) + (uint32_t)neg_code<decltype(two_products)::value>(xf[nb][4 * c + e], gs.mn, mult,
-                                                                                       (rnd[c] >> (8 * e)) & 0xFFu);
-            p[c] = 0u - nacc;                                    // four codes, first element most significant
-          }
-        };
-        if (any_exact2) {
-          // lanes that do not need it multiply by 256 afterwards too: a power of two, the same product
-          codes(std::true_type{}, gs.inv);
-        } else {
-          codes(std::false_type{}, invs);
-        }
-        uint32_t* dst = words + woff;
-        if (b == 8u) {
-          typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-          *reinterpret_cast<u32x4_any*>(dst + (e0 >> 2)) = u32x4_any{p[0], p[1], p[2], p[3]};
-        } else if (b == 4u) {
-          dst[(e0 >> 3)] = (p[0] << 16) | (p[1] & 0xFFFFu);
-          dst[(e0 >> 3) + 1] = (p[2] << 16) | (p[3] & 0xFFFFu);
-        } else if (b == 2u) {
-          dst[e0 >> 4] = (p[0] << 24) | ((p[1] & 0xFFu) << 16) | ((p[2] & 0xFFu) << 8) | (p[3] & 0xFFu);
-        } else {
-          const uint32_t half = ((p[0] & 0xFu) << 12) | ((p[1] & 0xFu) << 8) | ((p[2] & 0xFu) << 4) | (p[3] & 0xFu);
-          const uint32_t upper = other_half(half);               // the lane 32 away runs the same branch: same group, same width
-          if (lg == 0) dst[e0 >> 5] = (half << 16) | upper;
-        }
+        quantize_row(xf[nb], group, (uint32_t)(q * 32 + lg * 16), m * N + n_lane + nb * 32, seed_lo, seed_hi, lg);
       }
     }
   }
 }
 
+// Into how many tiles each 256 x 256 of the output is cut: 1 (k_linear_quantize_pack) or 2, 4, 8, 16 (k_linear_few_tiles).
+// The estimate: a round of 256 workgroups takes `fixed` (first operands, epilogue, last waves) and `step` per 64 values of k, each
+// between its value for a lone workgroup and for a full chip (shared cache and memory, clock).  Microseconds, fitted to
+// 23 shapes of 1 to 768 tiles of 256 x 256 and K = 256, 1024, 4096, all five forms measured on each; the form picked was
+// 0.7 % behind the best on average, 10 % at most.  Some of them, whole call, bfloat16, {2,4,8} or 4 bits:
+//   tiles of 256 x 256, K    1      2      4      8     16
+//       1, 1024           24.7   16.3    9.9    8.4    8.5
+//      16, 4096           67.9   39.9   25.1   19.4   17.5
+//      64, 1024           28.1   19.3   15.3   18.8   25.9
+//     100, 1024           27.9   21.9   24.4   32.0   37.2
+//     128, 4096           74.2   61.5   70.8   91.2  132.8
+//     192, 1024           34.3   43.7   43.8   52.3   66.4
+//     300, 4096          179.4  168.2  179.0  225.3  327.2
+int linear_cut(int64_t M, int64_t N, int64_t K) {
+#ifdef DAF_FORCE_TILES
+  return DAF_FORCE_TILES;
+#endif
+  static constexpr struct {
+    int cut;
+    float fixed_lone, fixed_full, step_lone, step_full;
+  } kForms[] = {{1, 7.9f, 12.6f, 0.82f, 1.38f}, {2, 6.3f, 9.2f, 0.41f, 0.78f}, {4, 1.9f, 4.9f, 0.26f, 0.48f},
+                {8, 0.0f, 3.3f, 0.21f, 0.29f},  {16, 2.5f, 2.4f, 0.11f, 0.19f}};
+  const int64_t whole = (M / kBM) * (N / kBN);
+  const float steps = (float)(K / kBK);
+  int best = 1;
+  float best_time = 0.0f;
+  for (const auto& f : kForms) {
+    const int64_t rounds = whole * f.cut / 256, rest = whole * f.cut % 256;
+    const float busy = (float)rest / 256.0f;
+    float time = (float)rounds * (f.fixed_full + steps * f.step_full);
+    if (rest > 0) time += f.fixed_lone + busy * (f.fixed_full - f.fixed_lone) + steps * (f.step_lone + busy * (f.step_full - f.step_lone));
+    if (f.cut == 1) time *= 0.97f;                 // at equal estimates the form that moves the fewest bytes
+    if (f.cut == 1 || time < best_time) {
+      best = f.cut;
+      best_time = time;
+    }
+  }
+  return best;
+}
+
 template <int DT, int GS_LOG2>
 hipError_t launch_gs(const daf_plan_t* p, const void* x, const void* w, int M, int N, int K, uint64_t seed, void* y,
                      uint32_t* words, float* mn, float* sc, hipStream_t stream) {
-  const unsigned grid = (unsigned)((M / kBM) * (N / kBN));
   const uint32_t lo = (uint32_t)seed, hi = (uint32_t)(seed >> 32);
-  if (words == nullptr)
-    hipLaunchKernelGGL((k_linear_quantize_pack<DT, GS_LOG2, false, false>), dim3(grid), dim3(kLinThreads), 0, stream,
-                       (const char*)x, (const char*)w, M, N, K, lo, hi, 8u, nullptr, nullptr, (char*)y, words, mn, sc);
-  else if (p->uniform_bits)
-    hipLaunchKernelGGL((k_linear_quantize_pack<DT, GS_LOG2, false, true>), dim3(grid), dim3(kLinThreads), 0, stream,
-                       (const char*)x, (const char*)w, M, N, K, lo, hi, (uint32_t)p->uniform_bits, nullptr, nullptr,
+  const bool quant = words != nullptr, mixed = quant && !p->uniform_bits;
+  const uint32_t uniform = mixed ? 0u : quant ? (uint32_t)p->uniform_bits : 8u;
+  auto launch = [&](auto kernel, int bm, int bn, int threads) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((M / bm) * (N / bn))), dim3(threads), 0, stream, (const char*)x,
+                       (const char*)w, M, N, K, lo, hi, uniform, mixed ? p->d_bits : nullptr, mixed ? p->d_off : nullptr,
                        (char*)y, words, mn, sc);
-  else
-    hipLaunchKernelGGL((k_linear_quantize_pack<DT, GS_LOG2, true, true>), dim3(grid), dim3(kLinThreads), 0, stream,
-                       (const char*)x, (const char*)w, M, N, K, lo, hi, 0u, p->d_bits, p->d_off, (char*)y, words, mn, sc);
-  return hipGetLastError();
+    return hipGetLastError();
+  };
+  const int cut = linear_cut(M, N, K);
+  if (cut == 1)
+    return launch(!quant  ? k_linear_quantize_pack<DT, GS_LOG2, false, false>
+                  : mixed ? k_linear_quantize_pack<DT, GS_LOG2, true, true>
+                          : k_linear_quantize_pack<DT, GS_LOG2, false, true>,
+                  kBM, kBN, kLinThreads);
+  auto few = [&](auto shape) {
+    using S = decltype(shape);
+    return launch(!quant  ? k_linear_few_tiles<DT, GS_LOG2, false, false, S>
+                  : mixed ? k_linear_few_tiles<DT, GS_LOG2, true, true, S>
+                          : k_linear_few_tiles<DT, GS_LOG2, false, true, S>,
+                  S::kBM, S::kBN, S::kThreads);
+  };
+  return cut == 2 ? few(FewBy2{}) : cut == 4 ? few(FewBy4{}) : cut == 8 ? few(FewBy8{}) : few(FewBy16<GS_LOG2>{});
 }
 
 template <int DT>
@@ -391,6 +321,14 @@ hipError_t launch_dt(const daf_plan_t* p, const void* x, const void* w, int M, i
 }
 
 }  // namespace
+
+int daf_linear_cut_of(int64_t M, int64_t N, int64_t K) { return linear_cut(M, N, K); }
+
+void daf_linear_few_tile_map(int id, int tiles_m, int tiles_n, int* tm, int* tn) {
+  const TileIndex t = few_tile_of_workgroup(id, tiles_m, tiles_n);
+  *tm = t.m;
+  *tn = t.n;
+}
 
 void daf_linear_tile_map(int id, int tiles_m, int tiles_n, int* tm, int* tn) {
   const TileIndex t = tile_of_workgroup(id, tiles_m, tiles_n);

@@ -124,3 +124,27 @@ def test_current_stream_without_the_private_functions(monkeypatch, missing):
     monkeypatch.setattr(binding, missing, None)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
     assert binding._stream_handle(None) == 0x1234
+
+
+def test_linear_few_tile_map_visits_every_tile_once():
+    """The same for the smaller tiles; the tiles of one die are a compact patch, and the cut is one that exists."""
+    import ctypes
+    from paper_2507_07149_amd.binding import load_library
+    L = load_library()
+    tm, tn = ctypes.c_int32(), ctypes.c_int32()
+    for tiles_m, tiles_n in ((1, 1), (1, 2), (2, 3), (4, 8), (8, 16), (16, 16), (7, 5), (3, 100), (64, 2), (10, 21)):
+        seen, dies = set(), {}
+        for i in range(tiles_m * tiles_n):
+            assert L.daf_linear_few_tile_of_workgroup(i, tiles_m, tiles_n, ctypes.byref(tm), ctypes.byref(tn)) == 0
+            assert 0 <= tm.value < tiles_m and 0 <= tn.value < tiles_n
+            seen.add((tm.value, tn.value))
+            dies.setdefault(i % 8, []).append((tm.value, tn.value))
+        assert len(seen) == tiles_m * tiles_n, (tiles_m, tiles_n)
+        assert L.daf_linear_few_tile_of_workgroup(tiles_m * tiles_n, tiles_m, tiles_n, ctypes.byref(tm), ctypes.byref(tn)) != 0
+        if (tiles_m, tiles_n) == (16, 16):
+            for tiles in dies.values():
+                assert len({m for m, _ in tiles}) <= 4 and len({n for _, n in tiles}) <= 9
+    for M, N, K in ((256, 256, 64), (256, 256, 1 << 20), (4096, 2048, 1024), (32768, 11008, 4096), (1 << 20, 1 << 12, 64)):
+        assert L.daf_linear_tiles_per_256(M, N, K) in (1, 2, 4, 8, 16)
+    assert L.daf_linear_tiles_per_256(32768, 11008, 4096) == 1
+    assert L.daf_linear_tiles_per_256(100, 256, 64) < 0

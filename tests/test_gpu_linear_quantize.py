@@ -166,3 +166,35 @@ def test_linear_quantize_pack_argument_errors(env):
         mn = torch.zeros(p.num_groups, device="cuda:0")
         daf.daf_linear_quantize_pack(p, x.float(), w.float(), 1, y.float(), words, mn, mn.clone())
     torch.cuda.synchronize()
+
+
+# M, N, steps of 64 and the tiles that each 256 x 256 of such an output is cut into
+_FORMS = [(1024, 1024, steps, 16) for steps in (16, 17, 18, 19, 22, 23)]
+_FORMS += [(512, 512, steps, 8) for steps in range(1, 10)]
+_FORMS += [(2048, 2048, steps, 4) for steps in (1, 2, 3, 4, 5, 6, 7)]
+_FORMS += [(4096, 2048, steps, 2) for steps in (1, 2, 3, 4, 5, 6)]
+_FORMS += [(4096, 4096, steps, 1) for steps in (1, 2, 3, 4, 5, 6, 7)]
+
+
+@pytest.mark.parametrize("M,N,steps,cut", _FORMS)
+@pytest.mark.parametrize("gs", [32, 64, 128])
+def test_linear_quantize_pack_every_tile_form(env, M, N, steps, cut, gs):
+    """Every size of output tile, with counts of steps around its pipeline's depth (3 to 8; the smallest tiles
+    are taken from 11 steps on) and every group size (whose
+    statistics lie in one wave, or in two or four); operands whose products are exact in any order."""
+    daf, orc = env
+    K = 64 * steps
+    assert daf.load_library().daf_linear_tiles_per_256(M, N, K) == cut
+    dtype = F16 if steps % 2 else BF16
+    rng = np.random.default_rng(M + N + steps + gs)
+    x, w = _integer_operands(rng, M, N, K, dtype)
+    bits = ("mixed", 1, 8)[(steps + gs // 32) % 3]
+    b = _bits_for(rng, M * N // gs, bits)
+    print("case", M, N, K, cut, gs, bits, flush=True)
+    y, words, mn, sc = _run(daf, x, w, gs, b, 31)
+    oy = to_numpy_bits((x.float() @ w.float().t()).to(torch_dtype(dtype)))     # exact, as the oracle's
+    assert np.array_equal(to_numpy_bits(y).view(oy.dtype).reshape(-1), oy.reshape(-1)), "y differs"
+    ow, omn, osc, _ = orc.quantize_pack(oy.reshape(-1), dtype, gs, b, 31)
+    assert np.array_equal(words, ow), "packed words differ"
+    assert np.array_equal(mn.view(np.uint32), omn.view(np.uint32)), "min differs"
+    assert np.array_equal(sc.view(np.uint32), osc.view(np.uint32)), "scale differs"
