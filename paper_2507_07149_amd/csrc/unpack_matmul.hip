@@ -245,7 +245,9 @@ __global__ __launch_bounds__((TileB<BK, (DT == kF32 ? 4 : 2)>::kThreads), (BK > 
   const bool on_x = TB::kAllThreadsOnX || xr < (uint32_t)kBM;          // (uniform per wave)
   const uint32_t row_bytes = (uint32_t)N * (uint32_t)ES;                // bytes per grad_y row
   const uint32_t gpr = (uint32_t)(K / gs);                              // groups per row of x
-  const uint32_t k_col = (uint32_t)k0 + 8u * co;
+  // The last tile of k may reach 64 columns past the output (K is a multiple of 64): their threads take the last
+  // columns once more, and nothing of theirs is stored.
+  const uint32_t k_col = BK > 64 ? min((uint32_t)k0 + 8u * co, (uint32_t)K - 8u) : (uint32_t)k0 + 8u * co;
   const uint32_t gk = k_col / (uint32_t)gs;
   const uint32_t in_group = k_col - gk * (uint32_t)gs;                  // multiple of 8
   const uint32_t wpgb = (uint32_t)gs >> 5;                              // words per group and bit of width
@@ -258,7 +260,7 @@ __global__ __launch_bounds__((TileB<BK, (DT == kF32 ? 4 : 2)>::kThreads), (BK > 
   // threads that need them through the ring: four small loads per thread and step of its own
   // would keep the memory pipeline busier than the tiles of grad_y do.
   const uint32_t g_first = (uint32_t)k0 / (uint32_t)gs;
-  const uint32_t n_groups = ((uint32_t)k0 + (uint32_t)BK - 1u) / (uint32_t)gs - g_first + 1u;   // <= kGroupsPerRow
+  const uint32_t n_groups = (min((uint32_t)k0 + (uint32_t)BK, (uint32_t)K) - 1u) / (uint32_t)gs - g_first + 1u;   // <= kGroupsPerRow
   const bool meta_wave = t < (uint32_t)TB::kMetaEntries;
   const uint32_t m_row = t / (uint32_t)TB::kGroupsPerRow, m_j = t % (uint32_t)TB::kGroupsPerRow;
   const bool meta_lane = meta_wave && m_j < n_groups;
@@ -508,13 +510,15 @@ __global__ __launch_bounds__((TileB<BK, (DT == kF32 ? 4 : 2)>::kThreads), (BK > 
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < kJ; ++j)
+    for (int j = 0; j < kJ; ++j) {
+      if (BK > 64 && k0 + TB::kWaveK * wk + 32 * j >= K) break;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int64_t n = 64 * wn + 32 * i + 8 * (r >> 2) + 4 * lg + (r & 3);
         const int64_t k = TB::kWaveK * wk + 32 * j + li;
         dst[n * ld + k] = acc[i][j][r];
       }
+    }
 }
 
 }  // namespace
@@ -542,7 +546,7 @@ __global__ __launch_bounds__(256) void k_sum_slices(float4* __restrict__ partial
   uint32_t tn, tk;
   tile_of_position(tile, tiles_n, (uint32_t)tiles_k, tn, tk);
   const uint32_t row = e / (uint32_t)bk4, col4 = e - row * (uint32_t)bk4;
-  if ((int64_t)tn * bn + row >= N) return;           // rows of the last tile of n past the output
+  if ((int64_t)tn * bn + row >= N || (int64_t)tk * (bk4 * 4) + 4 * col4 >= K) return;   // past the output in a last tile
   const int32_t first = (int32_t)blockIdx.y * n * stride;
   float4* p0 = partial + ((int64_t)first * count + ti) * tile4 + e;
   float4 s = *p0;
@@ -592,7 +596,7 @@ Schedule schedule_tile(int64_t M, int64_t N, int64_t K, int bn, int bk, int64_t 
   Schedule sc;
   sc.bn = bn;
   sc.bk = bk;
-  sc.tiles = ((N + bn - 1) / bn) * (K / bk);
+  sc.tiles = ((N + bn - 1) / bn) * ((K + bk - 1) / bk);
   const int64_t steps = M / kStepM;
   const double t_all_m = (double)steps * t_step, start = 2.0 * t_step;
   const double tile_bytes = (double)bn * bk * 4.0;
@@ -622,14 +626,27 @@ Schedule schedule(int64_t M, int64_t N, int64_t K, int es) {   // es: bytes per 
   // Per work-group and 32 values of m: the 16-bit kernels are bound by instruction issue, the binary32 kernel by its MFMAs
   // (128 per wave of 64 cycles each).
   const int bk = tile_bk(N, K);
-  const Schedule general = schedule_tile(M, N, K, kBN, bk, 256 * (bk == 256 ? 1 : bk == 128 ? 2 : 3),
-                                         es == 4 ? 8.0e-6 : bk == 256 ? 1.1e-6 : 1.25e-6);
+  const auto general_tile = [&](int cols) {
+    return schedule_tile(M, N, K, kBN, cols, 256 * (cols == 256 ? 1 : cols == 128 ? 2 : 3),
+                         es == 4 ? 8.0e-6 : cols == 256 ? 1.1e-6 : 1.25e-6);
+  };
+  Schedule general = general_tile(bk);
+  // K an odd multiple of 64, 16-bit formats: wider tiles too, the last of which lie half outside the output, where the
+  // estimates have them ahead (general 256 x 64 and 512 x 128: 8064 x 3392 x 5056 500 / 287 us, 4480 x 1152 x 2624 75.7 / 53.6,
+  // 3936 x 2112 x 704 42.8 / 34.1).  Not where the tiles of 256 x 64 fill their rounds almost exactly: the one form that
+  // still takes whole rounds and slices of such tiles (4096 x 4096 x 3136: 161 / 104).
+  const int64_t over = bk == 64 ? general.tiles % 768 : 0;
+  if (bk == 64 && general.tiles >= 768 && over > 0 && over <= 768 / 32) return general;
+  if (bk == 64 && es == 2) {
+    const Schedule wider = general_tile(128);
+    if (wider.seconds < general.seconds) general = wider;
+  }
   // The 512 x 128 tile starts slower (a pipeline four steps deep to fill) and runs faster per step: general kernel and
   // 512 x 128 in microseconds, bf16, m x n x k: 32768 x 4096 x 11008 3044 / 2495, 8192 x 3136 x 768 67.8 / 61.2;
   // below ten steps per compute unit the general kernel is ahead (4096 x 576 x 768, 6 steps: 22.3 / 24.6,
   // 4096 x 1024 x 1024, 8 steps: equal).  Outputs of 256 and more such tiles take it for any m (128 x 4096 x 4096: 19.2 / 18.9).
-  const int64_t wide_tiles = ((N + Wide::kBN - 1) / Wide::kBN) * (K / Wide::kBK);
-  const bool fits = es == 2 && N > kBN && K % Wide::kBK == 0 && (wide_tiles >= 256 || wide_tiles * (M / kStepM) >= 10 * 256);
+  const int64_t wide_tiles = ((N + Wide::kBN - 1) / Wide::kBN) * ((K + Wide::kBK - 1) / Wide::kBK);
+  const bool fits = es == 2 && N > kBN && (wide_tiles >= 256 || wide_tiles * (M / kStepM) >= 10 * 256);
   if (!fits) return general;
   // Where the last of few tiles of n is mostly outside the output, or a last round is nearly empty, the estimates decide
   // (32768 x 576 x 4352 235 / 270, 8192 x 768 x 4352 79.6 / 83.2, 512 x 1088 x 11008 27.0 / 34.0).  Near each other the
@@ -674,7 +691,7 @@ hipError_t daf_launch_unpack_matmul(const daf_plan_t* p, const uint32_t* words, 
   const int64_t M = p->n / K;
   const Schedule sc = schedule(M, N, K, dtype == daf::kF32 ? 4 : 2);
   const int bk = sc.bk;
-  const int32_t tiles_n = (int32_t)((N + sc.bn - 1) / sc.bn), tiles_k = (int32_t)(K / bk);
+  const int32_t tiles_n = (int32_t)((N + sc.bn - 1) / sc.bn), tiles_k = (int32_t)((K + bk - 1) / bk);
   const int64_t rest = sc.tiles - sc.whole;
   const unsigned blocks = (unsigned)(sc.whole + rest * sc.slices);
   const uint32_t whole = (uint32_t)sc.whole;

@@ -1,4 +1,4 @@
-// The weight-gradient kernel for 16-bit formats and outputs of more than 256 rows whose K is a multiple of 128: a
+// The weight-gradient kernel for 16-bit formats and outputs of more than 256 rows: a
 // tile of 512 (n) x 128 (k) on 8 waves, 32 values of m per step.  Included by unpack_matmul.hip, which
 // holds the operand helpers, the tile order and the general kernel.
 //
@@ -82,12 +82,12 @@ __global__ __launch_bounds__(Wide::kThreads, 2) void k_unpack_matmul_wide(
   // ---- x: thread (co, xr) owns columns 8 co .. 8 co + 7 of row xr.
   const uint32_t co = t & 15u, xr = t >> 4;
   const uint32_t gpr = (uint32_t)(K / gs);                              // groups per row of x
-  const uint32_t k_col = (uint32_t)k0 + 8u * co;
+  const uint32_t k_col = min((uint32_t)k0 + 8u * co, (uint32_t)K - 8u);   // (columns past the output: its last ones again, never stored)
   const uint32_t gk = k_col / (uint32_t)gs;
   const uint32_t in_group = k_col - gk * (uint32_t)gs;                  // a multiple of 8
   const uint32_t wpgb = (uint32_t)gs >> 5;                              // words per group and bit of width
   const uint32_t g_first = (uint32_t)k0 / (uint32_t)gs;
-  const uint32_t n_groups = ((uint32_t)k0 + (uint32_t)W::kBK - 1u) / (uint32_t)gs - g_first + 1u;
+  const uint32_t n_groups = (min((uint32_t)k0 + (uint32_t)W::kBK, (uint32_t)K) - 1u) / (uint32_t)gs - g_first + 1u;
   const uint32_t my_entry = W::kMetaAt + 16u * (xr * (uint32_t)W::kGroupsPerRow + (gk - g_first));
   const uint32_t x_store = W::kXAt + xr * (uint32_t)W::kXRow + ((16u * co) ^ (64u * (xr & 3u)));
 
@@ -316,13 +316,15 @@ __global__ __launch_bounds__(Wide::kThreads, 2) void k_unpack_matmul_wide(
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 4; ++j) {
+      if (k0 + 32 * j >= K) break;                   // the last tile of k may reach 64 columns past the output
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int64_t n = 64 * uw + 32 * i + 8 * (r >> 2) + 4 * lg + (r & 3);
         const int64_t k = 32 * j + li;
         dst[n * ld + k] = acc[i][j][r];
       }
+    }
 }
 
 }  // namespace

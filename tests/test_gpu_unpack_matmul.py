@@ -142,6 +142,15 @@ def test_grad_weight_general_kernel(env, steps, N, K, gs, bits, dtype, bk):
     _steps_case(env, steps, N, K, gs, bits, dtype, 256, bk)
 
 
+# K an odd multiple of 64: the last tile of k reaches 64 columns past the output, in both kernels, over all of m (the second
+# and third) and in slices; groups that end with the row inside that tile, one group per row among them.
+@pytest.mark.parametrize("steps,N,K,gs,bits,dtype,bn,bk", [(1280, 320, 192, 192, "mixed", BF16, 512, 128), (33, 4096, 2112, 32, "mixed", F16, 512, 128),
+                                                           (34, 2048, 4160, 64, 8, BF16, 512, 128), (512, 1024, 448, 64, 1, F16, 512, 128),
+                                                           (169, 64, 10176, 32, "mixed", BF16, 256, 128), (270, 64, 5824, 5824, 4, F16, 256, 128)])
+def test_grad_weight_odd_multiple_of_64_columns(env, steps, N, K, gs, bits, dtype, bn, bk):
+    _steps_case(env, steps, N, K, gs, bits, dtype, bn, bk)
+
+
 def _steps_case(env, steps, N, K, gs, bits, dtype, bn, bk):
     daf, orc = env
     print("case", bn, bk, steps, N, K, gs, bits, dtype, flush=True)
