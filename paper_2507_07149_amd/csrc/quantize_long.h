@@ -62,14 +62,13 @@ __device__ __forceinline__ void quantize_pack_long_body(
   }
 
   // 3. min/max of the slice, then of the group
-  float xf[S::kLoads][kEpl];
   {
     float a[2], c2[2];
 #pragma unroll
     for (int u = 0; u < S::kLoads; ++u) {
+      float v[kEpl];
 #pragma unroll
-      for (int e = 0; e < kEpl; ++e) xf[u][e] = chunk_elem<DT>(raw[u], e);
-      const float(&v)[kEpl] = xf[u];
+      for (int e = 0; e < kEpl; ++e) v[e] = chunk_elem<DT>(raw[u], e);
       float lo = vmin(vmin3(v[0], v[1], v[2]), v[3]), hi = vmax(vmax3(v[0], v[1], v[2]), v[3]);
       if (kEpl == 8) {
         lo = vmin3(lo, vmin3(v[4 % kEpl], v[5 % kEpl], v[6 % kEpl]), v[7 % kEpl]);
@@ -123,14 +122,16 @@ __device__ __forceinline__ void quantize_pack_long_body(
       uint32_t n0, n1;
       if constexpr (METRICS) {
         float err, mag, var;
-        if (need_exact2) quantize_chunk<DT, true, true>(xf[u], s.mn, invs, b, rnd[u], n0, n1, s.scale, &err, &mag, &var);
-        else             quantize_chunk<DT, false, true>(xf[u], s.mn, invs, b, rnd[u], n0, n1, s.scale, &err, &mag, &var);
+        if (need_exact2)
+          quantize_raw_chunk<DT, true, true>(raw[u], s.mn, invs, b, rnd[u], n0, n1, 8, true, s.scale, &err, &mag, &var);
+        else
+          quantize_raw_chunk<DT, false, true>(raw[u], s.mn, invs, b, rnd[u], n0, n1, 8, true, s.scale, &err, &mag, &var);
         m_err += err;
         m_mag += mag;
         m_var += var;
       } else {
-        if (need_exact2) quantize_chunk<DT, true>(xf[u], s.mn, invs, b, rnd[u], n0, n1);
-        else             quantize_chunk<DT, false>(xf[u], s.mn, invs, b, rnd[u], n0, n1);
+        if (need_exact2) quantize_raw_chunk<DT, true>(raw[u], s.mn, invs, b, rnd[u], n0, n1);
+        else             quantize_raw_chunk<DT, false>(raw[u], s.mn, invs, b, rnd[u], n0, n1);
       }
       stage_chunk<kEpl>(stage8, addr, b, n0, n1, lane);
     }

@@ -123,8 +123,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
     short_tile_load<DT>(&x[tile * (S::kLoads * kWave)], short_len, lane, raw);
     groups = (short_len + S::kGroupSize - 1) / S::kGroupSize;
   }
-  float xf[S::kLoads][S::kEpl];
-  tile_minmax<DT, LPG_LOG2>(raw, xf, stat, lane);
+  tile_minmax<DT, LPG_LOG2>(raw, stat, lane);
   wave_lds_sync();
   if (lane < groups) {
     float2 st = stat[lane * S::kLoadsPerGroup];
@@ -167,8 +166,7 @@ __global__ __launch_bounds__(kThreads) void k_group_minmax_units(const u32x4* __
   uint4 raw[S::kLoads];
   if (short_len > 0 && tile == n_tiles - 1) short_tile_load<DT>(&x[chunk0], short_len, lane, raw);
   else unit_tile_load<DT>(x, chunk0, n_chunks, lane, raw);
-  float xf[S::kLoads][S::kEpl];
-  const float2 st = unit_tile_stats<DT>(raw, xf, ustat_all[wave_in_block], k, m, part_log2, lane);
+  const float2 st = unit_tile_stats<DT>(raw, ustat_all[wave_in_block], k, m, part_log2, lane);
   if (lane < k) {
     out_min[tile * k_full + lane] = st.x + 0.0f;
     out_max[tile * k_full + lane] = st.y + 0.0f;

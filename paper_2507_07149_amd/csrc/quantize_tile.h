@@ -82,7 +82,6 @@ struct alignas(16) WaveLds {
 // used to go one by one through quantize_pack_group_body in a workgroup of their own, up to 63 chains of
 // dependent loads of ~3 us each behind four waves: 6774528 bfloat16 elements, groups of 64, three widths, both directions
 // 52.7 us, now 13.4.
-constexpr int kMaxEpl = 8;
 // `len` elements, 1 <= len < LOADS * kWave * kEpl, from `chunks` on; chunk u * kWave + lane goes to raw[u].
 template <int DT, int LOADS>
 __device__ __forceinline__ void short_tile_load(const u32x4* chunks, int len, int lane, uint4 (&raw)[LOADS]) {
@@ -113,9 +112,11 @@ __device__ __forceinline__ void short_tile_load(const u32x4* chunks, int len, in
 #pragma unroll
   for (int u = 0; u < LOADS; ++u) {
     const int c = u * kWave + lane;
-    raw[u] = c < whole    ? make_uint4(v[u].x, v[u].y, v[u].z, v[u].w)
-             : c == whole ? make_uint4(edge[0], edge[1], edge[2], edge[3])
-                          : make_uint4(end, end, end, end);
+    raw[u] = make_uint4(v[u].x, v[u].y, v[u].z, v[u].w);
+    if ((u + 1) * kWave > whole) {                   // (the whole wave)
+      if (c == whole) raw[u] = make_uint4(edge[0], edge[1], edge[2], edge[3]);
+      if (c > whole) raw[u] = make_uint4(end, end, end, end);
+    }
   }
 }
 // The first `len` elements of such a tile to `chunks`.
@@ -140,6 +141,12 @@ __device__ __forceinline__ void short_tile_store(u32x4* chunks, int len, int lan
   }
 }
 
+// Negated codes of a chunk (quantize_chunk) in which only the first `valid` elements exist: the others become 0.
+__device__ __forceinline__ uint32_t keep_codes(uint32_t nacc, uint32_t b, int valid) {
+  const uint32_t drop = (uint32_t)(4 - (valid < 0 ? 0 : valid > 4 ? 4 : valid)) * b;
+  return drop < 32u ? 0u - (((0u - nacc) >> drop) << drop) : 0u;
+}
+
 // Codes of one 16-byte chunk, accumulated most significant first and NEGATED (the element map
 // yields -code): nacc0 = -(elements 0..3), nacc1 = -(elements 4..7) (16-bit inputs only).
 //
@@ -148,13 +155,13 @@ __device__ __forceinline__ void short_tile_store(u32x4* chunks, int len, int lan
 // as the dequantizer computes it, mag += x^2, both in binary32; var = sum of T*(256-T), the
 // variance of the stochastic rounding in units of scale^2 / 65536 (exact integer).
 //
-// Elements from `valid` on (the tensor ends in this chunk or before it) count as code 0 and for no sum.
+// Elements from `valid` on (the tensor ends in this chunk or before it) count for no sum.
 template <int DT, bool EXACT2, bool METRICS = false>
 __device__ __forceinline__ void quantize_chunk(const float (&xf)[ElemTraits<DT>::kPerLoad], float mn,
                                                float invs, uint32_t b, const uint32_t* rnd,
                                                uint32_t& nacc0, uint32_t& nacc1, float scale = 0.0f,
                                                float* err = nullptr, float* mag = nullptr, float* var = nullptr,
-                                               int valid = kMaxEpl) {
+                                               int valid = 8) {
   constexpr int kEpl = ElemTraits<DT>::kPerLoad;
   uint32_t nacc[2] = {0u, 0u};
   float e2 = 0.0f, m2 = 0.0f;
@@ -166,9 +173,8 @@ __device__ __forceinline__ void quantize_chunk(const float (&xf)[ElemTraits<DT>:
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const float xv = xf[q * 4 + e];
-      int nc = neg_code<EXACT2>(xv, mn, invs, (rw >> (8 * e)) & 0xFFu, METRICS ? &rt[e] : nullptr);
+      const int nc = neg_code<EXACT2>(xv, mn, invs, (rw >> (8 * e)) & 0xFFu, METRICS ? &rt[e] : nullptr);
       const bool in = q * 4 + e < valid;
-      nc = in ? nc : 0;
       nacc[q] = (nacc[q] << b) + (uint32_t)nc;
       if (METRICS && !in) rt[e] = 0;
       if (METRICS && in) {
@@ -192,8 +198,7 @@ __device__ __forceinline__ void quantize_chunk(const float (&xf)[ElemTraits<DT>:
 // one mixed-precision fma per element (the widening conversion disappears into it).
 template <bool EXACT2>
 __device__ __forceinline__ void quantize_chunk_f16(const uint4& raw, float mn, float invs, uint32_t b,
-                                                   const uint32_t* rnd, uint32_t& nacc0, uint32_t& nacc1,
-                                                   int valid = kMaxEpl) {
+                                                   const uint32_t* rnd, uint32_t& nacc0, uint32_t& nacc1) {
   const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
   uint32_t nacc[2] = {0u, 0u};
 #pragma unroll
@@ -203,12 +208,37 @@ __device__ __forceinline__ void quantize_chunk_f16(const uint4& raw, float mn, f
     for (int e = 0; e < 4; ++e) {
       const uint32_t pair = w[q * 2 + (e >> 1)];
       const float d = (e & 1) ? min_minus_half<1>(pair, mn) : min_minus_half<0>(pair, mn);
-      const int nc = neg_code_of_difference<EXACT2>(d, invs, (rw >> (8 * e)) & 0xFFu);
-      nacc[q] = (nacc[q] << b) + (uint32_t)(q * 4 + e < valid ? nc : 0);
+      nacc[q] = (nacc[q] << b) + (uint32_t)neg_code_of_difference<EXACT2>(d, invs, (rw >> (8 * e)) & 0xFFu);
     }
   }
   nacc0 = nacc[0];
   nacc1 = nacc[1];
+}
+
+// A chunk from its loaded form.  binary16 without metrics needs nothing widened.  With metrics the values that the
+// statistics widened would hold twice the registers until here, so they are made again (the empty statement keeps the
+// compiler from keeping the first ones): 128 -> 96 registers, 4 -> 5 waves per SIMD, 361 M bfloat16 elements, groups of 64,
+// call with selection and plan 285 -> 279 us.  bfloat16 without metrics keeps them: 72 registers and 6 waves instead of 94 and 5
+// took 2 % longer (361 M elements, both directions, 318 -> 325 us; held to 5 waves 318).
+// SHORT: only the first `valid` elements of the chunk exist; `all`: the chunks of the whole wave do.
+template <int DT, bool EXACT2, bool METRICS = false, bool SHORT = false>
+__device__ __forceinline__ void quantize_raw_chunk(uint4& raw, float mn, float invs, uint32_t b, const uint32_t* rnd,
+                                                   uint32_t& nacc0, uint32_t& nacc1, int valid = 8, bool all = true,
+                                                   float scale = 0.0f, float* err = nullptr, float* mag = nullptr,
+                                                   float* var = nullptr) {
+  if constexpr (DT == kF16 && !METRICS) {
+    quantize_chunk_f16<EXACT2>(raw, mn, invs, b, rnd, nacc0, nacc1);
+  } else {
+    if (METRICS && DT != kF32) asm volatile("" : "+v"(raw.x), "+v"(raw.y), "+v"(raw.z), "+v"(raw.w));
+    float xf[ElemTraits<DT>::kPerLoad];
+#pragma unroll
+    for (int e = 0; e < ElemTraits<DT>::kPerLoad; ++e) xf[e] = chunk_elem<DT>(raw, e);
+    quantize_chunk<DT, EXACT2, METRICS>(xf, mn, invs, b, rnd, nacc0, nacc1, scale, err, mag, var, SHORT ? valid : 8);
+  }
+  if (SHORT && !all) {
+    nacc0 = keep_codes(nacc0, b, valid);
+    if (DT != kF32) nacc1 = keep_codes(nacc1, b, valid - 4);
+  }
 }
 
 // binary16 tiles: one [-max : min] dword (two binary16 halves, daf_device.h) per (load, lane run)
@@ -231,14 +261,13 @@ __device__ __forceinline__ void tile_minmax_f16(const uint4 (&raw)[TileShape<kF1
   }
 }
 
-// Widens the tile's chunks into xf and leaves one (min, max) pair per (load, lane run) segment
-// in stat[load * runs_per_load + run]; a group's segments are consecutive entries.
+// Leaves one (min, max) pair per (load, lane run) segment in stat[load * runs_per_load + run]; a group's
+// segments are consecutive entries.
 template <int DT, int LPG_LOG2, int DIV = 1>
-__device__ __forceinline__ void tile_minmax(const uint4 (&raw)[TileShape<DT, LPG_LOG2, DIV>::kLoads],
-                                            float (&xf)[TileShape<DT, LPG_LOG2, DIV>::kLoads][ElemTraits<DT>::kPerLoad],
-                                            float2* stat, int lane) {
+__device__ __forceinline__ void tile_minmax(const uint4 (&raw)[TileShape<DT, LPG_LOG2, DIV>::kLoads], float2* stat, int lane) {
   using S = TileShape<DT, LPG_LOG2, DIV>;
   constexpr int kEpl = S::kEpl;
+  float xf[S::kLoads][kEpl];
   static_assert(S::kLoads % 2 == 0, "loads are reduced in pairs");
   if constexpr (DT == kF32 && LPG_LOG2 >= 5 && S::kLoads == 16) {
     // groups of 32 or 64 lanes: all 16 loads are reduced together (transposed reduction)
@@ -470,20 +499,12 @@ __device__ __forceinline__ void quantize_pack_tile_body(
     }
 
     // 3. per-group min/max: in-lane over the chunk, then across the group's lanes.
-    //    binary16 tiles stay in their loaded form: packed minimum / maximum on the pairs here, and
-    //    the subtraction of step 5 widens on the fly (the metrics variant needs the widened values).
-    constexpr bool kPairs16 = (DT == kF16) && !METRICS;
-    float xf[kPairs16 ? 1 : S::kLoads][kEpl];
-    if constexpr (kPairs16) {
-      if constexpr (!EXT) tile_minmax_f16<LPG_LOG2, DIV>(raw, lds.stat, lane);
-    } else if constexpr (EXT) {
-#pragma unroll
-      for (int u = 0; u < S::kLoads; ++u) {
-#pragma unroll
-        for (int e = 0; e < kEpl; ++e) xf[u][e] = chunk_elem<DT>(raw[u], e);
-      }
-    } else {
-      tile_minmax<DT, LPG_LOG2, DIV>(raw, xf, lds.stat, lane);
+    //    binary16 tiles: packed minimum / maximum on the loaded pairs, and
+    //    the subtraction of step 5 widens on the fly.
+    constexpr bool kPairs16 = DT == kF16;
+    if constexpr (!EXT) {
+      if constexpr (kPairs16) tile_minmax_f16<LPG_LOG2, DIV>(raw, lds.stat, lane);
+      else tile_minmax<DT, LPG_LOG2, DIV>(raw, lds.stat, lane);
     }
     wave_lds_sync();
 
@@ -602,12 +623,13 @@ __device__ __forceinline__ void quantize_pack_tile_body(
           addr = (stage_base + head * 4u + (uint32_t)grp * (kGroupWords32 * B * 4u) + ((lig * kLaneBits) >> 3)) ^ kSwz;
         }
         uint32_t n0, n1;
-        const int valid = SHORT ? len - (u * kWave + lane) * kEpl : kMaxEpl;   // elements from here to the end
+        const int valid = SHORT ? len - (u * kWave + lane) * kEpl : 8;         // elements from here to the end
+        const bool all = !SHORT || (u + 1) * kWave * kEpl <= len;
         if constexpr (METRICS) {
           const float g_scale = lds.gscale[grp];
           float* sums = metric_sums[u & 1];
-          quantize_chunk<DT, kExact2, true>(xf[u], g_mn, g_invs, b, rnd[u], n0, n1, g_scale, &sums[0], &sums[1], &sums[2],
-                                            valid);
+          quantize_raw_chunk<DT, kExact2, true, SHORT>(raw[u], g_mn, g_invs, b, rnd[u], n0, n1, valid, all, g_scale, &sums[0],
+                                                       &sums[1], &sums[2]);
           if (u & 1) {                           // over the group's lanes, two loads at a time
             seg_sum6<S::kLaneLog2>(metric_sums[0], metric_sums[1]);
             if (lane_in_run == (uint32_t)S::kLpg - 1u) {
@@ -626,10 +648,8 @@ __device__ __forceinline__ void quantize_pack_tile_body(
               }
             }
           }
-        } else if constexpr (kPairs16) {
-          quantize_chunk_f16<kExact2>(raw[u], g_mn, g_invs, b, rnd[u], n0, n1, valid);
         } else {
-          quantize_chunk<DT, kExact2>(xf[u], g_mn, g_invs, b, rnd[u], n0, n1, 0.0f, nullptr, nullptr, nullptr, valid);
+          quantize_raw_chunk<DT, kExact2, false, SHORT>(raw[u], g_mn, g_invs, b, rnd[u], n0, n1, valid, all);
         }
         stage_chunk_at<kEpl>(addr, b, n0, n1, lane);
       }
@@ -666,13 +686,13 @@ __device__ __forceinline__ void quantize_pack_tile_body(
 }
 
 // Waves per SIMD of the tile kernel.  At least: as many as the whole tiles' registers allow; the short tile's code shall
-// not cost a wave (metrics: 128 registers instead of 131 and so 4 waves instead of 3, 361 M bfloat16 elements 233 -> 206 us).
+// not cost a wave (metrics, 361 M bfloat16 elements: 4 waves instead of 3, 311 -> 285 us, whole call).
 // At most: more waves than these scatter the streams of a binary32 tensor (both directions, 47 M elements, 2 bits, 4 / 5 / 6 / 8
 // waves: 70.3 / 69.1 / 67.1 / 68.0 us; 92 M, 8 bits: 158.5 / 157.0 / 159.7 / 160.9).
 template <int DT, int LPG_LOG2, bool METRICS>
 constexpr int tile_min_waves() {
   if (DT == kF32) return LPG_LOG2 == 10 ? 4 : 1;
-  if (METRICS) return LPG_LOG2 == 2 ? 5 : 4;
+  if (METRICS) return 5;
   return DT == kF16 ? (LPG_LOG2 == 2 ? 8 : 6) : (LPG_LOG2 == 2 ? 7 : 4);
 }
 template <int DT, int B, bool METRICS>
@@ -745,11 +765,12 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack_tile_batch(const Bat
   const int t = batch_entry_of(batch.ends, (uint32_t)gtile);
   if (t >= batch.n) return;                          // past the last tile (the grid is whole workgroups)
   const BatchEntry& e = batch.e[t];
-  const int64_t tile = gtile - (t ? batch.e[t - 1].tile_end : 0);
+  int64_t tile = gtile - (t ? batch.e[t - 1].tile_end : 0);
   if constexpr (SHORT) {
-    if (e.short_len > 0 && gtile == e.tile_end - 1) {
+    if (e.short_len > 0 && --tile < 0) {             // a tensor's short tile goes first, as in k_quantize_pack_tile
+      const int64_t last = e.tile_end - 1 - (t ? batch.e[t - 1].tile_end : 0);
       quantize_pack_tile_body<DT, LPG_LOG2, B, false, false, false, tile_div<DT, LPG_LOG2>(), false, true>(
-          static_cast<const u32x4*>(e.x), tile, wave_in_block, e.bits, e.off, e.seed_lo, e.seed_hi, e.words, e.mn, e.sc,
+          static_cast<const u32x4*>(e.x), last, wave_in_block, e.bits, e.off, e.seed_lo, e.seed_hi, e.words, e.mn, e.sc,
           nullptr, (int64_t)1, nullptr, nullptr, 0, e.short_len);
       return;
     }

@@ -69,23 +69,46 @@ __device__ __forceinline__ void unit_tile_relu(uint4 (&raw)[UnitShape<DT>::kLoad
   if constexpr (SHORT) short_tile_store<DT>(&out_y[chunk0], len, lane, raw);
 }
 
-// Widens the tile into xf and returns, in lane g < k, the (min, max) of group g of the tile
-// (k groups of m units each).  In-lane over the chunk, DPP across the unit's lanes, one pair
+// Returns, in lane g < k, the (min, max) of group g of the tile (k groups of m units each).  In-lane over the chunk, DPP across the unit's lanes, one pair
 // per unit to LDS; then 2^part_log2 lanes share a group's m units and combine.
 template <int DT>
 __device__ __forceinline__ float2 unit_tile_stats(const uint4 (&raw)[UnitShape<DT>::kLoads],
-                                                  float (&xf)[UnitShape<DT>::kLoads][ElemTraits<DT>::kPerLoad],
                                                   float2* ustat, int k, int m, int part_log2, int lane) {
   using S = UnitShape<DT>;
   constexpr int kEpl = S::kEpl;
+  const int part = 1 << part_log2;
+  int j = lane >> part_log2;
+  j = j < k ? j : k - 1;                                   // idle lanes repeat the last group
+  const int p0 = lane & (part - 1);                        // < m: part <= 64 / k <= m
+  const int src = (lane < k ? lane : k - 1) << part_log2;  // lane g takes group g's pair
+  if constexpr (DT == kF16) {                              // one [-max : min] dword per unit, nothing widened (daf_device.h)
+    uint32_t* ust = reinterpret_cast<uint32_t*>(ustat);
+#pragma unroll
+    for (int u = 0; u < S::kLoads; u += 4) {
+      uint32_t p[4];
+#pragma unroll
+      for (int h = 0; h < 4; ++h) p[h] = chunk_stat_f16(raw[u + h]);
+      seg_pk_min_x4<S::kLanesLog2>(p[0], p[1], p[2], p[3]);
+      if ((lane & ((1 << S::kLanesLog2) - 1)) == (1 << S::kLanesLog2) - 1) {
+#pragma unroll
+        for (int h = 0; h < 4; ++h) ust[(u + h) * S::kUnitsPerLoad + (lane >> S::kLanesLog2)] = p[h];
+      }
+    }
+    wave_lds_sync();
+    uint32_t st = ust[j * m + p0];
+    for (int i = p0 + part; i < m; i += part) st = pk_min_f16(st, ust[j * m + i]);
+    for (int d = 1; d < part; d <<= 1) st = pk_min_f16(st, (uint32_t)__shfl_xor((int)st, d));
+    st = (uint32_t)__shfl((int)st, src);
+    return make_float2(stat_f16_min(st), stat_f16_max(st));
+  }
 #pragma unroll
   for (int u = 0; u < S::kLoads; u += 2) {
-    float mn[2], mx[2];
+    float xf[2][kEpl], mn[2], mx[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
-      for (int e = 0; e < kEpl; ++e) xf[u + h][e] = chunk_elem<DT>(raw[u + h], e);
-      const float(&v)[kEpl] = xf[u + h];
+      for (int e = 0; e < kEpl; ++e) xf[h][e] = chunk_elem<DT>(raw[u + h], e);
+      const float(&v)[kEpl] = xf[h];
       if (kEpl == 4) {
         mn[h] = vmin(vmin3(v[0], v[1], v[2]), v[3]);
         mx[h] = vmax(vmax3(v[0], v[1], v[2]), v[3]);
@@ -102,10 +125,6 @@ __device__ __forceinline__ float2 unit_tile_stats(const uint4 (&raw)[UnitShape<D
   }
   wave_lds_sync();
 
-  const int part = 1 << part_log2;
-  int j = lane >> part_log2;
-  j = j < k ? j : k - 1;                                   // idle lanes repeat the last group
-  const int p0 = lane & (part - 1);                        // < m: part <= 64 / k <= m
   const float2* us = ustat + j * m;
   float2 st = us[p0];
   for (int i = p0 + part; i < m; i += part) {
@@ -117,7 +136,6 @@ __device__ __forceinline__ float2 unit_tile_stats(const uint4 (&raw)[UnitShape<D
     st.x = vmin(st.x, __shfl_xor(st.x, d));
     st.y = vmax(st.y, __shfl_xor(st.y, d));
   }
-  const int src = (lane < k ? lane : k - 1) << part_log2;  // lane g takes group g's pair
   st.x = __shfl(st.x, src);
   st.y = __shfl(st.y, src);
   return st;
@@ -211,8 +229,7 @@ __device__ __forceinline__ void quantize_pack_units_body(
   }
 
   // 3. + 4a. min/max per unit, then per group: lane g holds group g's pair
-  float xf[S::kLoads][kEpl];
-  const float2 st = unit_tile_stats<DT>(raw, xf, lds.ustat, k, m, part_log2, lane);
+  const float2 st = unit_tile_stats<DT>(raw, lds.ustat, k, m, part_log2, lane);
 
   // 4b. lane g of the wave finishes group g of the tile: scale, reciprocal, place in the run
   bool need_exact2;
@@ -275,14 +292,15 @@ __device__ __forceinline__ void quantize_pack_units_body(
       const uint32_t b = kMixed ? (gi.b & 0xFFu) : (uint32_t)B;
       const uint32_t addr = (gi.byte_off + (__umul24(lig, b * (uint32_t)kEpl) >> 3)) ^ (gi.b >> 8);
       uint32_t n0, n1;
-      const int valid = SHORT ? len - (int)c * kEpl : kMaxEpl;         // elements from here to the end
+      const int valid = SHORT ? len - (int)c * kEpl : 8;               // elements from here to the end
+      const bool all = !SHORT || (u + 1) * kWave * kEpl <= len;
       if constexpr (METRICS) {
         const float g_scale = mlds.gscale[grp];
         float err, mag, var, unused = 0.0f;
-        if (need_exact2)
-          quantize_chunk<DT, true, true>(xf[u], gi.mn, gi.invs, b, rnd[u], n0, n1, g_scale, &err, &mag, &var, valid);
+        if (SHORT || need_exact2)
+          quantize_raw_chunk<DT, true, true, SHORT>(raw[u], gi.mn, gi.invs, b, rnd[u], n0, n1, valid, all, g_scale, &err, &mag, &var);
         else
-          quantize_chunk<DT, false, true>(xf[u], gi.mn, gi.invs, b, rnd[u], n0, n1, g_scale, &err, &mag, &var, valid);
+          quantize_raw_chunk<DT, false, true>(raw[u], gi.mn, gi.invs, b, rnd[u], n0, n1, 8, true, g_scale, &err, &mag, &var);
         seg_sum2<S::kLanesLog2>(err, mag);       // over the unit's lanes (all valid, or none)
         seg_sum2<S::kLanesLog2>(var, unused);
         if ((lane & ((1 << S::kLanesLog2) - 1)) == (1 << S::kLanesLog2) - 1) {
@@ -291,10 +309,10 @@ __device__ __forceinline__ void quantize_pack_units_body(
           mlds.usum[2][c >> S::kLanesLog2] = var;
         }
       } else {
-        if (need_exact2)
-          quantize_chunk<DT, true>(xf[u], gi.mn, gi.invs, b, rnd[u], n0, n1, 0.0f, nullptr, nullptr, nullptr, valid);
+        if (SHORT || need_exact2)
+          quantize_raw_chunk<DT, true, false, SHORT>(raw[u], gi.mn, gi.invs, b, rnd[u], n0, n1, valid, all);
         else
-          quantize_chunk<DT, false>(xf[u], gi.mn, gi.invs, b, rnd[u], n0, n1, 0.0f, nullptr, nullptr, nullptr, valid);
+          quantize_raw_chunk<DT, false>(raw[u], gi.mn, gi.invs, b, rnd[u], n0, n1);
       }
       stage_chunk<kEpl>(stage8, addr, b, n0, n1, lane);
     }
@@ -366,10 +384,8 @@ struct UnitBatch {
   }
 };
 
-// (16-bit formats: 96 registers and five waves per SIMD instead of 99 and four, 24 tensors of 58 M elements in all, rows of 768 and
-// 3072, both directions: 78.2 -> 75.9 us.  With the short tiles' code that costs spills: 22.0 -> 22.5 us on a short list.)
 template <int DT, int B, bool SHORT>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DT == kF32 || SHORT ? 4 : 5)))
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void k_quantize_pack_units_batch(const UnitBatch batch) {
   const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t gtile = (int64_t)blockIdx.x * kWavesPerBlock + wave_in_block;
@@ -377,17 +393,19 @@ void k_quantize_pack_units_batch(const UnitBatch batch) {
   if (t >= batch.n) return;
   const UnitBatchEntry& e = batch.e[t];
   const int64_t first = t ? batch.e[t - 1].tile_end : 0;
+  int64_t tile = gtile - first;
   if constexpr (SHORT) {
-    if (e.short_len > 0 && gtile == e.tile_end - 1) {
-      quantize_pack_units_body<DT, B, false, false, true>(static_cast<const u32x4*>(e.x), gtile - first, wave_in_block,
+    if (e.short_len > 0 && --tile < 0) {             // a tensor's short tile goes first, as in k_quantize_pack_tile
+      quantize_pack_units_body<DT, B, false, false, true>(static_cast<const u32x4*>(e.x), e.tile_end - 1 - first, wave_in_block,
                                                           e.tile_end - first, e.m, e.k, e.k_last, e.magic, e.part_log2,
                                                           e.bits, e.off, e.seed_lo, e.seed_hi, e.words, e.mn, e.sc, nullptr,
                                                           nullptr, e.short_len);
       return;
     }
   }
-  quantize_pack_units_body<DT, B>(static_cast<const u32x4*>(e.x), gtile - first, wave_in_block, e.tile_end - first, e.m,
-                                  e.k, e.k_last, e.magic, e.part_log2, e.bits, e.off, e.seed_lo, e.seed_hi, e.words,
+  // (a list with short tiles: k_last belongs to them, the others are whole)
+  quantize_pack_units_body<DT, B>(static_cast<const u32x4*>(e.x), tile, wave_in_block, e.tile_end - first, e.m, e.k,
+                                  e.k_last, e.magic, e.part_log2, e.bits, e.off, e.seed_lo, e.seed_hi, e.words,
                                   e.mn, e.sc, nullptr, nullptr);
 }
 
