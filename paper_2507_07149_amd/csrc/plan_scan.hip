@@ -2,8 +2,8 @@
 //
 // The packed buffer concatenates the groups' codes (paper Sec. 3.3 speaks of packing the
 // compressed values together); with a bit width per group the position of group g is the
-// sum of the word counts of all groups before it.  Up to kOneGroups groups one workgroup does it in one launch;
-// up to kMaxSummedBlocks blocks of 2048 groups, per-block sums and a second launch in which every
+// sum of the word counts of all groups before it.  Up to kAheadMost groups one launch does it (k_plan_ahead); up
+// to kMaxSummedBlocks blocks of 2048 groups, per-block sums and a second launch in which every
 // block adds up the sums before its own and writes its offsets (5.6 M groups: 27 -> 23 us with the launch between
 // the two gone, 197 K: 11.6 -> 9.4); beyond that a single-block scan of the sums comes between them.
 #include "daf_device.h"
@@ -212,22 +212,67 @@ __global__ __launch_bounds__(kThreads) void k_plan_write_offsets(const uint8_t* 
   store_offsets(off, base, num_groups, block_off + before + incl - s, w);   // the thread's first group
 }
 
-// Few groups: one workgroup, kItems consecutive groups per thread.
-constexpr int kOneThreads = 1024;
-__global__ __launch_bounds__(kOneThreads) void k_plan_one(const uint8_t* __restrict__ src_bits, uint8_t* __restrict__ plan_bits,
-                                                          int64_t num_groups, int64_t n, int32_t gs,
-                                                          uint32_t* __restrict__ off, unsigned long long* __restrict__ total,
-                                                          int* __restrict__ bad_flag) {
-  constexpr int kWaves = kOneThreads / daf::kWave;
-  __shared__ uint32_t wave_tot[kWaves];
+// One launch: a workgroup has kItems consecutive groups per thread and adds up the widths of all groups before its own
+// for itself.  All those groups are whole ones, so their words are (group size / 32) times the sum of their widths, which
+// are sixteen to a load; a few tens of kilobytes from the cache cost less than a second launch.  Reads what other workgroups
+// have the copy of: the caller's widths are not the plan's own.
+constexpr int kAheadThreads = 1024;
+constexpr int kAheadGroups = kItems * kAheadThreads;
+
+// The sum of the widths of sixteen groups, one to a byte; a width outside {1,2,4,8} counts as 8 and is reported.
+__device__ __forceinline__ uint32_t sixteen_widths(const uint4& v, int* bad) {
+  uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  uint32_t wrong = 0u;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)      // a bit above the lowest four; more than one bit; no bit (without the first no carry leaves a byte)
+    wrong |= (w[i] & 0xF0F0F0F0u) | (w[i] & (w[i] - 0x01010101u)) | (~(w[i] + 0x7F7F7F7Fu) & 0x80808080u);
+  if (wrong != 0u) {
+    *bad = 1;
+    for (int i = 0; i < 4; ++i)
+      for (int j = 0; j < 32; j += 8) {
+        const uint32_t b = (w[i] >> j) & 0xFFu;
+        if (b != 1u && b != 2u && b != 4u) w[i] = (w[i] & ~(0xFFu << j)) | (8u << j);
+      }
+  }
+  uint32_t sum = 0u;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) sum = __builtin_amdgcn_udot4(w[i], 0x01010101u, sum, false);
+  return sum;
+}
+
+__global__ __launch_bounds__(kAheadThreads) void k_plan_ahead(const uint8_t* __restrict__ src_bits,
+                                                              uint8_t* __restrict__ plan_bits, int64_t num_groups, int64_t n,
+                                                              int32_t gs, uint32_t* __restrict__ off,
+                                                              unsigned long long* __restrict__ total,
+                                                              int* __restrict__ bad_flag) {
+  constexpr int kWaves = kAheadThreads / daf::kWave;
+  __shared__ uint32_t wave_tot[kWaves], wave_widths[kWaves];
   __shared__ unsigned long long wave_sum[kWaves];
-  const int64_t base = (int64_t)threadIdx.x * kItems;
+  const int64_t base = (int64_t)blockIdx.x * kAheadGroups + (int64_t)threadIdx.x * kItems;
   uint32_t w[kItems];
-  uint32_t s = 0;
+  uint32_t s = 0, widths = 0;
   unsigned long long sum = 0;
   int bad = 0;
   uint32_t b[kItems];
   load_widths(src_bits, base, num_groups, b);
+  // the groups before this workgroup's: a multiple of 16
+  const uint4* before_bits = reinterpret_cast<const uint4*>(src_bits);
+  const int before_pieces = (int)(blockIdx.x * (kAheadGroups / 16));
+  constexpr int kLoads = 8;
+  for (int i0 = (int)threadIdx.x; i0 < before_pieces; i0 += kLoads * kAheadThreads) {
+    uint4 v[kLoads];
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+      const int i = i0 + j * kAheadThreads;
+      v[j] = make_uint4(0x01010101u, 0x01010101u, 0x01010101u, 0x01010101u);
+      if (i < before_pieces) v[j] = before_bits[i];
+    }
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+      const uint32_t sixteen = sixteen_widths(v[j], &bad);
+      if (i0 + j * kAheadThreads < before_pieces) widths += sixteen;
+    }
+  }
 #pragma unroll
   for (int i = 0; i < kItems; ++i) {
     const int64_t g = base + i;
@@ -243,29 +288,34 @@ __global__ __launch_bounds__(kOneThreads) void k_plan_one(const uint8_t* __restr
   }
   store_widths(plan_bits, base, num_groups, b);
   const int lane = threadIdx.x & (daf::kWave - 1), wave = threadIdx.x >> 6;
-  const uint32_t incl = daf::wave_inclusive_sum(s);
+  const uint32_t incl = daf::wave_inclusive_sum(s), all_widths = daf::wave_inclusive_sum(widths);
   for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
   if (lane == daf::kWave - 1) {
     wave_tot[wave] = incl;
+    wave_widths[wave] = all_widths;
     wave_sum[wave] = sum;
   }
   const int any_bad = __syncthreads_or(bad);
   uint32_t before = 0u;
-  unsigned long long all = 0;
+  unsigned long long ahead = 0, own = 0;
 #pragma unroll
   for (int v = 0; v < kWaves; ++v) {
     before += (v < wave) ? wave_tot[v] : 0u;
-    all += wave_sum[v];
+    ahead += wave_widths[v];
+    own += wave_sum[v];
   }
-  store_offsets(off, base, num_groups, before + incl - s, w);
-  if (threadIdx.x == 0) {
-    *total = all;
-    *bad_flag = any_bad;
+  ahead *= (unsigned long long)((uint32_t)gs / 32u);
+  store_offsets(off, base, num_groups, (uint32_t)ahead + before + incl - s, w);
+  if (threadIdx.x == 0 && blockIdx.x == gridDim.x - 1) {
+    *total = ahead + own;
+    *bad_flag = any_bad;                               // of all groups: the last workgroup has read them all
   }
 }
 
-// One launch 7.0 us up to here (two launches 9.5); with twice as many groups per thread 10.1.
-constexpr int64_t kOneGroups = kItems * kOneThreads;
+// Up to 65536 groups: kernel alone 4.0 ... 5.6 us up to 16384 groups, 7.6 at 32768 and 8.2 at 65536, the two launches 9.4 and
+// the gap between them at all of these sizes; at 197000 groups the sums over all that comes before make it slower (call of four
+// launches 62.0 -> 65.4 us, at 524288 51.4 -> 60.3).
+constexpr int64_t kAheadMost = 1 << 16;
 constexpr int64_t kMaxSummedBlocks = 4096;            // 32 KB of block sums, read by every block
 
 }  // namespace
@@ -275,9 +325,11 @@ int64_t daf_plan_scan_blocks(int64_t num_groups) { return (num_groups + kBlockGr
 hipError_t daf_launch_plan_scan(const uint8_t* src_bits, uint8_t* plan_bits, int64_t num_groups, int64_t n,
                                 int32_t group_size, uint32_t* d_off, unsigned long long* d_block_sums, int64_t n_blocks,
                                 unsigned long long* d_total, int* d_bad, hipStream_t stream) {
-  if (num_groups <= kOneGroups) {
-    hipLaunchKernelGGL(k_plan_one, dim3(1), dim3(kOneThreads), 0, stream, src_bits, plan_bits, num_groups, n, group_size,
-                       d_off, d_total, d_bad);
+  const bool apart = src_bits + num_groups <= plan_bits || plan_bits + num_groups <= src_bits;
+  const bool aligned = (reinterpret_cast<uintptr_t>(src_bits) & 15u) == 0u;
+  if (num_groups <= kAheadGroups || (num_groups <= kAheadMost && apart && aligned)) {
+    hipLaunchKernelGGL(k_plan_ahead, dim3((unsigned)((num_groups + kAheadGroups - 1) / kAheadGroups)), dim3(kAheadThreads), 0,
+                       stream, src_bits, plan_bits, num_groups, n, group_size, d_off, d_total, d_bad);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_plan_block_sums, dim3((unsigned)n_blocks), dim3(kThreads), 0, stream, src_bits, plan_bits,

@@ -14,8 +14,8 @@
 // whose key equals T_k.  Keys are the bit patterns of the ranges, which order like the ranges
 // because a range is never negative.
 //
-// Up to kSmallGroups groups: one launch of one workgroup that keeps the keys in registers
-// (k_select_small).  More: six launches: zero the first counters; write the keys and count their first digit (and zero the
+// Up to kRankMost groups: one launch in which the ranks are counted (k_select_rank); where the widths are replaced in place,
+// up to kSmallGroups, one workgroup that keeps the keys in registers (k_select_small).  More: six launches: zero the first counters; write the keys and count their first digit (and zero the
 // other counters); count the second digit; count the third; count the keys equal to T_k per block of 4096
 // groups; classify.  What a pass decides (the bin that holds the rank) is worked out from its counters by
 // every workgroup of the next launch for itself: a scan of 2048 counters from the cache, next to the
@@ -574,6 +574,90 @@ __global__ __launch_bounds__(kSmallThreads) void k_select_small(const float* __r
   if (base < G) store_widths(out_bits + base, w, G - base);
 }
 
+// Few groups, ranks counted outright: a workgroup has kRankGroups groups, all keys in LDS, and counts for each of its
+// groups the keys that come before it, (range, index), a thread 1 / kRankParts of them.  No passes, no counters, one barrier
+// before the counting and one behind it.  Every workgroup reads all groups, so the widths written are not those read.
+constexpr int kRankThreads = 1024;
+constexpr int kRankGroups = 32, kRankParts = kRankThreads / kRankGroups;
+// Kernel alone, four classes, 512 / 4096 / 8192 groups: one workgroup with the keys in registers 13.7 / 16.5 / 20.1 us, this 4.3 / 6.4 /
+// 9.2; 12000 and 16384: 17.7 and 22.8 against 26 in six launches and the gaps between them. The work grows with the square.
+constexpr int64_t kRankMost = 16384;
+
+template <bool FROM_SCALE>
+__global__ __launch_bounds__(kRankThreads) void k_select_rank(const float* __restrict__ gmin, const float* __restrict__ gmax,
+                                                              const uint8_t* __restrict__ prev_bits, uint32_t prev_uniform,
+                                                              int G, Ranks ranks, int n_thresholds, uint32_t classes_packed,
+                                                              uint8_t* __restrict__ out_bits) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t keys[];         // G, then kRankParts x kRankGroups counts
+  const int padded = (G + 2 * kRankGroups - 1) / (2 * kRankGroups) * (2 * kRankGroups);
+  uint32_t* counts = keys + padded;
+  const int t = (int)threadIdx.x;
+  constexpr int kLoads = 8;
+  for (int g0 = t; g0 < padded; g0 += kLoads * kRankThreads) {
+    float lo[kLoads], hi[kLoads];
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+      const int g = g0 + j * kRankThreads;
+      lo[j] = g < G ? gmin[g] : 0.0f;
+      if (FROM_SCALE) {
+        const uint32_t b = (prev_bits != nullptr && g < G) ? (uint32_t)prev_bits[g] : prev_uniform;
+        hi[j] = (float)((1u << (b & 15u)) - 1u);
+      } else {
+        hi[j] = g < G ? gmax[g] : 0.0f;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+      const int g = g0 + j * kRankThreads;
+      // (behind the last group the highest key: nothing comes after it, and groups of that key have lower indexes)
+      if (g < padded) keys[g] = g < G ? f2u(FROM_SCALE ? lo[j] * hi[j] : hi[j] - lo[j]) : 0xFFFFFFFFu;
+    }
+  }
+  __syncthreads();
+
+  // Part p counts in the blocks of 32 keys p, p + kRankParts, ...: the two halves of a wave in neighbouring blocks.
+  const int tile = (int)blockIdx.x, me = t & (kRankGroups - 1), part = t / kRankGroups;
+  const int i = tile * kRankGroups + me;
+  const uint32_t key = keys[i];                                            // (i < padded)
+  const int blocks = padded / kRankGroups;                                 // even
+  uint32_t before = 0u;
+  for (int block = part; block < blocks; block += kRankParts) {
+    const uint4* k4 = reinterpret_cast<const uint4*>(keys + block * kRankGroups);
+    const int pair = __builtin_amdgcn_readfirstlane(block) >> 1;           // of the wave's two blocks
+    if (pair < tile >> 1) {                                                // all before i: an equal key comes first
+#pragma unroll
+      for (int q = 0; q < kRankGroups / 4; ++q) {
+        const uint4 v = k4[q];
+        before += (v.x <= key) + (v.y <= key) + (v.z <= key) + (v.w <= key);
+      }
+    } else if (pair > tile >> 1) {
+#pragma unroll
+      for (int q = 0; q < kRankGroups / 4; ++q) {
+        const uint4 v = k4[q];
+        before += (v.x < key) + (v.y < key) + (v.z < key) + (v.w < key);
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < kRankGroups / 4; ++q) {
+        const uint4 v = k4[q];
+        const uint32_t k[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) before += k[e] < key || (k[e] == key && block * kRankGroups + 4 * q + e < i);
+      }
+    }
+  }
+  counts[part * kRankGroups + me] = before;
+  __syncthreads();
+  if (t < kRankGroups && i < G) {
+    uint32_t rank = 0u;
+#pragma unroll
+    for (int p = 0; p < kRankParts; ++p) rank += counts[p * kRankGroups + t];
+    uint32_t cls = 0u;
+    for (int k = 0; k < n_thresholds; ++k) cls += rank >= ranks.r[k] ? 1u : 0u;
+    out_bits[i] = (uint8_t)(classes_packed >> (8u * cls));
+  }
+}
+
 }  // namespace
 
 int64_t daf_select_bits_workspace_size(int64_t G) {
@@ -601,15 +685,23 @@ hipError_t daf_launch_select_bits(const float* gmin, const float* gmax, const ui
   // thresholds skipped because R_k >= G sit at the end (R_k grows with k), so class = number of
   // satisfied thresholds still indexes `classes` correctly.
 
-  // One launch, 14 to 20 us up to here against 27 for the six; two and four times as many keys per thread: 32 and 59 us
-  // against 27 (one workgroup counts a pass alone).
-  if (G <= kSmallGroups) {
+  const bool apart = prev_bits == nullptr || out_bits + G <= prev_bits || prev_bits + G <= out_bits;
+  if (G <= kRankMost && apart) {
+    const unsigned blocks = (unsigned)((G + kRankGroups - 1) / kRankGroups);
+    const unsigned lds_bytes = (unsigned)(((G + 2 * kRankGroups - 1) / (2 * kRankGroups) * (2 * kRankGroups) + kRankThreads) * 4);
     if (gmax != nullptr)
-      hipLaunchKernelGGL(k_select_small<false>, dim3(1), dim3(kSmallThreads), 0, stream, gmin, gmax, nullptr, 0u, G, ranks,
-                         n_thr, packed, out_bits);
+      hipLaunchKernelGGL(k_select_rank<false>, dim3(blocks), dim3(kRankThreads), lds_bytes, stream, gmin, gmax, nullptr, 0u,
+                         (int)G, ranks, n_thr, packed, out_bits);
     else
-      hipLaunchKernelGGL(k_select_small<true>, dim3(1), dim3(kSmallThreads), 0, stream, gmin, nullptr, prev_bits,
-                         (uint32_t)prev_uniform, G, ranks, n_thr, packed, out_bits);
+      hipLaunchKernelGGL(k_select_rank<true>, dim3(blocks), dim3(kRankThreads), lds_bytes, stream, gmin, nullptr, prev_bits,
+                         (uint32_t)prev_uniform, (int)G, ranks, n_thr, packed, out_bits);
+    return hipGetLastError();
+  }
+  // The widths are replaced in place, few groups: one launch of one workgroup, 14 to 20 us up to here against 27 for the six;
+  // two and four times as many keys per thread: 32 and 59 us against 27.
+  if (G <= kSmallGroups && gmax == nullptr) {
+    hipLaunchKernelGGL(k_select_small<true>, dim3(1), dim3(kSmallThreads), 0, stream, gmin, nullptr, prev_bits,
+                       (uint32_t)prev_uniform, G, ranks, n_thr, packed, out_bits);
     return hipGetLastError();
   }
 
