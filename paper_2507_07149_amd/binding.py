@@ -1,5 +1,6 @@
 """ctypes binding of libdaf.so: same names as the C ABI, argument marshalling only."""
 import ctypes
+import functools
 import os
 from typing import Optional, Sequence
 
@@ -216,14 +217,16 @@ class Plan:
     def update(self, bits: torch.Tensor, stream=None) -> None:
         """daf_plan_update: new per-group widths (device uint8[G]) for this plan, enqueued on `stream`
         without synchronizing; `packed_words` reads as the 8-bit bound until `finish()`."""
-        a = _Args(self)
-        a.tensor("bits", bits, torch.uint8, self.num_groups, exact=True)
-        a.on_device()
-        rc = load_library().daf_plan_update(self.handle, bits.data_ptr(), _stream_handle(stream))
+        if not (_fits(bits, torch.uint8, self.num_groups) and bits.numel() == self.num_groups):
+            a = _Args(self)
+            a.tensor("bits", bits, torch.uint8, self.num_groups, exact=True)
+            a.on_device()
+        L = load_library()
+        rc = L.daf_plan_update(self.handle, bits.data_ptr(), _stream_handle(stream))
         if rc != 0:
             raise DafError(rc, "daf_plan_update")
         self._keep = bits
-        self.packed_words = int(load_library().daf_plan_packed_words(self.handle))
+        self.packed_words = L.daf_plan_packed_words(self.handle)
 
     def finish(self, stream=None) -> None:
         """daf_plan_finish: one synchronization; the exact packed size, and DafError if the last
@@ -455,22 +458,33 @@ def daf_unpack_matmul_grad_weight(plan: Plan, words: torch.Tensor, mn: torch.Ten
                                   workspace: Optional[torch.Tensor] = None, bits: Optional[torch.Tensor] = None,
                                   stream=None) -> None:
     """grad_y is [M, N]; out_grad_w is float32 [N, K]; the plan's tensor is read as [M, K]."""
-    a = _Args(plan)
-    a.packed(words, mn, scale)
-    a.bits(bits)
-    if out_grad_w.dim() != 2 or grad_y.dim() != 2:
-        raise ValueError("grad_y must be [M, N] and out_grad_w [N, K]")
-    if plan.num_elements % out_grad_w.shape[1] != 0:
-        raise ValueError("K = out_grad_w.shape[1] must divide the plan's element count")
-    a.tensor("grad_y", grad_y, _ELEM_DTYPES, (plan.num_elements // out_grad_w.shape[1]) * out_grad_w.shape[0], exact=True)
-    a.tensor("out_grad_w", out_grad_w, torch.float32, out_grad_w.numel())
-    need = daf_unpack_matmul_workspace_bytes(plan, out_grad_w.shape[0], out_grad_w.shape[1])
-    if need > 0 and workspace is not None:          # a missing workspace is the library's DAF_EINVAL
-        a.tensor("workspace", workspace, workspace.dtype, -(-need // workspace.element_size()))
-    N, K = out_grad_w.shape
-    if grad_y.shape[-1] != N:
-        raise ValueError("out_grad_w must be float32 [N, K] with N = grad_y.shape[-1]")
-    a.on_device()
+    need = -1
+    if (_is_packed(plan, words, mn, scale) and (bits is None or _fits(bits, torch.uint8, plan.num_groups))
+            and _fits(grad_y, grad_y.dtype, 0) and grad_y.dtype in _ELEM_DTYPES and _fits(out_grad_w, torch.float32, 0)
+            and out_grad_w.dim() == 2 and grad_y.dim() == 2):
+        N, K = out_grad_w.shape
+        M, columns = grad_y.shape
+        if columns == N and K > 0 and M * K == plan.num_elements:
+            need = daf_unpack_matmul_workspace_bytes(plan, N, K)
+            if need > 0 and workspace is not None and not _fits(workspace, workspace.dtype, -(-need // workspace.element_size())):
+                need = -1
+    if need < 0:
+        a = _Args(plan)
+        a.packed(words, mn, scale)
+        a.bits(bits)
+        if out_grad_w.dim() != 2 or grad_y.dim() != 2:
+            raise ValueError("grad_y must be [M, N] and out_grad_w [N, K]")
+        if plan.num_elements % out_grad_w.shape[1] != 0:
+            raise ValueError("K = out_grad_w.shape[1] must divide the plan's element count")
+        a.tensor("grad_y", grad_y, _ELEM_DTYPES, (plan.num_elements // out_grad_w.shape[1]) * out_grad_w.shape[0], exact=True)
+        a.tensor("out_grad_w", out_grad_w, torch.float32, out_grad_w.numel())
+        need = daf_unpack_matmul_workspace_bytes(plan, out_grad_w.shape[0], out_grad_w.shape[1])
+        if need > 0 and workspace is not None:      # a missing workspace is the library's DAF_EINVAL
+            a.tensor("workspace", workspace, workspace.dtype, -(-need // workspace.element_size()))
+        N, K = out_grad_w.shape
+        if grad_y.shape[-1] != N:
+            raise ValueError("out_grad_w must be float32 [N, K] with N = grad_y.shape[-1]")
+        a.on_device()
     rc = load_library().daf_unpack_matmul_grad_weight(
         plan.handle, words.data_ptr(), mn.data_ptr(), scale.data_ptr(), bits.data_ptr() if bits is not None else None,
         grad_y.data_ptr(), N, K, _DTYPE_ID[grad_y.dtype], out_grad_w.data_ptr(),
@@ -505,11 +519,13 @@ def daf_minmax(x: torch.Tensor, method: int, workspace: torch.Tensor, out_minmax
 
 
 def daf_group_minmax(plan: Plan, x: torch.Tensor, out_min: torch.Tensor, out_max: torch.Tensor, stream=None) -> None:
-    a = _Args(plan)
-    a.activation("x", x)
-    a.tensor("out_min", out_min, torch.float32, plan.num_groups)
-    a.tensor("out_max", out_max, torch.float32, plan.num_groups)
-    a.on_device()
+    if not (_is_activation(plan, x) and _fits(out_min, torch.float32, plan.num_groups)
+            and _fits(out_max, torch.float32, plan.num_groups)):
+        a = _Args(plan)
+        a.activation("x", x)
+        a.tensor("out_min", out_min, torch.float32, plan.num_groups)
+        a.tensor("out_max", out_max, torch.float32, plan.num_groups)
+        a.on_device()
     rc = load_library().daf_group_minmax(plan.handle, x.data_ptr(), _DTYPE_ID[x.dtype], out_min.data_ptr(),
                                          out_max.data_ptr(), _stream_handle(stream))
     if rc != 0:
@@ -521,18 +537,25 @@ def daf_select_bits_workspace(num_groups: int, device="cuda:0") -> torch.Tensor:
     return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
 
+@functools.lru_cache(maxsize=64)
+def _select_bits_need(num_groups: int) -> int:
+    return int(load_library().daf_select_bits_workspace_bytes(num_groups))
+
+
 def daf_select_bits(group_min: torch.Tensor, group_max: torch.Tensor, classes: Sequence[int], out_bits: torch.Tensor,
                     workspace: torch.Tensor, stream=None) -> None:
     G = group_min.numel() if isinstance(group_min, torch.Tensor) else 0
-    a = _Args()
-    a.tensor("group_min", group_min, torch.float32, max(G, 1))
-    a.tensor("group_max", group_max, torch.float32, G, exact=True)
-    a.tensor("out_bits", out_bits, torch.uint8, G)
-    a.tensor("workspace", workspace, torch.uint8, int(load_library().daf_select_bits_workspace_bytes(G)))
-    a.on_device()
-    cl = (ctypes.c_uint8 * len(classes))(*[int(c) for c in classes])
-    rc = load_library().daf_select_bits(group_min.data_ptr(), group_max.data_ptr(), group_min.numel(),
-                                        ctypes.cast(cl, ctypes.c_void_p), len(classes), out_bits.data_ptr(),
+    need = _select_bits_need(G)
+    if not (_fits(group_min, torch.float32, 1) and _fits(group_max, torch.float32, G) and group_max.numel() == G
+            and _fits(out_bits, torch.uint8, G) and _fits(workspace, torch.uint8, need)):
+        a = _Args()
+        a.tensor("group_min", group_min, torch.float32, max(G, 1))
+        a.tensor("group_max", group_max, torch.float32, G, exact=True)
+        a.tensor("out_bits", out_bits, torch.uint8, G)
+        a.tensor("workspace", workspace, torch.uint8, need)
+        a.on_device()
+    cl = bytes([int(c) & 0xFF for c in classes])
+    rc = load_library().daf_select_bits(group_min.data_ptr(), group_max.data_ptr(), G, cl, len(cl), out_bits.data_ptr(),
                                         workspace.data_ptr(), _stream_handle(stream))
     if rc != 0:
         raise DafError(rc, "daf_select_bits")
@@ -543,20 +566,21 @@ def daf_select_bits_from_scale(group_scale: torch.Tensor, prev_bits, classes: Se
     """Widths for the next iteration from the scales (and widths: a uint8 tensor, or one int for
     all groups) of an earlier daf_quantize_pack: no pass over the activation."""
     G = group_scale.numel() if isinstance(group_scale, torch.Tensor) else 0
-    a = _Args()
-    a.tensor("group_scale", group_scale, torch.float32, max(G, 1))
-    uniform = 0
-    if isinstance(prev_bits, torch.Tensor):
-        a.tensor("prev_bits", prev_bits, torch.uint8, G, exact=True)
-    else:
-        uniform = int(prev_bits)
-    a.tensor("out_bits", out_bits, torch.uint8, G)
-    a.tensor("workspace", workspace, torch.uint8, int(load_library().daf_select_bits_workspace_bytes(G)))
-    a.on_device()
-    cl = (ctypes.c_uint8 * len(classes))(*[int(c) for c in classes])
+    need = _select_bits_need(G)
+    per_group = isinstance(prev_bits, torch.Tensor)
+    if not (_fits(group_scale, torch.float32, 1) and _fits(out_bits, torch.uint8, G) and _fits(workspace, torch.uint8, need)
+            and (not per_group or (_fits(prev_bits, torch.uint8, G) and prev_bits.numel() == G))):
+        a = _Args()
+        a.tensor("group_scale", group_scale, torch.float32, max(G, 1))
+        if per_group:
+            a.tensor("prev_bits", prev_bits, torch.uint8, G, exact=True)
+        a.tensor("out_bits", out_bits, torch.uint8, G)
+        a.tensor("workspace", workspace, torch.uint8, need)
+        a.on_device()
+    cl = bytes([int(c) & 0xFF for c in classes])
     rc = load_library().daf_select_bits_from_scale(
-        group_scale.data_ptr(), prev_bits.data_ptr() if isinstance(prev_bits, torch.Tensor) else None, uniform, G,
-        ctypes.cast(cl, ctypes.c_void_p), len(classes), out_bits.data_ptr(), workspace.data_ptr(), _stream_handle(stream))
+        group_scale.data_ptr(), prev_bits.data_ptr() if per_group else None, 0 if per_group else int(prev_bits), G,
+        cl, len(cl), out_bits.data_ptr(), workspace.data_ptr(), _stream_handle(stream))
     if rc != 0:
         raise DafError(rc, "daf_select_bits_from_scale")
 
@@ -589,16 +613,18 @@ def daf_linear_quantize_pack(plan: Plan, x: torch.Tensor, weight: torch.Tensor, 
     N = weight.shape[0]
     if M * N != plan.num_elements:
         raise ValueError(f"the plan describes {plan.num_elements} elements, y has {M * N}")
-    a = _Args(plan)
-    a.tensor("x", x, x.dtype, M * K, exact=True)
-    a.tensor("weight", weight, x.dtype, N * K, exact=True)
-    a.activation("out_y", out_y)
     product_only = out_words is None and out_min is None and out_scale is None
-    if not product_only:
-        a.packed(out_words, out_min, out_scale, "out_")
-    if out_y.dtype != x.dtype:
-        raise ValueError("out_y must have the dtype of x")
-    a.on_device()
+    if not (_fits(x, x.dtype, 0) and _fits(weight, x.dtype, 0) and _is_activation(plan, out_y) and out_y.dtype is x.dtype
+            and (product_only or _is_packed(plan, out_words, out_min, out_scale))):
+        a = _Args(plan)
+        a.tensor("x", x, x.dtype, M * K, exact=True)
+        a.tensor("weight", weight, x.dtype, N * K, exact=True)
+        a.activation("out_y", out_y)
+        if not product_only:
+            a.packed(out_words, out_min, out_scale, "out_")
+        if out_y.dtype != x.dtype:
+            raise ValueError("out_y must have the dtype of x")
+        a.on_device()
     ptr = (lambda t: None) if product_only else (lambda t: t.data_ptr())
     rc = load_library().daf_linear_quantize_pack(plan.handle, x.data_ptr(), weight.data_ptr(), N, K, _DTYPE_ID[x.dtype],
                                                  seed, out_y.data_ptr(), ptr(out_words), ptr(out_min),
@@ -609,11 +635,13 @@ def daf_linear_quantize_pack(plan: Plan, x: torch.Tensor, weight: torch.Tensor, 
 
 def daf_quantize_pack_metrics(plan: Plan, x: torch.Tensor, seed: int, out_words: torch.Tensor, out_min: torch.Tensor,
                               out_scale: torch.Tensor, out_metrics: torch.Tensor, stream=None) -> None:
-    a = _Args(plan)
-    a.activation("x", x)
-    a.packed(out_words, out_min, out_scale, "out_")
-    a.tensor("out_metrics", out_metrics, torch.float32, 3 * plan.num_groups)
-    a.on_device()
+    if not (_is_activation(plan, x) and _is_packed(plan, out_words, out_min, out_scale)
+            and _fits(out_metrics, torch.float32, 3 * plan.num_groups)):
+        a = _Args(plan)
+        a.activation("x", x)
+        a.packed(out_words, out_min, out_scale, "out_")
+        a.tensor("out_metrics", out_metrics, torch.float32, 3 * plan.num_groups)
+        a.on_device()
     rc = load_library().daf_quantize_pack_metrics(plan.handle, x.data_ptr(), _DTYPE_ID[x.dtype], seed,
                                                   out_words.data_ptr(), out_min.data_ptr(), out_scale.data_ptr(),
                                                   out_metrics.data_ptr(), _stream_handle(stream))
