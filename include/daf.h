@@ -431,10 +431,14 @@ int daf_linear_quantize_pack(const daf_plan_t* plan, const void* x, const void* 
  * the kernel uses, so that tests without a GPU can check that it visits every tile once.
  * Returns DAF_EINVAL for an id outside [0, tiles_m * tiles_n) or a null pointer. */
 int daf_linear_tile_of_workgroup(int32_t id, int32_t tiles_m, int32_t tiles_n, int32_t* tile_m, int32_t* tile_n);
-/* The same for the smaller tiles that outputs of few 256 x 256 tiles are cut into, and into how many each of those is cut
- * for a product of these sizes (1: not at all; 2, 4, 8 or 16).  Host computations, for tuning and tests. */
-int daf_linear_few_tile_of_workgroup(int32_t id, int32_t tiles_m, int32_t tiles_n, int32_t* tile_m, int32_t* tile_n);
-int daf_linear_tiles_per_256(int64_t M, int64_t N, int64_t K);
+/* How an M x N output of a daf_linear_quantize_pack call is tiled: `*whole` 256 x 256 tiles of the sequence that
+ * daf_linear_tile_of_workgroup walks are taken as they are, the others are cut into the returned number (2, 4, 8, 16; 1: there
+ * are none) of smaller ones; and the map of those, the host copy of the kernel's own: workgroup `id` takes the tile of
+ * 256 / sub_m rows and 256 / sub_n columns with these indices, the tiles from position `first` on being cut.
+ * Host computations, for tuning and tests. */
+int daf_linear_tiling(int64_t M, int64_t N, int64_t K, int64_t* whole);
+int daf_linear_few_tile_of_workgroup(int32_t id, int32_t tiles_m, int32_t tiles_n, int32_t first, int32_t sub_m, int32_t sub_n,
+                                     int32_t* tile_m, int32_t* tile_n);
 
 /* ---- consumer fusion for an element-wise consumer -------------------------------------------
  *

@@ -80,10 +80,10 @@ def load_library():
     L.daf_linear_quantize_pack.restype = c.c_int
     L.daf_linear_tile_of_workgroup.argtypes = [i32, i32, i32, vp, vp]
     L.daf_linear_tile_of_workgroup.restype = c.c_int
-    L.daf_linear_few_tile_of_workgroup.argtypes = [i32, i32, i32, vp, vp]
+    L.daf_linear_few_tile_of_workgroup.argtypes = [i32, i32, i32, i32, i32, i32, vp, vp]
     L.daf_linear_few_tile_of_workgroup.restype = c.c_int
-    L.daf_linear_tiles_per_256.argtypes = [i64, i64, i64]
-    L.daf_linear_tiles_per_256.restype = c.c_int
+    L.daf_linear_tiling.argtypes = [i64, i64, i64, vp]
+    L.daf_linear_tiling.restype = c.c_int
     L.daf_unpack_relu_backward.argtypes = [vp, vp, vp, vp, vp, vp, vp, c.c_int, vp]
     L.daf_unpack_relu_backward.restype = c.c_int
     L.daf_unpack_matmul_schedule.argtypes = [vp, i64, i64, c.c_int, vp]

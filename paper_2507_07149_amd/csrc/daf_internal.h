@@ -87,8 +87,8 @@ int64_t daf_select_bits_workspace_size(int64_t num_groups);
 bool daf_linear_quantize_supported(const daf_plan_t* plan, int64_t N, int64_t K, int dtype);
 // The output tile (256 x 256) that workgroup `id` of the launch computes; a host copy of the kernel's own map.
 void daf_linear_tile_map(int id, int tiles_m, int tiles_n, int* tm, int* tn);
-void daf_linear_few_tile_map(int id, int tiles_m, int tiles_n, int* tm, int* tn);
-int daf_linear_cut_of(int64_t M, int64_t N, int64_t K);
+void daf_linear_few_tile_map(int id, int tiles_m, int tiles_n, int first, int sub_m, int sub_n, int* tm, int* tn);
+int daf_linear_cut_of(int64_t M, int64_t N, int64_t K, int64_t* whole);
 hipError_t daf_launch_linear_quantize_pack(const daf_plan_t* plan, const void* x, const void* w, int64_t N, int64_t K,
                                            int dtype, uint64_t seed, void* y, uint32_t* words, float* mn, float* sc,
                                            hipStream_t stream);

@@ -9,6 +9,7 @@
 //     whole cache lines, counted waits), and a step's operands are read into registers one step ahead, which frees
 //     a stage as soon as it has been read and leaves the matrix instructions nothing to wait for;
 //   - the workgroups of a die get consecutive tiles of panels of four tile rows, so that they share operand rows in its cache.
+// Large products take these tiles for what whole rounds of 256 workgroups leave over.
 #pragma once
 #include "linear_common.h"
 
@@ -33,14 +34,18 @@ using FewBy8 = FewTiles<64, 128, 2, 2, 6>;
 template <int GS_LOG2>
 using FewBy16 = typename std::conditional<GS_LOG2 == 7, FewTiles<32, 128, 1, 4, 6>, FewTiles<64, 64, 2, 2, 8>>::type;
 
-// blockIdx -> tile: every die (blockIdx mod 8) takes a run of consecutive positions, position -> tile as in
-// tile_of_workgroup.  A bijection.
-__host__ __device__ inline TileIndex few_tile_of_workgroup(int id, int tiles_m, int tiles_n) {
+// blockIdx -> tile.  The 256 x 256 tiles from position `first` of the sequence (tile_of_position) to its end, each cut
+// into sub_m x sub_n; every die (blockIdx mod 8) takes a run of consecutive ones.  Visits every tile once.
+__host__ __device__ inline TileIndex few_tile_of_workgroup(int id, int tiles_m, int tiles_n, int first, int sub_m, int sub_n) {
   constexpr int kDies = 8, kPanel = 4;
-  const int total = tiles_m * tiles_n, each = total / kDies, more = total % kDies;
+  const int subs = sub_m * sub_n, total = (tiles_m * tiles_n - first) * subs, each = total / kDies, more = total % kDies;
   const int die = id % kDies;
   const int pos = die * each + (die < more ? die : more) + id / kDies;
-  return tile_of_position(pos, tiles_m, tiles_n, kPanel);
+  const int sub = pos % subs;
+  TileIndex t = tile_of_position(first + pos / subs, tiles_m, tiles_n, kPanel);
+  t.m = t.m * sub_m + sub % sub_m;
+  t.n = t.n * sub_n + sub / sub_m;
+  return t;
 }
 
 template <int N>
@@ -52,7 +57,7 @@ template <int DT, int GS_LOG2, bool MIXED, bool QUANT, class S>
 __global__ __launch_bounds__(S::kThreads, 1) void k_linear_few_tiles(
     const char* __restrict__ x, const char* __restrict__ w, int M, int N, int K, uint32_t seed_lo, uint32_t seed_hi,
     uint32_t uniform_b, const uint8_t* __restrict__ bits, const uint32_t* __restrict__ off, char* __restrict__ y,
-    uint32_t* __restrict__ words, float* __restrict__ out_min, float* __restrict__ out_scale) {
+    uint32_t* __restrict__ words, float* __restrict__ out_min, float* __restrict__ out_scale, int first) {
   constexpr int kMB = S::kMB, kNB = S::kNB, kStages = S::kStages;
   __shared__ __align__(1024) char lds[kStages * S::kStageBytes];
   const int t = threadIdx.x, lane = t & (kWave - 1);
@@ -60,7 +65,7 @@ __global__ __launch_bounds__(S::kThreads, 1) void k_linear_few_tiles(
   const int wm = uw % S::kWavesM, wn = uw / S::kWavesM;
   const int li = lane & 31, lg = lane >> 5;
 
-  const TileIndex ti = few_tile_of_workgroup((int)blockIdx.x, M / S::kBM, N / S::kBN);
+  const TileIndex ti = few_tile_of_workgroup((int)blockIdx.x, M / 256, N / 256, first, 256 / S::kBM, 256 / S::kBN);
   const int64_t m0 = (int64_t)ti.m * S::kBM, n0 = (int64_t)ti.n * S::kBN;
   const int steps = K / 64;
   const int64_t row_bytes = (int64_t)K * 2;

@@ -242,7 +242,8 @@ __global__ __launch_bounds__(kLinThreads, 2) void k_linear_quantize_pack(
   }
 }
 
-// Into how many tiles each 256 x 256 of the output is cut: 1 (k_linear_quantize_pack) or 2, 4, 8, 16 (k_linear_few_tiles).
+// How an output is tiled: the first `whole` 256 x 256 tiles of the sequence as they are, whole rounds of 256 workgroups
+// (k_linear_quantize_pack), the rest cut into `cut` each (1: not cut, in the same launch; 2, 4, 8, 16: k_linear_few_tiles).
 // The estimate: a round of 256 workgroups takes `fixed` (first operands, epilogue, last waves) and `step` per 64 values of k, each
 // between its value for a lone workgroup and for a full chip (shared cache and memory, clock).  Microseconds, fitted to
 // 23 shapes of 1 to 768 tiles of 256 x 256 and K = 256, 1024, 4096, all five forms measured on each; the form picked was
@@ -255,30 +256,40 @@ __global__ __launch_bounds__(kLinThreads, 2) void k_linear_quantize_pack(
 //     128, 4096           74.2   61.5   70.8   91.2  132.8
 //     192, 1024           34.3   43.7   43.8   52.3   66.4
 //     300, 4096          179.4  168.2  179.0  225.3  327.2
-int linear_cut(int64_t M, int64_t N, int64_t K) {
-#ifdef DAF_FORCE_TILES
-  return DAF_FORCE_TILES;
-#endif
+struct LinearTiling {
+  int64_t whole;
+  int cut;
+};
+LinearTiling linear_tiling(int64_t M, int64_t N, int64_t K) {
   static constexpr struct {
     int cut;
     float fixed_lone, fixed_full, step_lone, step_full;
   } kForms[] = {{1, 7.9f, 12.6f, 0.82f, 1.38f}, {2, 6.3f, 9.2f, 0.41f, 0.78f}, {4, 1.9f, 4.9f, 0.26f, 0.48f},
                 {8, 0.0f, 3.3f, 0.21f, 0.29f},  {16, 2.5f, 2.4f, 0.11f, 0.19f}};
-  const int64_t whole = (M / kBM) * (N / kBN);
   const float steps = (float)(K / kBK);
-  int best = 1;
-  float best_time = 0.0f;
-  for (const auto& f : kForms) {
-    const int64_t rounds = whole * f.cut / 256, rest = whole * f.cut % 256;
+  auto estimate = [&](int form, int64_t tiles) {
+    const auto& f = kForms[form];
+    const int64_t rounds = tiles * f.cut / 256, rest = tiles * f.cut % 256;
     const float busy = (float)rest / 256.0f;
     float time = (float)rounds * (f.fixed_full + steps * f.step_full);
-    if (rest > 0) time += f.fixed_lone + busy * (f.fixed_full - f.fixed_lone) + steps * (f.step_lone + busy * (f.step_full - f.step_lone));
-    if (f.cut == 1) time *= 0.97f;                 // at equal estimates the form that moves the fewest bytes
-    if (f.cut == 1 || time < best_time) {
-      best = f.cut;
-      best_time = time;
+    if (rest > 0)
+      time += f.fixed_lone + busy * (f.fixed_full - f.fixed_lone) + steps * (f.step_lone + busy * (f.step_full - f.step_lone));
+    return time;
+  };
+  constexpr float kSecondLaunch = 4.0f;            // the gap between the two; with the rest cut, bfloat16, groups of 64, before and now:
+                                                   // 272 tiles, K 1024 65.7 / 49.2 us, 300, 4096 189 / 156, 576, 1024 117 / 107, 1056, 2048 306 / 286
+  const int64_t tiles = (M / kBM) * (N / kBN), rounds = tiles / 256 * 256;
+  LinearTiling best = {tiles, 1};
+  float best_time = estimate(0, rounds) + 0.97f * estimate(0, tiles - rounds);   // at equal estimates the form that moves the fewest bytes
+  for (int form = 1; form < 5; ++form)
+    for (const int64_t whole : {(int64_t)0, rounds}) {
+      if (whole == tiles || (whole == 0 && rounds > 256)) continue;
+      const float time = estimate(0, whole) + estimate(form, tiles - whole) + (whole > 0 ? kSecondLaunch : 0.0f);
+      if (time < best_time) {
+        best = {whole, kForms[form].cut};
+        best_time = time;
+      }
     }
-  }
   return best;
 }
 
@@ -288,26 +299,36 @@ hipError_t launch_gs(const daf_plan_t* p, const void* x, const void* w, int M, i
   const uint32_t lo = (uint32_t)seed, hi = (uint32_t)(seed >> 32);
   const bool quant = words != nullptr, mixed = quant && !p->uniform_bits;
   const uint32_t uniform = mixed ? 0u : quant ? (uint32_t)p->uniform_bits : 8u;
-  auto launch = [&](auto kernel, int bm, int bn, int threads) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((M / bm) * (N / bn))), dim3(threads), 0, stream, (const char*)x,
-                       (const char*)w, M, N, K, lo, hi, uniform, mixed ? p->d_bits : nullptr, mixed ? p->d_off : nullptr,
-                       (char*)y, words, mn, sc);
-    return hipGetLastError();
-  };
-  const int cut = linear_cut(M, N, K);
-  if (cut == 1)
-    return launch(!quant  ? k_linear_quantize_pack<DT, GS_LOG2, false, false>
+  const uint8_t* bits = mixed ? p->d_bits : nullptr;
+  const uint32_t* off = mixed ? p->d_off : nullptr;
+  const LinearTiling tiling = linear_tiling(M, N, K);
+  const int64_t tiles = (int64_t)(M / kBM) * (N / kBN);
+  if (tiling.whole > 0) {
+    auto kernel = !quant  ? k_linear_quantize_pack<DT, GS_LOG2, false, false>
                   : mixed ? k_linear_quantize_pack<DT, GS_LOG2, true, true>
-                          : k_linear_quantize_pack<DT, GS_LOG2, false, true>,
-                  kBM, kBN, kLinThreads);
+                          : k_linear_quantize_pack<DT, GS_LOG2, false, true>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)tiling.whole), dim3(kLinThreads), 0, stream, (const char*)x, (const char*)w, M,
+                       N, K, lo, hi, uniform, bits, off, (char*)y, words, mn, sc);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || tiling.whole == tiles) return e;
+  }
   auto few = [&](auto shape) {
     using S = decltype(shape);
-    return launch(!quant  ? k_linear_few_tiles<DT, GS_LOG2, false, false, S>
+    auto kernel = !quant  ? k_linear_few_tiles<DT, GS_LOG2, false, false, S>
                   : mixed ? k_linear_few_tiles<DT, GS_LOG2, true, true, S>
-                          : k_linear_few_tiles<DT, GS_LOG2, false, true, S>,
-                  S::kBM, S::kBN, S::kThreads);
+                          : k_linear_few_tiles<DT, GS_LOG2, false, true, S>;
+    const unsigned blocks = (unsigned)((tiles - tiling.whole) * (256 / S::kBM) * (256 / S::kBN));
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(S::kThreads), 0, stream, (const char*)x, (const char*)w, M, N, K, lo, hi,
+                       uniform, bits, off, (char*)y, words, mn, sc, (int)tiling.whole);
+    return hipGetLastError();
   };
-  return cut == 2 ? few(FewBy2{}) : cut == 4 ? few(FewBy4{}) : cut == 8 ? few(FewBy8{}) : few(FewBy16<GS_LOG2>{});
+  switch (tiling.cut) {
+    case 2: return few(FewBy2{});
+    case 4: return few(FewBy4{});
+    case 8: return few(FewBy8{});
+    case 16: return few(FewBy16<GS_LOG2>{});
+    default: return hipErrorInvalidValue;
+  }
 }
 
 template <int DT>
@@ -322,10 +343,14 @@ hipError_t launch_dt(const daf_plan_t* p, const void* x, const void* w, int M, i
 
 }  // namespace
 
-int daf_linear_cut_of(int64_t M, int64_t N, int64_t K) { return linear_cut(M, N, K); }
+int daf_linear_cut_of(int64_t M, int64_t N, int64_t K, int64_t* whole) {
+  const LinearTiling t = linear_tiling(M, N, K);
+  *whole = t.whole;
+  return t.cut;
+}
 
-void daf_linear_few_tile_map(int id, int tiles_m, int tiles_n, int* tm, int* tn) {
-  const TileIndex t = few_tile_of_workgroup(id, tiles_m, tiles_n);
+void daf_linear_few_tile_map(int id, int tiles_m, int tiles_n, int first, int sub_m, int sub_n, int* tm, int* tn) {
+  const TileIndex t = few_tile_of_workgroup(id, tiles_m, tiles_n, first, sub_m, sub_n);
   *tm = t.m;
   *tn = t.n;
 }

@@ -127,24 +127,33 @@ def test_current_stream_without_the_private_functions(monkeypatch, missing):
 
 
 def test_linear_few_tile_map_visits_every_tile_once():
-    """The same for the smaller tiles; the tiles of one die are a compact patch, and the cut is one that exists."""
+    """The same for the smaller tiles: with the 256 x 256 tiles before `first` they cover the output, each once; the tiles
+    of one die are a compact patch; and the tiling of a product is whole rounds of 256 and a cut that exists."""
     import ctypes
     from paper_2507_07149_amd.binding import load_library
     L = load_library()
     tm, tn = ctypes.c_int32(), ctypes.c_int32()
-    for tiles_m, tiles_n in ((1, 1), (1, 2), (2, 3), (4, 8), (8, 16), (16, 16), (7, 5), (3, 100), (64, 2), (10, 21)):
+    where = (ctypes.byref(tm), ctypes.byref(tn))
+    for tiles_m, tiles_n, first, sub_m, sub_n in ((1, 1, 0, 2, 1), (1, 2, 0, 4, 4), (2, 3, 0, 8, 2), (8, 8, 0, 2, 2), (7, 5, 0, 4, 2),
+                                                  (3, 100, 256, 2, 1), (9, 64, 512, 2, 2), (20, 15, 256, 4, 2), (64, 2, 0, 2, 1)):
         seen, dies = set(), {}
-        for i in range(tiles_m * tiles_n):
-            assert L.daf_linear_few_tile_of_workgroup(i, tiles_m, tiles_n, ctypes.byref(tm), ctypes.byref(tn)) == 0
-            assert 0 <= tm.value < tiles_m and 0 <= tn.value < tiles_n
+        count = (tiles_m * tiles_n - first) * sub_m * sub_n
+        for i in range(count):
+            assert L.daf_linear_few_tile_of_workgroup(i, tiles_m, tiles_n, first, sub_m, sub_n, *where) == 0
+            assert 0 <= tm.value < tiles_m * sub_m and 0 <= tn.value < tiles_n * sub_n
             seen.add((tm.value, tn.value))
             dies.setdefault(i % 8, []).append((tm.value, tn.value))
-        assert len(seen) == tiles_m * tiles_n, (tiles_m, tiles_n)
-        assert L.daf_linear_few_tile_of_workgroup(tiles_m * tiles_n, tiles_m, tiles_n, ctypes.byref(tm), ctypes.byref(tn)) != 0
-        if (tiles_m, tiles_n) == (16, 16):
+        assert len(seen) == count
+        assert L.daf_linear_few_tile_of_workgroup(count, tiles_m, tiles_n, first, sub_m, sub_n, *where) != 0
+        for i in range(first):
+            assert L.daf_linear_tile_of_workgroup(i, tiles_m, tiles_n, *where) == 0
+            assert (tm.value * sub_m, tn.value * sub_n) not in seen
+        if (tiles_m, tiles_n) == (8, 8):
             for tiles in dies.values():
-                assert len({m for m, _ in tiles}) <= 4 and len({n for _, n in tiles}) <= 9
-    for M, N, K in ((256, 256, 64), (256, 256, 1 << 20), (4096, 2048, 1024), (32768, 11008, 4096), (1 << 20, 1 << 12, 64)):
-        assert L.daf_linear_tiles_per_256(M, N, K) in (1, 2, 4, 8, 16)
-    assert L.daf_linear_tiles_per_256(32768, 11008, 4096) == 1
-    assert L.daf_linear_tiles_per_256(100, 256, 64) < 0
+                assert len({m for m, _ in tiles}) <= 8 and len({n for _, n in tiles}) <= 6
+    whole = ctypes.c_int64()
+    for M, N, K in ((256, 256, 64), (256, 256, 1 << 20), (4096, 2048, 1024), (5120, 3840, 1024), (32768, 11008, 4096), (1 << 20, 1 << 12, 64)):
+        cut, tiles = L.daf_linear_tiling(M, N, K, ctypes.byref(whole)), M * N // 65536
+        assert cut in (1, 2, 4, 8, 16) and 0 <= whole.value <= tiles
+        assert (cut == 1) == (whole.value == tiles) and (whole.value == tiles or whole.value % 256 == 0)
+    assert L.daf_linear_tiling(100, 256, 64, ctypes.byref(whole)) < 0

@@ -9,6 +9,8 @@ operands the order of the additions shows in the last place of y, so y is compar
 tolerance derived from the accumulation, and the packed output is checked through properties
 that hold for any y: min and scale are Eq. 1 of the y the kernel wrote, and the codes are within
 one step of it."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -168,12 +170,14 @@ def test_linear_quantize_pack_argument_errors(env):
     torch.cuda.synchronize()
 
 
-# M, N, steps of 64 and the tiles that each 256 x 256 of such an output is cut into
+# M, N, steps of 64 and the tiles that each 256 x 256 of such an output, or of what is left of it after one round of 256
+# whole ones, is cut into
 _FORMS = [(1024, 1024, steps, 16) for steps in (16, 17, 18, 19, 22, 23)]
 _FORMS += [(512, 512, steps, 8) for steps in range(1, 10)]
 _FORMS += [(2048, 2048, steps, 4) for steps in (1, 2, 3, 4, 5, 6, 7)]
 _FORMS += [(4096, 2048, steps, 2) for steps in (1, 2, 3, 4, 5, 6)]
 _FORMS += [(4096, 4096, steps, 1) for steps in (1, 2, 3, 4, 5, 6, 7)]
+_FORMS += [(4352, 4096, 5, 8), (5120, 3840, 3, 4), (6144, 4096, 16, 2)]
 
 
 @pytest.mark.parametrize("M,N,steps,cut", _FORMS)
@@ -184,7 +188,9 @@ def test_linear_quantize_pack_every_tile_form(env, M, N, steps, cut, gs):
     statistics lie in one wave, or in two or four); operands whose products are exact in any order."""
     daf, orc = env
     K = 64 * steps
-    assert daf.load_library().daf_linear_tiles_per_256(M, N, K) == cut
+    whole = ctypes.c_int64()
+    assert daf.load_library().daf_linear_tiling(M, N, K, ctypes.byref(whole)) == cut
+    assert whole.value == (0 if M * N < 256 * 65536 else 256)
     dtype = F16 if steps % 2 else BF16
     rng = np.random.default_rng(M + N + steps + gs)
     x, w = _integer_operands(rng, M, N, K, dtype)
