@@ -147,8 +147,8 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack_group(
                                                     words, out_min, out_scale, out_metrics, out_y, wave, n_waves);
 }
 
-// The leftovers of several tensors in one launch (list calls): one workgroup per entry takes the
-// entry's groups g_begin .. g_end - 1, its four waves a group each or (COOP) all four together.
+// The short last groups of several tensors with long groups in one launch (list calls): a workgroup per entry takes the
+// entry's groups g_begin .. g_end - 1, its four waves all four together.
 struct GroupBatchEntry {
   const void* x;
   const uint8_t* bits;
@@ -165,13 +165,12 @@ struct GroupBatch {
   int32_t n;
 };
 
-template <int DT, bool COOP>
+template <int DT>
 __global__ __launch_bounds__(kThreads) void k_quantize_pack_group_batch(const GroupBatch batch) {
   const GroupBatchEntry& e = batch.e[blockIdx.x];
-  quantize_pack_group_body<DT, false, false, COOP>(e.x, e.n, e.gs, e.g_begin, e.g_end, e.bits, e.off, e.uniform_bits,
-                                                   e.seed_lo, e.seed_hi, e.words, e.mn, e.sc, nullptr, nullptr,
-                                                   COOP ? (int64_t)0 : (int64_t)(threadIdx.x >> 6),
-                                                   COOP ? (int64_t)1 : (int64_t)kWavesPerBlock);
+  quantize_pack_group_body<DT, false, false, true>(e.x, e.n, e.gs, e.g_begin, e.g_end, e.bits, e.off, e.uniform_bits,
+                                                   e.seed_lo, e.seed_hi, e.words, e.mn, e.sc, nullptr, nullptr, (int64_t)0,
+                                                   (int64_t)1);
 }
 
 }  // namespace

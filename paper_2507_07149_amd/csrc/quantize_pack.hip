@@ -404,27 +404,21 @@ hipError_t launch_items(const daf_quantize_item_t* items, int32_t n_items, hipSt
     if (batch.n > 0 && err == hipSuccess) err = launch_batch<DT>(batch, cur_log2, cur_bits, stream);
     batch.clear();
   };
-  GroupBatch gbatch[2];                // leftovers: [0] a wave per group, [1] a workgroup per group
-  gbatch[0].n = gbatch[1].n = 0;
-  auto gflush = [&](int coop) {
-    GroupBatch& gb = gbatch[coop];
-    if (gb.n > 0 && err == hipSuccess) {
-      if (coop)
-        hipLaunchKernelGGL((k_quantize_pack_group_batch<DT, true>), dim3((unsigned)gb.n), dim3(kThreads), 0, stream, gb);
-      else
-        hipLaunchKernelGGL((k_quantize_pack_group_batch<DT, false>), dim3((unsigned)gb.n), dim3(kThreads), 0, stream, gb);
+  GroupBatch gbatch;                   // short last groups of items with long groups, a workgroup each
+  gbatch.n = 0;
+  auto gflush = [&]() {
+    if (gbatch.n > 0 && err == hipSuccess) {
+      hipLaunchKernelGGL((k_quantize_pack_group_batch<DT>), dim3((unsigned)gbatch.n), dim3(kThreads), 0, stream, gbatch);
       err = hipGetLastError();
     }
-    gb.n = 0;
+    gbatch.n = 0;
   };
   // the short last group of an item with long groups: the groups [g_begin, num_groups), group by group
   auto leftovers = [&](const daf_quantize_item_t& it, int64_t g_begin) {
     const daf_plan_t* p = it.plan;
     if (g_begin >= p->num_groups || err != hipSuccess) return;
-    const int coop = p->group_size >= 1024 ? 1 : 0;
-    GroupBatch& gb = gbatch[coop];
-    if (gb.n == 32) gflush(coop);
-    GroupBatchEntry& e = gb.e[gb.n++];
+    if (gbatch.n == 32) gflush();
+    GroupBatchEntry& e = gbatch.e[gbatch.n++];
     e.x = it.x;
     e.bits = p->d_bits;
     e.off = p->d_off;
@@ -571,8 +565,7 @@ hipError_t launch_items(const daf_quantize_item_t* items, int32_t n_items, hipSt
   flush();
   uflush();
   lflush();
-  gflush(0);
-  gflush(1);
+  gflush();
   return err;
 }
 
