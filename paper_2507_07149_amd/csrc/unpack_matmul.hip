@@ -260,7 +260,8 @@ __global__ __launch_bounds__((TileB<BK, (DT == kF32 ? 4 : 2)>::kThreads), (BK > 
   // threads that need them through the ring: four small loads per thread and step of its own
   // would keep the memory pipeline busier than the tiles of grad_y do.
   const uint32_t g_first = (uint32_t)k0 / (uint32_t)gs;
-  const uint32_t n_groups = (min((uint32_t)k0 + (uint32_t)BK, (uint32_t)K) - 1u) / (uint32_t)gs - g_first + 1u;   // <= kGroupsPerRow
+  const uint32_t k_end = BK > 64 ? min((uint32_t)k0 + (uint32_t)BK, (uint32_t)K) : (uint32_t)k0 + (uint32_t)BK;
+  const uint32_t n_groups = (k_end - 1u) / (uint32_t)gs - g_first + 1u;   // <= kGroupsPerRow
   const bool meta_wave = t < (uint32_t)TB::kMetaEntries;
   const uint32_t m_row = t / (uint32_t)TB::kGroupsPerRow, m_j = t % (uint32_t)TB::kGroupsPerRow;
   const bool meta_lane = meta_wave && m_j < n_groups;
@@ -546,7 +547,8 @@ __global__ __launch_bounds__(256) void k_sum_slices(float4* __restrict__ partial
   uint32_t tn, tk;
   tile_of_position(tile, tiles_n, (uint32_t)tiles_k, tn, tk);
   const uint32_t row = e / (uint32_t)bk4, col4 = e - row * (uint32_t)bk4;
-  if ((int64_t)tn * bn + row >= N || (int64_t)tk * (bk4 * 4) + 4 * col4 >= K) return;   // past the output in a last tile
+  // past the output in a last tile (N, K below 2^24)
+  if (tn * (uint32_t)bn + row >= (uint32_t)N || 4u * (tk * (uint32_t)bk4 + col4) >= (uint32_t)K) return;
   const int32_t first = (int32_t)blockIdx.y * n * stride;
   float4* p0 = partial + ((int64_t)first * count + ti) * tile4 + e;
   float4 s = *p0;
