@@ -101,6 +101,19 @@ def test_grad_weight_tall_and_skinny(env):
     _case(daf, orc, 8192, 256, 128, 64, 2, F32, 23)
 
 
+# The sum over the slices starts the loads of up to eight slices at a time: every remainder, once and twice eight, and two
+# levels (more than 16 slices) whose last group is short or whole.  One tile that N ends inside of; bound as in _case.
+@pytest.mark.parametrize("slices", [*range(2, 18), 25, 33, 40])
+def test_grad_weight_every_number_of_slices(env, slices):
+    daf, orc = env
+    print("case slices", slices, flush=True)
+    M, N, K = 128 * slices, 192, 64
+    plan = daf.daf_plan((M, K), 32, 4)
+    assert daf.daf_unpack_matmul_schedule(plan, N, K, torch.float32)["slices"] == slices
+    plan.destroy()
+    _case(daf, orc, M, N, K, 32, 4, F32, slices)
+
+
 def test_grad_weight_without_split_needs_no_workspace(env):
     daf, orc = env
     print("case no split", flush=True)
