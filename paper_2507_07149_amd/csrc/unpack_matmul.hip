@@ -661,10 +661,7 @@ Schedule schedule(int64_t M, int64_t N, int64_t K, int es) {   // es: bytes per 
   Schedule general = general_tile(bk);
   // K an odd multiple of 64, 16-bit formats: wider tiles too, the last of which lie half outside the output, where the
   // estimates have them ahead (general 256 x 64 and 512 x 128: 8064 x 3392 x 5056 500 / 287 us, 4480 x 1152 x 2624 75.7 / 53.6,
-  // 3936 x 2112 x 704 42.8 / 34.1).  Not where the tiles of 256 x 64 fill their rounds almost exactly: the one form that
-  // still takes whole rounds and slices of such tiles (4096 x 4096 x 3136: 161 / 104).
-  const int64_t over = bk == 64 ? general.tiles % 768 : 0;
-  if (bk == 64 && general.tiles >= 768 && over > 0 && over <= 768 / 32) return general;
+  // 3936 x 2112 x 704 42.8 / 34.1, 4096 x 4096 x 3136 161 / 104, 32768 x 4096 x 3136 1601 / 839).
   if (bk == 64 && es == 2) {
     const Schedule wider = general_tile(128);
     if (wider.seconds < general.seconds) general = wider;

@@ -151,6 +151,19 @@ def test_weight_gradient_tile(lib, m, n, k, dtype, tile):
     plan.destroy()
 
 
+@pytest.mark.parametrize("m,n,k", [(4096, 4096, 3136), (32768, 4096, 3136), (1024, 2048, 6208)])
+def test_weight_gradient_tile_of_an_odd_number_of_64_columns(lib, m, n, k):
+    """Outputs of a few 256 x 64 tiles more than whole rounds of 768: the 512 x 128 tile is faster there as well."""
+    import paper_2507_07149_amd as daf
+    import torch
+    assert 0 < (-(-n // 256) * (k // 64)) % 768 <= 24
+    plan = daf.daf_plan((m, k), 64, 4)
+    for dtype, tile in ((torch.float16, (512, 128)), (torch.bfloat16, (512, 128)), (torch.float32, (256, 64))):
+        s = daf.daf_unpack_matmul_schedule(plan, n, k, dtype)
+        assert (s["tile_n"], s["tile_k"]) == tile and s["tiles"] == -(-n // tile[0]) * -(-k // tile[1])
+    plan.destroy()
+
+
 # n, group size, width, element format, (relu backward, elements of the list) -> route; plans that need no device
 @pytest.mark.parametrize("n,gs,b,dtype,call,want", [
     (1 << 20, 64, 2, 0, (0, 0), 0), (1 << 20, 2048, 8, 0, (0, 0), 0), (1 << 20, 4096, 2, 1, (1, 0), 0),
