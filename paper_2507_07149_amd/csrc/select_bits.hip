@@ -516,7 +516,7 @@ __device__ __forceinline__ void small_pass(const uint32_t (&key)[kItems], int64_
 }
 
 template <bool FROM_SCALE>
-__global__ __launch_bounds__(kSmallThreads) void k_select_small(const float* __restrict__ gmin, const float* __restrict__ gmax,
+__global__ __launch_bounds__(kSmallThreads) void k_select_small(const float* gmin, const float* gmax,
                                                                 const uint8_t* prev_bits, uint32_t prev_uniform, int64_t G,
                                                                 Ranks ranks, int n_thresholds, uint32_t classes_packed,
                                                                 uint8_t* out_bits) {
@@ -525,7 +525,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_select_small(const float* __r
   __shared__ Decided shared;
   const int64_t base = (int64_t)threadIdx.x * kItems;
   uint32_t key[kItems];
-  // (out_bits may be prev_bits: all widths are read before the first barrier, and none is written before the last)
+  // (out_bits may lie over the inputs: all of them are read before the first barrier, and nothing is written before the last)
 #pragma unroll
   for (int i = 0; i < kItems; ++i) {
     const int64_t g = base + i;
@@ -685,7 +685,12 @@ hipError_t daf_launch_select_bits(const float* gmin, const float* gmax, const ui
   // thresholds skipped because R_k >= G sit at the end (R_k grows with k), so class = number of
   // satisfied thresholds still indexes `classes` correctly.
 
-  const bool apart = prev_bits == nullptr || out_bits + G <= prev_bits || prev_bits + G <= out_bits;
+  // The widths may replace an input, the earlier widths above all: then nothing may be written before all has been read.
+  auto clear_of = [&](const void* input, int64_t bytes) {
+    const uint8_t* p = static_cast<const uint8_t*>(input);
+    return p == nullptr || out_bits + G <= p || p + bytes <= out_bits;
+  };
+  const bool apart = clear_of(prev_bits, G) && clear_of(gmin, 4 * G) && clear_of(gmax, 4 * G);
   if (G <= kRankMost && apart) {
     const unsigned blocks = (unsigned)((G + kRankGroups - 1) / kRankGroups);
     const unsigned lds_bytes = (unsigned)(((G + 2 * kRankGroups - 1) / (2 * kRankGroups) * (2 * kRankGroups) + kRankThreads) * 4);
@@ -697,9 +702,9 @@ hipError_t daf_launch_select_bits(const float* gmin, const float* gmax, const ui
                          (uint32_t)prev_uniform, (int)G, ranks, n_thr, packed, out_bits);
     return hipGetLastError();
   }
-  // The widths are replaced in place, few groups: one launch of one workgroup, 14 to 20 us up to here against 27 for the six;
+  // The widths replace an input, few groups: one launch of one workgroup, 14 to 20 us up to here against 27 for the six;
   // two and four times as many keys per thread: 32 and 59 us against 27.
-  if (G <= kSmallGroups && gmax == nullptr) {
+  if (G <= kSmallGroups && prev_bits != nullptr) {
     hipLaunchKernelGGL(k_select_small<true>, dim3(1), dim3(kSmallThreads), 0, stream, gmin, nullptr, prev_bits,
                        (uint32_t)prev_uniform, G, ranks, n_thr, packed, out_bits);
     return hipGetLastError();

@@ -43,6 +43,30 @@ def test_select_bits(env, G, kind, classes):
     assert np.array_equal(bits.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("G", [33, 8192, 8193, 16384])
+@pytest.mark.parametrize("over", ["min", "max", "scale", "scale, one width"])
+def test_select_bits_over_an_input(env, G, over):
+    """The widths may be written over the statistics that they come from."""
+    daf, orc = env
+    rng = np.random.default_rng(G)
+    lo, span = rng.standard_normal(G).astype(np.float32), rng.random(G, dtype=np.float32)
+    prev = rng.choice([1, 2, 4, 8], G).astype(np.uint8) if over == "scale" else np.full(G, 2, np.uint8)
+    ws = daf.daf_select_bits_workspace(G)
+    print("case", G, over, flush=True)
+    if over in ("min", "max"):
+        hi = lo + span
+        a, b = torch.from_numpy(lo).cuda(), torch.from_numpy(hi).cuda()
+        out = (a if over == "min" else b).view(torch.uint8)[:G]
+        daf.daf_select_bits(a, b, (2, 4, 8), out, ws)
+        want = orc.select_bits(lo, hi, (2, 4, 8))
+    else:
+        a = torch.from_numpy(span).cuda()
+        out = a.view(torch.uint8)[3 * G:]
+        daf.daf_select_bits_from_scale(a, torch.from_numpy(prev).cuda() if over == "scale" else 2, (2, 4, 8), out, ws)
+        want = orc.select_bits(np.zeros(G, np.float32), span * ((1 << prev.astype(np.int64)) - 1).astype(np.float32), (2, 4, 8))
+    assert np.array_equal(out.cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("G", [2, 8, 8191, 8192, 8193, 16384, 16391, 65533, 65536, 65537, 200003])
 @pytest.mark.parametrize("skew", [0, 4, 1])
 @pytest.mark.parametrize("bad", [None, "first", "last"])
