@@ -14,8 +14,9 @@
 // whose key equals T_k.  Keys are the bit patterns of the ranges, which order like the ranges
 // because a range is never negative.
 //
-// Up to kRankMost groups: one launch in which the ranks are counted (k_select_rank); where the widths are replaced in place,
-// up to kSmallGroups, one workgroup that keeps the keys in registers (k_select_small).  More: six launches: zero the first counters; write the keys and count their first digit (and zero the
+// Up to kRankMost groups: one launch in which the ranks are counted (k_select_rank); where the widths of an earlier call are
+// replaced in place, up to kSmallGroups, one workgroup that keeps the keys in registers (k_select_small).  More, or widths
+// over the other inputs: six launches: zero the first counters; write the keys and count their first digit (and zero the
 // other counters); count the second digit; count the third; count the keys equal to T_k per block of 4096
 // groups; classify.  What a pass decides (the bin that holds the rank) is worked out from its counters by
 // every workgroup of the next launch for itself: a scan of 2048 counters from the cache, next to the
@@ -515,9 +516,9 @@ __device__ __forceinline__ void small_pass(const uint32_t (&key)[kItems], int64_
   }
 }
 
-template <bool FROM_SCALE>
-__global__ __launch_bounds__(kSmallThreads) void k_select_small(const float* gmin, const float* gmax,
-                                                                const uint8_t* prev_bits, uint32_t prev_uniform, int64_t G,
+// Only with the scales and widths of an earlier call; the new widths may lie over either: all are read before the first
+// barrier, and nothing is written before the last.
+__global__ __launch_bounds__(kSmallThreads) void k_select_small(const float* scale, const uint8_t* prev_bits, int64_t G,
                                                                 Ranks ranks, int n_thresholds, uint32_t classes_packed,
                                                                 uint8_t* out_bits) {
   __shared__ __attribute__((aligned(16))) uint32_t lh[kBins * kLdsCopies0];
@@ -525,19 +526,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_select_small(const float* gmi
   __shared__ Decided shared;
   const int64_t base = (int64_t)threadIdx.x * kItems;
   uint32_t key[kItems];
-  // (out_bits may lie over the inputs: all of them are read before the first barrier, and nothing is written before the last)
 #pragma unroll
   for (int i = 0; i < kItems; ++i) {
     const int64_t g = base + i;
-    key[i] = 0xFFFFFFFFu;
-    if (g < G) {
-      if (FROM_SCALE) {
-        const uint32_t b = prev_bits != nullptr ? (uint32_t)prev_bits[g] : prev_uniform;
-        key[i] = f2u(gmin[g] * (float)((1u << (b & 15u)) - 1u));
-      } else {
-        key[i] = f2u(gmax[g] - gmin[g]);
-      }
-    }
+    key[i] = g < G ? f2u(scale[g] * (float)((1u << (prev_bits[g] & 15u)) - 1u)) : 0xFFFFFFFFu;
   }
   Decided d;
 #pragma unroll
@@ -705,8 +697,8 @@ hipError_t daf_launch_select_bits(const float* gmin, const float* gmax, const ui
   // The widths replace an input, few groups: one launch of one workgroup, 14 to 20 us up to here against 27 for the six;
   // two and four times as many keys per thread: 32 and 59 us against 27.
   if (G <= kSmallGroups && prev_bits != nullptr) {
-    hipLaunchKernelGGL(k_select_small<true>, dim3(1), dim3(kSmallThreads), 0, stream, gmin, nullptr, prev_bits,
-                       (uint32_t)prev_uniform, G, ranks, n_thr, packed, out_bits);
+    hipLaunchKernelGGL(k_select_small, dim3(1), dim3(kSmallThreads), 0, stream, gmin, prev_bits, G, ranks, n_thr, packed,
+                       out_bits);
     return hipGetLastError();
   }
 
