@@ -374,6 +374,7 @@ int daf_linear_tile_of_workgroup(int32_t id, int32_t tiles_m, int32_t tiles_n, i
 int daf_linear_few_tile_of_workgroup(int32_t id, int32_t tiles_m, int32_t tiles_n, int32_t first, int32_t sub_m, int32_t sub_n,
                                      int32_t* tile_m, int32_t* tile_n) {
   if (tile_m == nullptr || tile_n == nullptr || tiles_m < 1 || tiles_n < 1 || sub_m < 1 || sub_n < 1 || first < 0 || id < 0 ||
+      (int64_t)tiles_m * tiles_n > 0x7fffffff || (int64_t)sub_m * sub_n > 0x7fffffff ||
       (int64_t)tiles_m * tiles_n * sub_m * sub_n > 0x7fffffff ||
       (int64_t)id >= ((int64_t)tiles_m * tiles_n - first) * sub_m * sub_n)
     return DAF_EINVAL;
@@ -385,7 +386,11 @@ int daf_linear_few_tile_of_workgroup(int32_t id, int32_t tiles_m, int32_t tiles_
 }
 
 int daf_linear_tiling(int64_t M, int64_t N, int64_t K, int64_t* whole) {
-  if (whole == nullptr || M < 256 || N < 256 || K < 64 || M % 256 != 0 || N % 256 != 0 || K % 64 != 0) return DAF_EINVAL;
+  // the shapes that daf_linear_quantize_pack takes
+  constexpr int64_t kMost = 1 << 24;
+  if (whole == nullptr || M < 256 || N < 256 || K < 64 || M % 256 != 0 || N % 256 != 0 || K % 64 != 0 || M > kMost ||
+      N > kMost || K > kMost || (M / 256) * (N / 256) >= (int64_t)1 << 31)
+    return DAF_EINVAL;
   return daf_linear_cut_of(M, N, K, whole);
 }
 

@@ -157,3 +157,20 @@ def test_linear_few_tile_map_visits_every_tile_once():
         assert cut in (1, 2, 4, 8, 16) and 0 <= whole.value <= tiles
         assert (cut == 1) == (whole.value == tiles) and (whole.value == tiles or whole.value % 256 == 0)
     assert L.daf_linear_tiling(100, 256, 64, ctypes.byref(whole)) < 0
+
+
+@pytest.mark.parametrize("M,N,K", [(1 << 62, 1 << 62, 64), (1 << 25, 256, 64), (256, 1 << 25, 64), (256, 256, 1 << 25),
+                                   (1 << 24, 1 << 24, 64)])
+def test_tiling_of_outputs_beyond_what_the_product_takes_is_refused(M, N, K):
+    import ctypes
+    whole = ctypes.c_int64(-7)
+    assert daf.load_library().daf_linear_tiling(M, N, K, ctypes.byref(whole)) == -1 and whole.value == -7
+
+
+def test_map_of_more_tiles_than_an_index_holds_is_refused():
+    """Also where the product of the counts leaves 64 bits (384773 * 49477 * 34724 * 27905 = 2^64 + 4)."""
+    import ctypes
+    where = [ctypes.byref(ctypes.c_int32(-7)) for _ in range(2)]
+    L = daf.load_library()
+    for counts in ((384773, 49477, 0, 34724, 27905), (1 << 30, 1 << 30, 0, 16, 16), (65536, 32768, 0, 1, 1)):
+        assert L.daf_linear_few_tile_of_workgroup(0, *counts, *where) == -1
