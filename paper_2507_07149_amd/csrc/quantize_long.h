@@ -123,9 +123,9 @@ __device__ __forceinline__ void quantize_pack_long_body(
       if constexpr (METRICS) {
         float err, mag, var;
         if (need_exact2)
-          quantize_raw_chunk<DT, true, true>(raw[u], s.mn, invs, b, rnd[u], n0, n1, 8, true, s.scale, &err, &mag, &var);
+          quantize_raw_chunk<DT, true, true>(raw[u], s.mn, invs, b, rnd[u], n0, n1, 8, s.scale, &err, &mag, &var);
         else
-          quantize_raw_chunk<DT, false, true>(raw[u], s.mn, invs, b, rnd[u], n0, n1, 8, true, s.scale, &err, &mag, &var);
+          quantize_raw_chunk<DT, false, true>(raw[u], s.mn, invs, b, rnd[u], n0, n1, 8, s.scale, &err, &mag, &var);
         m_err += err;
         m_mag += mag;
         m_var += var;

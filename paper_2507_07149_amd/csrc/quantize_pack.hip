@@ -100,42 +100,63 @@ __global__ __launch_bounds__(kThreads) void k_group_minmax_group(const void* __r
                               (int64_t)gridDim.x * kWavesPerBlock);
 }
 
+// The (min, max) of a group from the pairs of its segments, the last of them `last`.
+template <class S>
+__device__ __forceinline__ void store_group_minmax(const float2* stat, int group, int last, float* __restrict__ out_min,
+                                                   float* __restrict__ out_max) {
+  float2 st = stat[group * S::kLoadsPerGroup];
+#pragma unroll
+  for (int j = 1; j < S::kLoadsPerGroup; ++j) {
+    const float2 t = stat[min(group * S::kLoadsPerGroup + j, last)];
+    st.x = vmin(st.x, t.x);
+    st.y = vmax(st.y, t.y);
+  }
+  out_min[group] = st.x + 0.0f;
+  out_max[group] = st.y + 0.0f;
+}
+
+// The tile in which the tensor ends is dealt out to the waves of a workgroup of its own, the first of the grid: a quarter of
+// a tile's registers, so that it does not cost the whole tiles a wave, and it is done before they are (binary32, groups of
+// 256, 16777293 elements: 10.4 us as the grid's last wave, 7 waves per SIMD, 9.9 now with 8).
 template <int DT, int LPG_LOG2>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_group_minmax_tile(const u32x4* __restrict__ x, int64_t n_tiles,
+__global__ __launch_bounds__(kThreads) void k_group_minmax_tile(const u32x4* __restrict__ x, int64_t n_tiles,
                                                                 float* __restrict__ out_min,
                                                                 float* __restrict__ out_max, int short_len) {
   using S = TileShape<DT, LPG_LOG2>;
+  constexpr int kPartLog2 = S::kLaneLog2;                       // (the segments of a tile are those of its parts)
+  using P = TileShape<DT, kPartLog2, 4>;
+  constexpr int kParts = S::kElems / P::kElems;
+  static_assert(kParts <= kWavesPerBlock && kParts * P::kSegments == S::kSegments, "a wave per part");
   __shared__ float2 stat_all[kWavesPerBlock][kWave];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t tile = (int64_t)blockIdx.x * kWavesPerBlock + wave_in_block;
-  int groups = S::kGroups;
+  const unsigned first_block = short_len > 0 ? 1u : 0u;
+  if (blockIdx.x < first_block) {
+    const int len = short_len - wave_in_block * P::kElems;
+    if (wave_in_block < kParts && len > 0) {
+      uint4 raw[P::kLoads];
+      short_tile_load<DT>(&x[(n_tiles * kParts + wave_in_block) * (P::kLoads * kWave)], min(len, (int)P::kElems), lane, raw);
+      tile_minmax<DT, kPartLog2, 4>(raw, &stat_all[0][wave_in_block * P::kSegments], lane);
+    }
+    __syncthreads();
+    if ((int)threadIdx.x * S::kGroupSize < short_len)
+      store_group_minmax<S>(stat_all[0], (int)threadIdx.x, (short_len - 1) / (S::kLpg * S::kEpl),
+                            out_min + n_tiles * S::kGroups, out_max + n_tiles * S::kGroups);
+    return;
+  }
+  const int64_t tile = (int64_t)(blockIdx.x - first_block) * kWavesPerBlock + wave_in_block;
+  if (tile >= n_tiles) return;
   float2* stat = stat_all[wave_in_block];
   uint4 raw[S::kLoads];
-  if (tile < n_tiles) {
 #pragma unroll
-    for (int u = 0; u < S::kLoads; ++u) {
-      const u32x4 v = __builtin_nontemporal_load(&x[tile * (S::kLoads * kWave) + u * kWave + lane]);
-      raw[u] = make_uint4(v.x, v.y, v.z, v.w);
-    }
-  } else {                             // the tile in which the tensor ends
-    if (tile > n_tiles || short_len == 0) return;
-    short_tile_load<DT>(&x[tile * (S::kLoads * kWave)], short_len, lane, raw);
-    groups = (short_len + S::kGroupSize - 1) / S::kGroupSize;
+  for (int u = 0; u < S::kLoads; ++u) {
+    const u32x4 v = __builtin_nontemporal_load(&x[tile * (S::kLoads * kWave) + u * kWave + lane]);
+    raw[u] = make_uint4(v.x, v.y, v.z, v.w);
   }
   tile_minmax<DT, LPG_LOG2>(raw, stat, lane);
   wave_lds_sync();
-  if (lane < groups) {
-    float2 st = stat[lane * S::kLoadsPerGroup];
-#pragma unroll
-    for (int j = 1; j < S::kLoadsPerGroup; ++j) {
-      const float2 t = stat[lane * S::kLoadsPerGroup + j];
-      st.x = vmin(st.x, t.x);
-      st.y = vmax(st.y, t.y);
-    }
-    out_min[tile * S::kGroups + lane] = st.x + 0.0f;
-    out_max[tile * S::kGroups + lane] = st.y + 0.0f;
-  }
+  if (lane < S::kGroups)
+    store_group_minmax<S>(stat, lane, S::kSegments - 1, out_min + tile * S::kGroups, out_max + tile * S::kGroups);
 }
 
 __global__ void k_stat_to_outputs(const float2* __restrict__ stat, int64_t num_groups, float* __restrict__ out_min,
@@ -150,7 +171,7 @@ __global__ void k_stat_to_outputs(const float2* __restrict__ stat, int64_t num_g
 // Statistics only, for the group sizes of the unit path (32 * m elements, 3 <= m <= 128, m not a
 // power of two): the first steps of k_quantize_pack_units.
 template <int DT>
-__global__ __launch_bounds__(kThreads) void k_group_minmax_units(const u32x4* __restrict__ x, int64_t n_tiles, int32_t m,
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DT == kF32 ? 7 : 8))) void k_group_minmax_units(const u32x4* __restrict__ x, int64_t n_tiles, int32_t m,
                                                                  int32_t k_full, int32_t k_last, int32_t part_log2,
                                                                  float* __restrict__ out_min,
                                                                  float* __restrict__ out_max, int short_len) {
@@ -203,8 +224,8 @@ hipError_t launch_group_minmax(const daf_plan_t* p, const void* x, float* out_mi
       const int64_t n_tiles = full_groups / TileShape<DT, LOG2>::kGroups;                                       \
       const int short_len = (int)(p->n - n_tiles * TileShape<DT, LOG2>::kElems);                                \
       if (full_groups > 0) {                                                                                    \
-        hipLaunchKernelGGL((k_group_minmax_tile<DT, LOG2>), dim3((unsigned)((n_tiles + (short_len > 0) +        \
-                           kWavesPerBlock - 1) / kWavesPerBlock)), dim3(kThreads), 0, stream,                   \
+        hipLaunchKernelGGL((k_group_minmax_tile<DT, LOG2>), dim3((unsigned)((n_tiles + kWavesPerBlock - 1) /    \
+                           kWavesPerBlock) + (short_len > 0)), dim3(kThreads), 0, stream,                       \
                            static_cast<const u32x4*>(x), n_tiles, out_min, out_max, short_len);                 \
         fast_groups = p->num_groups;        /* the tile in which the tensor ends included */                    \
       }                                                                                                         \

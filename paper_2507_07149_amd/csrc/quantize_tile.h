@@ -78,7 +78,7 @@ struct alignas(16) WaveLds {
 // ---- the tile in which a tensor ends ---------------------------------------------------------
 // A tensor rarely ends with a whole tile.  What is left, whole groups and at last a short one, is one more tile whose
 // chunks past the end hold copies of the tensor's last element: they leave the short group's minimum and maximum as
-// they are, and their codes are set to 0, which is what a packed word holds behind its last element.  The groups
+// they are, and their codes are taken out of the last packed word again (end_run).  The groups
 // used to go one by one through quantize_pack_group_body in a workgroup of their own, up to 63 chains of
 // dependent loads of ~3 us each behind four waves: 6774528 bfloat16 elements, groups of 64, three widths, both directions
 // 52.7 us, now 13.4.
@@ -87,7 +87,7 @@ template <int DT, int LOADS>
 __device__ __forceinline__ void short_tile_load(const u32x4* chunks, int len, int lane, uint4 (&raw)[LOADS]) {
   constexpr int kEpl = ElemTraits<DT>::kPerLoad;
   const int whole = len / kEpl, last = len - 1;
-  // every load is issued before any is used, the elements one by one behind the chunks
+  // every load is issued before any is used, that of the last elements behind the chunks
   u32x4 v[LOADS];
 #pragma unroll
   for (int u = 0; u < LOADS; ++u) v[u] = u32x4{0u, 0u, 0u, 0u};
@@ -98,17 +98,15 @@ __device__ __forceinline__ void short_tile_load(const u32x4* chunks, int len, in
       v[u] = __builtin_nontemporal_load(&chunks[c < whole ? c : whole - 1]);
     }
   }
-  uint32_t elem[kEpl], edge[4], end;                 // the chunk the tensor ends in; a dword behind it
-#pragma unroll
-  for (int e = 0; e < kEpl; ++e) {
-    const int i = whole * kEpl + e < len ? whole * kEpl + e : last;
-    elem[e] = DT == kF32 ? reinterpret_cast<const uint32_t*>(chunks)[i] : reinterpret_cast<const uint16_t*>(chunks)[i];
-  }
-  end = elem[kEpl - 1];                              // fewer than kEpl are left: the last element
+  // The chunk the tensor ends in, behind its end the last element: an element per lane, handed out as scalars (the same in all
+  // lanes they took a register per element, which is what made whole tiles spill beside this).
+  const int i = min(whole * kEpl + (lane & (kEpl - 1)), last);
+  const uint32_t elem = DT == kF32 ? reinterpret_cast<const uint32_t*>(chunks)[i] : reinterpret_cast<const uint16_t*>(chunks)[i];
+  auto of = [&](int e) { return (uint32_t)__builtin_amdgcn_readlane((int)elem, e); };
+  uint32_t edge[4], end = of(kEpl - 1);              // fewer than kEpl are left: the last element
   if (DT != kF32) end |= end << 16;
 #pragma unroll
-  for (int e = 0; e < 4; ++e)
-    edge[e] = DT == kF32 ? elem[e] : elem[(2 * e) % kEpl] | (elem[(2 * e + 1) % kEpl] << 16);
+  for (int e = 0; e < 4; ++e) edge[e] = DT == kF32 ? of(e) : of((2 * e) % kEpl) | (of((2 * e + 1) % kEpl) << 16);
 #pragma unroll
   for (int u = 0; u < LOADS; ++u) {
     const int c = u * kWave + lane;
@@ -139,12 +137,6 @@ __device__ __forceinline__ void short_tile_store(u32x4* chunks, int len, int lan
       }
     }
   }
-}
-
-// Negated codes of a chunk (quantize_chunk) in which only the first `valid` elements exist: the others become 0.
-__device__ __forceinline__ uint32_t keep_codes(uint32_t nacc, uint32_t b, int valid) {
-  const uint32_t drop = (uint32_t)(4 - (valid < 0 ? 0 : valid > 4 ? 4 : valid)) * b;
-  return drop < 32u ? 0u - (((0u - nacc) >> drop) << drop) : 0u;
 }
 
 // Codes of one 16-byte chunk, accumulated most significant first and NEGATED (the element map
@@ -220,10 +212,10 @@ __device__ __forceinline__ void quantize_chunk_f16(const uint4& raw, float mn, f
 // compiler from keeping the first ones): 128 -> 96 registers, 4 -> 5 waves per SIMD, 361 M bfloat16 elements, groups of 64,
 // call with selection and plan 285 -> 279 us.  bfloat16 without metrics keeps them: 72 registers and 6 waves instead of 94 and 5
 // took 2 % longer (361 M elements, both directions, 318 -> 325 us; held to 5 waves 318).
-// SHORT: only the first `valid` elements of the chunk exist; `all`: the chunks of the whole wave do.
+// SHORT: only the first `valid` elements of the chunk exist.
 template <int DT, bool EXACT2, bool METRICS = false, bool SHORT = false>
 __device__ __forceinline__ void quantize_raw_chunk(uint4& raw, float mn, float invs, uint32_t b, const uint32_t* rnd,
-                                                   uint32_t& nacc0, uint32_t& nacc1, int valid = 8, bool all = true,
+                                                   uint32_t& nacc0, uint32_t& nacc1, int valid = 8,
                                                    float scale = 0.0f, float* err = nullptr, float* mag = nullptr,
                                                    float* var = nullptr) {
   if constexpr (DT == kF16 && !METRICS) {
@@ -235,10 +227,12 @@ __device__ __forceinline__ void quantize_raw_chunk(uint4& raw, float mn, float i
     for (int e = 0; e < ElemTraits<DT>::kPerLoad; ++e) xf[e] = chunk_elem<DT>(raw, e);
     quantize_chunk<DT, EXACT2, METRICS>(xf, mn, invs, b, rnd, nacc0, nacc1, scale, err, mag, var, SHORT ? valid : 8);
   }
-  if (SHORT && !all) {
-    nacc0 = keep_codes(nacc0, b, valid);
-    if (DT != kF32) nacc1 = keep_codes(nacc1, b, valid - 4);
-  }
+}
+// The last word of a run that ends with a short group, of `bits` bits: what the codes of the copies behind the tensor's last
+// element (short_tile_load) left in it becomes 0.
+__device__ __forceinline__ void end_run(uint32_t* last_word, uint32_t bits, int lane) {
+  if ((bits & 31u) != 0u && lane == 0) *last_word &= ~0u << (32u - (bits & 31u));
+  wave_lds_sync();
 }
 
 // binary16 tiles: one [-max : min] dword (two binary16 halves, daf_device.h) per (load, lane run)
@@ -511,6 +505,7 @@ __device__ __forceinline__ void quantize_pack_tile_body(
     // 4. lane g of the wave finishes group g of the tile: scale, reciprocal, place in the run
     bool need_exact2;
     uint32_t tile_words;
+    [[maybe_unused]] uint32_t last_bits;        // of the short group
     {
       float2 st;
       if constexpr (FOLD) {
@@ -548,8 +543,10 @@ __device__ __forceinline__ void quantize_pack_tile_body(
         woff = (uint32_t)lane * (kGroupWords32 * B);
       }
       // (a short tile's run is laid out in LDS as if all its groups were there and whole; what leaves ends early)
-      if constexpr (SHORT)
-        tile_words = (uint32_t)__builtin_amdgcn_readlane((int)(woff + ((last_len * my_b + 31u) >> 5)), n_groups - 1);
+      if constexpr (SHORT) {
+        last_bits = last_len * (uint32_t)__builtin_amdgcn_readlane((int)my_b, n_groups - 1);
+        tile_words = (uint32_t)__builtin_amdgcn_readlane((int)woff, n_groups - 1) + ((last_bits + 31u) >> 5);
+      }
       if (lane < S::kGroups) {
         if ((!EXT || tile_in_group == 0u) && (!SHORT || lane < n_groups)) {
           if (kMixed) {
@@ -602,6 +599,8 @@ __device__ __forceinline__ void quantize_pack_tile_body(
     //    groups whose reciprocal times 256 overflows is rare.)
     auto quantize_tile = [&](auto exact2) {
       constexpr bool kExact2 = decltype(exact2)::value;
+      // (what the two copies have in common would be computed before the branch, a register more than there are)
+      if (METRICS && DT == kF16 && kExact2) asm volatile("" ::: "memory");
       [[maybe_unused]] float metric_sums[2][3];  // error, magnitude, variance of the last two loads
 #pragma unroll
       for (int u = 0; u < S::kLoads; ++u) {
@@ -623,12 +622,11 @@ __device__ __forceinline__ void quantize_pack_tile_body(
           addr = (stage_base + head * 4u + (uint32_t)grp * (kGroupWords32 * B * 4u) + ((lig * kLaneBits) >> 3)) ^ kSwz;
         }
         uint32_t n0, n1;
-        const int valid = SHORT ? len - (u * kWave + lane) * kEpl : 8;         // elements from here to the end
-        const bool all = !SHORT || (u + 1) * kWave * kEpl <= len;
+        [[maybe_unused]] const int valid = SHORT ? len - (u * kWave + lane) * kEpl : 8;         // elements from here to the end
         if constexpr (METRICS) {
           const float g_scale = lds.gscale[grp];
           float* sums = metric_sums[u & 1];
-          quantize_raw_chunk<DT, kExact2, true, SHORT>(raw[u], g_mn, g_invs, b, rnd[u], n0, n1, valid, all, g_scale, &sums[0],
+          quantize_raw_chunk<DT, kExact2, true, SHORT>(raw[u], g_mn, g_invs, b, rnd[u], n0, n1, valid, g_scale, &sums[0],
                                                        &sums[1], &sums[2]);
           if (u & 1) {                           // over the group's lanes, two loads at a time
             seg_sum6<S::kLaneLog2>(metric_sums[0], metric_sums[1]);
@@ -649,7 +647,7 @@ __device__ __forceinline__ void quantize_pack_tile_body(
             }
           }
         } else {
-          quantize_raw_chunk<DT, kExact2, false, SHORT>(raw[u], g_mn, g_invs, b, rnd[u], n0, n1, valid, all);
+          quantize_raw_chunk<DT, kExact2, false, SHORT>(raw[u], g_mn, g_invs, b, rnd[u], n0, n1);
         }
         stage_chunk_at<kEpl>(addr, b, n0, n1, lane);
       }
@@ -657,6 +655,7 @@ __device__ __forceinline__ void quantize_pack_tile_body(
     if (need_exact2) quantize_tile(std::true_type{});
     else             quantize_tile(std::false_type{});
     wave_lds_sync();
+    if constexpr (SHORT) end_run(&lds.stage[head + tile_words - 1u], last_bits, lane);
 
     // 6. the tile's words are one contiguous run of the packed buffer; they leave in 16-byte
     //    pieces (single words at a ragged start or end) with streaming stores: the words are read
@@ -675,18 +674,25 @@ __device__ __forceinline__ void quantize_pack_tile_body(
                                   : (w < span && (!SHORT || w >= full_begin))))
         __builtin_nontemporal_store(lds.stage[w], dst + w);
     }
-    if (METRICS && lane < n_groups) {
-      const float sc = lds.gscale[lane];
-      float* m = out_metrics + 3 * (g0 + lane);
-      m[0] = lds.stat[lane].x;
-      m[1] = lds.stat[lane].y;
-      m[2] = (lds.gvar[lane] * 1.52587890625e-05f) * (sc * sc);
+    if constexpr (METRICS) {
+      // (the lane counted anew: its addresses from step 4 would hold registers until here)
+      const int g = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+      if (g < n_groups) {
+        const float sc = lds.gscale[g];
+        float* m = out_metrics + 3 * (g0 + g);
+        m[0] = lds.stat[g].x;
+        m[1] = lds.stat[g].y;
+        m[2] = (lds.gvar[g] * 1.52587890625e-05f) * (sc * sc);
+      }
     }
   }
 }
 
-// Waves per SIMD of the tile kernel.  At least: as many as the whole tiles' registers allow; the short tile's code shall
-// not cost a wave (metrics, 361 M bfloat16 elements: 4 waves instead of 3, 311 -> 285 us, whole call).
+// Waves per SIMD of the tile kernel.  At least: as many as the whole tiles' registers allow without spilling; the short tile's
+// code shall not cost a wave (metrics, 361 M bfloat16 elements, groups of 64: 4 waves instead of 3, 311 -> 285 us, whole call).
+// Metrics in 16-bit formats: 5, without a spill (binary16, 361 M elements, groups of 64, 5 waves with spills / without / 4 waves:
+// 294 / 288 / 294 us; 180 M, groups of 128 151.2 / 149.9 / 151.3, of 256 149.3 / 148.2 / 148.9; from card to card the middle one
+// moves by 2 % either way).
 // At most: more waves than these scatter the streams of a binary32 tensor (both directions, 47 M elements, 2 bits, 4 / 5 / 6 / 8
 // waves: 70.3 / 69.1 / 67.1 / 68.0 us; 92 M, 8 bits: 158.5 / 157.0 / 159.7 / 160.9).
 template <int DT, int LPG_LOG2, bool METRICS>
@@ -757,9 +763,12 @@ struct Batch {
 };
 static_assert(kMaxBatch <= kBatchSlots, "one cumulative count per entry");
 
-// SHORT: some tensors of the list end inside a tile.  Lists of whole tiles have the kernel without that code.
+// SHORT: some tensors of the list end inside a tile.  Lists of whole tiles have the kernel without that code, and with it there
+// shall be as many waves per SIMD as without.
 template <int DT, int LPG_LOG2, int B, bool SHORT>
-__global__ __launch_bounds__(kThreads) void k_quantize_pack_tile_batch(const Batch batch) {
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(!SHORT ? 1 : DT == kF16 ? 6 : DT == kF32 && LPG_LOG2 == 10 ? 4 : 1)))
+void k_quantize_pack_tile_batch(const Batch batch) {
   const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t gtile = (int64_t)blockIdx.x * kWavesPerBlock + wave_in_block;
   const int t = batch_entry_of(batch.ends, (uint32_t)gtile);

@@ -234,6 +234,7 @@ __device__ __forceinline__ void quantize_pack_units_body(
   // 4b. lane g of the wave finishes group g of the tile: scale, reciprocal, place in the run
   bool need_exact2;
   uint32_t tile_words;
+  [[maybe_unused]] uint32_t last_bits;                       // of the short group
   {
     const GroupScale s = group_scale(st.x, st.y, my_b);
     const float invs = s.inv * kScale;
@@ -248,8 +249,10 @@ __device__ __forceinline__ void quantize_pack_units_body(
       tile_words = units * (uint32_t)B;
       woff = (uint32_t)lane * (group_words32 * (uint32_t)B);
     }
-    if constexpr (SHORT)
-      tile_words = (uint32_t)__builtin_amdgcn_readlane((int)(woff + ((last_len * my_b + 31u) >> 5)), k - 1);
+    if constexpr (SHORT) {
+      last_bits = last_len * (uint32_t)__builtin_amdgcn_readlane((int)my_b, k - 1);
+      tile_words = (uint32_t)__builtin_amdgcn_readlane((int)woff, k - 1) + ((last_bits + 31u) >> 5);
+    }
     if (lane < k) {
       out_min[g0 + lane] = s.mn;
       out_scale[g0 + lane] = s.scale;
@@ -280,44 +283,60 @@ __device__ __forceinline__ void quantize_pack_units_body(
   wave_lds_sync();
 
   // 5. quantize every chunk of the tile and drop its bits at their place in the staged run
+  //    (EXACT2: 0 and 1 as quantize_chunk's, 2: by need_exact2, chunk by chunk)
+  auto quantize_tile = [&](auto exact2) {
+    constexpr int kExact2 = decltype(exact2)::value;
+    // (what two copies of the loop have in common would be computed before the branch and held)
+    if (METRICS && kExact2 == 1 && !SHORT) asm volatile("" ::: "memory");
+    // (the lane counted anew, or the chunk numbers of step 1 would hold registers until here: 5 waves per SIMD instead of 4
+    // in lists of bfloat16 tensors; with 8 bits it made lists 0.5 % slower)
+    const int first = SHORT || (DT == kBF16 && B != 8) ? (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) : lane;
 #pragma unroll
-  for (int u = 0; u < S::kLoads; ++u) {
-    const uint32_t c = (uint32_t)(u * kWave + lane);
-    if (c < n_chunks) {
-      // (24-bit multiplications: every product here is far below 2^24, and the full 32-bit
-      // multiplication runs at a quarter of the rate)
-      const uint32_t grp = __umul24(c >> S::kLanesLog2, magic) >> 16;   // unit / m
-      const uint32_t lig = c - __umul24(grp, group_chunks);            // chunk inside its group
-      const GroupInfo gi = lds.info[grp];
-      const uint32_t b = kMixed ? (gi.b & 0xFFu) : (uint32_t)B;
-      const uint32_t addr = (gi.byte_off + (__umul24(lig, b * (uint32_t)kEpl) >> 3)) ^ (gi.b >> 8);
-      uint32_t n0, n1;
-      const int valid = SHORT ? len - (int)c * kEpl : 8;               // elements from here to the end
-      const bool all = !SHORT || (u + 1) * kWave * kEpl <= len;
-      if constexpr (METRICS) {
-        const float g_scale = mlds.gscale[grp];
-        float err, mag, var, unused = 0.0f;
-        if (SHORT || need_exact2)
-          quantize_raw_chunk<DT, true, true, SHORT>(raw[u], gi.mn, gi.invs, b, rnd[u], n0, n1, valid, all, g_scale, &err, &mag, &var);
-        else
-          quantize_raw_chunk<DT, false, true>(raw[u], gi.mn, gi.invs, b, rnd[u], n0, n1, 8, true, g_scale, &err, &mag, &var);
-        seg_sum2<S::kLanesLog2>(err, mag);       // over the unit's lanes (all valid, or none)
-        seg_sum2<S::kLanesLog2>(var, unused);
-        if ((lane & ((1 << S::kLanesLog2) - 1)) == (1 << S::kLanesLog2) - 1) {
-          mlds.usum[0][c >> S::kLanesLog2] = err;
-          mlds.usum[1][c >> S::kLanesLog2] = mag;
-          mlds.usum[2][c >> S::kLanesLog2] = var;
+    for (int u = 0; u < S::kLoads; ++u) {
+      const uint32_t c = (uint32_t)(u * kWave + first);
+      if (c < n_chunks) {
+        // (24-bit multiplications: every product here is far below 2^24, and the full 32-bit
+        // multiplication runs at a quarter of the rate)
+        const uint32_t grp = __umul24(c >> S::kLanesLog2, magic) >> 16;   // unit / m
+        const uint32_t lig = c - __umul24(grp, group_chunks);            // chunk inside its group
+        const GroupInfo gi = lds.info[grp];
+        const uint32_t b = kMixed ? (gi.b & 0xFFu) : (uint32_t)B;
+        const uint32_t addr = (gi.byte_off + (__umul24(lig, b * (uint32_t)kEpl) >> 3)) ^ (gi.b >> 8);
+        uint32_t n0, n1;
+        const bool exact = kExact2 == 1 || (kExact2 == 2 && need_exact2);
+        if constexpr (METRICS) {
+          const int valid = SHORT ? len - (int)c * kEpl : 8;           // elements from here to the end
+          const float g_scale = mlds.gscale[grp];
+          float err, mag, var, unused = 0.0f;
+          if (exact)
+            quantize_raw_chunk<DT, true, true, SHORT>(raw[u], gi.mn, gi.invs, b, rnd[u], n0, n1, valid, g_scale, &err, &mag, &var);
+          else
+            quantize_raw_chunk<DT, false, true>(raw[u], gi.mn, gi.invs, b, rnd[u], n0, n1, 8, g_scale, &err, &mag, &var);
+          seg_sum2<S::kLanesLog2>(err, mag);       // over the unit's lanes (all valid, or none)
+          seg_sum2<S::kLanesLog2>(var, unused);
+          if ((lane & ((1 << S::kLanesLog2) - 1)) == (1 << S::kLanesLog2) - 1) {
+            mlds.usum[0][c >> S::kLanesLog2] = err;
+            mlds.usum[1][c >> S::kLanesLog2] = mag;
+            mlds.usum[2][c >> S::kLanesLog2] = var;
+          }
+        } else {
+          if (exact) quantize_raw_chunk<DT, true>(raw[u], gi.mn, gi.invs, b, rnd[u], n0, n1);
+          else       quantize_raw_chunk<DT, false>(raw[u], gi.mn, gi.invs, b, rnd[u], n0, n1);
         }
-      } else {
-        if (SHORT || need_exact2)
-          quantize_raw_chunk<DT, true, false, SHORT>(raw[u], gi.mn, gi.invs, b, rnd[u], n0, n1, valid, all);
-        else
-          quantize_raw_chunk<DT, false>(raw[u], gi.mn, gi.invs, b, rnd[u], n0, n1);
+        stage_chunk<kEpl>(stage8, addr, b, n0, n1, lane);
       }
-      stage_chunk<kEpl>(stage8, addr, b, n0, n1, lane);
     }
+  };
+  if constexpr (SHORT) {
+    quantize_tile(std::integral_constant<int, 1>{});
+  } else if constexpr (METRICS) {                          // a copy of the loop each: a branch in every chunk spilled
+    if (need_exact2) quantize_tile(std::integral_constant<int, 1>{});
+    else             quantize_tile(std::integral_constant<int, 0>{});
+  } else {
+    quantize_tile(std::integral_constant<int, 2>{});
   }
   wave_lds_sync();
+  if constexpr (SHORT) end_run(&lds.stage[tile_words - 1u], last_bits, lane);
 
   // 6. the tile's words are one contiguous run in the packed buffer
   uint32_t* dst = words + tile_base;
@@ -385,7 +404,7 @@ struct UnitBatch {
 };
 
 template <int DT, int B, bool SHORT>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(SHORT && DT == kBF16 && B != 8 ? 5 : 4)))
 void k_quantize_pack_units_batch(const UnitBatch batch) {
   const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t gtile = (int64_t)blockIdx.x * kWavesPerBlock + wave_in_block;

@@ -96,3 +96,24 @@ def test_every_end(dtype, gs, bits):
         _check_packed(bufs, want, "list")
     for plan in plans:
         plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("gs", [32, 64, 256, 2048, 4096])
+def test_statistics_of_ends_around_the_parts_that_waves_take(dtype, gs):
+    """The statistics of such a tile are taken by up to four waves, 1024 elements each."""
+    import paper_2507_07149_amd as daf
+    from oracle import daf_oracle as orc
+    for n in sorted({base + 1024 * part + d for base in (4096, 8192) for part in range(4) for d in (-1, 0, 1, 7, 9)}):
+        print("case", dtype, gs, n, flush=True)
+        x = (torch.randn(n, generator=torch.Generator().manual_seed(n)) * 2).to(torch_dtype(dtype))
+        x[-1] = (9.0, -9.0, 0.0)[n % 3]
+        G = -(-n // gs)
+        plan = daf.daf_plan((n,), gs, 2)
+        (lo_all, lo), (hi_all, hi) = _guarded(G, torch.float32, 7.0), _guarded(G, torch.float32, 7.0)
+        daf.daf_group_minmax(plan, x.cuda(), lo, hi)
+        olo, ohi = orc.group_minmax(to_numpy_bits(x), dtype, gs)
+        assert np.array_equal(lo.cpu().numpy().view(np.uint32), olo.view(np.uint32))
+        assert np.array_equal(hi.cpu().numpy().view(np.uint32), ohi.view(np.uint32))
+        assert bool((lo_all[G:] == 7.0).all() and (hi_all[G:] == 7.0).all())
+        plan.destroy()
