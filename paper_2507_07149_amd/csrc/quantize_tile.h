@@ -694,7 +694,8 @@ __device__ __forceinline__ void quantize_pack_tile_body(
 // 294 / 288 / 294 us; 180 M, groups of 128 151.2 / 149.9 / 151.3, of 256 149.3 / 148.2 / 148.9; from card to card the middle one
 // moves by 2 % either way).
 // At most: more waves than these scatter the streams of a binary32 tensor (both directions, 47 M elements, 2 bits, 4 / 5 / 6 / 8
-// waves: 70.3 / 69.1 / 67.1 / 68.0 us; 92 M, 8 bits: 158.5 / 157.0 / 159.7 / 160.9).
+// waves: 70.3 / 69.1 / 67.1 / 68.0 us; 92 M, 8 bits: 158.5 / 157.0 / 159.7 / 160.9; as many as fit / at most these: relu 2 bits
+// 147.4 / 145.5, relu four widths 152.8 / 150.9, 51 M elements, four widths 81.7 / 81.7, 94 M, {2,4,8} 151.5 / 149.7).
 template <int DT, int LPG_LOG2, bool METRICS>
 constexpr int tile_min_waves() {
   if (DT == kF32) return LPG_LOG2 == 10 ? 4 : 1;
@@ -763,11 +764,19 @@ struct Batch {
 };
 static_assert(kMaxBatch <= kBatchSlots, "one cumulative count per entry");
 
+// At most as many waves per SIMD as a single tensor's kernel has, in groups of 4096 three (17 tensors of 206 M elements, both
+// directions, as many as fit / at most these: groups of 256, 2 bits 829.6 / 823.0 us, 8 bits 1021.9 / 1010.6, four widths
+// 941.8 / 920.5; of 2048, 2 bits 841.9 / 843.2; of 4096, 1 bit 856.6 / 847.4, 2 bits 844.2 / 837.7, 4 bits 935.4 / 934.2, 8 bits
+// 1011.6 / 1007.9, four widths 922.6 / 905.4).
+template <int DT, int LPG_LOG2, int B>
+constexpr int list_max_waves() {
+  return DT == kF32 && LPG_LOG2 == 10 ? 3 : tile_max_waves<DT, B, false>();
+}
 // SHORT: some tensors of the list end inside a tile.  Lists of whole tiles have the kernel without that code, and with it there
 // shall be as many waves per SIMD as without.
 template <int DT, int LPG_LOG2, int B, bool SHORT>
 __global__ __launch_bounds__(kThreads)
-__attribute__((amdgpu_waves_per_eu(!SHORT ? 1 : DT == kF16 ? 6 : DT == kF32 && LPG_LOG2 == 10 ? 4 : 1)))
+__attribute__((amdgpu_waves_per_eu(SHORT && DT == kF16 ? 6 : 1, list_max_waves<DT, LPG_LOG2, B>())))
 void k_quantize_pack_tile_batch(const Batch batch) {
   const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t gtile = (int64_t)blockIdx.x * kWavesPerBlock + wave_in_block;
