@@ -204,3 +204,24 @@ def test_linear_quantize_pack_every_tile_form(env, M, N, steps, cut, gs):
     assert np.array_equal(words, ow), "packed words differ"
     assert np.array_equal(mn.view(np.uint32), omn.view(np.uint32)), "min differs"
     assert np.array_equal(sc.view(np.uint32), osc.view(np.uint32)), "scale differs"
+
+
+@pytest.mark.parametrize("M,N,steps,cut", [(1024, 1024, 17, 16), (512, 512, 5, 8), (2048, 2048, 4, 4), (4096, 2048, 3, 2),
+                                           (4096, 4096, 4, 1), (4352, 4096, 5, 8), (5120, 3840, 3, 4)])
+@pytest.mark.parametrize("gs", [32, 64, 128])
+@pytest.mark.parametrize("dtype", [F16, BF16])
+def test_product_alone_every_tile_form(env, M, N, steps, cut, gs, dtype):
+    """The call without packed outputs, in every size of output tile and in whole tiles with cut ones behind them; operands
+    whose products are exact in any order.  Nothing is written behind y."""
+    daf, _ = env
+    K = 64 * steps
+    assert daf.load_library().daf_linear_tiling(M, N, K, ctypes.byref(ctypes.c_int64())) == cut
+    x, w = _integer_operands(np.random.default_rng(M + N + steps + gs), M, N, K, dtype)
+    print("case product alone", M, N, K, cut, gs, dtype, flush=True)
+    plan = daf.daf_plan((M, N), gs, 4)
+    whole = torch.full((M + 1, N), 7.0, dtype=x.dtype, device="cuda:0")
+    daf.daf_linear_quantize_pack(plan, x.cuda(), w.cuda(), 3, whole[:M], None, None, None)
+    want = (x.float() @ w.float().t()).to(x.dtype)                             # exact, as the oracle's
+    assert np.array_equal(to_numpy_bits(whole[:M].cpu()), to_numpy_bits(want)), "y differs"
+    assert bool((whole[M:] == 7.0).all()), "y written behind its end"
+    plan.destroy()
