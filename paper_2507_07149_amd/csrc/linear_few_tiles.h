@@ -1,10 +1,11 @@
 // The linear layer with a quantizing epilogue, for outputs that are too few tiles of 256 x 256 to occupy the chip.
 //
 // A tile of 256 x 256 takes one compute unit ~1.17 us per 64 values of k whatever the other 255 do, so a product of
-// 512 x 5120 x 1792 (40 tiles) takes as long as one of six times its size.  Here the tiles are 128 x 128, or
-// 64 x 64 (32 x 128 where a group is 128 elements), on 4 waves and with one wave per SIMD:
-//   - what bounds it is the LDS: 64 KB of operand reads and 32 KB of arriving tiles per 128 x 128 step, 750 cycles at
-//     128 bytes per cycle beside 512 cycles of matrix instructions; and, the smaller the product, the way of the operands
+// 512 x 5120 x 1792 (40 tiles) takes as long as one of six times its size.  Here the tiles are 128 x 256, 128 x 128, 64 x 128 or
+// 64 x 64 (32 x 128 where a group is 128 elements): 2, 4, 8 or 16 out of one of 256 x 256, on 4 waves and with one wave per SIMD:
+//   - what bounds it is the LDS (128 x 128: 64 KB of operand reads and 32 KB of arriving tiles per step, 750 cycles at
+//     128 bytes per cycle beside 512 cycles of matrix instructions; the others have more reads for each of
+//     those, 128 x 256 fewer) and, the smaller the product, the way of the operands
 //     from memory.  So STAGES steps of operands are on their way or waiting in LDS (loads straight into LDS,
 //     whole cache lines, counted waits), and a step's operands are read into registers one step ahead, which frees
 //     a stage as soon as it has been read and leaves the matrix instructions nothing to wait for;

@@ -317,7 +317,7 @@ __global__ __launch_bounds__(kAheadThreads) void k_plan_ahead(const uint8_t* __r
   }
 }
 
-// Up to 65536 groups: kernel alone 4.0 ... 5.6 us up to 16384 groups, 7.6 at 32768 and 8.2 at 65536, the two launches 9.4 and
+// Up to 65536 groups: kernel alone 4.0 ... 5.3 us up to 8192 groups, 6.1 at 16384, 7.6 at 32768 and 8.2 at 65536, the two launches 9.4 and
 // the gap between them at all of these sizes; at 197000 groups the sums over all that comes before make it slower (call of four
 // launches 62.0 -> 65.4 us, at 524288 51.4 -> 60.3).
 constexpr int64_t kAheadMost = 1 << 16;

@@ -691,8 +691,8 @@ __device__ __forceinline__ void quantize_pack_tile_body(
 // Waves per SIMD of the tile kernel.  At least: as many as the whole tiles' registers allow without spilling; the short tile's
 // code shall not cost a wave (metrics, 361 M bfloat16 elements, groups of 64: 4 waves instead of 3, 311 -> 285 us, whole call).
 // Metrics in 16-bit formats: 5, without a spill (binary16, 361 M elements, groups of 64, 5 waves with spills / without / 4 waves:
-// 294 / 288 / 294 us; 180 M, groups of 128 151.2 / 149.9 / 151.3, of 256 149.3 / 148.2 / 148.9; from card to card the middle one
-// moves by 2 % either way).
+// 294 / 288 / 294 us; 180 M, groups of 128 151.2 / 149.9 / 151.3, of 256 149.3 / 148.2 / 148.9; the middle
+// one moves by card, in groups of 128 and 256 from 2 % ahead of the first to 4 % behind it).
 // At most: more waves than these scatter the streams of a binary32 tensor (both directions, 47 M elements, 2 bits, 4 / 5 / 6 / 8
 // waves: 70.3 / 69.1 / 67.1 / 68.0 us; 92 M, 8 bits: 158.5 / 157.0 / 159.7 / 160.9; as many as fit / at most these: relu 2 bits
 // 147.4 / 145.5, relu four widths 152.8 / 150.9, 51 M elements, four widths 81.7 / 81.7, 94 M, {2,4,8} 151.5 / 149.7).
