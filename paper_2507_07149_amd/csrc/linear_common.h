@@ -126,19 +126,16 @@ __device__ __forceinline__ LinearGroup linear_group(const GroupScale& gs, uint32
 // Quantizes and packs the lane's 16 elements; `e0` is the first one's place in the group, `flat` in the tensor.
 __device__ __forceinline__ void quantize_row(const float (&xf)[16], const LinearGroup& g, uint32_t e0, int64_t flat,
                                              uint32_t seed_lo, uint32_t seed_hi, int lg) {
-  const uint4 rnd4 = philox_block((uint64_t)(flat >> 4), seed_lo, seed_hi);
-  const uint32_t rnd[4] = {rnd4.x, rnd4.y, rnd4.z, rnd4.w};
+  const uint4 rnd4 = philox_block<true>((uint64_t)(flat >> 4), seed_lo, seed_hi);
   const uint32_t b = g.b;
-  uint32_t p[4];
+  uint32_t q[4];                                           // four codes each, first element in the most significant byte
   auto codes = [&](auto two_products, float mult) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      uint32_t nacc = 0u;
+    for (int c = 0; c < 4; c += 2) {
+      int t[8];
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        nacc = (nacc << b) + (uint32_t)neg_code<decltype(two_products)::value>(xf[4 * c + e], g.mn, mult,
-                                                                                (rnd[c] >> (8 * e)) & 0xFFu);
-      p[c] = 0u - nacc;                                    // four codes, first element most significant
+      for (int e = 0; e < 8; ++e) t[e] = neg_position<decltype(two_products)::value>(g.mn - xf[4 * c + e], mult);
+      code_bytes(t, c ? rnd4.z : rnd4.x, c ? rnd4.w : rnd4.y, q[c], q[c + 1]);
     }
   };
   if (g.any_exact2) {
@@ -150,14 +147,14 @@ __device__ __forceinline__ void quantize_row(const float (&xf)[16], const Linear
   uint32_t* dst = g.words;
   if (b == 8u) {
     typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-    *reinterpret_cast<u32x4_any*>(dst + (e0 >> 2)) = u32x4_any{p[0], p[1], p[2], p[3]};
+    *reinterpret_cast<u32x4_any*>(dst + (e0 >> 2)) = u32x4_any{q[0], q[1], q[2], q[3]};
   } else if (b == 4u) {
-    dst[(e0 >> 3)] = (p[0] << 16) | (p[1] & 0xFFFFu);
-    dst[(e0 >> 3) + 1] = (p[2] << 16) | (p[3] & 0xFFFFu);
+    dst[(e0 >> 3)] = pack_codes<4>(q[0], q[1]);
+    dst[(e0 >> 3) + 1] = pack_codes<4>(q[2], q[3]);
   } else if (b == 2u) {
-    dst[e0 >> 4] = (p[0] << 24) | ((p[1] & 0xFFu) << 16) | ((p[2] & 0xFFu) << 8) | (p[3] & 0xFFu);
+    dst[e0 >> 4] = (pack_codes<2>(q[0], q[1]) << 16) | pack_codes<2>(q[2], q[3]);
   } else {
-    const uint32_t half = ((p[0] & 0xFu) << 12) | ((p[1] & 0xFu) << 8) | ((p[2] & 0xFu) << 4) | (p[3] & 0xFu);
+    const uint32_t half = (pack_codes<1>(q[0], q[1]) << 8) | pack_codes<1>(q[2], q[3]);
     const uint32_t upper = other_half(half);               // the lane 32 away runs the same branch: same group, same width
     if (lg == 0) dst[e0 >> 5] = (half << 16) | upper;
   }

@@ -35,7 +35,7 @@ __device__ __forceinline__ void quantize_pack_long_body(
   const int n_waves = (int)(blockDim.x >> 6);
   LongWaveLds& lds = reinterpret_cast<LongWaveLds*>(dyn_lds)[wave];
   float4* wstat = reinterpret_cast<float4*>(dyn_lds + (size_t)n_waves * sizeof(LongWaveLds));   // 16 bytes per wave
-  uint8_t* stage8 = reinterpret_cast<uint8_t*>(lds.stage);
+  const uint32_t stage_base = (uint32_t)reinterpret_cast<uintptr_t>(lds.stage);      // LDS byte address, as in the tile kernel
 
   const int32_t unit0 = wave * units_per_wave;               // first unit of this wave's slice
   const uint32_t units = (uint32_t)((m - unit0 < units_per_wave) ? m - unit0 : units_per_wave);   // >= 1
@@ -50,14 +50,14 @@ __device__ __forceinline__ void quantize_pack_long_body(
   const uint32_t b = kMixed ? (uint32_t)bits[g] : (uint32_t)B;
   const uint32_t group_base = kMixed ? off[g] : (uint32_t)g * ((uint32_t)m * (uint32_t)B);
 
-  // 2. random bytes of the slice (two Philox blocks per unit)
+  // 2. random bytes of the slice, complemented (two Philox blocks per unit)
   {
     const uint64_t blk0 = (uint64_t)first_unit * 2u;
     uint4* dst = reinterpret_cast<uint4*>(lds.rand_bytes);
 #pragma unroll
     for (int q = 0; q < S::kPhilox; ++q) {
       const uint32_t i = (uint32_t)(q * kWave + lane);
-      if (i < units * 2u) dst[i] = philox_block(blk0 + i, seed_lo, seed_hi);
+      if (i < units * 2u) dst[i] = philox_block<true>(blk0 + i, seed_lo, seed_hi);
     }
   }
 
@@ -118,22 +118,22 @@ __device__ __forceinline__ void quantize_pack_long_body(
   for (int u = 0; u < S::kLoads; ++u) {
     const uint32_t c = (uint32_t)(u * kWave + lane);
     if (c < n_chunks) {
-      const uint32_t addr = (__umul24(c, lane_bits) >> 3) ^ swz;
-      uint32_t n0, n1;
+      const uint32_t addr = (stage_base + (__umul24(c, lane_bits) >> 3)) ^ swz;
+      uint32_t q[kEpl / 4];
       if constexpr (METRICS) {
         float err, mag, var;
         if (need_exact2)
-          quantize_raw_chunk<DT, true, true>(raw[u], s.mn, invs, b, rnd[u], n0, n1, 8, s.scale, &err, &mag, &var);
+          quantize_raw_chunk<DT, true, true>(raw[u], s.mn, invs, rnd[u], q, 8, s.scale, &err, &mag, &var);
         else
-          quantize_raw_chunk<DT, false, true>(raw[u], s.mn, invs, b, rnd[u], n0, n1, 8, s.scale, &err, &mag, &var);
+          quantize_raw_chunk<DT, false, true>(raw[u], s.mn, invs, rnd[u], q, 8, s.scale, &err, &mag, &var);
         m_err += err;
         m_mag += mag;
         m_var += var;
       } else {
-        if (need_exact2) quantize_raw_chunk<DT, true>(raw[u], s.mn, invs, b, rnd[u], n0, n1);
-        else             quantize_raw_chunk<DT, false>(raw[u], s.mn, invs, b, rnd[u], n0, n1);
+        if (need_exact2) quantize_raw_chunk<DT, true>(raw[u], s.mn, invs, rnd[u], q);
+        else             quantize_raw_chunk<DT, false>(raw[u], s.mn, invs, rnd[u], q);
       }
-      stage_chunk<kEpl>(stage8, addr, b, n0, n1, lane);
+      stage_chunk<kEpl, false>(addr, b, q, lane);
     }
   }
   wave_lds_sync();

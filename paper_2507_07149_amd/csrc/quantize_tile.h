@@ -52,14 +52,15 @@ using QTile = TileShape<DT, LPG_LOG2, tile_div<DT, LPG_LOG2>()>;
 struct alignas(16) GroupInfo {   // what every lane of a group needs for the element map
   float mn;
   float invs;                    // inv*256, or inv on the two-multiplication path
-  uint32_t b;                    // width; bits 8..9: byte-address swizzle of the staged run (3, 2 or 0)
-  uint32_t byte_off;             // byte offset of the group inside the tile's packed run
+  uint32_t b;                    // width; bits 24..25: byte-address swizzle of the staged run (3, 2 or 0).  (24-bit products and
+                                 // 16-bit compares take the width without a mask.)
+  uint32_t byte_off;             // LDS byte address of the group's first packed word
 };
 
 template <int DT, int LPG_LOG2, int DIV = 1>
 struct alignas(16) WaveLds {
   using S = TileShape<DT, LPG_LOG2, DIV>;
-  // First the random bytes of the tile (byte e serves tile element e); once every lane has
+  // First the complemented random bytes of the tile (byte e serves tile element e); once every lane has
   // taken its bytes into registers the same memory stages the tile's packed words (at most
   // 8 bits per element, so the run always fits).
   // The staged run starts up to three words in, so that 16-byte pieces of it line up with
@@ -139,93 +140,63 @@ __device__ __forceinline__ void short_tile_store(u32x4* chunks, int len, int lan
   }
 }
 
-// Codes of one 16-byte chunk, accumulated most significant first and NEGATED (the element map
-// yields -code): nacc0 = -(elements 0..3), nacc1 = -(elements 4..7) (16-bit inputs only).
+// Codes of one 16-byte chunk, one to a byte (code_bytes): q[0] elements 0..3, q[1] elements 4..7 (16-bit inputs).
+// not_rnd: the complements of the chunk's random bytes, one dword per four elements.
 //
 // METRICS: also returns this lane's share of the group's importance sums (Sec. 3.2 names
 // quantization error and tensor magnitude): err += (x - xhat)^2 with xhat = fma(code, scale, mn)
 // as the dequantizer computes it, mag += x^2, both in binary32; var = sum of T*(256-T), the
 // variance of the stochastic rounding in units of scale^2 / 65536 (exact integer).
 //
-// Elements from `valid` on (the tensor ends in this chunk or before it) count for no sum.
-template <int DT, bool EXACT2, bool METRICS = false>
-__device__ __forceinline__ void quantize_chunk(const float (&xf)[ElemTraits<DT>::kPerLoad], float mn,
-                                               float invs, uint32_t b, const uint32_t* rnd,
-                                               uint32_t& nacc0, uint32_t& nacc1, float scale = 0.0f,
-                                               float* err = nullptr, float* mag = nullptr, float* var = nullptr,
-                                               int valid = 8) {
+// Elements from `valid` on (SHORT: the tensor ends in this chunk or before it) count for no sum.
+//
+// A chunk comes in its loaded form.  binary16 without metrics is never widened: min - x is
+// one mixed-precision fma per element.  With metrics the values that the
+// statistics widened would hold twice the registers until here, so they are made again (the empty statement keeps the
+// compiler from keeping the first ones): 128 -> 96 registers, 4 -> 5 waves per SIMD, 361 M bfloat16 elements, groups of 64,
+// call with selection and plan 285 -> 279 us.  AGAIN: the same without metrics.  Tiles of bfloat16 keep them (93 M elements,
+// groups of 256, 2 bits, both directions, 4 waves with kept values 70.3 us, 5 waves with values made again 71.9; other
+// widths 0.995 to 1.01 of each other), units make them again (rows of 768 and 3072 in lists, five choices of widths, 0.98 to 0.99).
+template <int DT, bool EXACT2, bool METRICS = false, bool SHORT = false, bool AGAIN = false>
+__device__ __forceinline__ void quantize_raw_chunk(uint4& raw, float mn, float invs, const uint32_t* not_rnd,
+                                                   uint32_t (&q)[ElemTraits<DT>::kPerLoad / 4], int valid = 8,
+                                                   float scale = 0.0f, float* err = nullptr, float* mag = nullptr,
+                                                   float* var = nullptr) {
   constexpr int kEpl = ElemTraits<DT>::kPerLoad;
-  uint32_t nacc[2] = {0u, 0u};
-  float e2 = 0.0f, m2 = 0.0f;
-  uint32_t t_sum = 0u, t_sq = 0u;
+  if ((METRICS || AGAIN) && DT != kF32) asm volatile("" : "+v"(raw.x), "+v"(raw.y), "+v"(raw.z), "+v"(raw.w));
+  const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+  int t[kEpl];
 #pragma unroll
-  for (int q = 0; q < kEpl / 4; ++q) {
-    const uint32_t rw = rnd[q];                 // the random bytes of four consecutive elements
-    int rt[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float xv = xf[q * 4 + e];
-      const int nc = neg_code<EXACT2>(xv, mn, invs, (rw >> (8 * e)) & 0xFFu, METRICS ? &rt[e] : nullptr);
-      const bool in = q * 4 + e < valid;
-      nacc[q] = (nacc[q] << b) + (uint32_t)nc;
-      if (METRICS && !in) rt[e] = 0;
-      if (METRICS && in) {
-        const float d = xv - __builtin_fmaf((float)(-nc), scale, mn);
-        e2 = __builtin_fmaf(d, d, e2);
-        m2 = __builtin_fmaf(xv, xv, m2);
-      }
-    }
-    if (METRICS) sr_variance_sums(rt, t_sum, t_sq);
+  for (int e = 0; e < kEpl; ++e) {
+    float d;
+    if constexpr (DT == kF16 && !METRICS) d = (e & 1) ? min_minus_half<1>(w[e >> 1], mn) : min_minus_half<0>(w[e >> 1], mn);
+    else d = mn - chunk_elem<DT>(raw, e);
+    t[e] = neg_position<EXACT2>(d, invs);
   }
-  nacc0 = nacc[0];
-  nacc1 = nacc[1];
-  if (METRICS) {
+  if constexpr (kEpl == 4) q[0] = code_bytes(t, not_rnd[0]);
+  else code_bytes(t, not_rnd[0], not_rnd[1], q[0], q[kEpl / 4 - 1]);
+  if constexpr (METRICS) {
+    float e2 = 0.0f, m2 = 0.0f;
+    uint32_t t_sum = 0u, t_sq = 0u;
+#pragma unroll
+    for (int c = 0; c < kEpl / 4; ++c) {
+      int rt[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool in = !SHORT || c * 4 + e < valid;
+        rt[e] = in ? t[c * 4 + e] : 0;
+        if (in) {
+          const float xv = chunk_elem<DT>(raw, c * 4 + e);
+          const float d = xv - __builtin_fmaf((float)((q[c] >> (24 - 8 * e)) & 0xFFu), scale, mn);
+          e2 = __builtin_fmaf(d, d, e2);
+          m2 = __builtin_fmaf(xv, xv, m2);
+        }
+      }
+      sr_variance_sums(rt, t_sum, t_sq);
+    }
     *err = e2;
     *mag = m2;
     *var = (float)(256u * t_sum - t_sq);
-  }
-}
-
-// The same for a chunk of eight binary16 values taken straight from the loaded dwords: min - x is
-// one mixed-precision fma per element (the widening conversion disappears into it).
-template <bool EXACT2>
-__device__ __forceinline__ void quantize_chunk_f16(const uint4& raw, float mn, float invs, uint32_t b,
-                                                   const uint32_t* rnd, uint32_t& nacc0, uint32_t& nacc1) {
-  const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-  uint32_t nacc[2] = {0u, 0u};
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const uint32_t rw = rnd[q];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const uint32_t pair = w[q * 2 + (e >> 1)];
-      const float d = (e & 1) ? min_minus_half<1>(pair, mn) : min_minus_half<0>(pair, mn);
-      nacc[q] = (nacc[q] << b) + (uint32_t)neg_code_of_difference<EXACT2>(d, invs, (rw >> (8 * e)) & 0xFFu);
-    }
-  }
-  nacc0 = nacc[0];
-  nacc1 = nacc[1];
-}
-
-// A chunk from its loaded form.  binary16 without metrics needs nothing widened.  With metrics the values that the
-// statistics widened would hold twice the registers until here, so they are made again (the empty statement keeps the
-// compiler from keeping the first ones): 128 -> 96 registers, 4 -> 5 waves per SIMD, 361 M bfloat16 elements, groups of 64,
-// call with selection and plan 285 -> 279 us.  bfloat16 without metrics keeps them: 72 registers and 6 waves instead of 94 and 5
-// took 2 % longer (361 M elements, both directions, 318 -> 325 us; held to 5 waves 318).
-// SHORT: only the first `valid` elements of the chunk exist.
-template <int DT, bool EXACT2, bool METRICS = false, bool SHORT = false>
-__device__ __forceinline__ void quantize_raw_chunk(uint4& raw, float mn, float invs, uint32_t b, const uint32_t* rnd,
-                                                   uint32_t& nacc0, uint32_t& nacc1, int valid = 8,
-                                                   float scale = 0.0f, float* err = nullptr, float* mag = nullptr,
-                                                   float* var = nullptr) {
-  if constexpr (DT == kF16 && !METRICS) {
-    quantize_chunk_f16<EXACT2>(raw, mn, invs, b, rnd, nacc0, nacc1);
-  } else {
-    if (METRICS && DT != kF32) asm volatile("" : "+v"(raw.x), "+v"(raw.y), "+v"(raw.z), "+v"(raw.w));
-    float xf[ElemTraits<DT>::kPerLoad];
-#pragma unroll
-    for (int e = 0; e < ElemTraits<DT>::kPerLoad; ++e) xf[e] = chunk_elem<DT>(raw, e);
-    quantize_chunk<DT, EXACT2, METRICS>(xf, mn, invs, b, rnd, nacc0, nacc1, scale, err, mag, var, SHORT ? valid : 8);
   }
 }
 // The last word of a run that ends with a short group, of `bits` bits: what the codes of the copies behind the tensor's last
@@ -311,47 +282,72 @@ __device__ __forceinline__ void tile_minmax(const uint4 (&raw)[TileShape<DT, LPG
   }
 }
 
-// Drops the codes of one chunk (negated accumulators n0, n1 as quantize_chunk returns them) at
-// byte address `addr` of the staged word run: a nibble pair, a byte, a halfword or whole words.
+// The stores of one chunk where the width differs from lane to lane: all four follow each other, each under its lanes' mask.
+// (From conditions the compiler makes a tree of branches, 20 scalar instructions and up to six jumps a chunk.)  `width`: its lower
+// 16 bits.  EPL 4: of 1-bit codes only the even lanes store.
+// (The wait states at the end: a DPP instruction may follow a vector write of EXEC after five.)
 template <int EPL>
-__device__ __forceinline__ void stage_chunk(uint8_t* stage8, uint32_t addr, uint32_t b, uint32_t n0, uint32_t n1,
-                                            int lane);
-
-// The same with `addr` an absolute LDS byte address (the staging area's own address already
-// added in, once per group instead of once per store).
-template <int EPL>
-__device__ __forceinline__ void stage_chunk_at(uint32_t addr, uint32_t b, uint32_t n0, uint32_t n1, int lane) {
-  typedef __attribute__((address_space(3))) uint8_t lds_u8;
-  stage_chunk<EPL>((uint8_t*)(lds_u8*)(uintptr_t)addr, 0u, b, n0, n1, lane);
+__device__ __forceinline__ void store_by_width(uint32_t addr, uint32_t width, uint32_t q0, uint32_t q1, uint32_t w4, uint32_t w2,
+                                               uint32_t w1) {
+  uint64_t all;
+  if constexpr (EPL == 4) {
+    asm volatile("s_mov_b64 %0, exec\n"
+                 "v_cmpx_eq_u16 vcc, 8, %2\n ds_write_b32 %1, %3\n s_mov_b64 exec, %0\n"
+                 "v_cmpx_eq_u16 vcc, 4, %2\n ds_write_b16 %1, %4\n s_mov_b64 exec, %0\n"
+                 "v_cmpx_eq_u16 vcc, 2, %2\n ds_write_b8 %1, %5\n s_mov_b64 exec, %0\n"
+                 "v_cmpx_eq_u16 vcc, 1, %2\n s_and_b64 exec, exec, %7\n ds_write_b8 %1, %6\n s_mov_b64 exec, %0\n s_nop 2"
+                 : "=&s"(all)
+                 : "v"(addr), "v"(width), "v"(q0), "v"(w4), "v"(w2), "v"(w1), "s"(0x5555555555555555ull)
+                 : "memory", "vcc", "scc");
+  } else {
+    const uint64_t q = ((uint64_t)q1 << 32) | q0;
+    asm volatile("s_mov_b64 %0, exec\n"
+                 "v_cmpx_eq_u16 vcc, 8, %2\n ds_write_b64 %1, %3\n s_mov_b64 exec, %0\n"
+                 "v_cmpx_eq_u16 vcc, 4, %2\n ds_write_b32 %1, %4\n s_mov_b64 exec, %0\n"
+                 "v_cmpx_eq_u16 vcc, 2, %2\n ds_write_b16 %1, %5\n s_mov_b64 exec, %0\n"
+                 "v_cmpx_eq_u16 vcc, 1, %2\n ds_write_b8 %1, %6\n s_mov_b64 exec, %0\n s_nop 2"
+                 : "=&s"(all)
+                 : "v"(addr), "v"(width), "v"(q), "v"(w4), "v"(w2), "v"(w1)
+                 : "memory", "vcc", "scc");
+  }
 }
 
-template <int EPL>
-__device__ __forceinline__ void stage_chunk(uint8_t* stage8, uint32_t addr, uint32_t b, uint32_t n0, uint32_t n1,
-                                            int lane) {
-  if (EPL == 4) {
-    const uint32_t acc = 0u - n0;
-    if (b == 1u) {           // 4 bits per lane: the even lane takes its odd neighbour's nibble
-      const uint32_t nb = dpp<kDppXor1>(acc, acc);
-      if ((lane & 1) == 0) stage8[addr] = (uint8_t)((acc << 4) | nb);
+// Drops the codes of one chunk (bytes, as quantize_raw_chunk returns them) at LDS byte address `addr` of the staged word run: a
+// nibble pair, a byte, a halfword or whole words.  PER_LANE: `b` differs from lane to lane, and only its lower 16 bits count.
+template <int EPL, bool PER_LANE>
+__device__ __forceinline__ void stage_chunk(uint32_t addr, uint32_t b, const uint32_t (&q)[EPL / 4], int lane) {
+  typedef __attribute__((address_space(3))) uint8_t lds_u8;
+  uint8_t* at = (uint8_t*)(lds_u8*)(uintptr_t)addr;
+  if constexpr (EPL == 4) {
+    // 1 bit: the even lane takes its odd neighbour's nibble
+    auto nibbles = [&] {
+      const uint32_t bits = pack_codes<1>(q[0]), nb = dpp<kDppXor1>(bits, bits);
+      return (bits << 4) | nb;
+    };
+    if constexpr (PER_LANE) {
+      store_by_width<EPL>(addr, b, q[0], 0u, pack_codes<4>(q[0]), pack_codes<2>(q[0]), nibbles());
+    } else if (b == 1u) {
+      const uint32_t both = nibbles();
+      if ((lane & 1) == 0) *at = (uint8_t)both;
     } else if (b == 2u) {
-      stage8[addr] = (uint8_t)acc;
+      *at = (uint8_t)pack_codes<2>(q[0]);
     } else if (b == 4u) {
-      *reinterpret_cast<uint16_t*>(stage8 + addr) = (uint16_t)acc;
+      *reinterpret_cast<uint16_t*>(at) = (uint16_t)pack_codes<4>(q[0]);
     } else {
-      *reinterpret_cast<uint32_t*>(stage8 + addr) = acc;
+      *reinterpret_cast<uint32_t*>(at) = q[0];
     }
   } else {
-    if (b == 8u) {
-      *reinterpret_cast<uint2*>(stage8 + addr) = make_uint2(0u - n0, 0u - n1);
+    const uint32_t q0 = q[0], q1 = q[EPL / 4 - 1];
+    if constexpr (PER_LANE) {
+      store_by_width<EPL>(addr, b, q0, q1, pack_codes<4>(q0, q1), pack_codes<2>(q0, q1), pack_codes<1>(q0, q1));
+    } else if (b == 8u) {
+      *reinterpret_cast<uint2*>(at) = make_uint2(q0, q1);
+    } else if (b == 4u) {
+      *reinterpret_cast<uint32_t*>(at) = pack_codes<4>(q0, q1);
+    } else if (b == 2u) {
+      *reinterpret_cast<uint16_t*>(at) = (uint16_t)pack_codes<2>(q0, q1);
     } else {
-      const uint32_t both = 0u - ((n0 << (4u * b)) + n1);
-      if (b == 4u) {
-        *reinterpret_cast<uint32_t*>(stage8 + addr) = both;
-      } else if (b == 2u) {
-        *reinterpret_cast<uint16_t*>(stage8 + addr) = (uint16_t)both;
-      } else {
-        stage8[addr] = (uint8_t)both;
-      }
+      *at = (uint8_t)pack_codes<1>(q0, q1);
     }
   }
 }
@@ -483,13 +479,15 @@ __device__ __forceinline__ void quantize_pack_tile_body(
     // word in the packed buffer modulo 4: 16-byte pieces of the two then coincide.
     const uint32_t head = ((uint32_t)(reinterpret_cast<uintptr_t>(words) >> 2) + tile_base) & 3u;
 
-    // 2. random bytes of the tile (independent of the data; overlaps the loads' latency)
+    // 2. random bytes of the tile, complemented (independent of the data; overlaps the loads' latency)
     {
-      const uint64_t blk0 = (uint64_t)tile * (S::kElems / kElemsPerPhilox);
+      constexpr int kBlocks = S::kElems / kElemsPerPhilox;
+      static_assert((kBlocks & (kBlocks - 1)) == 0, "a tile's block numbers agree in their upper halves");
+      const uint64_t blk0 = (uint64_t)tile * kBlocks;
       uint4* dst = reinterpret_cast<uint4*>(lds.rand_bytes);
 #pragma unroll
       for (int m = 0; m < S::kPhilox; ++m)
-        dst[m * kWave + lane] = philox_block(blk0 + (uint64_t)(m * kWave + lane), seed_lo, seed_hi);
+        dst[m * kWave + lane] = philox_block<true>((uint32_t)blk0 + (uint32_t)(m * kWave + lane), (uint32_t)(blk0 >> 32), seed_lo, seed_hi);
     }
 
     // 3. per-group min/max: in-lane over the chunk, then across the group's lanes.
@@ -566,7 +564,7 @@ __device__ __forceinline__ void quantize_pack_tile_body(
         // A lane's bits are written as a byte (swizzle 3), a halfword (2) or whole words (0).
         const uint32_t lane_bits = (uint32_t)kEpl * my_b;
         const uint32_t swz = (lane_bits <= 8u) ? 3u : (lane_bits == 16u) ? 2u : 0u;
-        gi.b = my_b | (swz << 8);
+        gi.b = my_b | (swz << 24);
         gi.byte_off = stage_base + (woff + head) * 4u;
         lds.info[lane] = gi;
         if (METRICS) lds.gscale[lane] = s.scale;
@@ -611,9 +609,9 @@ __device__ __forceinline__ void quantize_pack_tile_body(
         uint32_t b, addr;
         if (kMixed) {
           const GroupInfo gi = lds.info[grp];
-          g_mn = gi.mn; g_invs = gi.invs; b = gi.b & 0xFFu;
+          g_mn = gi.mn; g_invs = gi.invs; b = gi.b;
           // byte address of this lane's bits: lig * (kEpl*b) bits = lig*b*kEpl/8 bytes
-          addr = (gi.byte_off + ((lig * b * (uint32_t)kEpl) >> 3)) ^ (gi.b >> 8);
+          addr = (gi.byte_off + (kEpl == 8 ? __umul24(lig, gi.b) : __umul24(lig, gi.b) >> 1)) ^ (gi.b >> 24);
         } else {
           const float2 mi = *reinterpret_cast<const float2*>(&lds.info[grp]);
           g_mn = mi.x; g_invs = mi.y; b = B;
@@ -621,12 +619,12 @@ __device__ __forceinline__ void quantize_pack_tile_body(
           constexpr uint32_t kSwz = (kLaneBits <= 8u) ? 3u : (kLaneBits == 16u) ? 2u : 0u;
           addr = (stage_base + head * 4u + (uint32_t)grp * (kGroupWords32 * B * 4u) + ((lig * kLaneBits) >> 3)) ^ kSwz;
         }
-        uint32_t n0, n1;
+        uint32_t q[kEpl / 4];
         [[maybe_unused]] const int valid = SHORT ? len - (u * kWave + lane) * kEpl : 8;         // elements from here to the end
         if constexpr (METRICS) {
           const float g_scale = lds.gscale[grp];
           float* sums = metric_sums[u & 1];
-          quantize_raw_chunk<DT, kExact2, true, SHORT>(raw[u], g_mn, g_invs, b, rnd[u], n0, n1, valid, g_scale, &sums[0],
+          quantize_raw_chunk<DT, kExact2, true, SHORT>(raw[u], g_mn, g_invs, rnd[u], q, valid, g_scale, &sums[0],
                                                        &sums[1], &sums[2]);
           if (u & 1) {                           // over the group's lanes, two loads at a time
             seg_sum6<S::kLaneLog2>(metric_sums[0], metric_sums[1]);
@@ -647,9 +645,9 @@ __device__ __forceinline__ void quantize_pack_tile_body(
             }
           }
         } else {
-          quantize_raw_chunk<DT, kExact2, false, SHORT>(raw[u], g_mn, g_invs, b, rnd[u], n0, n1);
+          quantize_raw_chunk<DT, kExact2, false, SHORT>(raw[u], g_mn, g_invs, rnd[u], q);
         }
-        stage_chunk_at<kEpl>(addr, b, n0, n1, lane);
+        stage_chunk<kEpl, kMixed>(addr, b, q, lane);
       }
     };
     if (need_exact2) quantize_tile(std::true_type{});
@@ -770,6 +768,7 @@ static_assert(kMaxBatch <= kBatchSlots, "one cumulative count per entry");
 // 1011.6 / 1007.9, four widths 922.6 / 905.4).
 template <int DT, int LPG_LOG2, int B>
 constexpr int list_max_waves() {
+  if (DT == kBF16 && LPG_LOG2 >= 5) return 4;                       // what all widths' registers allow, with short tiles and without
   return DT == kF32 && LPG_LOG2 == 10 ? 3 : tile_max_waves<DT, B, false>();
 }
 // SHORT: some tensors of the list end inside a tile.  Lists of whole tiles have the kernel without that code, and with it there

@@ -191,7 +191,7 @@ __device__ __forceinline__ void quantize_pack_units_body(
   const int lane = threadIdx.x & (kWave - 1);
   UnitLds<DT>& lds = unit_lds<DT>()[wave_in_block];
   [[maybe_unused]] auto& mlds = unit_metrics_lds<METRICS>()[wave_in_block];
-  uint8_t* stage8 = reinterpret_cast<uint8_t*>(lds.stage);
+  const uint32_t stage_base = (uint32_t)reinterpret_cast<uintptr_t>(lds.stage);      // LDS byte address, as in the tile kernel
 
   const int k = (SHORT || tile == n_tiles - 1) ? k_last : k_full;     // the last tile may hold fewer groups
   const uint32_t units = (uint32_t)(k * m);                  // units of the tile, <= 128
@@ -217,14 +217,14 @@ __device__ __forceinline__ void quantize_pack_units_body(
     tile_base = (uint32_t)tile * ((uint32_t)(k_full * m) * (uint32_t)B);
   }
 
-  // 2. random bytes of the tile (two Philox blocks per unit)
+  // 2. random bytes of the tile, complemented (two Philox blocks per unit)
   {
     const uint64_t blk0 = (uint64_t)tile * (uint64_t)((uint32_t)(k_full * m) * 2u);
     uint4* dst = reinterpret_cast<uint4*>(lds.rand_bytes);
 #pragma unroll
     for (int q = 0; q < S::kPhilox; ++q) {
       const uint32_t i = (uint32_t)(q * kWave + lane);
-      if (i < units * 2u) dst[i] = philox_block(blk0 + i, seed_lo, seed_hi);
+      if (i < units * 2u) dst[i] = philox_block<true>(blk0 + i, seed_lo, seed_hi);
     }
   }
 
@@ -261,8 +261,8 @@ __device__ __forceinline__ void quantize_pack_units_body(
       gi.invs = need_exact2 ? s.inv : invs;
       const uint32_t lane_bits = (uint32_t)kEpl * my_b;
       const uint32_t swz = (lane_bits <= 8u) ? 3u : (lane_bits == 16u) ? 2u : 0u;
-      gi.b = my_b | (swz << 8);
-      gi.byte_off = woff * 4u;
+      gi.b = my_b | (swz << 24);
+      gi.byte_off = stage_base + woff * 4u;
       lds.info[lane] = gi;
       if constexpr (METRICS) mlds.gscale[lane] = s.scale;
     }
@@ -300,18 +300,18 @@ __device__ __forceinline__ void quantize_pack_units_body(
         const uint32_t grp = __umul24(c >> S::kLanesLog2, magic) >> 16;   // unit / m
         const uint32_t lig = c - __umul24(grp, group_chunks);            // chunk inside its group
         const GroupInfo gi = lds.info[grp];
-        const uint32_t b = kMixed ? (gi.b & 0xFFu) : (uint32_t)B;
-        const uint32_t addr = (gi.byte_off + (__umul24(lig, b * (uint32_t)kEpl) >> 3)) ^ (gi.b >> 8);
-        uint32_t n0, n1;
+        const uint32_t b = kMixed ? gi.b : (uint32_t)B;
+        const uint32_t addr = (gi.byte_off + (kEpl == 8 ? __umul24(lig, b) : __umul24(lig, b) >> 1)) ^ (gi.b >> 24);
+        uint32_t q[kEpl / 4];
         const bool exact = kExact2 == 1 || (kExact2 == 2 && need_exact2);
         if constexpr (METRICS) {
           const int valid = SHORT ? len - (int)c * kEpl : 8;           // elements from here to the end
           const float g_scale = mlds.gscale[grp];
           float err, mag, var, unused = 0.0f;
           if (exact)
-            quantize_raw_chunk<DT, true, true, SHORT>(raw[u], gi.mn, gi.invs, b, rnd[u], n0, n1, valid, g_scale, &err, &mag, &var);
+            quantize_raw_chunk<DT, true, true, SHORT>(raw[u], gi.mn, gi.invs, rnd[u], q, valid, g_scale, &err, &mag, &var);
           else
-            quantize_raw_chunk<DT, false, true>(raw[u], gi.mn, gi.invs, b, rnd[u], n0, n1, 8, g_scale, &err, &mag, &var);
+            quantize_raw_chunk<DT, false, true>(raw[u], gi.mn, gi.invs, rnd[u], q, 8, g_scale, &err, &mag, &var);
           seg_sum2<S::kLanesLog2>(err, mag);       // over the unit's lanes (all valid, or none)
           seg_sum2<S::kLanesLog2>(var, unused);
           if ((lane & ((1 << S::kLanesLog2) - 1)) == (1 << S::kLanesLog2) - 1) {
@@ -320,10 +320,10 @@ __device__ __forceinline__ void quantize_pack_units_body(
             mlds.usum[2][c >> S::kLanesLog2] = var;
           }
         } else {
-          if (exact) quantize_raw_chunk<DT, true>(raw[u], gi.mn, gi.invs, b, rnd[u], n0, n1);
-          else       quantize_raw_chunk<DT, false>(raw[u], gi.mn, gi.invs, b, rnd[u], n0, n1);
+          if (exact) quantize_raw_chunk<DT, true, false, SHORT, true>(raw[u], gi.mn, gi.invs, rnd[u], q);
+          else       quantize_raw_chunk<DT, false, false, SHORT, true>(raw[u], gi.mn, gi.invs, rnd[u], q);
         }
-        stage_chunk<kEpl>(stage8, addr, b, n0, n1, lane);
+        stage_chunk<kEpl, kMixed>(addr, b, q, lane);
       }
     }
   };
@@ -356,7 +356,7 @@ __device__ __forceinline__ void quantize_pack_units_body(
 }
 
 template <int DT, int B, bool RELU = false, bool METRICS = false>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_quantize_pack_units(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DT == kBF16 && !METRICS ? 5 : 4, DT == kBF16 && !METRICS ? 5 : 8))) void k_quantize_pack_units(
     typename std::conditional<RELU, const u32x4*, const u32x4* __restrict__>::type x, int64_t n_tiles, int32_t m,
     int32_t k_full, int32_t k_last, uint32_t magic, int32_t part_log2,
     const uint8_t* __restrict__ bits, const uint32_t* __restrict__ off, uint32_t seed_lo, uint32_t seed_hi,
@@ -404,7 +404,7 @@ struct UnitBatch {
 };
 
 template <int DT, int B, bool SHORT>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(SHORT && DT == kBF16 && B != 8 ? 5 : 4)))
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DT == kBF16 ? 5 : 4, DT == kBF16 ? 5 : 8)))
 void k_quantize_pack_units_batch(const UnitBatch batch) {
   const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t gtile = (int64_t)blockIdx.x * kWavesPerBlock + wave_in_block;
