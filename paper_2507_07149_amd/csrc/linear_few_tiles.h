@@ -112,6 +112,21 @@ __global__ __launch_bounds__(S::kThreads, 1) void k_linear_few_tiles(
     else b[parity][j - kNB][ks] = *reinterpret_cast<const u32x4*>(pb[ks] + at + (j - kNB) * 32 * S::kRowBytes);
   };
 
+  constexpr int kGs = 1 << GS_LOG2, kWaveN = kNB * 32;
+  constexpr int kShare = kGs > kWaveN ? kGs / kWaveN : 1;               // waves (along n) that share a group
+  constexpr int kGroups = kGs > kWaveN ? 1 : kWaveN / kGs, kBlocksPerGroup = kNB / kGroups;
+  const int64_t m_lane = m0 + wm * kMB * 32 + li, n_lane = n0 + wn * kWaveN + lg * 16;
+  // the lane's groups' widths and offsets first: behind the stores of y a wait for them would be one for those too
+  [[maybe_unused]] uint32_t group_b[kMB][kGroups], group_off[kMB][kGroups];
+  if constexpr (QUANT && MIXED) {
+#pragma unroll
+    for (int i = 0; i < kMB * kGroups; ++i) {
+      const int64_t g = ((m_lane + i / kGroups * 32) * N + n0 + wn * kWaveN + i % kGroups * kGs) >> GS_LOG2;
+      group_b[i / kGroups][i % kGroups] = bits[g];
+      group_off[i / kGroups][i % kGroups] = off[g];
+    }
+  }
+
 #pragma unroll
   for (int st = 0; st < kStages; ++st)
 #pragma unroll
@@ -152,11 +167,7 @@ __global__ __launch_bounds__(S::kThreads, 1) void k_linear_few_tiles(
   wait_loads_and_reads<0>();
 
   // ---- epilogue ----
-  constexpr int kGs = 1 << GS_LOG2, kWaveN = kNB * 32;
-  constexpr int kShare = kGs > kWaveN ? kGs / kWaveN : 1;               // waves (along n) that share a group
-  constexpr int kGroups = kGs > kWaveN ? 1 : kWaveN / kGs, kBlocksPerGroup = kNB / kGroups;
   float xf[kMB][kNB][16], gmn[kMB][kGroups], gmx[kMB][kGroups];
-  const int64_t m_lane = m0 + wm * kMB * 32 + li, n_lane = n0 + wn * kWaveN + lg * 16;
 #pragma unroll
   for (int mb = 0; mb < kMB; ++mb) {
 #pragma unroll
@@ -205,8 +216,8 @@ __global__ __launch_bounds__(S::kThreads, 1) void k_linear_few_tiles(
 #pragma unroll
     for (int gi = 0; gi < kGroups; ++gi) {
       const int64_t g = (m * N + n0 + wn * kWaveN + gi * kGs) >> GS_LOG2;
-      const uint32_t gb = MIXED ? (uint32_t)bits[g] : uniform_b;
-      const uint32_t woff = MIXED ? off[g] : (uint32_t)(g * (int64_t)((kGs * uniform_b) >> 5));
+      const uint32_t gb = MIXED ? group_b[mb][gi] : uniform_b;
+      const uint32_t woff = MIXED ? group_off[mb][gi] : (uint32_t)(g * (int64_t)((kGs * uniform_b) >> 5));
       const GroupScale gs = group_scale(gmn[mb][gi], gmx[mb][gi], gb);
       if (lg == 0 && wn % kShare == 0) {
         out_min[g] = gs.mn;
