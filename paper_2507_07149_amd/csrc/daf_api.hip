@@ -111,6 +111,7 @@ int daf_plan(const int64_t* shape, int ndim, int32_t group_size, const uint8_t* 
   p->d_big_scratch = nullptr;
   p->d_scan = nullptr;
   p->scan_blocks = 0;
+  p->d_posts = nullptr;
   p->pending = 0;
   {
     const int64_t full = n / group_size, tail = n - full * group_size;
@@ -158,7 +159,7 @@ int daf_plan(const int64_t* shape, int ndim, int32_t group_size, const uint8_t* 
       break;
     }
     const size_t off_bytes = (((size_t)G * sizeof(uint32_t)) + 15) & ~(size_t)15;
-    const size_t sums_bytes = (((size_t)(n_blocks + 2) * sizeof(unsigned long long)) + 15) & ~(size_t)15;
+    const size_t sums_bytes = (((size_t)(n_blocks + 2 + daf_plan_scan_posts(G)) * sizeof(unsigned long long)) + 15) & ~(size_t)15;
     char* base = nullptr;
     if (hipMalloc(reinterpret_cast<void**>(&base), off_bytes + sums_bytes + (size_t)G) != hipSuccess) { rc = DAF_ENOMEM; break; }
     p->d_off = reinterpret_cast<uint32_t*>(base);          // the allocation's address: freed through d_off
@@ -167,9 +168,10 @@ int daf_plan(const int64_t* shape, int ndim, int32_t group_size, const uint8_t* 
     if (big && hipMalloc(&p->d_big_scratch, (size_t)big_bytes) != hipSuccess) { rc = DAF_ENOMEM; break; }
     p->d_scan = d_sums;
     p->scan_blocks = n_blocks;
+    p->d_posts = d_sums + n_blocks + 2;
     unsigned long long* d_total = d_sums + n_blocks;
     int* d_bad = reinterpret_cast<int*>(d_sums + n_blocks + 1);
-    if (daf_launch_plan_scan(bits, p->d_bits, G, n, group_size, p->d_off, d_sums, n_blocks, d_total, d_bad, st) != hipSuccess) { rc = DAF_EDEVICE; break; }
+    if (daf_launch_plan_scan(bits, p->d_bits, G, n, group_size, p->d_off, d_sums, n_blocks, d_total, d_bad, p->d_posts, true, st) != hipSuccess) { rc = DAF_EDEVICE; break; }
     if (hipMemcpyAsync(h_pinned, d_total, sizeof(ScanResult), hipMemcpyDeviceToHost, st) != hipSuccess) { rc = DAF_EDEVICE; break; }
     if (hipStreamSynchronize(st) != hipSuccess) { rc = DAF_EDEVICE; break; }
     h = *h_pinned;
@@ -189,18 +191,34 @@ namespace {
 struct ScanResult { unsigned long long total; int bad; int pad; };
 }
 
-int daf_plan_update(daf_plan_t* plan, const uint8_t* bits, void* stream) {
+namespace {
+int plan_update(daf_plan_t* plan, const uint8_t* bits, void* stream, int polls) {
   if (plan == nullptr || bits == nullptr) return DAF_EINVAL;
   if (plan->uniform_bits != 0 || plan->d_scan == nullptr) return DAF_EINVAL;   // per-group-width plans only
   if (plan->bound_words >= (int64_t)1 << 32) return DAF_EUNSUPPORTED;          // offsets are 32-bit words
   unsigned long long* d_total = plan->d_scan + plan->scan_blocks;
   int* d_bad = reinterpret_cast<int*>(plan->d_scan + plan->scan_blocks + 1);
   if (daf_launch_plan_scan(bits, plan->d_bits, plan->num_groups, plan->n, plan->group_size, plan->d_off, plan->d_scan,
-                           plan->scan_blocks, d_total, d_bad, static_cast<hipStream_t>(stream)) != hipSuccess)
+                           plan->scan_blocks, d_total, d_bad, plan->d_posts, false, static_cast<hipStream_t>(stream),
+                           polls) != hipSuccess)
     return DAF_EDEVICE;
   plan->pending = 1;
   plan->total_words = plan->bound_words;
   return DAF_OK;
+}
+}  // namespace
+
+int daf_plan_update(daf_plan_t* plan, const uint8_t* bits, void* stream) { return plan_update(plan, bits, stream, kPostPolls); }
+
+// For the tests, which make every workgroup do without the others' sums (polls 0).
+int daf_internal_plan_update(daf_plan_t* plan, const uint8_t* bits, int polls, void* stream) {
+  return plan_update(plan, bits, stream, polls);
+}
+int daf_internal_select_bits(const float* group_min, const float* group_max, int64_t num_groups, const uint8_t* classes,
+                             int32_t n_classes, uint8_t* out_bits, void* workspace, int polls, void* stream) {
+  const hipError_t e = daf_launch_select_bits(group_min, group_max, nullptr, 0, num_groups, classes, n_classes, out_bits,
+                                              workspace, static_cast<hipStream_t>(stream), polls);
+  return e == hipSuccess ? DAF_OK : DAF_EDEVICE;
 }
 
 int daf_plan_finish(daf_plan_t* plan, void* stream) {

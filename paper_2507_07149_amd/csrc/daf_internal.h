@@ -19,6 +19,7 @@ struct daf_plan_s {
                          // per group, written by the quantize call's first pass (else null)
   unsigned long long* d_scan;  // mixed plans: the scan's block sums, then the total and the invalid-width flag
   int64_t scan_blocks;
+  unsigned long long* d_posts; // what the workgroups of a width update tell each other, 0 between calls; inside the same allocation
   int64_t bound_words;   // packed size if every group had 8 bits: what total_words reads while an
                          // update's exact size has not been fetched (pending != 0)
   int32_t pending;
@@ -36,13 +37,19 @@ bool daf_quantize_reads_once(const daf_plan_t* plan);
 // unknown dtype.  A host computation.
 int daf_quantize_route(const daf_plan_t* plan, int dtype);
 
+// Where workgroups of one launch tell each other their sums: how often one looks for another's (about a microsecond each) before it
+// works the sum out itself.
+constexpr int kPostPolls = 256;
+
 // Launchers.  Each returns hipSuccess or the first HIP error.
 // src_bits: the caller's widths; plan_bits: the plan's copy, written by the scan with every width
 // outside {1,2,4,8} replaced by 8 (and *d_bad set).  No value needs clearing beforehand.
 hipError_t daf_launch_plan_scan(const uint8_t* src_bits, uint8_t* plan_bits, int64_t num_groups, int64_t n,
                                 int32_t group_size, uint32_t* d_off, unsigned long long* d_block_sums, int64_t n_blocks,
-                                unsigned long long* d_total, int* d_bad, hipStream_t stream);
+                                unsigned long long* d_total, int* d_bad, unsigned long long* d_posts, bool new_plan,
+                                hipStream_t stream, int polls = kPostPolls);
 int64_t daf_plan_scan_blocks(int64_t num_groups);
+int64_t daf_plan_scan_posts(int64_t num_groups);
 
 // out_metrics: null, or 3 floats per group (sum (x-xhat)^2, sum x^2, rounding variance); not with groups longer than a tile.
 // out_relu_y: null, or the buffer that receives max(x, +0), which is then what gets quantized (may be x
@@ -97,4 +104,4 @@ hipError_t daf_launch_linear_quantize_pack(const daf_plan_t* plan, const void* x
 // with b = prev_bits[g] (device) or prev_uniform when prev_bits is null.
 hipError_t daf_launch_select_bits(const float* gmin, const float* gmax, const uint8_t* prev_bits, int32_t prev_uniform,
                                   int64_t num_groups, const uint8_t* classes, int n_classes, uint8_t* out_bits,
-                                  void* workspace, hipStream_t stream);
+                                  void* workspace, hipStream_t stream, int polls = kPostPolls);

@@ -2,10 +2,10 @@
 //
 // The packed buffer concatenates the groups' codes (paper Sec. 3.3 speaks of packing the
 // compressed values together); with a bit width per group the position of group g is the
-// sum of the word counts of all groups before it.  Up to kAheadMost groups one launch does it (k_plan_ahead); up
-// to kMaxSummedBlocks blocks of 2048 groups, per-block sums and a second launch in which every
-// block adds up the sums before its own and writes its offsets (5.6 M groups: 27 -> 23 us with the launch between
-// the two gone, 197 K: 11.6 -> 9.4); beyond that a single-block scan of the sums comes between them.
+// sum of the word counts of all groups before it.  Up to kAheadMost groups one launch does it (k_plan_ahead); new widths for a
+// plan that exists take one launch as well, whose workgroups tell each other their sums (k_plan_once).  A new plan of
+// up to kMaxSummedBlocks blocks of 2048 groups: per-block sums and a second launch in which every
+// block adds up the sums before its own and writes its offsets; beyond that a single-block scan of the sums comes between them.
 #include "daf_device.h"
 #include "daf_internal.h"
 
@@ -73,7 +73,12 @@ constexpr unsigned long long kBadBit = 1ull << 63;
 __global__ __launch_bounds__(kThreads) void k_plan_block_sums(const uint8_t* __restrict__ src_bits,
                                                               uint8_t* __restrict__ plan_bits,
                                                               int64_t num_groups, int64_t n, int32_t gs,
-                                                              unsigned long long* __restrict__ block_sums) {
+                                                              unsigned long long* __restrict__ block_sums,
+                                                              unsigned long long* __restrict__ posts) {
+  if (posts != nullptr && threadIdx.x == 0) {            // a new plan's: empty, as k_plan_once leaves them
+    posts[blockIdx.x] = 0ull;
+    if (blockIdx.x == 0) posts[gridDim.x] = 0ull;
+  }
   __shared__ unsigned long long lds[4];
   const int64_t base = (int64_t)blockIdx.x * kBlockGroups + (int64_t)threadIdx.x * kItems;
   unsigned long long s = 0;
@@ -222,20 +227,29 @@ __global__ __launch_bounds__(kThreads) void k_plan_write_offsets(const uint8_t* 
 constexpr int kAheadThreads = 1024;
 constexpr int kAheadGroups = kItems * kAheadThreads;
 
+// Not 0 where one of the four bytes is none of 1, 2, 4, 8: a bit above the lowest four; more than one bit; no bit (without
+// the first no carry leaves a byte).
+__device__ __forceinline__ uint32_t wrong_widths(uint32_t w) {
+  return (w & 0xF0F0F0F0u) | (w & (w - 0x01010101u)) | (~(w + 0x7F7F7F7Fu) & 0x80808080u);
+}
+// The four bytes with 8 in the place of every wrong width.
+__device__ __forceinline__ uint32_t mended_widths(uint32_t w) {
+  for (int j = 0; j < 32; j += 8) {
+    const uint32_t b = (w >> j) & 0xFFu;
+    if (b != 1u && b != 2u && b != 4u) w = (w & ~(0xFFu << j)) | (8u << j);
+  }
+  return w;
+}
+
 // The sum of the widths of sixteen groups, one to a byte; a width outside {1,2,4,8} counts as 8 and is reported.
 __device__ __forceinline__ uint32_t sixteen_widths(const uint4& v, int* bad) {
   uint32_t w[4] = {v.x, v.y, v.z, v.w};
   uint32_t wrong = 0u;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)      // a bit above the lowest four; more than one bit; no bit (without the first no carry leaves a byte)
-    wrong |= (w[i] & 0xF0F0F0F0u) | (w[i] & (w[i] - 0x01010101u)) | (~(w[i] + 0x7F7F7F7Fu) & 0x80808080u);
+  for (int i = 0; i < 4; ++i) wrong |= wrong_widths(w[i]);
   if (wrong != 0u) {
     *bad = 1;
-    for (int i = 0; i < 4; ++i)
-      for (int j = 0; j < 32; j += 8) {
-        const uint32_t b = (w[i] >> j) & 0xFFu;
-        if (b != 1u && b != 2u && b != 4u) w[i] = (w[i] & ~(0xFFu << j)) | (8u << j);
-      }
+    for (int i = 0; i < 4; ++i) w[i] = mended_widths(w[i]);
   }
   uint32_t sum = 0u;
 #pragma unroll
@@ -322,14 +336,187 @@ __global__ __launch_bounds__(kAheadThreads) void k_plan_ahead(const uint8_t* __r
 // launches 62.0 -> 65.4 us, at 524288 51.4 -> 60.3).
 constexpr int64_t kAheadMost = 1 << 16;
 constexpr int64_t kMaxSummedBlocks = 4096;            // 32 KB of block sums, read by every block
+// Rounds of k_plan_once: launches one behind the other, one / two / four rounds: 197 K groups 6.7 / 8.6 / 12.2 us, 1 M 8.3 / 9.0 / 12.3, 2 M
+// 11.9 / 9.7 / 12.7, 3 M 15.7 / 12.1 / 12.8, 5.6 M 26 / 19 / 14 (17 on another card), 9.4 M 39 / 27 / 25.  Two launches before: 197 K 8.9, 1 M 10.0, 2 M 12.4,
+// 5.6 M 23.0.
+constexpr int64_t kOnceRounds2 = 5 << 18, kOnceRounds4 = 13 << 18;
+
+
+// One launch for any number of groups.  Every workgroup posts the sum of its own groups' words, takes the sums of those before
+// it from their posts, all at a time, and writes its offsets: widths are read once, and the second launch, its gap and its reading of
+// the widths fall away.  Two launches are bound by latency where there are few groups (197 K: 4.7 + 4.7 us and the gap) and by the rate at
+// which waves can be started where there are many (5.6 M in blocks of 2048: 11 + 14.5 us, where 34 MB move): so a thread has
+// ROUNDS times kItems groups, every kItems of them behind another's of the same round.
+//
+// Nothing waits for long: a post that is not there after `polls` looks (about a microsecond each) is done without, and the workgroup adds up
+// the widths of all groups before its own itself.  So the result needs no order of the workgroups and no
+// two of them at the same time.
+//
+// posts[0 .. gridDim.x) are 0 when the launch begins, and so is `finished`; the last workgroup to finish leaves them so
+// again.  A post is an exchange whose result is waited for before the workgroup counts itself as finished: it
+// cannot arrive behind that clearing.
+//
+// Sums of a workgroup's words stay below 2^32: group sizes up to kOnceMostSize.
+constexpr unsigned long long kPosted = 1ull << 62;
+constexpr int kOnceThreads = 512;
+constexpr int32_t kOnceMostSize = 1 << 18;
+
+template <int ROUNDS>
+__global__ __launch_bounds__(kOnceThreads) void k_plan_once(const uint8_t* __restrict__ src_bits, uint8_t* __restrict__ plan_bits,
+                                                            int64_t num_groups, int64_t n, int32_t gs, uint32_t* __restrict__ off,
+                                                            unsigned long long* __restrict__ posts,
+                                                            unsigned long long* __restrict__ finished,
+                                                            unsigned long long* __restrict__ total, int* __restrict__ bad_flag,
+                                                            int polls) {
+  constexpr int kWaves = kOnceThreads / daf::kWave, kRound = kOnceThreads * kItems;
+  static_assert((long long)ROUNDS * kRound * (kOnceMostSize / 4) < 1ll << 32, "a workgroup's words in 32 bits");
+  __shared__ uint32_t wave_tot[ROUNDS * kWaves];
+  __shared__ unsigned long long wave_sum[kWaves];
+  __shared__ bool last_to_finish;
+  const int64_t first = (int64_t)blockIdx.x * (ROUNDS * kRound);
+  const int lane = threadIdx.x & (daf::kWave - 1), wave = threadIdx.x >> 6;
+  const uint32_t per_bit = (uint32_t)gs >> 5;            // words of a whole group and bit of width, at most 2^13
+  // Eight widths to a register pair.  Where all eight groups are there and none is the tensor's last, sums are dot products and
+  // offsets one multiplication each: group by group, 32 groups a thread took 8 us of vector instructions.
+  const bool aligned = (reinterpret_cast<uintptr_t>(src_bits) & 7u) == 0u, aligned_copy = (reinterpret_cast<uintptr_t>(plan_bits) & 7u) == 0u;
+  auto base_of = [&](int r) { return first + r * kRound + (int64_t)threadIdx.x * kItems; };
+  auto whole = [&](int r) { return base_of(r) + kItems < num_groups; };
+  auto byte_of = [](const uint2& v, int i) { return ((i < 4 ? v.x : v.y) >> (8 * (i & 3))) & 0xFFu; };
+  auto words_of = [&](uint32_t width, int64_t g) {       // of a valid width
+    int unused = 0;
+    return g == num_groups - 1 ? group_words(width, g, num_groups, n, gs, &unused) : per_bit * width;
+  };
+  uint2 b[ROUNDS];
+  uint32_t s[ROUNDS], incl[ROUNDS];
+  int bad = 0;
+  if (aligned && first + ROUNDS * kRound < num_groups) {                    // all loads under way together
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) b[r] = *reinterpret_cast<const uint2*>(src_bits + base_of(r));
+  } else {
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      b[r] = make_uint2(0u, 0u);
+#pragma unroll
+      for (int i = 0; i < kItems; ++i) {
+        const uint32_t v = base_of(r) + i < num_groups ? (uint32_t)src_bits[base_of(r) + i] : 0u;
+        (i < 4 ? b[r].x : b[r].y) |= v << (8 * (i & 3));
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    if (whole(r)) {
+      if ((wrong_widths(b[r].x) | wrong_widths(b[r].y)) != 0u) {
+        bad = 1;
+        b[r] = make_uint2(mended_widths(b[r].x), mended_widths(b[r].y));
+      }
+      s[r] = per_bit * __builtin_amdgcn_udot4(b[r].x, 0x01010101u, __builtin_amdgcn_udot4(b[r].y, 0x01010101u, 0u, false), false);
+    } else {
+      const uint2 mended = make_uint2(mended_widths(b[r].x), mended_widths(b[r].y));
+      s[r] = 0u;
+      for (int i = 0; i < kItems; ++i) {
+        if (base_of(r) + i >= num_groups) break;
+        bad |= byte_of(b[r], i) != byte_of(mended, i) ? 1 : 0;
+        s[r] += words_of(byte_of(mended, i), base_of(r) + i);
+      }
+      b[r] = mended;
+    }
+    incl[r] = daf::wave_inclusive_sum(s[r]);
+    if (lane == daf::kWave - 1) wave_tot[r * kWaves + wave] = incl[r];
+  }
+  const int any_bad = __syncthreads_or(bad);
+  uint32_t own = 0u, before[ROUNDS];                     // words of the workgroup, and before the wave's of each round
+#pragma unroll
+  for (int i = 0; i < ROUNDS * kWaves; ++i) {
+    if (i % kWaves == wave) before[i / kWaves] = own;
+    own += wave_tot[i];
+  }
+  unsigned long long posted = 0;
+  if (threadIdx.x == 0)
+    posted = __hip_atomic_exchange(&posts[blockIdx.x], own | kPosted | (any_bad ? kBadBit : 0ull), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    if (aligned_copy && whole(r)) {
+      *reinterpret_cast<uint2*>(plan_bits + base_of(r)) = b[r];
+    } else {
+      for (int i = 0; i < kItems; ++i)
+        if (base_of(r) + i < num_groups) plan_bits[base_of(r) + i] = (uint8_t)byte_of(b[r], i);
+    }
+  }
+
+  unsigned long long ahead = 0;
+  int missed = 0, bad_ahead = 0;
+  for (unsigned i = threadIdx.x; i < blockIdx.x; i += kOnceThreads) {
+    unsigned long long v = 0;
+    for (int p = 0; p < polls && !(v & kPosted); ++p) v = __hip_atomic_load(&posts[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    missed |= (v & kPosted) ? 0 : 1;
+    bad_ahead |= (v & kBadBit) ? 1 : 0;
+    ahead += v & ~(kBadBit | kPosted);
+  }
+  if (__syncthreads_or(missed)) {
+    ahead = 0;
+    for (int64_t g0 = (int64_t)threadIdx.x * kItems; g0 < first; g0 += kRound) {
+      uint32_t earlier[kItems];
+      load_widths(src_bits, g0, num_groups, earlier);
+#pragma unroll
+      for (int i = 0; i < kItems; ++i) {
+        int bad_here = 0;
+        const uint32_t words = group_words(earlier[i], g0 + i, num_groups, n, gs, &bad_here);
+        ahead += bad_here ? 8u * per_bit : words;
+        bad_ahead |= bad_here;
+      }
+    }
+  }
+  // (all posts this workgroup wants are read: it may count itself as finished, and its offsets go out meanwhile)
+  unsigned long long others = 0;
+  if (threadIdx.x == 0) {
+    asm volatile("" : : "v"((uint32_t)posted) : "memory");                 // the exchange is done
+    others = __hip_atomic_fetch_add(finished, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  for (int o = 32; o > 0; o >>= 1) ahead += __shfl_xor(ahead, o);
+  if (lane == daf::kWave - 1) wave_sum[wave] = ahead;
+  const int any_bad_ahead = __syncthreads_or(bad_ahead);
+  ahead = 0;
+#pragma unroll
+  for (int i = 0; i < kWaves; ++i) ahead += wave_sum[i];
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    uint32_t w[kItems];
+    if (whole(r)) {
+#pragma unroll
+      for (int i = 0; i < kItems; ++i) w[i] = __umul24(byte_of(b[r], i), per_bit);
+    } else {
+#pragma unroll
+      for (int i = 0; i < kItems; ++i) w[i] = base_of(r) + i < num_groups ? words_of(byte_of(b[r], i), base_of(r) + i) : 0u;
+    }
+    store_offsets(off, base_of(r), num_groups, (uint32_t)ahead + before[r] + incl[r] - s[r], w);
+  }
+  if (threadIdx.x == 0) {
+    if (blockIdx.x == gridDim.x - 1) {
+      *total = ahead + own;
+      *bad_flag = (any_bad || any_bad_ahead) ? 1 : 0;
+    }
+    last_to_finish = others == gridDim.x - 1u;
+  }
+  __syncthreads();
+  if (last_to_finish) {
+    for (unsigned i = threadIdx.x; i < gridDim.x; i += kOnceThreads)
+      __hip_atomic_store(&posts[i], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) __hip_atomic_store(finished, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
 
 }  // namespace
 
 int64_t daf_plan_scan_blocks(int64_t num_groups) { return (num_groups + kBlockGroups - 1) / kBlockGroups; }
 
+int64_t daf_plan_scan_posts(int64_t num_groups) { return daf_plan_scan_blocks(num_groups) + 1; }
+
 hipError_t daf_launch_plan_scan(const uint8_t* src_bits, uint8_t* plan_bits, int64_t num_groups, int64_t n,
                                 int32_t group_size, uint32_t* d_off, unsigned long long* d_block_sums, int64_t n_blocks,
-                                unsigned long long* d_total, int* d_bad, hipStream_t stream) {
+                                unsigned long long* d_total, int* d_bad, unsigned long long* d_posts, bool new_plan,
+                                hipStream_t stream, int polls) {
   const bool apart = src_bits + num_groups <= plan_bits || plan_bits + num_groups <= src_bits;
   const bool aligned = (reinterpret_cast<uintptr_t>(src_bits) & 15u) == 0u;
   if (num_groups <= kAheadGroups || (num_groups <= kAheadMost && apart && aligned)) {
@@ -338,8 +525,18 @@ hipError_t daf_launch_plan_scan(const uint8_t* src_bits, uint8_t* plan_bits, int
                        src_bits, plan_bits, num_groups, n, group_size, d_off, d_total, d_bad);
     return hipGetLastError();
   }
+  // (A new plan's posts are empty once k_plan_block_sums has been through.  Widths in the plan's own copy would be replaced while
+  // others read them.)
+  if (!new_plan && num_groups > kAheadMost && apart && group_size <= kOnceMostSize) {
+    const int rounds = num_groups > kOnceRounds4 ? 4 : num_groups > kOnceRounds2 ? 2 : 1;
+    const int64_t per_block = (int64_t)rounds * kOnceThreads * kItems;
+    hipLaunchKernelGGL(rounds == 4 ? k_plan_once<4> : rounds == 2 ? k_plan_once<2> : k_plan_once<1>, dim3((unsigned)((num_groups + per_block - 1) / per_block)),
+                       dim3(kOnceThreads), 0, stream, src_bits, plan_bits, num_groups, n, group_size, d_off, d_posts,
+                       d_posts + n_blocks, d_total, d_bad, polls);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_plan_block_sums, dim3((unsigned)n_blocks), dim3(kThreads), 0, stream, src_bits, plan_bits,
-                     num_groups, n, group_size, d_block_sums);
+                     num_groups, n, group_size, d_block_sums, new_plan ? d_posts : nullptr);
   if (n_blocks <= kMaxSummedBlocks) {
     hipLaunchKernelGGL(k_plan_write_offsets<false>, dim3((unsigned)n_blocks), dim3(kThreads), 0, stream, plan_bits,
                        num_groups, n, group_size, d_block_sums, d_off, d_total, d_bad);

@@ -16,13 +16,12 @@
 //
 // Up to kRankMost groups: one launch in which the ranks are counted (k_select_rank); where the widths of an earlier call are
 // replaced in place, up to kSmallGroups, one workgroup that keeps the keys in registers (k_select_small).  More, or widths
-// over the other inputs: six launches: zero the first counters; write the keys and count their first digit (and zero the
-// other counters); count the second digit; count the third; count the keys equal to T_k per block of 4096
-// groups; classify.  What a pass decides (the bin that holds the rank) is worked out from its counters by
+// over the other inputs: five launches: zero the first counters; write the keys and count their first digit (and zero the
+// other counters); count the second digit; count the third; classify, with the keys equal to T_k counted by the way
+// (k_select_classify).  What a pass decides (the bin that holds the rank) is worked out from its counters by
 // every workgroup of the next launch for itself: a scan of 2048 counters from the cache, next to the
 // keys that are on their way, instead of a ticket, a last workgroup and its trips past the caches at the end
-// of every launch.  The same for the ties: a block of the last launch adds up the tie counts of the blocks
-// before it.  Nothing crosses workgroups inside a launch.  Selection alone, four classes, before (ticket and last
+// of every launch.  Selection alone, four classes, before (ticket and last
 // workgroup in four of six launches) and now: 500 groups 39 / 14 us, 8192 40 / 20, 197 K 49 / 29, 1 M 54 / 34, 5.6 M 94 / 66;
 // all ranges equal: 197 K 53 / 38, 5.6 M 127 / 104.
 #include "daf_device.h"
@@ -204,16 +203,18 @@ template <bool FROM_SCALE>
 __global__ __launch_bounds__(kThreads) void k_select_keys(const float* __restrict__ gmin, const float* __restrict__ gmax,
                                                           const uint8_t* __restrict__ prev_bits, uint32_t prev_uniform,
                                                           int64_t G, uint32_t* __restrict__ keys,
-                                                          SelectState* __restrict__ st, int n_thresholds) {
+                                                          SelectState* __restrict__ st, int n_thresholds,
+                                                          unsigned long long* __restrict__ posts, int64_t n_blocks) {
   constexpr int kLoads = 8;
   __shared__ __attribute__((aligned(16))) uint32_t lh[kBins * kLdsCopies0];
   for (int i = threadIdx.x; i < kBins * kLdsCopies0 / 4; i += kThreads)
     reinterpret_cast<uint4*>(lh)[i] = make_uint4(0u, 0u, 0u, 0u);
-  {                                                       // the later passes' counters
+  {                                                       // the later passes' counters, and the posts
     uint4* later = reinterpret_cast<uint4*>(&st->hist[1][0][0][0]);
     constexpr int kPieces = (kPasses - 1) * kHistCopies * kMaxThresholds * kBins / 4;
     for (int i = blockIdx.x * kThreads + threadIdx.x; i < kPieces; i += gridDim.x * kThreads)
       later[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n_blocks; i += (int64_t)gridDim.x * kThreads) posts[i] = 0ull;
   }
   __syncthreads();
   const int lane = threadIdx.x & (kWave - 1);
@@ -338,55 +339,6 @@ __device__ __forceinline__ void load_keys(const uint32_t* __restrict__ keys, int
     if (base + i >= G) key[i] = 0xFFFFFFFFu;
 }
 
-// Per block of 4096 consecutive groups: how many keys equal each threshold.
-__global__ __launch_bounds__(kThreads) void k_select_ties(const uint32_t* __restrict__ keys, int64_t G,
-                                                          SelectState* __restrict__ st, Ranks ranks, int n_thresholds,
-                                                          uint32_t* __restrict__ block_ties, int64_t n_blocks) {
-  __shared__ uint32_t cnt[kMaxThresholds];
-  __shared__ uint32_t wave_tot[kThreads / kWave];
-  __shared__ Decided shared;
-  const Decided d = decided_after<kPasses - 1>(st, ranks, n_thresholds, wave_tot, &shared);
-  for (int64_t b = blockIdx.x; b < n_blocks; b += gridDim.x) {
-    if (threadIdx.x < kMaxThresholds) cnt[threadIdx.x] = 0u;
-    __syncthreads();
-    const int64_t base = b * kBlockGroups + (int64_t)threadIdx.x * kItems;
-    uint32_t c[kMaxThresholds] = {0u, 0u, 0u};
-    uint32_t key[kItems];
-    load_keys(keys, base, G, key);
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-      if (base + i < G) {
-#pragma unroll
-        for (int k = 0; k < kMaxThresholds; ++k)
-          if (k < n_thresholds) c[k] += (key[i] == d.prefix[k]) ? 1u : 0u;
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < kMaxThresholds; ++k)
-      if (k < n_thresholds && c[k]) atomicAdd(&cnt[k], c[k]);
-    __syncthreads();
-    if (threadIdx.x < (unsigned)n_thresholds) block_ties[(int64_t)threadIdx.x * n_blocks + b] = cnt[threadIdx.x];
-    __syncthreads();
-  }
-}
-
-// More blocks than a block of k_select_classify wants to add up: their tie counts become running sums first
-// (one workgroup per threshold).
-constexpr int64_t kMaxSummedBlocks = 2048;
-__global__ __launch_bounds__(kThreads) void k_select_scan_ties(uint32_t* __restrict__ block_ties, int64_t n_blocks) {
-  __shared__ uint32_t wave_tot[kThreads / kWave];
-  uint32_t* ties = block_ties + (int64_t)blockIdx.x * n_blocks;
-  uint32_t carry = 0u;
-  for (int64_t i0 = 0; i0 < n_blocks; i0 += kThreads) {
-    const int64_t i = i0 + threadIdx.x;
-    const uint32_t v = i < n_blocks ? ties[i] : 0u;
-    uint32_t total;
-    const uint32_t before = block_exclusive_sum(v, wave_tot, &total);
-    if (i < n_blocks) ties[i] = carry + before;
-    carry += total;
-  }
-}
-
 // Eight widths of consecutive groups, bytes of two words, `count` of them inside the array.
 __device__ __forceinline__ void store_widths(uint8_t* __restrict__ out, const uint8_t (&w)[kItems], int64_t count) {
   if (count >= kItems && (reinterpret_cast<uintptr_t>(out) & 7u) == 0u) {
@@ -400,47 +352,131 @@ __device__ __forceinline__ void store_widths(uint8_t* __restrict__ out, const ui
   }
 }
 
-// rank(g) >= R_k  iff  key_g > T_k, or key_g == T_k and at least E_k equal keys come before g.
+// rank(g) >= R_k  iff  key_g > T_k, or key_g == T_k and at least E_k equal keys come before g.  A block of 4096 groups posts
+// how many of its keys equal each T_k, and one that has such keys takes the counts of the blocks before it from their posts.
+// (Counting in a launch of its own and classifying in the next: 197 K groups 4.4 + 5.2 us and the gap.)
+// Nothing waits for long: a post that is not there after `polls` looks (about a microsecond each) is done without, and the block
+// counts the equal keys before its own itself.  So the result needs no order of the workgroups and no two of them
+// at the same time.  The posts were emptied by k_select_keys.
+constexpr unsigned long long kPosted = 1ull << 63;
+constexpr int kPostBits = 16;                            // of one threshold's count, at most kBlockGroups
+// ROUNDS: a workgroup has that many blocks of 4096 groups, a wave the 512 * ROUNDS next to each other (what is decided
+// is worked out once for all of them, and fewer waves have to be started).
+constexpr int kMostRounds = 2;
+static_assert(kMostRounds * kBlockGroups < 1 << kPostBits && kMaxThresholds * kPostBits < 63, "a post holds the counts of all thresholds");
+
+template <int ROUNDS>
 __global__ __launch_bounds__(kThreads) void k_select_classify(const uint32_t* __restrict__ keys, int64_t G,
-                                                              const SelectState* __restrict__ st, int n_thresholds,
-                                                              uint32_t classes_packed, const uint32_t* __restrict__ block_ties,
-                                                              int64_t n_blocks, bool scanned, uint8_t* __restrict__ out_bits) {
-  __shared__ uint32_t wave_tot[kThreads / kWave];
-  const int64_t base = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * kItems;
-  uint32_t key[kItems];
-  load_keys(keys, base, G, key);
-  uint8_t w[kItems];
-  uint32_t cls[kItems];
+                                                              SelectState* __restrict__ st, Ranks ranks, int n_thresholds,
+                                                              uint32_t classes_packed, unsigned long long* __restrict__ posts,
+                                                              int polls, uint8_t* __restrict__ out_bits) {
+  constexpr int kWaves = kThreads / kWave, kWaveGroups = kWave * kItems;
+  __shared__ uint32_t wave_tot[kWaves], wave_equal[kMaxThresholds][kWaves], wave_ahead[kMaxThresholds][kWaves];
+  __shared__ Decided shared;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+  const int64_t first = (int64_t)blockIdx.x * (ROUNDS * kBlockGroups);
+  auto base_of = [&](int r) { return first + (wave * ROUNDS + r) * kWaveGroups + lane * kItems; };
+  uint32_t key[ROUNDS][kItems], cls[ROUNDS][kItems];
 #pragma unroll
-  for (int i = 0; i < kItems; ++i) cls[i] = 0u;
-  for (int k = 0; k < n_thresholds; ++k) {
-    const uint32_t T = st->after[kPasses - 1].prefix[k], E = st->after[kPasses - 1].rank[k];      // (uniform)
-    uint32_t before = 0u;                                  // equal keys before the thread's first
-    if (E != 0u) {                                         // (0: every equal key counts)
-      const uint32_t* ties = block_ties + (int64_t)k * n_blocks;
-      uint32_t total, sum = 0u;
-      if (scanned) {
-        sum = ties[blockIdx.x];
-      } else {
-        for (int64_t i = threadIdx.x; i < (int64_t)blockIdx.x; i += kThreads) sum += ties[i];
-        (void)block_exclusive_sum(sum, wave_tot, &total);
-        sum = total;
+  for (int r = 0; r < ROUNDS; ++r) {
+    load_keys(keys, base_of(r), G, key[r]);
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) cls[r][i] = 0u;
+  }
+  if (n_thresholds > 0) {
+    const Decided d = decided_after<kPasses - 1>(st, ranks, n_thresholds, wave_tot, &shared);
+    uint32_t before[kMaxThresholds][ROUNDS];             // equal keys before a thread's first of a round, in the wave, then in all
+#pragma unroll
+    for (int k = 0; k < kMaxThresholds; ++k) {
+      uint32_t carry = 0u;
+#pragma unroll
+      for (int r = 0; r < ROUNDS; ++r) {
+        before[k][r] = 0u;
+        if (k >= n_thresholds || d.rank[k] == 0u) continue;            // (E_k = 0: every equal key counts)
+        uint32_t mine = 0u;
+#pragma unroll
+        for (int i = 0; i < kItems; ++i) mine += (base_of(r) + i < G && key[r][i] == d.prefix[k]) ? 1u : 0u;
+        const uint32_t incl = wave_inclusive_sum(mine);
+        before[k][r] = carry + incl - mine;
+        carry += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
       }
-      uint32_t mine = 0u;
+      if (lane == 0) wave_equal[k][wave] = carry;
+    }
+    __syncthreads();
+    uint32_t wanted = 0u;
+    unsigned long long post = kPosted;
 #pragma unroll
-      for (int i = 0; i < kItems; ++i) mine += (base + i < G && key[i] == T) ? 1u : 0u;
-      before = sum + block_exclusive_sum(mine, wave_tot, &total);
+    for (int k = 0; k < kMaxThresholds; ++k) {
+      uint32_t earlier = 0u, total = 0u;
+#pragma unroll
+      for (int v = 0; v < kWaves; ++v) {
+        const uint32_t c = wave_equal[k][v];
+        earlier += v < wave ? c : 0u;
+        total += c;
+      }
+#pragma unroll
+      for (int r = 0; r < ROUNDS; ++r) before[k][r] += earlier;
+      post |= (unsigned long long)total << (k * kPostBits);
+      wanted |= total;
+    }
+    if (threadIdx.x == 0) __hip_atomic_store(&posts[blockIdx.x], post, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (wanted != 0u && blockIdx.x > 0u) {               // (the same in all threads)
+      uint32_t c[kMaxThresholds] = {0u, 0u, 0u};
+      int missed = 0;
+      for (unsigned i = threadIdx.x; i < blockIdx.x; i += kThreads) {
+        unsigned long long v = 0ull;
+        for (int p = 0; p < polls && !(v & kPosted); ++p) v = __hip_atomic_load(&posts[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        missed |= (v & kPosted) ? 0 : 1;
+#pragma unroll
+        for (int k = 0; k < kMaxThresholds; ++k) c[k] += (uint32_t)(v >> (k * kPostBits)) & ((1u << kPostBits) - 1u);
+      }
+      if (__syncthreads_or(missed)) {
+#pragma unroll
+        for (int k = 0; k < kMaxThresholds; ++k) c[k] = 0u;
+        for (int64_t g0 = (int64_t)threadIdx.x * kItems; g0 < first; g0 += kBlockGroups) {
+          uint32_t other[kItems];
+          load_keys(keys, g0, G, other);
+#pragma unroll
+          for (int i = 0; i < kItems; ++i)
+#pragma unroll
+            for (int k = 0; k < kMaxThresholds; ++k) c[k] += k < n_thresholds && other[i] == d.prefix[k] ? 1u : 0u;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kMaxThresholds; ++k) {
+        const uint32_t sum = wave_inclusive_sum(c[k]);
+        if (lane == kWave - 1) wave_ahead[k][wave] = sum;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < kMaxThresholds; ++k)
+#pragma unroll
+        for (int v = 0; v < kWaves; ++v)
+#pragma unroll
+          for (int r = 0; r < ROUNDS; ++r) before[k][r] += wave_ahead[k][v];
     }
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-      const bool equal = key[i] == T;
-      if (key[i] > T || (equal && before >= E)) ++cls[i];
-      before += equal ? 1u : 0u;
+    for (int k = 0; k < kMaxThresholds; ++k) {
+      if (k >= n_thresholds) continue;
+      const uint32_t T = d.prefix[k], E = d.rank[k];
+#pragma unroll
+      for (int r = 0; r < ROUNDS; ++r) {
+#pragma unroll
+        for (int i = 0; i < kItems; ++i) {
+          const bool equal = key[r][i] == T;
+          if (key[r][i] > T || (equal && before[k][r] >= E)) ++cls[r][i];
+          before[k][r] += equal ? 1u : 0u;
+        }
+      }
     }
   }
 #pragma unroll
-  for (int i = 0; i < kItems; ++i) w[i] = (uint8_t)(classes_packed >> (8u * cls[i]));
-  if (base < G) store_widths(out_bits + base, w, G - base);
+  for (int r = 0; r < ROUNDS; ++r) {
+    uint8_t w[kItems];
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) w[i] = (uint8_t)(classes_packed >> (8u * cls[r][i]));
+    if (base_of(r) < G) store_widths(out_bits + base_of(r), w, G - base_of(r));
+  }
 }
 
 // ---- few groups: one workgroup, the keys in registers ------------------------------------------------------------
@@ -650,6 +686,11 @@ __global__ __launch_bounds__(kRankThreads) void k_select_rank(const float* __res
   }
 }
 
+// Rounds of k_select_classify: selection alone, four classes, launches one behind the other, one / two / four rounds: 197 K groups 24.2 / 25.6 /
+// 29.5 us, 1.5 M 35.9 / 37.0 / 41.5, 2 M 39.1 / 37.6 / 44.1, 5.6 M 60.6 / 58.1 / 64.0.  Six launches before: 27.0, 39.2, 40.6, 62.9; all ranges equal
+// 197 K 38.3 -> 29.8, 5.6 M 103.7 -> 71.5.
+constexpr int64_t kClassifyRounds2 = 7 << 18;
+
 }  // namespace
 
 int64_t daf_select_bits_workspace_size(int64_t G) {
@@ -659,10 +700,10 @@ int64_t daf_select_bits_workspace_size(int64_t G) {
 
 hipError_t daf_launch_select_bits(const float* gmin, const float* gmax, const uint8_t* prev_bits, int32_t prev_uniform,
                                   int64_t G, const uint8_t* classes, int n_classes, uint8_t* out_bits, void* workspace,
-                                  hipStream_t stream) {
+                                  hipStream_t stream, int polls) {
   SelectState* st = static_cast<SelectState*>(workspace);
   uint32_t* keys = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + ((sizeof(SelectState) + 15) / 16) * 16);
-  uint32_t* block_ties = keys + ((G + 3) / 4) * 4;
+  unsigned long long* posts = reinterpret_cast<unsigned long long*>(keys + ((G + 3) / 4) * 4);      // a multiple of 16 bytes in
   const int64_t n_blocks = (G + kBlockGroups - 1) / kBlockGroups;
 
   // thresholds R_k = ceil(k*G/C) that some rank can reach (R_k < G); the rest never apply
@@ -710,21 +751,19 @@ hipError_t daf_launch_select_bits(const float* gmin, const float* gmax, const ui
   const unsigned kblocks = (unsigned)((G + 8 * kThreads - 1) / (8 * kThreads));                  // eight keys per thread and trip
   if (gmax != nullptr)
     hipLaunchKernelGGL(k_select_keys<false>, dim3(kblocks < cap ? kblocks : cap), dim3(kThreads), 0, stream, gmin, gmax,
-                       nullptr, 0u, G, keys, st, n_thr);
+                       nullptr, 0u, G, keys, st, n_thr, posts, n_blocks);
   else
     hipLaunchKernelGGL(k_select_keys<true>, dim3(kblocks < cap ? kblocks : cap), dim3(kThreads), 0, stream, gmin, nullptr,
-                       prev_bits, (uint32_t)prev_uniform, G, keys, st, n_thr);
-  const bool scanned = n_blocks > kMaxSummedBlocks;
+                       prev_bits, (uint32_t)prev_uniform, G, keys, st, n_thr, posts, n_blocks);
   if (n_thr > 0) {
     const unsigned cblocks = (unsigned)((((G + 3) >> 2) + 4 * kThreads - 1) / (4 * kThreads));   // sixteen keys per thread and trip
     const unsigned hblocks = cblocks < cap ? cblocks : cap;
     hipLaunchKernelGGL(k_select_hist<1>, dim3(hblocks), dim3(kThreads), 0, stream, keys, G, st, ranks, n_thr);
     hipLaunchKernelGGL(k_select_hist<2>, dim3(hblocks), dim3(kThreads), 0, stream, keys, G, st, ranks, n_thr);
-    hipLaunchKernelGGL(k_select_ties, dim3((unsigned)(n_blocks < cap ? n_blocks : cap)), dim3(kThreads), 0, stream, keys,
-                       G, st, ranks, n_thr, block_ties, n_blocks);
-    if (scanned) hipLaunchKernelGGL(k_select_scan_ties, dim3((unsigned)n_thr), dim3(kThreads), 0, stream, block_ties, n_blocks);
   }
-  hipLaunchKernelGGL(k_select_classify, dim3((unsigned)n_blocks), dim3(kThreads), 0, stream, keys, G, st, n_thr, packed,
-                     block_ties, n_blocks, scanned, out_bits);
+  const int rounds = G > kClassifyRounds2 ? 2 : 1;
+  hipLaunchKernelGGL(rounds == 2 ? k_select_classify<2> : k_select_classify<1>,
+                     dim3((unsigned)((n_blocks + rounds - 1) / rounds)), dim3(kThreads), 0, stream, keys, G, st, ranks, n_thr, packed,
+                     posts, polls, out_bits);
   return hipGetLastError();
 }

@@ -1,0 +1,100 @@
+"""Width updates and width selection whose workgroups tell each other their sums inside one launch, around the numbers of groups
+where a workgroup ends and the forms change, against the oracle: called again and again on one plan and one workspace, with every
+workgroup left to work the others' sums out for itself (no look at the posts), and replayed from a graph."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+GROUPS = [65537, 4096 * 17 - 1, 4096 * 17, 4096 * 17 + 1, (1 << 20) - 7, (1 << 20) + 1, 8192 * 200 + 5]
+
+
+@pytest.fixture(scope="module")
+def env():
+    import paper_2507_07149_amd as daf
+    from oracle import daf_oracle as orc
+    assert torch.cuda.is_available()
+    return daf, orc, daf.load_library()
+
+
+def _stream():
+    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+
+
+def _update(lib, plan, bits, polls):
+    return lib.daf_internal_plan_update(ctypes.c_void_p(plan.handle),
+                                        ctypes.c_void_p(bits.data_ptr()), polls, _stream())
+
+
+@pytest.mark.parametrize("G", GROUPS)
+@pytest.mark.parametrize("skew", [0, 3])
+def test_update(env, G, skew):
+    daf, orc, lib = env
+    gs, n = 64, G * 64 - 37
+    rng = np.random.default_rng(G)
+    plan = daf.daf_plan((n,), gs, torch.ones(G, dtype=torch.uint8, device="cuda:0"))
+    for i, polls in enumerate([256, 0, 256, 1, 256]):
+        b = rng.choice([1, 2, 4, 8], G).astype(np.uint8)
+        if i == 2:
+            b[G // 2] = 3                                           # reported, and counted as 8
+        whole = torch.zeros(G + 32, dtype=torch.uint8, device="cuda:0")
+        whole[skew: skew + G] = torch.from_numpy(b).cuda()
+        print("case", G, skew, polls, flush=True)
+        assert _update(lib, plan, whole[skew: skew + G], polls) == 0
+        if i == 2:
+            with pytest.raises(daf.DafError):
+                plan.update(whole[skew: skew + G])
+                plan.finish()
+            b[G // 2] = 8
+        else:
+            assert lib.daf_plan_finish(ctypes.c_void_p(plan.handle), _stream()) == 0
+        off, total = orc.plan(n, gs, b)
+        torch.cuda.synchronize()
+        assert np.array_equal(plan.offsets().numpy().view(np.uint32), off)
+    plan.destroy()
+
+
+def test_update_replayed(env):
+    daf, orc, _ = env
+    G, gs = 4096 * 21 + 9, 32
+    rng = np.random.default_rng(5)
+    bits = torch.from_numpy(rng.choice([1, 2, 4, 8], G).astype(np.uint8)).cuda()
+    plan = daf.daf_plan((G * gs,), gs, bits)
+    plan.update(bits)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        plan.update(bits)
+    for i in range(6):
+        b = rng.choice([1, 2, 4, 8], G).astype(np.uint8)
+        bits.copy_(torch.from_numpy(b))
+        graph.replay()
+        if i % 2:
+            torch.cuda.synchronize()
+            plan.update(bits)
+        torch.cuda.synchronize()
+        assert np.array_equal(plan.offsets().numpy().view(np.uint32), orc.plan(G * gs, gs, b)[0])
+    plan.destroy()
+
+
+@pytest.mark.parametrize("G", [16385, 4096 * 5 - 1, 4096 * 5 + 1, 197000, 1500001])
+@pytest.mark.parametrize("kind", ["random", "ties", "equal", "half zero"])
+@pytest.mark.parametrize("polls", [256, 0])
+def test_select(env, G, kind, polls):
+    daf, orc, lib = env
+    rng = np.random.default_rng(G)
+    hi = {"random": rng.random(G, dtype=np.float32), "ties": rng.choice(np.array([0.0, 0.5, 0.5, 2.0], np.float32), G),
+          "equal": np.ones(G, np.float32), "half zero": np.maximum(rng.standard_normal(G), 0).astype(np.float32)}[kind]
+    lo = np.zeros(G, np.float32)
+    ws = daf.daf_select_bits_workspace(G)
+    out = torch.full((G + 64,), 77, dtype=torch.uint8, device="cuda:0")
+    a, b = torch.from_numpy(lo).cuda(), torch.from_numpy(hi).cuda()
+    for classes in ((1, 2, 4, 8), (2, 8)):
+        print("case", G, kind, polls, classes, flush=True)
+        assert lib.daf_internal_select_bits(ctypes.c_void_p(a.data_ptr()), ctypes.c_void_p(b.data_ptr()), ctypes.c_int64(G),
+                                            (ctypes.c_uint8 * len(classes))(*classes), len(classes), ctypes.c_void_p(out.data_ptr()),
+                                            ctypes.c_void_p(ws.data_ptr()), polls, _stream()) == 0
+        assert np.array_equal(out[:G].cpu().numpy(), orc.select_bits(lo, hi, classes))
+        assert bool((out[G:] == 77).all())
