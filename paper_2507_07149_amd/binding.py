@@ -9,6 +9,11 @@ import torch
 F32, F16, BF16 = 0, 1, 2
 _DTYPE_ID = {torch.float32: F32, torch.float16: F16, torch.bfloat16: BF16}
 
+try:
+    from . import _fast_calls            # csrc/fast_calls.cpp: checks, pointers, stream and call of the inner loop's calls in one step
+except ImportError:                      # built against another torch: the checks below and ctypes do the same
+    _fast_calls = None
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libdaf.so")
 _lib = None
@@ -105,6 +110,13 @@ def load_library():
     L.daf_minmax_workspace_init.restype = c.c_int
     L.daf_minmax.argtypes = [vp, c.c_int, i64, c.c_int, vp, vp, vp]
     L.daf_minmax.restype = c.c_int
+    if _fast_calls is not None:
+        names = ("daf_quantize_pack", "daf_quantize_pack_static", "daf_unpack_dequantize", "daf_quantize_pack_metrics",
+                 "daf_relu_quantize_pack", "daf_unpack_relu_backward", "daf_group_minmax", "daf_select_bits",
+                 "daf_select_bits_from_scale", "daf_select_bits_workspace_bytes", "daf_plan_update", "daf_linear_quantize_pack",
+                 "daf_unpack_matmul_grad_weight", "daf_unpack_matmul_workspace_bytes", "daf_plan_num_elements",
+                 "daf_plan_num_groups", "daf_plan_packed_words")
+        _fast_calls.bind({name: c.cast(getattr(L, name), vp).value for name in names}, Plan)
     _lib = L
     return L
 
@@ -177,8 +189,8 @@ class _Args:
                 raise ValueError(f"{name}: must be a device (cuda) tensor")
 
 
-# The same checks in one pass, for the calls of a training step's inner loop: True when every check of _Args
-# passes.  When one does not, the caller runs the _Args checks, which raise the error.
+# The same checks in one pass, for the calls of a training step's inner loop where the native step (_fast_calls) has not taken
+# them: True when every check of _Args passes.  When one does not, the caller runs the _Args checks, which raise the error.
 def _fits(t, dtype, numel: int) -> bool:
     return isinstance(t, torch.Tensor) and t.dtype is dtype and t.is_contiguous() and t.numel() >= numel and t.is_cuda
 
@@ -191,6 +203,16 @@ def _is_activation(plan, t) -> bool:
 def _is_packed(plan, words, mn, scale) -> bool:
     return (_fits(words, torch.int32, plan.packed_words) and _fits(mn, torch.float32, plan.num_groups)
             and _fits(scale, torch.float32, plan.num_groups))
+
+
+class _NoFastCalls:
+    """In the place of the native step where it has not been built for this torch: every call goes the general way."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+_fast = _fast_calls if _fast_calls is not None else _NoFastCalls()
 
 
 class Plan:
@@ -217,16 +239,17 @@ class Plan:
     def update(self, bits: torch.Tensor, stream=None) -> None:
         """daf_plan_update: new per-group widths (device uint8[G]) for this plan, enqueued on `stream`
         without synchronizing; `packed_words` reads as the 8-bit bound until `finish()`."""
-        if not (_fits(bits, torch.uint8, self.num_groups) and bits.numel() == self.num_groups):
-            a = _Args(self)
-            a.tensor("bits", bits, torch.uint8, self.num_groups, exact=True)
-            a.on_device()
-        L = load_library()
-        rc = L.daf_plan_update(self.handle, bits.data_ptr(), _stream_handle(stream))
+        rc = _fast.plan_update(self, bits, stream)
+        if rc is None:
+            if not (_fits(bits, torch.uint8, self.num_groups) and bits.numel() == self.num_groups):
+                a = _Args(self)
+                a.tensor("bits", bits, torch.uint8, self.num_groups, exact=True)
+                a.on_device()
+            rc = load_library().daf_plan_update(self.handle, bits.data_ptr(), _stream_handle(stream))
         if rc != 0:
             raise DafError(rc, "daf_plan_update")
         self._keep = bits
-        self.packed_words = L.daf_plan_packed_words(self.handle)
+        self.packed_words = load_library().daf_plan_packed_words(self.handle)
 
     def finish(self, stream=None) -> None:
         """daf_plan_finish: one synchronization; the exact packed size, and DafError if the last
@@ -303,6 +326,14 @@ def daf_plan(shape: Sequence[int], group_size: int, bits, stream=None) -> Plan:
 
 def daf_quantize_pack(plan: Plan, x: torch.Tensor, seed: int, out_words: torch.Tensor, out_min: torch.Tensor,
                       out_scale: torch.Tensor, stream=None) -> None:
+    rc = _fast.quantize_pack(plan, x, seed, out_words, out_min, out_scale, stream)
+    if rc is None:
+        rc = _general_quantize_pack(plan, x, seed, out_words, out_min, out_scale, stream)
+    if rc != 0:
+        raise DafError(rc, "daf_quantize_pack")
+
+
+def _general_quantize_pack(plan, x, seed, out_words, out_min, out_scale, stream):
     if not (_is_activation(plan, x) and _is_packed(plan, out_words, out_min, out_scale)):
         a = _Args(plan)
         a.activation("x", x)
@@ -311,8 +342,7 @@ def daf_quantize_pack(plan: Plan, x: torch.Tensor, seed: int, out_words: torch.T
     rc = load_library().daf_quantize_pack(plan.handle, x.data_ptr(), _DTYPE_ID[x.dtype], seed,
                                           out_words.data_ptr(), out_min.data_ptr(), out_scale.data_ptr(),
                                           _stream_handle(stream))
-    if rc != 0:
-        raise DafError(rc, "daf_quantize_pack")
+    return rc
 
 
 STATIC_SCRATCH_BYTES = 2 << 20      # DAF_STATIC_SCRATCH_BYTES of daf.h
@@ -321,6 +351,14 @@ STATIC_SCRATCH_BYTES = 2 << 20      # DAF_STATIC_SCRATCH_BYTES of daf.h
 def daf_quantize_pack_static(plan: Plan, x: torch.Tensor, seed: int, out_words: torch.Tensor, out_min: torch.Tensor,
                              out_scale: torch.Tensor, stream=None) -> None:
     """daf_quantize_pack that allocates nothing: the two-pass route's scratch is the library's static buffer."""
+    rc = _fast.quantize_pack_static(plan, x, seed, out_words, out_min, out_scale, stream)
+    if rc is None:
+        rc = _general_quantize_pack_static(plan, x, seed, out_words, out_min, out_scale, stream)
+    if rc != 0:
+        raise DafError(rc, "daf_quantize_pack_static")
+
+
+def _general_quantize_pack_static(plan, x, seed, out_words, out_min, out_scale, stream):
     if not (_is_activation(plan, x) and _is_packed(plan, out_words, out_min, out_scale)):
         a = _Args(plan)
         a.activation("x", x)
@@ -329,12 +367,19 @@ def daf_quantize_pack_static(plan: Plan, x: torch.Tensor, seed: int, out_words: 
     rc = load_library().daf_quantize_pack_static(plan.handle, x.data_ptr(), _DTYPE_ID[x.dtype], seed,
                                                  out_words.data_ptr(), out_min.data_ptr(), out_scale.data_ptr(),
                                                  _stream_handle(stream))
-    if rc != 0:
-        raise DafError(rc, "daf_quantize_pack_static")
+    return rc
 
 
 def daf_unpack_dequantize(plan: Plan, words: torch.Tensor, mn: torch.Tensor, scale: torch.Tensor,
                           out_x: torch.Tensor, bits: Optional[torch.Tensor] = None, stream=None) -> None:
+    rc = _fast.unpack_dequantize(plan, words, mn, scale, out_x, bits, stream)
+    if rc is None:
+        rc = _general_unpack_dequantize(plan, words, mn, scale, out_x, bits, stream)
+    if rc != 0:
+        raise DafError(rc, "daf_unpack_dequantize")
+
+
+def _general_unpack_dequantize(plan, words, mn, scale, out_x, bits, stream):
     if not (_is_packed(plan, words, mn, scale) and _is_activation(plan, out_x)
             and (bits is None or _fits(bits, torch.uint8, plan.num_groups))):
         a = _Args(plan)
@@ -345,8 +390,7 @@ def daf_unpack_dequantize(plan: Plan, words: torch.Tensor, mn: torch.Tensor, sca
     rc = load_library().daf_unpack_dequantize(plan.handle, words.data_ptr(), mn.data_ptr(), scale.data_ptr(),
                                               bits.data_ptr() if bits is not None else None,
                                               out_x.data_ptr(), _DTYPE_ID[out_x.dtype], _stream_handle(stream))
-    if rc != 0:
-        raise DafError(rc, "daf_unpack_dequantize")
+    return rc
 
 
 class _QuantizeItem(ctypes.Structure):
@@ -417,6 +461,14 @@ def daf_unpack_dequantize_batch(items, stream=None) -> None:
 def daf_unpack_relu_backward(plan: Plan, words: torch.Tensor, mn: torch.Tensor, scale: torch.Tensor,
                              grad_y: torch.Tensor, out_grad_z: torch.Tensor, bits: Optional[torch.Tensor] = None,
                              stream=None) -> None:
+    rc = _fast.unpack_relu_backward(plan, words, mn, scale, grad_y, out_grad_z, bits, stream)
+    if rc is None:
+        rc = _general_unpack_relu_backward(plan, words, mn, scale, grad_y, out_grad_z, bits, stream)
+    if rc != 0:
+        raise DafError(rc, "daf_unpack_relu_backward")
+
+
+def _general_unpack_relu_backward(plan, words, mn, scale, grad_y, out_grad_z, bits, stream):
     if not (_is_packed(plan, words, mn, scale) and _is_activation(plan, grad_y) and _is_activation(plan, out_grad_z)
             and out_grad_z.dtype == grad_y.dtype and (bits is None or _fits(bits, torch.uint8, plan.num_groups))):
         a = _Args(plan)
@@ -431,8 +483,7 @@ def daf_unpack_relu_backward(plan: Plan, words: torch.Tensor, mn: torch.Tensor, 
                                                  bits.data_ptr() if bits is not None else None, grad_y.data_ptr(),
                                                  out_grad_z.data_ptr(), _DTYPE_ID[grad_y.dtype],
                                                  _stream_handle(stream))
-    if rc != 0:
-        raise DafError(rc, "daf_unpack_relu_backward")
+    return rc
 
 
 def daf_unpack_matmul_workspace_bytes(plan: Plan, N: int, K: int) -> int:
@@ -458,6 +509,14 @@ def daf_unpack_matmul_grad_weight(plan: Plan, words: torch.Tensor, mn: torch.Ten
                                   workspace: Optional[torch.Tensor] = None, bits: Optional[torch.Tensor] = None,
                                   stream=None) -> None:
     """grad_y is [M, N]; out_grad_w is float32 [N, K]; the plan's tensor is read as [M, K]."""
+    rc = _fast.unpack_matmul_grad_weight(plan, words, mn, scale, grad_y, out_grad_w, workspace, bits, stream)
+    if rc is None:
+        rc = _general_unpack_matmul_grad_weight(plan, words, mn, scale, grad_y, out_grad_w, workspace, bits, stream)
+    if rc != 0:
+        raise DafError(rc, "daf_unpack_matmul_grad_weight")
+
+
+def _general_unpack_matmul_grad_weight(plan, words, mn, scale, grad_y, out_grad_w, workspace, bits, stream):
     need = -1
     if (_is_packed(plan, words, mn, scale) and (bits is None or _fits(bits, torch.uint8, plan.num_groups))
             and _fits(grad_y, grad_y.dtype, 0) and grad_y.dtype in _ELEM_DTYPES and _fits(out_grad_w, torch.float32, 0)
@@ -489,8 +548,7 @@ def daf_unpack_matmul_grad_weight(plan: Plan, words: torch.Tensor, mn: torch.Ten
         plan.handle, words.data_ptr(), mn.data_ptr(), scale.data_ptr(), bits.data_ptr() if bits is not None else None,
         grad_y.data_ptr(), N, K, _DTYPE_ID[grad_y.dtype], out_grad_w.data_ptr(),
         workspace.data_ptr() if workspace is not None else None, _stream_handle(stream))
-    if rc != 0:
-        raise DafError(rc, "daf_unpack_matmul_grad_weight")
+    return rc
 
 
 REDUCE_TWO_PASS, REDUCE_ATOMIC = 0, 1
@@ -519,6 +577,14 @@ def daf_minmax(x: torch.Tensor, method: int, workspace: torch.Tensor, out_minmax
 
 
 def daf_group_minmax(plan: Plan, x: torch.Tensor, out_min: torch.Tensor, out_max: torch.Tensor, stream=None) -> None:
+    rc = _fast.group_minmax(plan, x, out_min, out_max, stream)
+    if rc is None:
+        rc = _general_group_minmax(plan, x, out_min, out_max, stream)
+    if rc != 0:
+        raise DafError(rc, "daf_group_minmax")
+
+
+def _general_group_minmax(plan, x, out_min, out_max, stream):
     if not (_is_activation(plan, x) and _fits(out_min, torch.float32, plan.num_groups)
             and _fits(out_max, torch.float32, plan.num_groups)):
         a = _Args(plan)
@@ -528,8 +594,7 @@ def daf_group_minmax(plan: Plan, x: torch.Tensor, out_min: torch.Tensor, out_max
         a.on_device()
     rc = load_library().daf_group_minmax(plan.handle, x.data_ptr(), _DTYPE_ID[x.dtype], out_min.data_ptr(),
                                          out_max.data_ptr(), _stream_handle(stream))
-    if rc != 0:
-        raise DafError(rc, "daf_group_minmax")
+    return rc
 
 
 def daf_select_bits_workspace(num_groups: int, device="cuda:0") -> torch.Tensor:
@@ -544,6 +609,14 @@ def _select_bits_need(num_groups: int) -> int:
 
 def daf_select_bits(group_min: torch.Tensor, group_max: torch.Tensor, classes: Sequence[int], out_bits: torch.Tensor,
                     workspace: torch.Tensor, stream=None) -> None:
+    rc = _fast.select_bits(group_min, group_max, classes, out_bits, workspace, stream)
+    if rc is None:
+        rc = _general_select_bits(group_min, group_max, classes, out_bits, workspace, stream)
+    if rc != 0:
+        raise DafError(rc, "daf_select_bits")
+
+
+def _general_select_bits(group_min, group_max, classes, out_bits, workspace, stream):
     G = group_min.numel() if isinstance(group_min, torch.Tensor) else 0
     need = _select_bits_need(G)
     if not (_fits(group_min, torch.float32, 1) and _fits(group_max, torch.float32, G) and group_max.numel() == G
@@ -557,14 +630,21 @@ def daf_select_bits(group_min: torch.Tensor, group_max: torch.Tensor, classes: S
     cl = bytes([int(c) & 0xFF for c in classes])
     rc = load_library().daf_select_bits(group_min.data_ptr(), group_max.data_ptr(), G, cl, len(cl), out_bits.data_ptr(),
                                         workspace.data_ptr(), _stream_handle(stream))
-    if rc != 0:
-        raise DafError(rc, "daf_select_bits")
+    return rc
 
 
 def daf_select_bits_from_scale(group_scale: torch.Tensor, prev_bits, classes: Sequence[int], out_bits: torch.Tensor,
                                workspace: torch.Tensor, stream=None) -> None:
     """Widths for the next iteration from the scales (and widths: a uint8 tensor, or one int for
     all groups) of an earlier daf_quantize_pack: no pass over the activation."""
+    rc = _fast.select_bits_from_scale(group_scale, prev_bits, classes, out_bits, workspace, stream)
+    if rc is None:
+        rc = _general_select_bits_from_scale(group_scale, prev_bits, classes, out_bits, workspace, stream)
+    if rc != 0:
+        raise DafError(rc, "daf_select_bits_from_scale")
+
+
+def _general_select_bits_from_scale(group_scale, prev_bits, classes, out_bits, workspace, stream):
     G = group_scale.numel() if isinstance(group_scale, torch.Tensor) else 0
     need = _select_bits_need(G)
     per_group = isinstance(prev_bits, torch.Tensor)
@@ -581,12 +661,19 @@ def daf_select_bits_from_scale(group_scale: torch.Tensor, prev_bits, classes: Se
     rc = load_library().daf_select_bits_from_scale(
         group_scale.data_ptr(), prev_bits.data_ptr() if per_group else None, 0 if per_group else int(prev_bits), G,
         cl, len(cl), out_bits.data_ptr(), workspace.data_ptr(), _stream_handle(stream))
-    if rc != 0:
-        raise DafError(rc, "daf_select_bits_from_scale")
+    return rc
 
 
 def daf_relu_quantize_pack(plan: Plan, z: torch.Tensor, seed: int, out_y: torch.Tensor, out_words: torch.Tensor,
                            out_min: torch.Tensor, out_scale: torch.Tensor, stream=None) -> None:
+    rc = _fast.relu_quantize_pack(plan, z, seed, out_y, out_words, out_min, out_scale, stream)
+    if rc is None:
+        rc = _general_relu_quantize_pack(plan, z, seed, out_y, out_words, out_min, out_scale, stream)
+    if rc != 0:
+        raise DafError(rc, "daf_relu_quantize_pack")
+
+
+def _general_relu_quantize_pack(plan, z, seed, out_y, out_words, out_min, out_scale, stream):
     if not (_is_activation(plan, z) and _is_activation(plan, out_y) and _is_packed(plan, out_words, out_min, out_scale)
             and out_y.dtype == z.dtype):
         a = _Args(plan)
@@ -599,14 +686,21 @@ def daf_relu_quantize_pack(plan: Plan, z: torch.Tensor, seed: int, out_y: torch.
     rc = load_library().daf_relu_quantize_pack(plan.handle, z.data_ptr(), _DTYPE_ID[z.dtype], seed, out_y.data_ptr(),
                                                out_words.data_ptr(), out_min.data_ptr(), out_scale.data_ptr(),
                                                _stream_handle(stream))
-    if rc != 0:
-        raise DafError(rc, "daf_relu_quantize_pack")
+    return rc
 
 
 def daf_linear_quantize_pack(plan: Plan, x: torch.Tensor, weight: torch.Tensor, seed: int, out_y: torch.Tensor,
                              out_words: torch.Tensor, out_min: torch.Tensor, out_scale: torch.Tensor, stream=None) -> None:
     """y = x @ weight.T with the quantize+pack of y in the product's epilogue; `plan` describes y.
     With out_words, out_min and out_scale all None: the product alone."""
+    rc = _fast.linear_quantize_pack(plan, x, weight, seed, out_y, out_words, out_min, out_scale, stream)
+    if rc is None:
+        rc = _general_linear_quantize_pack(plan, x, weight, seed, out_y, out_words, out_min, out_scale, stream)
+    if rc != 0:
+        raise DafError(rc, "daf_linear_quantize_pack")
+
+
+def _general_linear_quantize_pack(plan, x, weight, seed, out_y, out_words, out_min, out_scale, stream):
     if x.dim() != 2 or weight.dim() != 2 or x.shape[1] != weight.shape[1]:
         raise ValueError("x must be [M, K] and weight [N, K]")
     M, K = x.shape
@@ -629,12 +723,19 @@ def daf_linear_quantize_pack(plan: Plan, x: torch.Tensor, weight: torch.Tensor, 
     rc = load_library().daf_linear_quantize_pack(plan.handle, x.data_ptr(), weight.data_ptr(), N, K, _DTYPE_ID[x.dtype],
                                                  seed, out_y.data_ptr(), ptr(out_words), ptr(out_min),
                                                  ptr(out_scale), _stream_handle(stream))
-    if rc != 0:
-        raise DafError(rc, "daf_linear_quantize_pack")
+    return rc
 
 
 def daf_quantize_pack_metrics(plan: Plan, x: torch.Tensor, seed: int, out_words: torch.Tensor, out_min: torch.Tensor,
                               out_scale: torch.Tensor, out_metrics: torch.Tensor, stream=None) -> None:
+    rc = _fast.quantize_pack_metrics(plan, x, seed, out_words, out_min, out_scale, out_metrics, stream)
+    if rc is None:
+        rc = _general_quantize_pack_metrics(plan, x, seed, out_words, out_min, out_scale, out_metrics, stream)
+    if rc != 0:
+        raise DafError(rc, "daf_quantize_pack_metrics")
+
+
+def _general_quantize_pack_metrics(plan, x, seed, out_words, out_min, out_scale, out_metrics, stream):
     if not (_is_activation(plan, x) and _is_packed(plan, out_words, out_min, out_scale)
             and _fits(out_metrics, torch.float32, 3 * plan.num_groups)):
         a = _Args(plan)
@@ -645,5 +746,4 @@ def daf_quantize_pack_metrics(plan: Plan, x: torch.Tensor, seed: int, out_words:
     rc = load_library().daf_quantize_pack_metrics(plan.handle, x.data_ptr(), _DTYPE_ID[x.dtype], seed,
                                                   out_words.data_ptr(), out_min.data_ptr(), out_scale.data_ptr(),
                                                   out_metrics.data_ptr(), _stream_handle(stream))
-    if rc != 0:
-        raise DafError(rc, "daf_quantize_pack_metrics")
+    return rc

@@ -1,4 +1,4 @@
-"""Build libdaf.so (HIP, gfx950 only) in-tree next to this file.
+"""Build libdaf.so (HIP, gfx950 only) and the Python module _fast_calls in-tree next to this file.
 
     python -m paper_2507_07149_amd.build
 
@@ -10,6 +10,7 @@ hipcc cross-compiles without a GPU.  Flags that matter:
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -17,6 +18,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdaf.so")
+FAST_CALLS = os.path.join(HERE, "_fast_calls.so")
 # (source, object name, extra flags): quantize_pack.hip is built once per element format
 SOURCES = [("quantize_pack.hip", "quantize_pack_f32", ["-DDAF_DT=0"]),
            ("quantize_pack.hip", "quantize_pack_f16", ["-DDAF_DT=1"]),
@@ -48,10 +50,24 @@ def _compile(item) -> str:
     return obj
 
 
+def _compile_fast_calls() -> None:
+    """The Python module with the inner loop's calls: host code against the headers of the torch that is installed."""
+    import torch
+    at = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(HIPCC)))
+    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                    "-I" + os.path.join(ROOT, "include"), "-isystem", os.path.join(at, "include"), "-isystem",
+                    os.path.join(at, "include", "torch", "csrc", "api", "include"), "-isystem", os.path.join(rocm, "include"),
+                    "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "fast_calls.cpp"), "-o", FAST_CALLS,
+                    "-L" + os.path.join(at, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], check=True)
+
+
 def build() -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=8) as ex:
+        fast = ex.submit(_compile_fast_calls)
         objs = list(ex.map(_compile, SOURCES))
+        fast.result()
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
     return LIB
 

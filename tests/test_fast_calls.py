@@ -1,0 +1,91 @@
+"""The native step of the inner loop's calls (csrc/fast_calls.cpp): it takes the usual arguments, and leaves everything else to the
+general checks without having done anything."""
+import pytest
+import torch
+
+import paper_2507_07149_amd as daf
+from paper_2507_07149_amd import binding
+
+
+class Tagged(torch.Tensor):
+    pass
+
+
+def _case(device):
+    n, gs = 8192, 128
+    G = n // gs
+    t = {"x": torch.randn(n, device=device), "y": torch.empty(n, device=device), "bits": torch.full((G,), 4, dtype=torch.uint8, device=device),
+         "next": torch.empty(G, dtype=torch.uint8, device=device), "words": torch.zeros(n // 4, dtype=torch.int32, device=device),
+         "min": torch.empty(G, device=device), "scale": torch.empty(G, device=device), "metrics": torch.empty(3 * G, device=device),
+         "lo": torch.empty(G, device=device), "hi": torch.empty(G, device=device), "ws": daf.daf_select_bits_workspace(G, device)}
+    plan = daf.daf_plan((n,), gs, t["bits"] if device != "cpu" else 4)
+    calls = {
+        "quantize_pack": [plan, "x", 3, "words", "min", "scale", None],
+        "quantize_pack_static": [plan, "x", 3, "words", "min", "scale", None],
+        "unpack_dequantize": [plan, "words", "min", "scale", "y", None, None],
+        "quantize_pack_metrics": [plan, "x", 3, "words", "min", "scale", "metrics", None],
+        "relu_quantize_pack": [plan, "x", 3, "y", "words", "min", "scale", None],
+        "unpack_relu_backward": [plan, "words", "min", "scale", "x", "y", "bits", None],
+        "group_minmax": [plan, "x", "lo", "hi", None],
+        "select_bits": ["lo", "hi", (2, 4, 8), "next", "ws", None],
+        "select_bits_from_scale": ["scale", "bits", [2, 4, 8], "next", "ws", None],
+        "plan_update": [plan, "bits", None],
+    }
+    return plan, t, calls
+
+
+def _call(name, args, t, **other):
+    return getattr(binding._fast_calls, name)(*[other.get(a, t.get(a)) if isinstance(a, str) else a for a in args])
+
+
+def test_the_module_is_built():
+    assert binding._fast_calls is not None and binding._fast is binding._fast_calls
+
+
+def test_host_tensors_are_left_to_the_general_checks():
+    plan, t, calls = _case("cpu")
+    for name, args in calls.items():
+        assert _call(name, args, t) is None, name
+    plan.destroy()
+    assert _call("quantize_pack", calls["quantize_pack"], t) is None
+
+
+@pytest.mark.gpu
+def test_usual_arguments_are_taken_and_others_left():
+    plan, t, calls = _case("cuda:0")
+    for name, args in calls.items():
+        assert _call(name, args, t) == 0, name
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    assert _call("quantize_pack", calls["quantize_pack"][:-1] + [side], t) == 0
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    want = [t[k].clone() for k in ("words", "min", "scale")]
+    binding._general_quantize_pack(plan, t["x"], 3, t["words"].zero_(), t["min"], t["scale"], None)
+    assert all(torch.equal(a, t[k]) for a, k in zip(want, ("words", "min", "scale")))
+    for name, args in calls.items():
+        for i, a in enumerate(args):
+            if not isinstance(a, str):
+                continue
+            good = t[a]
+            for bad in (good.cpu(), good[:-1], torch.stack([good, good], 1)[:, 0], good.view(torch.int16), good.as_subclass(Tagged), [0], None):
+                if (bad is None and a == "bits") or (a == "words" and bad is not None and getattr(bad, "is_cuda", False)
+                                                     and type(bad) is torch.Tensor and bad.dtype == torch.int32 and bad.is_contiguous()):
+                    continue                                         # (the words' buffer is larger than it has to be)
+                if a == "lo" and name == "select_bits" and bad is not None and getattr(bad, "is_cuda", False) and len(bad) == len(good) - 1:
+                    continue                                         # (there the first argument says how many groups; the second differs then)
+                assert getattr(binding._fast_calls, name)(*[bad if j == i else t.get(b) if isinstance(b, str) else b
+                                                            for j, b in enumerate(args)]) is None, (name, a, type(bad))
+    assert binding._fast_calls.quantize_pack(plan, t["x"], 3.0, t["words"], t["min"], t["scale"], None) is None
+    assert binding._fast_calls.quantize_pack(object(), t["x"], 3, t["words"], t["min"], t["scale"], None) is None
+    assert binding._fast_calls.quantize_pack(plan, t["x"], 3) is None
+
+    seen = []
+
+    def traced(x):
+        seen.append(binding._fast_calls.quantize_pack(plan, x, 3, t["words"], t["min"], t["scale"], None))
+        return x
+    torch.vmap(traced)(t["x"].unsqueeze(0))
+    assert seen == [None]
+    torch.cuda.synchronize()
+    plan.destroy()
