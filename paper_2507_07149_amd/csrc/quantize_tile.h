@@ -647,7 +647,9 @@ __device__ __forceinline__ void quantize_pack_tile_body(
         } else {
           quantize_raw_chunk<DT, kExact2, false, SHORT>(raw[u], g_mn, g_invs, rnd[u], q);
         }
-        stage_chunk<kEpl, kMixed>(addr, b, q, lane);
+        // (a load's 64 lanes are of one group: its width is a scalar)
+        constexpr bool kPerLane = kMixed && S::kLaneLog2 < 6;
+        stage_chunk<kEpl, kPerLane>(addr, kMixed && !kPerLane ? (uint32_t)__builtin_amdgcn_readfirstlane((int)b) & 0xFFu : b, q, lane);
       }
     };
     if (need_exact2) quantize_tile(std::true_type{});

@@ -283,9 +283,16 @@ __device__ __forceinline__ void quantize_pack_units_body(
   wave_lds_sync();
 
   // 5. quantize every chunk of the tile and drop its bits at their place in the staged run
-  //    (EXACT2: 0 and 1 as quantize_chunk's, 2: by need_exact2, chunk by chunk)
-  auto quantize_tile = [&](auto exact2) {
+  //    (EXACT2: 0 and 1 as quantize_chunk's, 2: by need_exact2, chunk by chunk.  ONE: the tile is one group, whose entry is read
+  //    once and whose width is a scalar: no search for a chunk's group, one store a chunk.)
+  auto quantize_tile = [&](auto exact2, auto one) {
     constexpr int kExact2 = decltype(exact2)::value;
+    constexpr bool kOne = decltype(one)::value;
+    [[maybe_unused]] GroupInfo only;
+    if constexpr (kOne) {
+      only = lds.info[0];
+      only.b = (uint32_t)__builtin_amdgcn_readfirstlane((int)only.b);
+    }
     // (what two copies of the loop have in common would be computed before the branch and held)
     if (METRICS && kExact2 == 1 && !SHORT) asm volatile("" ::: "memory");
     // (the lane counted anew, or the chunk numbers of step 1 would hold registers until here: 5 waves per SIMD instead of 4
@@ -297,9 +304,11 @@ __device__ __forceinline__ void quantize_pack_units_body(
       if (c < n_chunks) {
         // (24-bit multiplications: every product here is far below 2^24, and the full 32-bit
         // multiplication runs at a quarter of the rate)
-        const uint32_t grp = __umul24(c >> S::kLanesLog2, magic) >> 16;   // unit / m
-        const uint32_t lig = c - __umul24(grp, group_chunks);            // chunk inside its group
-        const GroupInfo gi = lds.info[grp];
+        const uint32_t grp = kOne ? 0u : __umul24(c >> S::kLanesLog2, magic) >> 16;   // unit / m
+        const uint32_t lig = kOne ? c : c - __umul24(grp, group_chunks);             // chunk inside its group
+        GroupInfo gi;
+        if constexpr (kOne) gi = only;
+        else gi = lds.info[grp];
         const uint32_t b = kMixed ? gi.b : (uint32_t)B;
         const uint32_t addr = (gi.byte_off + (kEpl == 8 ? __umul24(lig, b) : __umul24(lig, b) >> 1)) ^ (gi.b >> 24);
         uint32_t q[kEpl / 4];
@@ -323,17 +332,18 @@ __device__ __forceinline__ void quantize_pack_units_body(
           if (exact) quantize_raw_chunk<DT, true, false, SHORT, true>(raw[u], gi.mn, gi.invs, rnd[u], q);
           else       quantize_raw_chunk<DT, false, false, SHORT, true>(raw[u], gi.mn, gi.invs, rnd[u], q);
         }
-        stage_chunk<kEpl, kMixed>(addr, b, q, lane);
+        stage_chunk<kEpl, kMixed && !kOne>(addr, kOne ? b & 0xFFu : b, q, lane);
       }
     }
   };
   if constexpr (SHORT) {
-    quantize_tile(std::integral_constant<int, 1>{});
+    quantize_tile(std::integral_constant<int, 1>{}, std::false_type{});
   } else if constexpr (METRICS) {                          // a copy of the loop each: a branch in every chunk spilled
-    if (need_exact2) quantize_tile(std::integral_constant<int, 1>{});
-    else             quantize_tile(std::integral_constant<int, 0>{});
+    if (need_exact2) quantize_tile(std::integral_constant<int, 1>{}, std::false_type{});
+    else             quantize_tile(std::integral_constant<int, 0>{}, std::false_type{});
   } else {
-    quantize_tile(std::integral_constant<int, 2>{});
+    if (k_full == 1) quantize_tile(std::integral_constant<int, 2>{}, std::true_type{});
+    else             quantize_tile(std::integral_constant<int, 2>{}, std::false_type{});
   }
   wave_lds_sync();
   if constexpr (SHORT) end_run(&lds.stage[tile_words - 1u], last_bits, lane);
