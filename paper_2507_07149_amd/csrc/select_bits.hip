@@ -24,6 +24,8 @@
 // of every launch.  Selection alone, four classes, before (ticket and last
 // workgroup in four of six launches) and now: 500 groups 39 / 14 us, 8192 40 / 20, 197 K 49 / 29, 1 M 54 / 34, 5.6 M 94 / 66;
 // all ranges equal: 197 K 53 / 38, 5.6 M 127 / 104.
+#include <type_traits>
+
 #include "daf_device.h"
 #include "daf_internal.h"
 
@@ -195,17 +197,17 @@ __device__ __forceinline__ void decide(Decided& d, const Bins<PASS>& bins, int n
 
 // keys[g] = bit pattern of the group's range, and in the same pass the histogram of the keys'
 // leading digit (every key counts for every threshold, so one histogram serves all).  A wave
-// takes 512 consecutive groups per trip, eight loads of each array in flight per lane.
+// takes 64 * LOADS consecutive groups per trip, that many loads of each array in flight per lane.
 // FROM_SCALE = false: the range is gmax - gmin.  FROM_SCALE = true: gmin holds the groups' scales of
 // an earlier quantize call and prev_bits (or, when null, prev_uniform) the widths it ran with; the
 // range is scale * (2^b - 1), Eq. 1 (left) turned round, in binary32.
-template <bool FROM_SCALE>
+template <bool FROM_SCALE, int LOADS>
 __global__ __launch_bounds__(kThreads) void k_select_keys(const float* __restrict__ gmin, const float* __restrict__ gmax,
                                                           const uint8_t* __restrict__ prev_bits, uint32_t prev_uniform,
                                                           int64_t G, uint32_t* __restrict__ keys,
                                                           SelectState* __restrict__ st, int n_thresholds,
                                                           unsigned long long* __restrict__ posts, int64_t n_blocks) {
-  constexpr int kLoads = 8;
+  constexpr int kLoads = LOADS;
   __shared__ __attribute__((aligned(16))) uint32_t lh[kBins * kLdsCopies0];
   for (int i = threadIdx.x; i < kBins * kLdsCopies0 / 4; i += kThreads)
     reinterpret_cast<uint4*>(lh)[i] = make_uint4(0u, 0u, 0u, 0u);
@@ -268,7 +270,7 @@ __device__ __forceinline__ Decided decided_after(SelectState* __restrict__ st, c
 }
 
 // Histogram of the PASS-th digit among the keys whose higher digits equal the prefix.
-template <int PASS>
+template <int PASS, int LOADS>
 __global__ __launch_bounds__(kThreads) void k_select_hist(const uint32_t* __restrict__ keys, int64_t G,
                                                           SelectState* __restrict__ st, Ranks ranks, int n_thresholds) {
   constexpr int kShift = pass_shift(PASS), kDigitBins = 1 << pass_bits(PASS);
@@ -281,9 +283,9 @@ __global__ __launch_bounds__(kThreads) void k_select_hist(const uint32_t* __rest
   const uint32_t(&prefix)[kMaxThresholds] = d.prefix;
   const Slices slices = shared_slices(prefix, PASS);
   const int64_t stride = (int64_t)gridDim.x * kThreads;
-  // Sixteen keys per lane and trip: four 16-byte loads issued together (the key array is padded
-  // to whole chunks), so that enough bytes are in flight; a wave takes 256 consecutive chunks.
-  constexpr int kLoads = 4;
+  // LOADS 16-byte loads per lane and trip issued together (the key array is padded to whole chunks), so that enough bytes are in
+  // flight; a wave takes 64 * LOADS consecutive chunks.
+  constexpr int kLoads = LOADS;
   const int64_t n_chunks = (G + 3) >> 2;
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t wave_stride = stride / kWave * (kWave * kLoads);
@@ -686,6 +688,10 @@ __global__ __launch_bounds__(kRankThreads) void k_select_rank(const float* __res
   }
 }
 
+// Keys per thread and trip in the launches that write and count them (2 / 4, 8 / 8, 8 / 16: the writing launch, the counting ones).  Few make more
+// workgroups, whose start and counting take less time, but each adds its counts to the shared ones.  Selection alone, four classes: 65 K
+// groups 21.0 / 22.5 / 24.1 us, 131 K 21.7 / 22.6 / 24.0, 197 K 23.2 / 22.9 / 24.4, 400 K 27.9 / 24.5 / 25.4, 700 K 35.9 / 28.9 / 28.8.
+constexpr int64_t kFewKeys = 5 << 15, kManyKeys = 1 << 19;
 // Rounds of k_select_classify: selection alone, four classes, launches one behind the other, one / two / four rounds: 197 K groups 24.2 / 25.6 /
 // 29.5 us, 1.5 M 35.9 / 37.0 / 41.5, 2 M 39.1 / 37.6 / 44.1, 5.6 M 60.6 / 58.1 / 64.0.  Six launches before: 27.0, 39.2, 40.6, 62.9; all ranges equal
 // 197 K 38.3 -> 29.8, 5.6 M 103.7 -> 71.5.
@@ -748,18 +754,23 @@ hipError_t daf_launch_select_bits(const float* gmin, const float* gmax, const ui
   // with 256, 384 and 512 workgroups, 73 with 768).
   const unsigned cap = kMaxWorkgroups;
   hipLaunchKernelGGL(k_select_init, dim3((kHistCopies * kBins / 4 + kThreads - 1) / kThreads), dim3(kThreads), 0, stream, st);
-  const unsigned kblocks = (unsigned)((G + 8 * kThreads - 1) / (8 * kThreads));                  // eight keys per thread and trip
-  if (gmax != nullptr)
-    hipLaunchKernelGGL(k_select_keys<false>, dim3(kblocks < cap ? kblocks : cap), dim3(kThreads), 0, stream, gmin, gmax,
-                       nullptr, 0u, G, keys, st, n_thr, posts, n_blocks);
-  else
-    hipLaunchKernelGGL(k_select_keys<true>, dim3(kblocks < cap ? kblocks : cap), dim3(kThreads), 0, stream, gmin, nullptr,
-                       prev_bits, (uint32_t)prev_uniform, G, keys, st, n_thr, posts, n_blocks);
+  const int key_loads = G > kFewKeys ? 8 : 2, loads = G > kManyKeys ? 4 : G > kFewKeys ? 2 : 1;
+  auto workgroups = [&](int64_t per_thread) {
+    const int64_t n = (G + per_thread * kThreads - 1) / (per_thread * kThreads);
+    return dim3((unsigned)(n < cap ? n : cap));
+  };
+  const auto write_keys = gmax != nullptr ? (key_loads == 8 ? k_select_keys<false, 8> : k_select_keys<false, 2>)
+                                          : (key_loads == 8 ? k_select_keys<true, 8> : k_select_keys<true, 2>);
+  hipLaunchKernelGGL(write_keys, workgroups(key_loads), dim3(kThreads), 0, stream, gmin, gmax, gmax != nullptr ? nullptr : prev_bits,
+                     gmax != nullptr ? 0u : (uint32_t)prev_uniform, G, keys, st, n_thr, posts, n_blocks);
   if (n_thr > 0) {
-    const unsigned cblocks = (unsigned)((((G + 3) >> 2) + 4 * kThreads - 1) / (4 * kThreads));   // sixteen keys per thread and trip
-    const unsigned hblocks = cblocks < cap ? cblocks : cap;
-    hipLaunchKernelGGL(k_select_hist<1>, dim3(hblocks), dim3(kThreads), 0, stream, keys, G, st, ranks, n_thr);
-    hipLaunchKernelGGL(k_select_hist<2>, dim3(hblocks), dim3(kThreads), 0, stream, keys, G, st, ranks, n_thr);
+    auto count = [&](auto pass) {
+      constexpr int P = decltype(pass)::value;
+      const auto kernel = loads == 4 ? k_select_hist<P, 4> : loads == 2 ? k_select_hist<P, 2> : k_select_hist<P, 1>;
+      hipLaunchKernelGGL(kernel, workgroups(4 * loads), dim3(kThreads), 0, stream, keys, G, st, ranks, n_thr);
+    };
+    count(std::integral_constant<int, 1>{});
+    count(std::integral_constant<int, 2>{});
   }
   const int rounds = G > kClassifyRounds2 ? 2 : 1;
   hipLaunchKernelGGL(rounds == 2 ? k_select_classify<2> : k_select_classify<1>,
