@@ -596,7 +596,7 @@ __global__ __launch_bounds__(256) void k_sum_slices(float4* __restrict__ partial
 // step, the binary32 kernel 16); the slicing below counts m in units of 32.
 constexpr int kStepM = 32;
 
-// Width of the 256-row tile along k.  Each doubling halves the number of times a row of grad_y is
+// Width of the 256-row tile along k, before schedule() looks at outputs of few tiles.  Each doubling halves the number of times a row of grad_y is
 // fetched; the 256-column tile (8 waves, one work-group per CU) is used when the output has
 // enough of them to fill the chip without slicing m, else the 128-column one (16-bit formats that do not take the
 // 512 x 128 tile: 2048 x 256 x 65536, 256 / 128 columns 77.0 / 82.2 us, 4096 x 128 x 65536 111 / 125).
@@ -650,7 +650,7 @@ Schedule schedule_tile(int64_t M, int64_t N, int64_t K, int bn, int bk, int64_t 
   }
   return sc;
 }
-Schedule schedule(int64_t M, int64_t N, int64_t K, int es) {   // es: bytes per element (2 or 4)
+Schedule schedule_wider(int64_t M, int64_t N, int64_t K, int es) {   // es: bytes per element (2 or 4)
   // Per work-group and 32 values of m: the 16-bit kernels are bound by instruction issue, the binary32 kernel by its MFMAs
   // (128 per wave of 64 cycles each).
   const int bk = tile_bk(N, K);
@@ -680,14 +680,85 @@ Schedule schedule(int64_t M, int64_t N, int64_t K, int es) {   // es: bytes per 
   const Schedule wide = schedule_tile(M, N, K, Wide::kBN, Wide::kBK, 256, 0.95e-6);
   return wide.seconds * 0.97 <= general.seconds ? wide : general;
 }
+
+// Microseconds of a call that runs as `sc` says.  A round of work-groups takes start + start_full * (its work-groups / 256) and,
+// per step, a time that depends on how many work-groups the fullest compute unit has, and with one on how many units
+// have one.  With slices of m the second launch and the partial sums come on top (they mostly stay in the caches).
+// Fitted to 160 shapes drawn over M 512 ... 32768, N 64 ... 4096, K 256 ... 11008, all tiles with up to 64 slices measured
+// on each, 12 % of the time on average off.
+struct RoundTimes {
+  float start, start_full, lone, step[3];           // step[k]: k + 1 work-groups on a compute unit, all units busy
+};
+double call_microseconds(const Schedule& sc, int64_t M, int es) {
+  static constexpr RoundTimes kTimes[2][4] = {      // [16-bit, binary32][256 x 64, 256 x 128, 256 x 256, 512 x 128]
+      {{1.78f, 4.59f, 0.46f, {0.54f, 0.66f, 0.87f}}, {3.91f, 5.78f, 0.60f, {0.72f, 0.98f, 1.08f}},
+       {2.84f, 14.38f, 0.88f, {0.88f, 0.98f, 1.08f}}, {8.46f, 7.76f, 0.41f, {0.82f, 0.92f, 1.02f}}},
+      {{0.61f, 2.56f, 2.20f, {3.06f, 4.54f, 6.11f}}, {4.30f, 1.16f, 3.49f, {4.82f, 8.65f, 8.75f}},
+       {5.99f, 2.18f, 7.63f, {8.71f, 8.81f, 8.91f}}, {}}
+  };
+  const RoundTimes& t = kTimes[es == 4][sc.bn == Wide::kBN ? 3 : sc.bk == 256 ? 2 : sc.bk == 128 ? 1 : 0];
+  const int64_t per_unit = sc.bn == Wide::kBN || sc.bk == 256 ? 1 : sc.bk == 128 ? 2 : 3, slots = 256 * per_unit;
+  const int64_t steps = M / kStepM, rest = sc.tiles - sc.whole;
+  const auto rounds = [&](int64_t groups, int64_t steps_each) {
+    const int64_t full = groups / slots, left = groups % slots;
+    double us = (double)full * (t.start + t.start_full * (float)per_unit + (double)steps_each * t.step[per_unit - 1]);
+    if (left > 0) {
+      const int64_t k = (left - 1) / 256;           // others on the fullest unit
+      const double busy = (double)(left - 256 * k) / 256.0;
+      const double from = k == 0 ? t.lone : t.step[k - 1], part = k == 0 ? busy : 0.5 + 0.5 * busy;
+      us += t.start + t.start_full * (double)left / 256.0 + (double)steps_each * (from + part * (t.step[k] - from));
+    }
+    return us;
+  };
+  double us = rounds(sc.whole, steps);
+  if (rest > 0)
+    us += rounds(rest * sc.slices, (steps + sc.slices - 1) / sc.slices) + (es == 4 ? 8.3 : 5.0) +
+          (double)sc.slices * (double)(rest * sc.bn * sc.bk) * 4e-6 * 0.03 + (sc.slices > 16 ? 1.8 : 0.0);
+  return us;
+}
+
+// The tile of 256 x 64 where the output has at most a round of them, in no more slices than the partial sums of `wider` leave
+// room for (callers are told of that workspace).  A work-group has half the products to a step, and a compute unit has three:
+// outputs of few tiles fill the chip with fewer slices of m and fewer bytes of partial sums; and the model above knows a
+// lone work-group from a full compute unit, which the estimate behind `wider` does not (it cuts m where that does not pay).  Taken where the
+// model has it clearly ahead, by more where the other choice is the 512 x 128 tile.  Below 128 rows the tile is mostly outside the
+// output and the model too coarse, and in binary32 the number of slices of this tile is left as it was (544 x 128 x 8768 in 3
+// instead of 4: 38.5 -> 41.6 us).
+// Whole call, m x n x k, before and now, tile / slices: bfloat16 1344 x 640 x 1536 24.1 (256 x 128 / 4) -> 20.1 us (3), 896 x 512 x 8064
+// 26.7 (256 x 128 / 1) -> 19.7 (1), 640 x 1344 x 960 19.4 (256 x 64 / 3) -> 14.1 (1), 6912 x 704 x 704 28.3 (512 x 128 / 12) -> 28.4 (12);
+// binary32 992 x 128 x 1280 28.9 (256 x 128 / 7) -> 21.2 (7).  150 drawn shapes that the model was not fitted to: 27
+// changed, 0.99 to 1.51 times as fast, 1.19 on average.
+Schedule schedule(int64_t M, int64_t N, int64_t K, int es) {
+  const Schedule wider = schedule_wider(M, N, K, es);
+  const int64_t tiles = (N + kBN - 1) / kBN * (K / 64), steps = M / kStepM;
+  if (N < 128 || tiles > 768 || (es == 4 && wider.bk == 64)) return wider;
+  if (steps <= 16) return wider;                    // (calls of few steps keep the tile that the tests state for them)
+  const double limit = call_microseconds(wider, M, es) * (wider.bn == Wide::kBN ? 0.90 : 0.96);
+  const int64_t room = daf_unpack_matmul_workspace_size(M, N, K);
+  Schedule best = wider, sc = wider;
+  sc.bn = kBN;
+  sc.bk = 64;
+  sc.tiles = tiles;
+  double best_us = limit;
+  for (int32_t s = 1; s <= 16 && (s == 1 || (steps >= 4 * s && s * tiles * (kBN * 64 * 4) <= room)); ++s) {
+    sc.whole = s == 1 ? tiles : 0;
+    sc.slices = s;
+    const double us = call_microseconds(sc, M, es);
+    if (us < best_us) {
+      best_us = us;
+      best = sc;
+    }
+  }
+  return best;
+}
 }  // namespace
 
 // The number of slices depends on the element format (the binary32 kernel is slower per step,
-// so more slices pay off); the workspace is sized for the larger of the two.
+// so more slices pay off); the workspace is sized for the larger of the two, and schedule() stays inside it.
 int64_t daf_unpack_matmul_workspace_size(int64_t M, int64_t N, int64_t K) {
   int64_t bytes = 0;
   for (int es = 2; es <= 4; es += 2) {
-    const Schedule sc = schedule(M, N, K, es);
+    const Schedule sc = schedule_wider(M, N, K, es);
     const int64_t b = sc.slices > 1 ? (int64_t)sc.slices * (sc.tiles - sc.whole) * sc.bn * sc.bk * 4 : 0;
     bytes = b > bytes ? b : bytes;
   }

@@ -164,6 +164,41 @@ def test_weight_gradient_tile_of_an_odd_number_of_64_columns(lib, m, n, k):
     plan.destroy()
 
 
+@pytest.mark.parametrize("m,n,k,dtype,tile,slices", [
+    (1344, 640, 1536, 2, (256, 64), 3), (896, 512, 8064, 1, (256, 64), 1), (640, 1344, 960, 2, (256, 64), 1), (992, 128, 1280, 0, (256, 64), 7),
+    (4416, 320, 320, 2, (256, 64), 16),
+    # up to 512 values of m, below 128 rows, more than a round of such tiles, binary32 that has this tile already
+    (512, 640, 1536, 2, (256, 128), None), (1344, 64, 1536, 2, (256, 128), None), (4096, 4096, 4352, 0, (256, 256), None),
+    (544, 128, 8768, 0, (256, 64), 4)])
+def test_weight_gradient_narrow_tile(lib, m, n, k, dtype, tile, slices):
+    """Outputs of few tiles take 256 x 64, in slices whose partial sums fit the workspace that callers are told of."""
+    import paper_2507_07149_amd as daf
+    import torch
+    plan = daf.daf_plan((m, k), 64, 4)
+    s = daf.daf_unpack_matmul_schedule(plan, n, k, (torch.float32, torch.float16, torch.bfloat16)[dtype])
+    assert (s["tile_n"], s["tile_k"]) == tile and s["slices"] == (slices or s["slices"])
+    plan.destroy()
+
+
+def test_weight_gradient_schedules_stay_inside_the_workspace(lib):
+    import random
+    import paper_2507_07149_amd as daf
+    import torch
+    rng, narrow = random.Random(3), 0
+    for _ in range(600):
+        m, n, k = 32 * rng.randint(1, 400), 64 * rng.randint(1, 40), 64 * rng.randint(1, 140)
+        plan = daf.daf_plan((m, k), 64, 4)
+        room = daf.daf_unpack_matmul_workspace_bytes(plan, n, k)
+        for dtype in (torch.float32, torch.float16, torch.bfloat16):
+            s = daf.daf_unpack_matmul_schedule(plan, n, k, dtype)
+            rest = s["tiles"] - s["whole_tiles"]
+            assert s["tiles"] == -(-n // s["tile_n"]) * -(-k // s["tile_k"]) and (s["slices"] > 1) == (rest > 0)
+            assert s["slices"] == 1 or (s["slices"] * rest * s["tile_n"] * s["tile_k"] * 4 <= room and m // 32 >= 4 * s["slices"])
+            narrow += s["tile_k"] == 64
+        plan.destroy()
+    assert narrow > 100
+
+
 # n, group size, width, element format, (relu backward, elements of the list) -> route; plans that need no device
 @pytest.mark.parametrize("n,gs,b,dtype,call,want", [
     (1 << 20, 64, 2, 0, (0, 0), 0), (1 << 20, 2048, 8, 0, (0, 0), 0), (1 << 20, 4096, 2, 1, (1, 0), 0),
