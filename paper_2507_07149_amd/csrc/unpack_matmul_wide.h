@@ -14,7 +14,8 @@
 //     (the same instructions in the order they are thought of: 3.13 ms, dealt out: 2.97, on the 256 x 256 tile).
 // 32768 x 4096 x 11008 bfloat16 {2,4,8}: 3.23 -> 2.65 ms (915 -> 1115 TFLOP/s; matrix cores busy 47 -> 67 % of
 // the cycles, at 1.86 -> 1.59 GHz: the chip's power now sets the clock); 32768 x 3072 x 768 binary16 {1,2,4,8}: 213 ->
-// 174 us.
+// 174 us.  Since then: 134 instead of 146 instructions per wave and step 2630 -> 2633 us (fewer cycles at a lower clock); 4 waves of 128 x 128
+// with 512 registers each, a third less LDS traffic, 2908 (one wave per SIMD is bound by issue: 240 instructions in 1024 cycles).
 #pragma once
 
 namespace {
