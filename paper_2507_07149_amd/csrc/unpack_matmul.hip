@@ -717,21 +717,18 @@ double call_microseconds(const Schedule& sc, int64_t M, int es) {
   return us;
 }
 
-// The tile of 256 x 64 where the output has at most a round of them, in no more slices than the partial sums of `wider` leave
-// room for (callers are told of that workspace).  A work-group has half the products to a step, and a compute unit has three:
-// outputs of few tiles fill the chip with fewer slices of m and fewer bytes of partial sums; and the model above knows a
-// lone work-group from a full compute unit, which the estimate behind `wider` does not (it cuts m where that does not pay).  Taken where the
-// model has it clearly ahead, by more where the other choice is the 512 x 128 tile.  Below 128 rows the tile is mostly outside the
-// output and the model too coarse, and in binary32 the number of slices of this tile is left as it was (544 x 128 x 8768 in 3
-// instead of 4: 38.5 -> 41.6 us).
-// Whole call, m x n x k, before and now, tile / slices: bfloat16 1344 x 640 x 1536 24.1 (256 x 128 / 4) -> 20.1 us (3), 896 x 512 x 8064
-// 26.7 (256 x 128 / 1) -> 19.7 (1), 640 x 1344 x 960 19.4 (256 x 64 / 3) -> 14.1 (1), 6912 x 704 x 704 28.3 (512 x 128 / 12) -> 28.4 (12);
-// binary32 992 x 128 x 1280 28.9 (256 x 128 / 7) -> 21.2 (7).  150 drawn shapes that the model was not fitted to: 27
-// changed, 0.99 to 1.51 times as fast, 1.19 on average.
+// The tile of 256 x 64 where the output has at most a round of them, instead of a wider one, in no fewer slices of m than the wider one's
+// (one sum over all of m is further from the exact one than a sum of slices: 640 x 1344 x 960 over all of m instead of 3 slices would
+// take 14.1 instead of 19.4 us, with 1.6e-7 instead of 1.0e-7) and no more than the partial sums of `wider` leave room for (callers are
+// told of that workspace).  A work-group has half the products to a step, and a compute unit has three: outputs of few tiles fill
+// the chip better at the same number of slices.  Taken where the model has it clearly ahead, by more where the other choice is the 512 x 128 tile; below
+// 128 rows the tile is mostly outside the output and the model too coarse.
+// Whole call, m x n x k, both tiles measured: bfloat16 896 x 512 x 8064 26.7 -> 19.7 us, binary16 672 x 320 x 5376 19.4 -> 14.6, binary32
+// 992 x 128 x 1280 28.9 -> 21.2, 544 x 128 x 3968 31.4 -> 22.9.
 Schedule schedule(int64_t M, int64_t N, int64_t K, int es) {
   const Schedule wider = schedule_wider(M, N, K, es);
   const int64_t tiles = (N + kBN - 1) / kBN * (K / 64), steps = M / kStepM;
-  if (N < 128 || tiles > 768 || (es == 4 && wider.bk == 64)) return wider;
+  if (N < 128 || tiles > 768 || wider.bk == 64) return wider;
   if (steps <= 16) return wider;                    // (calls of few steps keep the tile that the tests state for them)
   const double limit = call_microseconds(wider, M, es) * (wider.bn == Wide::kBN ? 0.90 : 0.96);
   const int64_t room = daf_unpack_matmul_workspace_size(M, N, K);
@@ -740,7 +737,7 @@ Schedule schedule(int64_t M, int64_t N, int64_t K, int es) {
   sc.bk = 64;
   sc.tiles = tiles;
   double best_us = limit;
-  for (int32_t s = 1; s <= 16 && (s == 1 || (steps >= 4 * s && s * tiles * (kBN * 64 * 4) <= room)); ++s) {
+  for (int32_t s = wider.slices; s <= 16 && (s == 1 || (steps >= 4 * s && s * tiles * (kBN * 64 * 4) <= room)); ++s) {
     sc.whole = s == 1 ? tiles : 0;
     sc.slices = s;
     const double us = call_microseconds(sc, M, es);
