@@ -98,6 +98,10 @@ int daf_plan(const int64_t* shape, int ndim, int32_t group_size,
  *   stream   the scan is enqueued here; calls that use the plan must be ordered after it (same
  *            stream, or an event).
  *
+ * Updates of one plan must not overlap in time, with each other or with calls that use the plan: the
+ * widths and offsets of a plan whose updates overlap are undefined (any mixture) until the next update
+ * that does not overlap with another.
+ *
  * After daf_plan_update the exact packed size is not known to the host: daf_plan_packed_words
  * returns daf_plan_packed_words_bound (the size with 8 bits for every group; allocate out_words
  * for that) until daf_plan_finish, which synchronizes `stream` once, fetches the exact size and

@@ -19,7 +19,7 @@ struct daf_plan_s {
                          // per group, written by the quantize call's first pass (else null)
   unsigned long long* d_scan;  // mixed plans: the scan's block sums, then the total and the invalid-width flag
   int64_t scan_blocks;
-  unsigned long long* d_posts; // what the workgroups of a width update tell each other, 0 between calls; inside the same allocation
+  unsigned long long* d_posts; // what the workgroups of a width update tell each other, then OnceRounds (plan_scan.hip); inside the same allocation
   int64_t bound_words;   // packed size if every group had 8 bits: what total_words reads while an
                          // update's exact size has not been fetched (pending != 0)
   int32_t pending;

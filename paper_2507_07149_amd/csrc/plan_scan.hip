@@ -75,7 +75,7 @@ __global__ __launch_bounds__(kThreads) void k_plan_block_sums(const uint8_t* __r
                                                               int64_t num_groups, int64_t n, int32_t gs,
                                                               unsigned long long* __restrict__ block_sums,
                                                               unsigned long long* __restrict__ posts) {
-  if (posts != nullptr && threadIdx.x == 0) {            // a new plan's: empty, as k_plan_once leaves them
+  if (posts != nullptr && threadIdx.x == 0) {            // a new plan's: empty, and before its first launch of k_plan_once
     posts[blockIdx.x] = 0ull;
     if (blockIdx.x == 0) posts[gridDim.x] = 0ull;
   }
@@ -352,27 +352,36 @@ constexpr int64_t kOnceRounds2 = 5 << 18, kOnceRounds4 = 13 << 18;
 // the widths of all groups before its own itself.  So the result needs no order of the workgroups and no
 // two of them at the same time.
 //
-// posts[0 .. gridDim.x) are 0 when the launch begins, and so is `finished`; the last workgroup to finish leaves them so
-// again.  A post is an exchange whose result is waited for before the workgroup counts itself as finished: it
-// cannot arrive behind that clearing.
+// Posts stay where they are, and each carries the number of its launch on this plan: rounds.epoch, which every workgroup reads
+// before it counts itself in rounds.started, a counter that wraps at the number of workgroups and then moves the epoch on.  A
+// workgroup counts itself after its reading, so no launch's number is read again once all launches begun so far are through: whatever
+// overlapping updates of one plan leave behind, a later one takes for absent.  (Posts that the last workgroup to finish emptied were
+// damaged for good by an overlap.)  Where epochs differ inside overlapping launches, posts are absent and sums worked out.
 //
-// Sums of a workgroup's words stay below 2^32: group sizes up to kOnceMostSize.
-constexpr unsigned long long kPosted = 1ull << 62;
+// A post: bits 0 .. 31 the sum, 32 .. 62 the epoch plus one, 63 an invalid width.  Sums of a workgroup's words stay below 2^32:
+// group sizes up to kOnceMostSize.
+struct OnceRounds {                                      // 0 in a new plan
+  uint32_t started, epoch;
+};
+static_assert(sizeof(OnceRounds) == sizeof(unsigned long long), "one word behind the posts");
+constexpr uint32_t kTagMask = 0x7FFFFFFFu;
 constexpr int kOnceThreads = 512;
 constexpr int32_t kOnceMostSize = 1 << 18;
 
 template <int ROUNDS>
 __global__ __launch_bounds__(kOnceThreads) void k_plan_once(const uint8_t* __restrict__ src_bits, uint8_t* __restrict__ plan_bits,
                                                             int64_t num_groups, int64_t n, int32_t gs, uint32_t* __restrict__ off,
-                                                            unsigned long long* __restrict__ posts,
-                                                            unsigned long long* __restrict__ finished,
+                                                            unsigned long long* __restrict__ posts, OnceRounds* __restrict__ launches,
                                                             unsigned long long* __restrict__ total, int* __restrict__ bad_flag,
                                                             int polls) {
   constexpr int kWaves = kOnceThreads / daf::kWave, kRound = kOnceThreads * kItems;
   static_assert((long long)ROUNDS * kRound * (kOnceMostSize / 4) < 1ll << 32, "a workgroup's words in 32 bits");
   __shared__ uint32_t wave_tot[ROUNDS * kWaves];
   __shared__ unsigned long long wave_sum[kWaves];
-  __shared__ bool last_to_finish;
+  __shared__ uint32_t shared_tag;
+  // (A cached load, next to the widths: where launches overlap it may be an epoch behind, which is as good as an earlier start.)
+  if (threadIdx.x == 0)
+    shared_tag = (__hip_atomic_load(&launches->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) + 1u) & kTagMask;
   const int64_t first = (int64_t)blockIdx.x * (ROUNDS * kRound);
   const int lane = threadIdx.x & (daf::kWave - 1), wave = threadIdx.x >> 6;
   const uint32_t per_bit = (uint32_t)gs >> 5;            // words of a whole group and bit of width, at most 2^13
@@ -431,10 +440,13 @@ __global__ __launch_bounds__(kOnceThreads) void k_plan_once(const uint8_t* __res
     if (i % kWaves == wave) before[i / kWaves] = own;
     own += wave_tot[i];
   }
-  unsigned long long posted = 0;
-  if (threadIdx.x == 0)
-    posted = __hip_atomic_exchange(&posts[blockIdx.x], own | kPosted | (any_bad ? kBadBit : 0ull), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+  const uint32_t tag = shared_tag;
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(&posts[blockIdx.x], own | (unsigned long long)tag << 32 | (any_bad ? kBadBit : 0ull), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    if (atomicInc(&launches->started, gridDim.x - 1u) == gridDim.x - 1u)
+      __hip_atomic_fetch_add(&launches->epoch, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
     if (aligned_copy && whole(r)) {
@@ -449,10 +461,14 @@ __global__ __launch_bounds__(kOnceThreads) void k_plan_once(const uint8_t* __res
   int missed = 0, bad_ahead = 0;
   for (unsigned i = threadIdx.x; i < blockIdx.x; i += kOnceThreads) {
     unsigned long long v = 0;
-    for (int p = 0; p < polls && !(v & kPosted); ++p) v = __hip_atomic_load(&posts[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    missed |= (v & kPosted) ? 0 : 1;
-    bad_ahead |= (v & kBadBit) ? 1 : 0;
-    ahead += v & ~(kBadBit | kPosted);
+    bool there = false;
+    for (int p = 0; p < polls && !there; ++p) {
+      v = __hip_atomic_load(&posts[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      there = ((uint32_t)(v >> 32) & kTagMask) == tag;
+    }
+    missed |= there ? 0 : 1;
+    bad_ahead |= there && (v & kBadBit) ? 1 : 0;
+    ahead += (uint32_t)v;
   }
   if (__syncthreads_or(missed)) {
     ahead = 0;
@@ -467,12 +483,6 @@ __global__ __launch_bounds__(kOnceThreads) void k_plan_once(const uint8_t* __res
         bad_ahead |= bad_here;
       }
     }
-  }
-  // (all posts this workgroup wants are read: it may count itself as finished, and its offsets go out meanwhile)
-  unsigned long long others = 0;
-  if (threadIdx.x == 0) {
-    asm volatile("" : : "v"((uint32_t)posted) : "memory");                 // the exchange is done
-    others = __hip_atomic_fetch_add(finished, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   for (int o = 32; o > 0; o >>= 1) ahead += __shfl_xor(ahead, o);
   if (lane == daf::kWave - 1) wave_sum[wave] = ahead;
@@ -492,18 +502,9 @@ __global__ __launch_bounds__(kOnceThreads) void k_plan_once(const uint8_t* __res
     }
     store_offsets(off, base_of(r), num_groups, (uint32_t)ahead + before[r] + incl[r] - s[r], w);
   }
-  if (threadIdx.x == 0) {
-    if (blockIdx.x == gridDim.x - 1) {
-      *total = ahead + own;
-      *bad_flag = (any_bad || any_bad_ahead) ? 1 : 0;
-    }
-    last_to_finish = others == gridDim.x - 1u;
-  }
-  __syncthreads();
-  if (last_to_finish) {
-    for (unsigned i = threadIdx.x; i < gridDim.x; i += kOnceThreads)
-      __hip_atomic_store(&posts[i], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (threadIdx.x == 0) __hip_atomic_store(finished, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x == 0 && blockIdx.x == gridDim.x - 1) {
+    *total = ahead + own;
+    *bad_flag = (any_bad || any_bad_ahead) ? 1 : 0;
   }
 }
 
@@ -532,7 +533,7 @@ hipError_t daf_launch_plan_scan(const uint8_t* src_bits, uint8_t* plan_bits, int
     const int64_t per_block = (int64_t)rounds * kOnceThreads * kItems;
     hipLaunchKernelGGL(rounds == 4 ? k_plan_once<4> : rounds == 2 ? k_plan_once<2> : k_plan_once<1>, dim3((unsigned)((num_groups + per_block - 1) / per_block)),
                        dim3(kOnceThreads), 0, stream, src_bits, plan_bits, num_groups, n, group_size, d_off, d_posts,
-                       d_posts + n_blocks, d_total, d_bad, polls);
+                       reinterpret_cast<OnceRounds*>(d_posts + n_blocks), d_total, d_bad, polls);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_plan_block_sums, dim3((unsigned)n_blocks), dim3(kThreads), 0, stream, src_bits, plan_bits,

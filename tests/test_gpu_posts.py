@@ -79,6 +79,35 @@ def test_update_replayed(env):
     plan.destroy()
 
 
+@pytest.mark.parametrize("G", [65537, 4096 * 40 + 3, (13 << 18) + 77])
+def test_update_after_overlapping_updates(env, G):
+    """Updates of one plan that overlap give no defined offsets (equal widths: the right ones), but leave nothing behind: the next
+    update alone is right."""
+    daf, orc, _ = env
+    gs = 32
+    rng = np.random.default_rng(G)
+    host = [rng.choice([1, 2, 4, 8], G).astype(np.uint8) for _ in range(3)]
+    bits = [torch.from_numpy(b).cuda() for b in host]
+    want = [orc.plan(G * gs, gs, b)[0] for b in host]
+    plan = daf.daf_plan((G * gs,), gs, bits[0])
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    torch.cuda.synchronize()
+    for same in (False, True):
+        print("case", G, same, flush=True)
+        for i in range(60):
+            for k, s in enumerate(streams):
+                plan.update(bits[1 if same else (i + k) % 3], stream=s)
+            if i % 10 == 9:
+                torch.cuda.synchronize()
+                if same:
+                    assert np.array_equal(plan.offsets().numpy().view(np.uint32), want[1])
+                for k in (0, 2):
+                    plan.update(bits[k])
+                    torch.cuda.synchronize()
+                    assert np.array_equal(plan.offsets().numpy().view(np.uint32), want[k]), (same, i, k)
+    plan.destroy()
+
+
 @pytest.mark.parametrize("G", [16385, 4096 * 5 - 1, 4096 * 5 + 1, 197000, 1500001])
 @pytest.mark.parametrize("kind", ["random", "ties", "equal", "half zero"])
 @pytest.mark.parametrize("polls", [256, 0])
