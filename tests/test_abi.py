@@ -134,7 +134,7 @@ def test_quantize_route_of_uniform_plans(lib, n, gs, dtype, want):
     (512, 1088, 11008, 2, (256, 128)),
     # one tile of n: never; enough of them for the wider general tile
     (4096, 256, 4096, 2, (256, 128)), (2048, 256, 65536, 1, (256, 256)), (4096, 128, 65536, 2, (256, 256)),
-    (4096, 4096, 4096, 0, (256, 256)), (256, 256, 192, 2, (256, 64)), (512, 1024, 1024, 1, (256, 128))])
+    (4096, 4096, 4096, 0, (256, 256)), (256, 256, 192, 2, (256, 64)), (512, 1024, 1024, 1, (256, 64))])
 def test_weight_gradient_tile(lib, m, n, k, dtype, tile):
     import paper_2507_07149_amd as daf
     import torch
@@ -166,8 +166,11 @@ def test_weight_gradient_tile_of_an_odd_number_of_64_columns(lib, m, n, k):
 
 @pytest.mark.parametrize("m,n,k,dtype,tile,slices", [
     (1344, 640, 1536, 2, (256, 64), 4), (896, 512, 8064, 1, (256, 64), 1), (672, 320, 5376, 1, (256, 64), 1), (992, 128, 1280, 0, (256, 64), 7),
-    # up to 512 values of m, below 128 rows, more than a round of such tiles, shapes that have this tile already
-    (512, 640, 1536, 2, (256, 128), None), (1344, 64, 1536, 2, (256, 128), None), (4096, 4096, 4352, 0, (256, 256), None),
+    # few steps along m
+    (512, 640, 1536, 2, (256, 64), 2), (512, 1024, 1024, 1, (256, 64), 4), (64, 512, 256, 2, (256, 64), 1), (32, 256, 1280, 2, (256, 64), 1),
+    (96, 192, 8064, 0, (256, 64), 1),
+    # below 128 rows, more than a round of such tiles, shapes that have this tile already
+    (1344, 64, 1536, 2, (256, 128), None), (4096, 4096, 4352, 0, (256, 256), None),
     (544, 128, 8768, 0, (256, 64), 4), (640, 1344, 960, 2, (256, 64), 3)])
 def test_weight_gradient_narrow_tile(lib, m, n, k, dtype, tile, slices):
     """Outputs of few tiles take 256 x 64, in no fewer slices than the wider tile, whose partial sums fit the workspace that callers are told of."""

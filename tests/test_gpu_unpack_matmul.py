@@ -164,9 +164,11 @@ def test_grad_weight_odd_multiple_of_64_columns(env, steps, N, K, gs, bits, dtyp
     _steps_case(env, steps, N, K, gs, bits, dtype, bn, bk)
 
 
-# Outputs of few tiles: 256 x 64, over all of m and in slices; ends of n inside the tile.
+# Outputs of few tiles: 256 x 64, over all of m and in slices, from one step along m; ends of n inside the tile.
 @pytest.mark.parametrize("steps,N,K,gs,bits,dtype", [(20, 1344, 960, 32, "mixed", BF16), (17, 128, 640, 64, 2, F16), (42, 640, 768, 768, "mixed", F16),
-                                                     (21, 320, 5376, 64, "mixed", BF16), (31, 128, 640, 128, 8, F32)])
+                                                     (21, 320, 5376, 64, "mixed", BF16), (31, 128, 640, 128, 8, F32),
+                                                     (1, 256, 1280, 64, "mixed", BF16), (2, 192, 1280, 32, 4, F16), (3, 192, 8064, 32, "mixed", F32),
+                                                     (15, 320, 768, 768, "mixed", BF16), (16, 1024, 1024, 128, 1, F16)])
 def test_grad_weight_few_tiles(env, steps, N, K, gs, bits, dtype):
     _steps_case(env, steps, N, K, gs, bits, dtype, 256, 64)
 
