@@ -11,8 +11,16 @@ _DTYPE_ID = {torch.float32: F32, torch.float16: F16, torch.bfloat16: BF16}
 
 try:
     from . import _fast_calls            # csrc/fast_calls.cpp: checks, pointers, stream and call of the inner loop's calls in one step
-except ImportError:                      # built against another torch: the checks below and ctypes do the same
+except ImportError:                      # not built, or against a torch whose symbols differ: the checks below and ctypes do the same
     _fast_calls = None
+
+
+def _of_this_torch(module):
+    """The module if it was compiled against the torch that runs, whose tensors it reads directly; else None."""
+    return module if getattr(module, "torch_version", None) == torch.__version__ else None
+
+
+_fast_calls = _of_this_torch(_fast_calls)
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libdaf.so")

@@ -18,7 +18,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdaf.so")
-FAST_CALLS = os.path.join(HERE, "_fast_calls.so")
+FAST_CALLS = os.path.join(HERE, "_fast_calls" + sysconfig.get_config_var("EXT_SUFFIX"))      # of this interpreter alone
 # (source, object name, extra flags): quantize_pack.hip is built once per element format
 SOURCES = [("quantize_pack.hip", "quantize_pack_f32", ["-DDAF_DT=0"]),
            ("quantize_pack.hip", "quantize_pack_f16", ["-DDAF_DT=1"]),
@@ -51,24 +51,32 @@ def _compile(item) -> str:
 
 
 def _compile_fast_calls() -> None:
-    """The Python module with the inner loop's calls: host code against the headers of the torch that is installed."""
+    """The Python module with the inner loop's calls: host code against the headers of the torch that is installed.  Raises where
+    g++, those headers or Python's do not work together; no module is left then, not an earlier one either."""
+    for name in os.listdir(HERE):
+        if name.startswith("_fast_calls") and name.endswith(".so"):
+            os.remove(os.path.join(HERE, name))
     import torch
     at = os.path.dirname(torch.__file__)
     rocm = os.path.dirname(os.path.dirname(os.path.realpath(HIPCC)))
     subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-                    "-I" + os.path.join(ROOT, "include"), "-isystem", os.path.join(at, "include"), "-isystem",
+                    f'-DDAF_TORCH_VERSION="{torch.__version__}"', "-I" + os.path.join(ROOT, "include"), "-isystem", os.path.join(at, "include"), "-isystem",
                     os.path.join(at, "include", "torch", "csrc", "api", "include"), "-isystem", os.path.join(rocm, "include"),
                     "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "fast_calls.cpp"), "-o", FAST_CALLS,
                     "-L" + os.path.join(at, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], check=True)
 
 
 def build() -> str:
+    """The library; and the Python module where it compiles, without which the binding's calls go through ctypes."""
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=8) as ex:
         fast = ex.submit(_compile_fast_calls)
         objs = list(ex.map(_compile, SOURCES))
-        fast.result()
-    subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
+        subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
+        try:
+            fast.result()
+        except (ImportError, OSError, subprocess.CalledProcessError) as e:
+            sys.stderr.write(f"_fast_calls was not built ({e}): calls go through ctypes, with about 2 us more host time each\n")
     return LIB
 
 

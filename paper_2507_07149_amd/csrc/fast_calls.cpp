@@ -364,5 +364,7 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fast_calls", nullptr, -1, methods
 PyMODINIT_FUNC PyInit__fast_calls() {
   handle_name = PyUnicode_InternFromString("_h");
   stream_name = PyUnicode_InternFromString("cuda_stream");
-  return PyModule_Create(&module);
+  PyObject* m = PyModule_Create(&module);
+  if (m != nullptr && PyModule_AddStringConstant(m, "torch_version", DAF_TORCH_VERSION) < 0) Py_CLEAR(m);
+  return m;
 }

@@ -1,10 +1,17 @@
 """The native step of the inner loop's calls (csrc/fast_calls.cpp): it takes the usual arguments, and leaves everything else to the
 general checks without having done anything."""
+import os
+import subprocess
+import types
+
 import pytest
 import torch
 
 import paper_2507_07149_amd as daf
-from paper_2507_07149_amd import binding
+from paper_2507_07149_amd import binding, build
+
+
+needs_the_module = pytest.mark.skipif(binding._fast_calls is None, reason="the module does not compile here (test_the_module_is_built)")
 
 
 class Tagged(torch.Tensor):
@@ -39,9 +46,83 @@ def _call(name, args, t, **other):
 
 
 def test_the_module_is_built():
+    if not os.path.exists(build.FAST_CALLS):
+        try:
+            build._compile_fast_calls()
+        except (ImportError, OSError, subprocess.CalledProcessError) as e:
+            pytest.skip(f"does not compile here: {e}")
     assert binding._fast_calls is not None and binding._fast is binding._fast_calls
 
 
+def test_the_library_is_linked_where_the_module_does_not_compile(monkeypatch, tmp_path, capsys):
+    steps = []
+    stale = tmp_path / "_fast_calls.so"
+    stale.write_bytes(b"")
+    monkeypatch.setattr(build, "HERE", str(tmp_path))
+    monkeypatch.setattr(build, "OBJ", str(tmp_path / "obj"))
+    monkeypatch.setattr(build, "_compile", lambda item: item[1])
+
+    def run(command, **other):
+        steps.append(command[0])
+        if command[0] == "g++":
+            raise subprocess.CalledProcessError(1, command)
+    monkeypatch.setattr(build.subprocess, "run", run)
+    assert build.build() == build.LIB
+    assert sorted(steps) == sorted(["g++", build.HIPCC]) and not stale.exists()
+    assert "was not built" in capsys.readouterr().err
+
+
+def test_a_module_of_another_torch_is_not_used():
+    assert binding._of_this_torch(types.SimpleNamespace(torch_version=torch.__version__)) is not None
+    for other in (types.SimpleNamespace(torch_version="1.0"), types.SimpleNamespace(), None):
+        assert binding._of_this_torch(other) is None
+    assert binding._fast_calls is None or binding._fast_calls.torch_version == torch.__version__
+
+
+PUBLIC = {"group_minmax": "daf_group_minmax", "quantize_pack": "daf_quantize_pack", "quantize_pack_static": "daf_quantize_pack_static",
+          "quantize_pack_metrics": "daf_quantize_pack_metrics", "relu_quantize_pack": "daf_relu_quantize_pack",
+          "unpack_dequantize": "daf_unpack_dequantize", "unpack_relu_backward": "daf_unpack_relu_backward",
+          "select_bits": "daf_select_bits", "select_bits_from_scale": "daf_select_bits_from_scale"}
+
+
+def _public_call(name, args, t):
+    plan, args = args[0], [t.get(a) if isinstance(a, str) else a for a in args]
+    (plan.update if name == "plan_update" else getattr(daf, PUBLIC[name]))(*(args[1:] if name == "plan_update" else args))
+
+
+def test_without_the_module_the_general_checks_refuse(monkeypatch):
+    monkeypatch.setattr(binding, "_fast", binding._NoFastCalls())
+    plan, t, calls = _case("cpu")
+    for name, args in calls.items():
+        with pytest.raises(ValueError):
+            _public_call(name, args, t)
+    plan.destroy()
+
+
+@pytest.mark.gpu
+def test_without_the_module_every_call_does_the_same(monkeypatch):
+    plan, t, calls = _case("cuda:0")
+    torch.manual_seed(0)
+    t["x"].copy_(torch.randn(t["x"].numel()))
+    order = ("group_minmax", "select_bits", "quantize_pack", "quantize_pack_static", "quantize_pack_metrics", "unpack_dequantize",
+             "unpack_relu_backward", "relu_quantize_pack", "select_bits_from_scale", "plan_update")
+    assert set(order) == set(calls)
+    seen = []
+    for fast in (binding._fast, binding._NoFastCalls()):
+        monkeypatch.setattr(binding, "_fast", fast)
+        for name in order:
+            for key in ("words", "y", "next"):
+                t[key].zero_()
+            _public_call(name, calls[name], t)
+            torch.cuda.synchronize()
+            seen.append({k: v.clone() for k, v in t.items() if k != "ws"})
+    n = len(order)
+    for name, a, b in zip(order, seen[:n], seen[n:]):
+        assert all(torch.equal(a[k], b[k]) for k in a), name
+    plan.destroy()
+
+
+@needs_the_module
 def test_host_tensors_are_left_to_the_general_checks():
     plan, t, calls = _case("cpu")
     for name, args in calls.items():
@@ -50,6 +131,7 @@ def test_host_tensors_are_left_to_the_general_checks():
     assert _call("quantize_pack", calls["quantize_pack"], t) is None
 
 
+@needs_the_module
 @pytest.mark.gpu
 def test_usual_arguments_are_taken_and_others_left():
     plan, t, calls = _case("cuda:0")
