@@ -123,8 +123,11 @@ PyObject* run(Py_ssize_t got, Py_ssize_t wanted, Make make) {
       auto call = make(c);
       if (c.ok) {
         int rc;
+        // (An exception from the library's C functions ends the process, as it did on its way through ctypes: caught below, it would
+        // come back to the interpreter without the lock.)
+        auto without_the_lock = [&]() noexcept { rc = call(); };
         Py_BEGIN_ALLOW_THREADS
-        rc = call();
+        without_the_lock();
         Py_END_ALLOW_THREADS
         return PyLong_FromLong(rc);
       }
