@@ -210,15 +210,8 @@ int plan_update(daf_plan_t* plan, const uint8_t* bits, void* stream, int polls) 
 
 int daf_plan_update(daf_plan_t* plan, const uint8_t* bits, void* stream) { return plan_update(plan, bits, stream, kPostPolls); }
 
-// For the tests, which make every workgroup do without the others' sums (polls 0).
 int daf_internal_plan_update(daf_plan_t* plan, const uint8_t* bits, int polls, void* stream) {
   return plan_update(plan, bits, stream, polls);
-}
-int daf_internal_select_bits(const float* group_min, const float* group_max, int64_t num_groups, const uint8_t* classes,
-                             int32_t n_classes, uint8_t* out_bits, void* workspace, int polls, void* stream) {
-  const hipError_t e = daf_launch_select_bits(group_min, group_max, nullptr, 0, num_groups, classes, n_classes, out_bits,
-                                              workspace, static_cast<hipStream_t>(stream), polls);
-  return e == hipSuccess ? DAF_OK : DAF_EDEVICE;
 }
 
 int daf_plan_finish(daf_plan_t* plan, void* stream) {
@@ -533,8 +526,9 @@ int64_t daf_select_bits_workspace_bytes(int64_t num_groups) {
   return num_groups < 1 ? -1 : daf_select_bits_workspace_size(num_groups);
 }
 
-int daf_select_bits(const float* group_min, const float* group_max, int64_t num_groups, const uint8_t* classes,
-                    int32_t n_classes, uint8_t* out_bits, void* workspace, void* stream) {
+namespace {
+int select_bits(const float* group_min, const float* group_max, int64_t num_groups, const uint8_t* classes, int32_t n_classes,
+                uint8_t* out_bits, void* workspace, int polls, void* stream) {
   if (group_min == nullptr || group_max == nullptr || classes == nullptr || out_bits == nullptr ||
       workspace == nullptr || num_groups < 1 || n_classes < 1 || n_classes > 4)
     return DAF_EINVAL;
@@ -543,8 +537,19 @@ int daf_select_bits(const float* group_min, const float* group_max, int64_t num_
     if (!valid_width(classes[c])) return DAF_EINVAL;
   if (num_groups >= (int64_t)1 << 32) return DAF_EUNSUPPORTED;
   const hipError_t e = daf_launch_select_bits(group_min, group_max, nullptr, 0, num_groups, classes, n_classes, out_bits,
-                                              workspace, static_cast<hipStream_t>(stream));
+                                              workspace, static_cast<hipStream_t>(stream), polls);
   return e == hipSuccess ? DAF_OK : DAF_EDEVICE;
+}
+}  // namespace
+
+int daf_select_bits(const float* group_min, const float* group_max, int64_t num_groups, const uint8_t* classes,
+                    int32_t n_classes, uint8_t* out_bits, void* workspace, void* stream) {
+  return select_bits(group_min, group_max, num_groups, classes, n_classes, out_bits, workspace, kPostPolls, stream);
+}
+
+int daf_internal_select_bits(const float* group_min, const float* group_max, int64_t num_groups, const uint8_t* classes,
+                             int32_t n_classes, uint8_t* out_bits, void* workspace, int polls, void* stream) {
+  return select_bits(group_min, group_max, num_groups, classes, n_classes, out_bits, workspace, polls, stream);
 }
 
 int daf_select_bits_from_scale(const float* group_scale, const uint8_t* group_bits, int32_t uniform_bits,

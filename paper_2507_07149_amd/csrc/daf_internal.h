@@ -41,6 +41,12 @@ int daf_quantize_route(const daf_plan_t* plan, int dtype);
 // works the sum out itself.
 constexpr int kPostPolls = 256;
 
+// daf_plan_update and daf_select_bits (the same argument checks) with another number of looks: tests have no other way to make every
+// workgroup do without the others' sums (polls 0).  No part of the interface, for no other use.
+extern "C" int daf_internal_plan_update(daf_plan_t* plan, const uint8_t* bits, int polls, void* stream);
+extern "C" int daf_internal_select_bits(const float* group_min, const float* group_max, int64_t num_groups, const uint8_t* classes,
+                                        int32_t n_classes, uint8_t* out_bits, void* workspace, int polls, void* stream);
+
 // Launchers.  Each returns hipSuccess or the first HIP error.
 // src_bits: the caller's widths; plan_bits: the plan's copy, written by the scan with every width
 // outside {1,2,4,8} replaced by 8 (and *d_bad set).  No value needs clearing beforehand.

@@ -125,6 +125,23 @@ def test_quantize_route_of_uniform_plans(lib, n, gs, dtype, want):
     lib.daf_plan_destroy(p)
 
 
+def test_calls_with_another_number_of_looks_check_their_arguments_too(lib):
+    classes = (ctypes.c_uint8 * 3)(2, 4, 8)
+    wrong = (ctypes.c_uint8 * 3)(2, 3, 8)
+    ptr = ctypes.c_void_p
+
+    def select(lo=4096, hi=4096, G=100, cl=classes, n=3, out=4096, ws=4096):
+        return lib.daf_internal_select_bits(ptr(lo), ptr(hi), ctypes.c_int64(G), cl, n, ptr(out), ptr(ws), 0, None)
+    for bad in (dict(lo=None), dict(hi=None), dict(out=None), dict(ws=None), dict(ws=4104), dict(lo=4098), dict(G=0), dict(n=0),
+                dict(n=5), dict(cl=wrong)):
+        assert select(**bad) == -1, bad
+    assert select(G=1 << 32) == -2
+    rc, p = _plan(lib, (64,), 32, [2])
+    assert lib.daf_internal_plan_update(None, ptr(16), 0, None) == -1 and lib.daf_internal_plan_update(p, None, 0, None) == -1
+    assert lib.daf_internal_plan_update(p, ptr(16), 0, None) == -1                   # one width
+    lib.daf_plan_destroy(p)
+
+
 # m, n, k, element format -> tile of the weight gradient: 512 x 128 only where it is not slower than the general kernel
 @pytest.mark.parametrize("m,n,k,dtype,tile", [
     (32768, 4096, 11008, 2, (512, 128)), (32768, 3072, 768, 1, (512, 128)), (128, 4096, 4096, 2, (512, 128)),
