@@ -8,7 +8,8 @@ import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
-GROUPS = [65537, 4096 * 17 - 1, 4096 * 17, 4096 * 17 + 1, (1 << 20) - 7, (1 << 20) + 1, 8192 * 200 + 5]
+# one round of 4096 groups to a workgroup, two (from 5 << 18), four (from 13 << 18)
+GROUPS = [65537, 4096 * 17 - 1, 4096 * 17, 4096 * 17 + 1, (1 << 20) - 7, (1 << 20) + 1, 8192 * 200 + 5, (13 << 18) + 4096 + 3]
 
 
 @pytest.fixture(scope="module")
@@ -35,30 +36,27 @@ def test_update(env, G, skew):
     gs, n = 64, G * 64 - 37
     rng = np.random.default_rng(G)
     plan = daf.daf_plan((n,), gs, torch.ones(G, dtype=torch.uint8, device="cuda:0"))
-    for i, polls in enumerate([256, 0, 256, 1, 256]):
+    # a wrong width (reported, and counted as 8): in the first workgroup with no look at its post, and in the middle
+    for polls, wrong in [(256, None), (0, 5), (0, None), (256, G // 2), (1, None), (0, G - 1), (256, None)]:
         b = rng.choice([1, 2, 4, 8], G).astype(np.uint8)
-        if i == 2:
-            b[G // 2] = 3                                           # reported, and counted as 8
+        if wrong is not None:
+            b[wrong] = 3
         whole = torch.zeros(G + 32, dtype=torch.uint8, device="cuda:0")
         whole[skew: skew + G] = torch.from_numpy(b).cuda()
-        print("case", G, skew, polls, flush=True)
+        print("case", G, skew, polls, wrong, flush=True)
         assert _update(lib, plan, whole[skew: skew + G], polls) == 0
-        if i == 2:
-            with pytest.raises(daf.DafError):
-                plan.update(whole[skew: skew + G])
-                plan.finish()
-            b[G // 2] = 8
-        else:
-            assert lib.daf_plan_finish(ctypes.c_void_p(plan.handle), _stream()) == 0
+        assert lib.daf_plan_finish(ctypes.c_void_p(plan.handle), _stream()) == (0 if wrong is None else -1)
+        b[b == 3] = 8
         off, total = orc.plan(n, gs, b)
-        torch.cuda.synchronize()
+        assert lib.daf_plan_packed_words(ctypes.c_void_p(plan.handle)) == total
         assert np.array_equal(plan.offsets().numpy().view(np.uint32), off)
     plan.destroy()
 
 
-def test_update_replayed(env):
+@pytest.mark.parametrize("G", [4096 * 21 + 9, (5 << 18) + 9, (13 << 18) + 9])
+def test_update_replayed(env, G):
     daf, orc, _ = env
-    G, gs = 4096 * 21 + 9, 32
+    gs = 32
     rng = np.random.default_rng(5)
     bits = torch.from_numpy(rng.choice([1, 2, 4, 8], G).astype(np.uint8)).cuda()
     plan = daf.daf_plan((G * gs,), gs, bits)
@@ -108,7 +106,7 @@ def test_update_after_overlapping_updates(env, G):
     plan.destroy()
 
 
-@pytest.mark.parametrize("G", [16385, 4096 * 5 - 1, 4096 * 5 + 1, 197000, 1500001])
+@pytest.mark.parametrize("G", [16385, 4096 * 5 - 1, 4096 * 5 + 1, 197000, 1500001, (7 << 18) + 8192 + 3])
 @pytest.mark.parametrize("kind", ["random", "ties", "equal", "half zero"])
 @pytest.mark.parametrize("polls", [256, 0])
 def test_select(env, G, kind, polls):
