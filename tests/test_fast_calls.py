@@ -171,3 +171,47 @@ def test_usual_arguments_are_taken_and_others_left():
     assert seen == [None]
     torch.cuda.synchronize()
     plan.destroy()
+
+
+@needs_the_module
+@pytest.mark.gpu
+def test_operands_of_products_that_are_taken_and_left():
+    """The linear layer and the weight gradient: shapes, sizes taken from the operands and the workspace's bytes."""
+    m, k, n, gs = 4096, 128, 256, 64
+    fast, dev = binding._fast_calls, "cuda:0"
+    full = lambda *shape, dtype=torch.bfloat16: torch.zeros(shape, dtype=dtype, device=dev)
+    y_plan, x_plan = daf.daf_plan((m, n), gs, 4), daf.daf_plan((m, k), gs, 4)
+
+    def packed(plan):
+        return [full(plan.packed_words, dtype=torch.int32), full(plan.num_groups, dtype=torch.float32), full(plan.num_groups, dtype=torch.float32)]
+    linear = [y_plan, full(m, k), full(n, k), 3, full(m, n), *packed(y_plan), None]
+    need = daf.daf_unpack_matmul_workspace_bytes(x_plan, n, k)
+    assert need >= 16
+    grad = [x_plan, *packed(x_plan), full(m, n), full(n, k, dtype=torch.float32), full(need, dtype=torch.uint8), None, None]
+
+    def left(call, args, i, *bad):
+        for b in bad:
+            assert call(*args[:i], b, *args[i + 1:]) is None, (call.__name__, i, getattr(b, "shape", b))
+    assert fast.linear_quantize_pack(*linear) == 0 and fast.unpack_matmul_grad_weight(*grad) == 0
+    assert fast.unpack_matmul_grad_weight(*grad[:6], full(need // 4, dtype=torch.float32), None, None) == 0
+    for i in (1, 2, 4, 5, 6, 7):
+        left(fast.linear_quantize_pack, linear, i, None, [0], linear[i].cpu(), linear[i][:-1], linear[i].double(), linear[i].as_subclass(Tagged))
+    left(fast.linear_quantize_pack, linear, 1, full(m, 2 * k), full(m * k), full(1, m, k), full(k, m).t(), full(m, 2 * k)[:, :k],
+         full(m, k, dtype=torch.float16), full(m, k, dtype=torch.int16))
+    left(fast.linear_quantize_pack, linear, 2, full(n, 2 * k), full(n * k), full(k, n).t(), full(2 * n, k), full(n, k, dtype=torch.float16))
+    left(fast.linear_quantize_pack, linear, 4, full(m, n, dtype=torch.float16), full(n, m).t())
+    left(fast.linear_quantize_pack, linear, 0, x_plan, None)
+    for i in (1, 2, 3, 4, 5, 6):
+        left(fast.unpack_matmul_grad_weight, grad, i, [0], grad[i].cpu(), grad[i][:-1], grad[i].as_subclass(Tagged))
+    for i in (1, 2, 3, 4, 5):
+        left(fast.unpack_matmul_grad_weight, grad, i, None)
+    left(fast.unpack_matmul_grad_weight, grad, 4, full(m, n // 2), full(m // 2, n), full(m * n), full(n, m).t(), full(m, n, dtype=torch.float64))
+    left(fast.unpack_matmul_grad_weight, grad, 5, full(n, k), full(n * k, dtype=torch.float32), full(2 * n, k, dtype=torch.float32),
+         full(n, k // 2, dtype=torch.float32), full(n, 2 * k, dtype=torch.float32), full(k, n, dtype=torch.float32).t())
+    left(fast.unpack_matmul_grad_weight, grad, 6, full(need // 4 - 1, dtype=torch.float32), full(2 * need, dtype=torch.uint8)[::2])
+    left(fast.unpack_matmul_grad_weight, grad, 7, full(x_plan.num_groups - 1, dtype=torch.uint8), full(x_plan.num_groups, dtype=torch.int32))
+    left(fast.unpack_matmul_grad_weight, grad, 0, y_plan, None)
+    torch.cuda.synchronize()
+    for plan in (x_plan, y_plan):
+        plan.destroy()
+        assert fast.linear_quantize_pack(plan, *linear[1:]) is None and fast.unpack_matmul_grad_weight(plan, *grad[1:]) is None
