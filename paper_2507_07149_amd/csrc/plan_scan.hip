@@ -3,8 +3,8 @@
 // The packed buffer concatenates the groups' codes (paper Sec. 3.3 speaks of packing the
 // compressed values together); with a bit width per group the position of group g is the
 // sum of the word counts of all groups before it.  Up to kAheadMost groups one launch does it (k_plan_ahead); new widths for a
-// plan that exists take one launch as well, whose workgroups tell each other their sums (k_plan_once).  A new plan of
-// up to kMaxSummedBlocks blocks of 2048 groups: per-block sums and a second launch in which every
+// plan that exists take one launch as well, from kAheadMostUpdated groups on one whose workgroups tell each other their sums
+// (k_plan_once).  A new plan of up to kMaxSummedBlocks blocks of 2048 groups: per-block sums and a second launch in which every
 // block adds up the sums before its own and writes its offsets; beyond that a single-block scan of the sums comes between them.
 #include "daf_device.h"
 #include "daf_internal.h"
@@ -257,13 +257,16 @@ __device__ __forceinline__ uint32_t sixteen_widths(const uint4& v, int* bad) {
   return sum;
 }
 
-template <bool AHEAD>
+// NEW_PLAN: with posts to empty, as in k_plan_block_sums.  They lie behind the total and the flag: with arguments for them an update of
+// 12288 groups took 0.08 us more.
+template <bool AHEAD, bool NEW_PLAN>
 __global__ __launch_bounds__(kAheadThreads) void k_plan_ahead(const uint8_t* __restrict__ src_bits,
                                                               uint8_t* __restrict__ plan_bits, int64_t num_groups, int64_t n,
                                                               int32_t gs, uint32_t* __restrict__ off,
                                                               unsigned long long* __restrict__ total,
                                                               int* __restrict__ bad_flag) {
   constexpr int kWaves = kAheadThreads / daf::kWave;
+  if (NEW_PLAN && blockIdx.x == 0 && threadIdx.x < (num_groups + kBlockGroups - 1) / kBlockGroups + 1) total[2 + threadIdx.x] = 0ull;
   __shared__ uint32_t wave_tot[kWaves];
   [[maybe_unused]] __shared__ uint32_t wave_widths[kWaves];
   __shared__ unsigned long long wave_sum[kWaves];
@@ -331,16 +334,20 @@ __global__ __launch_bounds__(kAheadThreads) void k_plan_ahead(const uint8_t* __r
   }
 }
 
-// Up to 65536 groups: kernel alone 4.0 ... 5.3 us up to 8192 groups, 6.1 at 16384, 7.6 at 32768 and 8.2 at 65536, the two launches 9.4 and
-// the gap between them at all of these sizes; at 197000 groups the sums over all that comes before make it slower (call of four
-// launches 62.0 -> 65.4 us, at 524288 51.4 -> 60.3).
-constexpr int64_t kAheadMost = 1 << 16;
+// A new plan of up to 65536 groups: k_plan_ahead alone 4.0 ... 5.3 us up to 8192 groups, 5.8 at 10000, 6.4 at 16384, 7.3 at 32768 and 7.4 at
+// 65536, the two launches 8.4 from there to 197000; at 197000 groups the sums over all that comes before make it slower (call of
+// four launches 62.0 -> 65.4 us, at 524288 51.4 -> 60.3).  An update leaves it for k_plan_once earlier, which a new plan, whose posts are
+// not empty yet, cannot take: ahead / once, launches one behind the other: 10000 groups 5.8 / 6.3 us, 12288 5.9 / 6.4, 14336 5.9 / 5.7,
+// 16384 6.4 / 5.7, 20480 6.4 / 6.2, 32768 7.3 / 5.9, 65536 7.4 / 5.8.
+constexpr int64_t kAheadMost = 1 << 16, kAheadMostUpdated = 7 << 11;
+static_assert(kAheadMost / kBlockGroups + 1 <= kAheadThreads, "k_plan_ahead's first workgroup empties the posts");
 constexpr int64_t kMaxSummedBlocks = 4096;            // 32 KB of block sums, read by every block
-// Rounds of k_plan_once: launches one behind the other, one / two / four rounds: 197 K groups 6.7 / 8.6 / 12.2 us, 1 M 8.3 / 9.0 / 12.3, 2 M
-// 11.9 / 9.7 / 12.7, 3 M 15.7 / 12.1 / 12.8, 5.6 M 26 / 19 / 14 (17 on another card), 9.4 M 39 / 27 / 25.  Two launches before: 197 K 8.9, 1 M 10.0, 2 M 12.4,
-// 5.6 M 23.0.
+// Rounds of k_plan_once: launches one behind the other, one / two / four rounds, and the form with a launch for the sums (above
+// kMaxSummedBlocks two) in front: 70 K groups 6.7 / 8.0 / 10.7, 8.4 us, 197 K 6.6 / 8.2 / 12.0, 8.6, 1 M 7.7 / 8.3 / 11.6, 9.8, 2 M 11.5 /
+// 9.3 / 12.0, 12.2, 3 M 15.6 / 11.5 / 12.2, 15.0, 5.6 M 31 / 17 / 14, 23, 9.4 M 76 / 35 / 24, 39, 20 M 176 / 94 / 51, 79, 100 M 1062 / 592 / 314,
+// 374, 400 M 4868 / 2270 / 1266, 1606.  (A workgroup of 16384 groups reads 8 bytes for each one before it: at 400 M groups, the most a plan
+// has room for being 537 M, 0.1 MB on average, out of the caches.)
 constexpr int64_t kOnceRounds2 = 5 << 18, kOnceRounds4 = 13 << 18;
-
 
 // One launch for any number of groups.  Every workgroup posts the sum of its own groups' words, takes the sums of those before
 // it from their posts, all at a time, and writes its offsets: widths are read once, and the second launch, its gap and its reading of
@@ -518,17 +525,19 @@ hipError_t daf_launch_plan_scan(const uint8_t* src_bits, uint8_t* plan_bits, int
                                 int32_t group_size, uint32_t* d_off, unsigned long long* d_block_sums, int64_t n_blocks,
                                 unsigned long long* d_total, int* d_bad, unsigned long long* d_posts, bool new_plan,
                                 hipStream_t stream, int polls) {
+  if (d_posts != d_total + 2) return hipErrorInvalidValue;            // (k_plan_ahead finds them so)
   const bool apart = src_bits + num_groups <= plan_bits || plan_bits + num_groups <= src_bits;
   const bool aligned = (reinterpret_cast<uintptr_t>(src_bits) & 15u) == 0u;
-  if (num_groups <= kAheadGroups || (num_groups <= kAheadMost && apart && aligned)) {
+  // (Widths in the plan's own copy would be replaced while others read them.)
+  const bool once = !new_plan && num_groups > kAheadMostUpdated && apart && group_size <= kOnceMostSize;
+  if (!once && (num_groups <= kAheadGroups || (num_groups <= kAheadMost && apart && aligned))) {
     const unsigned blocks = (unsigned)((num_groups + kAheadGroups - 1) / kAheadGroups);
-    hipLaunchKernelGGL(blocks > 1 ? k_plan_ahead<true> : k_plan_ahead<false>, dim3(blocks), dim3(kAheadThreads), 0, stream,
-                       src_bits, plan_bits, num_groups, n, group_size, d_off, d_total, d_bad);
+    const auto kernel = blocks == 1 ? k_plan_ahead<false, false> : new_plan ? k_plan_ahead<true, true> : k_plan_ahead<true, false>;
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kAheadThreads), 0, stream, src_bits, plan_bits, num_groups, n, group_size, d_off,
+                       d_total, d_bad);
     return hipGetLastError();
   }
-  // (A new plan's posts are empty once k_plan_block_sums has been through.  Widths in the plan's own copy would be replaced while
-  // others read them.)
-  if (!new_plan && num_groups > kAheadMost && apart && group_size <= kOnceMostSize) {
+  if (once) {
     const int rounds = num_groups > kOnceRounds4 ? 4 : num_groups > kOnceRounds2 ? 2 : 1;
     const int64_t per_block = (int64_t)rounds * kOnceThreads * kItems;
     hipLaunchKernelGGL(rounds == 4 ? k_plan_once<4> : rounds == 2 ? k_plan_once<2> : k_plan_once<1>, dim3((unsigned)((num_groups + per_block - 1) / per_block)),

@@ -9,7 +9,7 @@ import torch
 
 pytestmark = pytest.mark.gpu
 # one round of 4096 groups to a workgroup, two (from 5 << 18), four (from 13 << 18)
-GROUPS = [65537, 4096 * 17 - 1, 4096 * 17, 4096 * 17 + 1, (1 << 20) - 7, (1 << 20) + 1, 8192 * 200 + 5, (13 << 18) + 4096 + 3]
+GROUPS = [14337, 4096 * 4, 32769, 65536, 65537, 4096 * 17 - 1, 4096 * 17, 4096 * 17 + 1, (1 << 20) - 7, (1 << 20) + 1, 8192 * 200 + 5, (13 << 18) + 4096 + 3]
 
 
 @pytest.fixture(scope="module")
@@ -77,7 +77,7 @@ def test_update_replayed(env, G):
     plan.destroy()
 
 
-@pytest.mark.parametrize("G", [65537, 4096 * 40 + 3, (13 << 18) + 77])
+@pytest.mark.parametrize("G", [14337, 65537, 4096 * 40 + 3, (13 << 18) + 77])
 def test_update_after_overlapping_updates(env, G):
     """Updates of one plan that overlap give no defined offsets (equal widths: the right ones), but leave nothing behind: the next
     update alone is right."""
