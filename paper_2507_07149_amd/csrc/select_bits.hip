@@ -21,9 +21,10 @@
 // (k_select_classify).  What a pass decides (the bin that holds the rank) is worked out from its counters by
 // every workgroup of the next launch for itself: a scan of 2048 counters from the cache, next to the
 // keys that are on their way, instead of a ticket, a last workgroup and its trips past the caches at the end
-// of every launch.  Selection alone, four classes, before (ticket and last
-// workgroup in four of six launches) and now: 500 groups 39 / 14 us, 8192 40 / 20, 197 K 49 / 29, 1 M 54 / 34, 5.6 M 94 / 66;
-// all ranges equal: 197 K 53 / 38, 5.6 M 127 / 104.
+// of every launch.  Selection alone, four classes, with tickets and last workgroups in four of six launches, then in six without, now: 500 groups
+// 39, 14, 3.9 us (one launch by then), 8192 40, 20, 8.7, 197 K 49, 29, 22.8, 1 M 54, 34, 29, 5.6 M 94, 66, 58; all ranges equal: 197 K 53,
+// 38, 25.8, 5.6 M 127, 104, 72.  Six launches and these, random and all equal: 20 M 138 / 121 and 309 / 191, 100 M 640 / 550 and
+// 1490 / 942, 400 M 2550 / 2155 and 5980 / 4290.
 #include <type_traits>
 
 #include "daf_device.h"
@@ -609,9 +610,11 @@ __global__ __launch_bounds__(kSmallThreads) void k_select_small(const float* sca
 // before the counting and one behind it.  Every workgroup reads all groups, so the widths written are not those read.
 constexpr int kRankThreads = 1024;
 constexpr int kRankGroups = 32, kRankParts = kRankThreads / kRankGroups;
-// Kernel alone, four classes, 512 / 4096 / 8192 groups: one workgroup with the keys in registers 13.7 / 16.5 / 20.1 us, this 4.3 / 6.4 /
-// 9.2; 12000 and 16384: 17.7 and 22.8 against 26 in six launches and the gaps between them. The work grows with the square.
-constexpr int64_t kRankMost = 16384;
+// Four classes, launches one behind the other, 512 / 2048 / 4096 / 8192 groups: one workgroup with the keys in registers 13.2 / 13.8 /
+// 15.0 / 17.6 us, five launches 18.9 / 19.4 / 19.7 / 19.8, this 3.9 / 4.8 / 6.0 / 8.7; 12000: 17 against 20.1 in five, 14336 19.2 / 20.2, 15360
+// 20.5 / 20.4, 16384 21.7 / 20.2, and with a wait behind every call the same line (14336 31 / 33, 15360 32.5 / 33, 16384 33.8 / 32.8).  The work
+// grows with the square.
+constexpr int64_t kRankMost = 15 << 10;
 
 template <bool FROM_SCALE>
 __global__ __launch_bounds__(kRankThreads) void k_select_rank(const float* __restrict__ gmin, const float* __restrict__ gmax,
@@ -693,8 +696,9 @@ __global__ __launch_bounds__(kRankThreads) void k_select_rank(const float* __res
 // groups 21.0 / 22.5 / 24.1 us, 131 K 21.7 / 22.6 / 24.0, 197 K 23.2 / 22.9 / 24.4, 400 K 27.9 / 24.5 / 25.4, 700 K 35.9 / 28.9 / 28.8.
 constexpr int64_t kFewKeys = 5 << 15, kManyKeys = 1 << 19;
 // Rounds of k_select_classify: selection alone, four classes, launches one behind the other, one / two / four rounds: 197 K groups 24.2 / 25.6 /
-// 29.5 us, 1.5 M 35.9 / 37.0 / 41.5, 2 M 39.1 / 37.6 / 44.1, 5.6 M 60.6 / 58.1 / 64.0.  Six launches before: 27.0, 39.2, 40.6, 62.9; all ranges equal
-// 197 K 38.3 -> 29.8, 5.6 M 103.7 -> 71.5.
+// 29.5 us, 1.5 M 35.9 / 37.0 / 41.5, 2 M 39.1 / 37.6 / 44.1, 5.6 M 60.6 / 58.1 / 64.0 (from here on all with 8 and 16 keys to a thread).  Six
+// launches before: 27.0, 39.2, 40.6, 62.9.  One / two rounds with all ranges equal, where every workgroup reads all posts before its own: 1.5 M
+// 36.3 / 36.3, 5.6 M 77 / 72, 20 M 210 / 196.
 constexpr int64_t kClassifyRounds2 = 7 << 18;
 
 }  // namespace
@@ -741,8 +745,8 @@ hipError_t daf_launch_select_bits(const float* gmin, const float* gmax, const ui
                          (uint32_t)prev_uniform, (int)G, ranks, n_thr, packed, out_bits);
     return hipGetLastError();
   }
-  // The widths replace an input, few groups: one launch of one workgroup, 14 to 20 us up to here against 27 for the six;
-  // two and four times as many keys per thread: 32 and 59 us against 27.
+  // The widths replace an input, few groups: one launch of one workgroup, 13.2 us at 512 groups to 17.6 at kSmallGroups, where the five
+  // launches take 18.9 to 20.2; with two and four times as many keys per thread it took 32 and 59.
   if (G <= kSmallGroups && prev_bits != nullptr) {
     hipLaunchKernelGGL(k_select_small, dim3(1), dim3(kSmallThreads), 0, stream, gmin, prev_bits, G, ranks, n_thr, packed,
                        out_bits);

@@ -15,7 +15,7 @@ def env():
     return daf, orc
 
 
-@pytest.mark.parametrize("G", [1, 31, 32, 33, 63, 64, 65, 1023, 1024, 1025, 8191, 8192, 8193, 16351, 16383, 16384, 16385])
+@pytest.mark.parametrize("G", [1, 31, 32, 33, 63, 64, 65, 1023, 1024, 1025, 8191, 8192, 8193, 15359, 15360, 15361, 16351, 16383, 16384, 16385])
 @pytest.mark.parametrize("kind", ["random", "ties", "equal", "sorted"])
 @pytest.mark.parametrize("classes", [(1, 2, 4, 8), (2, 4, 8), (4, 8), (2,)])
 def test_select_bits(env, G, kind, classes):
