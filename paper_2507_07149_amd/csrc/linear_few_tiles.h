@@ -116,7 +116,9 @@ __global__ __launch_bounds__(S::kThreads, 1) void k_linear_few_tiles(
   constexpr int kShare = kGs > kWaveN ? kGs / kWaveN : 1;               // waves (along n) that share a group
   constexpr int kGroups = kGs > kWaveN ? 1 : kWaveN / kGs, kBlocksPerGroup = kNB / kGroups;
   const int64_t m_lane = m0 + wm * kMB * 32 + li, n_lane = n0 + wn * kWaveN + lg * 16;
-  // the lane's groups' widths and offsets first: behind the stores of y a wait for them would be one for those too
+  // The lane's groups' widths and offsets first: behind the stores of y a wait for them would be one for those too.  (Groups of 32 as
+  // well: ahead of the first operands or behind the last is 2 % either way here and the same over ten shapes, 256 x 256 x 512
+  // 6.5 / 6.55 us, 1024 x 1024 x 1024 6.9 / 6.7, 2048 x 1024 x 4096 25.0 / 25.2.)
   [[maybe_unused]] uint32_t group_b[kMB][kGroups], group_off[kMB][kGroups];
   if constexpr (QUANT && MIXED) {
 #pragma unroll

@@ -283,7 +283,7 @@ __device__ __forceinline__ void quantize_pack_units_body(
   wave_lds_sync();
 
   // 5. quantize every chunk of the tile and drop its bits at their place in the staged run
-  //    (EXACT2: 0 and 1 as quantize_chunk's, 2: by need_exact2, chunk by chunk.  ONE: the tile is one group, whose entry is read
+  //    (EXACT2: 0 and 1 as quantize_raw_chunk's, 2: by need_exact2, chunk by chunk.  ONE: the tile is one group, whose entry is read
   //    once and whose width is a scalar: no search for a chunk's group, one store a chunk.)
   auto quantize_tile = [&](auto exact2, auto one) {
     constexpr int kExact2 = decltype(exact2)::value;

@@ -58,8 +58,8 @@ def test_update_then_quantize_without_sync(dtype, gs, n):
 
 @pytest.mark.parametrize("G", [8191, 8192, 8193, 4096 * 2048, 4096 * 2048 + 1])
 def test_offsets_at_the_limits_of_the_scan_forms(G):
-    """One launch up to 8192 groups; two up to 4096 blocks of 2048 groups; three above.  The last group is
-    short, an invalid width sits in the last block."""
+    """A new plan: one workgroup up to 8192 groups, one launch up to 65536, two up to 4096 blocks of 2048 groups, three above; an
+    update: one launch.  The last group is short, an invalid width sits in the last block."""
     gs, n = 32, 32 * G - 7
     rng = np.random.default_rng(G)
     bits = rng.choice([1, 2, 4, 8], G).astype(np.uint8)
