@@ -142,6 +142,14 @@ def test_many_tiles_full_parity(H, dtype, gs, bits, n_tiles):
     H.assert_full_parity(w, H.run_hip(w))
 
 
+@pytest.mark.timeout(400)
+@pytest.mark.parametrize("gs,bits,n", [(64, 2, 4096 * (5 << 12)), (128, "mixed", 4096 * ((5 << 12) + 1) + 77), (4096, 1, 4096 * ((5 << 12) + 1))])
+def test_binary16_launches_either_side_of_the_limit_for_four_waves(H, gs, bits, n):
+    w = _workload(F16, n, gs, bits, seed=78, rng_seed=gs)
+    print("case", w.name, flush=True)
+    H.assert_full_parity(w, H.run_hip(w))
+
+
 @pytest.mark.parametrize("dtype", [F32, F16, BF16])
 @pytest.mark.parametrize("bits", [1, 2, 8, "mixed"])
 @pytest.mark.parametrize("n,gs", [(4096 * 9 + 77, 8192), (4096 * 12, 4096 * 4), (4096 * 7 + 4095, 4096 * 3),
