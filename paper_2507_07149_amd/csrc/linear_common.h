@@ -123,6 +123,21 @@ __device__ __forceinline__ LinearGroup linear_group(const GroupScale& gs, uint32
   return g;
 }
 
+// Widths and offsets of GROUPS (1, 2 or 4) consecutive groups of a row, the first one's number a multiple of GROUPS, from the plan's own
+// copies, which begin at multiples of 16 bytes.
+template <int GROUPS>
+struct RowGroups {
+  struct alignas(GROUPS) { uint8_t of[GROUPS]; } b;
+  struct alignas(4 * GROUPS) { uint32_t of[GROUPS]; } off;
+};
+template <int GROUPS>
+__device__ __forceinline__ RowGroups<GROUPS> row_groups(const uint8_t* __restrict__ bits, const uint32_t* __restrict__ off, int64_t g) {
+  RowGroups<GROUPS> r;
+  r.b = *reinterpret_cast<const decltype(r.b)*>(bits + g);
+  r.off = *reinterpret_cast<const decltype(r.off)*>(off + g);
+  return r;
+}
+
 // Quantizes and packs the lane's 16 elements; `e0` is the first one's place in the group, `flat` in the tensor.
 __device__ __forceinline__ void quantize_row(const float (&xf)[16], const LinearGroup& g, uint32_t e0, int64_t flat,
                                              uint32_t seed_lo, uint32_t seed_hi, int lg) {

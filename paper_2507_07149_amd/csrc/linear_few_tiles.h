@@ -116,17 +116,13 @@ __global__ __launch_bounds__(S::kThreads, 1) void k_linear_few_tiles(
   constexpr int kShare = kGs > kWaveN ? kGs / kWaveN : 1;               // waves (along n) that share a group
   constexpr int kGroups = kGs > kWaveN ? 1 : kWaveN / kGs, kBlocksPerGroup = kNB / kGroups;
   const int64_t m_lane = m0 + wm * kMB * 32 + li, n_lane = n0 + wn * kWaveN + lg * 16;
-  // The lane's groups' widths and offsets first: behind the stores of y a wait for them would be one for those too.  (Groups of 32 as
-  // well: ahead of the first operands or behind the last is 2 % either way here and the same over ten shapes, 256 x 256 x 512
-  // 6.5 / 6.55 us, 1024 x 1024 x 1024 6.9 / 6.7, 2048 x 1024 x 4096 25.0 / 25.2.)
-  [[maybe_unused]] uint32_t group_b[kMB][kGroups], group_off[kMB][kGroups];
+  // The lane's groups' widths and offsets first, one load each for those of a row: behind the stores of y a wait for them would be one
+  // for those too.  (Groups of 32, bfloat16, one load a group / a row: 2048 x 1024 x 4096 27.9 / 26.1 us, 1792 x 4096 x 1344 31.0 / 29.9; group by
+  // group where they are used 26.7 and 31.0.)
+  [[maybe_unused]] RowGroups<kGroups> row[kMB];
   if constexpr (QUANT && MIXED) {
 #pragma unroll
-    for (int i = 0; i < kMB * kGroups; ++i) {
-      const int64_t g = ((m_lane + i / kGroups * 32) * N + n0 + wn * kWaveN + i % kGroups * kGs) >> GS_LOG2;
-      group_b[i / kGroups][i % kGroups] = bits[g];
-      group_off[i / kGroups][i % kGroups] = off[g];
-    }
+    for (int i = 0; i < kMB; ++i) row[i] = row_groups<kGroups>(bits, off, ((m_lane + i * 32) * N + n0 + wn * kWaveN) >> GS_LOG2);
   }
 
 #pragma unroll
@@ -218,8 +214,8 @@ __global__ __launch_bounds__(S::kThreads, 1) void k_linear_few_tiles(
 #pragma unroll
     for (int gi = 0; gi < kGroups; ++gi) {
       const int64_t g = (m * N + n0 + wn * kWaveN + gi * kGs) >> GS_LOG2;
-      const uint32_t gb = MIXED ? group_b[mb][gi] : uniform_b;
-      const uint32_t woff = MIXED ? group_off[mb][gi] : (uint32_t)(g * (int64_t)((kGs * uniform_b) >> 5));
+      const uint32_t gb = MIXED ? (uint32_t)row[mb].b.of[gi] : uniform_b;
+      const uint32_t woff = MIXED ? row[mb].off.of[gi] : (uint32_t)(g * (int64_t)((kGs * uniform_b) >> 5));
       const GroupScale gs = group_scale(gmn[mb][gi], gmx[mb][gi], gb);
       if (lg == 0 && wn % kShare == 0) {
         out_min[g] = gs.mn;

@@ -133,22 +133,6 @@ __global__ __launch_bounds__(kLinThreads, 2) void k_linear_quantize_pack(
     return *reinterpret_cast<const u32x4*>(pb[ks] + parity * kOperandBytes + mb * 32 * kRowBytes);
   };
 
-  // Widths and offsets of this lane's groups, on their way before the stores of y: behind those every wait for one of them was
-  // a wait for the stores as well (loads and stores are counted together, in order), four times a tile.  Groups of 32 have
-  // sixteen of them, which in front of the first operands cost more than behind the last (16384 x 4096 x 1024 179.4 -> 182.4 us).
-  // 8192 x 4096 x 512, groups of 128, {2,4,8}: 59.7 -> 58.1 us; 2048 x 1024 x 512, groups of 64: 7.63 -> 7.49.
-  constexpr int kGs = 1 << GS_LOG2, kBlocksPerGroup = kGs / 32, kGroups = 4 / kBlocksPerGroup;
-  [[maybe_unused]] uint32_t group_b[2][kGroups], group_off[2][kGroups];
-  auto load_groups = [&] {
-#pragma unroll
-    for (int i = 0; i < 2 * kGroups; ++i) {
-      const int64_t g = ((m0 + wm * 64 + i / kGroups * 32 + li) * N + n0 + wn * 128 + i % kGroups * kGs) >> GS_LOG2;
-      group_b[i / kGroups][i % kGroups] = bits[g];
-      group_off[i / kGroups][i % kGroups] = off[g];
-    }
-  };
-  if constexpr (QUANT && MIXED && kGs > 32) load_groups();
-
   u32x4 a[2][4], b[2][2][4];                 // a[nb % 2][ks], b[step % 2][mb][ks]
   fetch_x(0, 0, 0); fetch_x(0, 1, 0); fetch_x(1, 0, 0); fetch_x(1, 1, 0); fetch_w(0, 0);
   fetch_w(1, 0); fetch_w(2, 0); fetch_x(0, 0, 1); fetch_x(0, 1, 1);
@@ -213,8 +197,18 @@ __global__ __launch_bounds__(kLinThreads, 2) void k_linear_quantize_pack(
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
   // ---- epilogue, by blocks of 32 x 32 (linear_common.h) ----
-  if constexpr (QUANT && MIXED && kGs == 32) {
-    load_groups();
+  // Widths and offsets of the lane's groups, one load each for those of a row, behind the last operands and before the stores of y: after
+  // those every wait for one of them was a wait for the stores as well (loads and stores are counted together, in order), four
+  // times a tile; in front of the first operands they hold those up.  bfloat16, {2,4,8}, group by group where they are used / one load a row in
+  // front of the first operands / here: groups of 32 8960 x 1024 x 512 25.3 / 23.3 / 23.4 us, 8192 x 4096 x 512 62.1 / 61.3 / 60.4, 32768 x 2048 x 512
+  // 116.7 / 114.0 / 113.0; of 64 8192 x 4096 x 512 56.4 / 55.4 / 55.2, 32768 x 768 x 3072 142 / 138 / 139; of 128 8192 x 4096 x 512
+  // 52.9 / 53.7 / 53.1, 8192 x 11008 x 256 115.1 / 115.2 / 113.0.
+  constexpr int kGs = 1 << GS_LOG2, kBlocksPerGroup = kGs / 32, kGroups = 4 / kBlocksPerGroup;
+  [[maybe_unused]] RowGroups<kGroups> row[2];
+  if constexpr (QUANT && MIXED) {
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+      row[mb] = row_groups<kGroups>(bits, off, ((m0 + wm * 64 + mb * 32 + li) * N + n0 + wn * 128) >> GS_LOG2);
     asm volatile("" ::: "memory");
   }
 #pragma unroll
@@ -244,8 +238,8 @@ __global__ __launch_bounds__(kLinThreads, 2) void k_linear_quantize_pack(
       mn = both_halves_min(mn);
       mx = both_halves_max(mx);
       const int64_t g = (m * N + n0 + wn * 128 + gi * kGs) >> GS_LOG2;
-      const uint32_t b = MIXED ? group_b[mb][gi] : uniform_b;
-      const uint32_t woff = MIXED ? group_off[mb][gi] : (uint32_t)(g * (int64_t)((kGs * uniform_b) >> 5));
+      const uint32_t b = MIXED ? (uint32_t)row[mb].b.of[gi] : uniform_b;
+      const uint32_t woff = MIXED ? row[mb].off.of[gi] : (uint32_t)(g * (int64_t)((kGs * uniform_b) >> 5));
       const GroupScale gs = group_scale(mn, mx, b);
       if (lg == 0) {
         out_min[g] = gs.mn;
