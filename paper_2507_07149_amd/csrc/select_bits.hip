@@ -611,10 +611,11 @@ __global__ __launch_bounds__(kSmallThreads) void k_select_small(const float* sca
 constexpr int kRankThreads = 1024;
 constexpr int kRankGroups = 32, kRankParts = kRankThreads / kRankGroups;
 // Four classes, launches one behind the other, 512 / 2048 / 4096 / 8192 groups: one workgroup with the keys in registers 13.2 / 13.8 /
-// 15.0 / 17.6 us, five launches 18.9 / 19.4 / 19.7 / 19.8, this 3.9 / 4.8 / 6.0 / 8.7; 12000: 17 against 20.1 in five, 14336 19.2 / 20.2, 15360
-// 20.5 / 20.4, 16384 21.7 / 20.2, and with a wait behind every call the same line (14336 31 / 33, 15360 32.5 / 33, 16384 33.8 / 32.8).  The work
-// grows with the square.
-constexpr int64_t kRankMost = 15 << 10;
+// 15.0 / 17.6 us, five launches 18.9 / 19.4 / 19.7 / 19.8, this 3.9 / 4.8 / 6.0 / 8.7; 12000: 17 against 20.1 in five.  The work grows with the
+// square, and the keys fill the LDS at 16384 groups; there, five / this: random ranges, four / three / two classes 22.3 / 21.7, 20.2 / 20.8,
+// 18.1 / 20.8, maxima of a gelu's groups 23.7 / 21.6, 21.1 / 20.8, 19.3 / 20.8, all equal 23.9 / 21.2, 21.9 / 20.8, 19.7 / 20.8; another card, random, four
+// classes 20.2 / 21.7.
+constexpr int64_t kRankMost = 16 << 10;
 
 template <bool FROM_SCALE>
 __global__ __launch_bounds__(kRankThreads) void k_select_rank(const float* __restrict__ gmin, const float* __restrict__ gmax,
