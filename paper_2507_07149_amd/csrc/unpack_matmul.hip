@@ -726,15 +726,16 @@ double call_microseconds(const Schedule& sc, int64_t M, int es) {
 // Taken where the model has it ahead by more than it is wrong by between these two tiles.  240 shapes of other draws than those it
 // was fitted to, on which it has the narrow tile ahead at all; time by the model, narrow over wider tile -> measured gain, mean (smallest):
 // below 0.80 1.32 (1.19), to 0.85 1.21 (1.13), to 0.90 1.17 (1.07), to 0.96 1.09 (0.99), to 1 1.02 (0.84); where the wider one is the
-// 512 x 128 tile 0.85 to 0.90 1.09 (1.05), to 0.96 1.01 (0.90), to 1 0.91 (0.75): hence the two limits.  The rule takes 190 of the 838
-// shapes drawn, 32 to 32768 values of m, and they gain 1.23 in the mean, 0.99 to 1.54.  896 x 512 x 8064 bfloat16 26.7 -> 19.7 us,
+// 512 x 128 tile 0.85 to 0.90 1.09 (1.05), to 0.96 1.01 (0.90), to 1 0.91 (0.75): hence the two limits.  Of another 372 shapes,
+// from 0.90 to 0.96, 16 bits gain 1.11 (1.00), binary32 0.99 (0.96): hence the lower limit for it.  With the higher one for both the rule takes
+// 190 of 838 shapes drawn, 32 to 32768 values of m, and they gain 1.23 in the mean, 0.99 to 1.54.  896 x 512 x 8064 bfloat16 26.7 -> 19.7 us,
 // 672 x 320 x 5376 binary16 19.4 -> 14.6, 992 x 128 x 1280 binary32 28.9 -> 21.2; few steps: 64 x 512 x 256 bfloat16 6.8 -> 5.2,
 // 512 x 1024 x 1024 binary16 19.1 -> 17.7, 96 x 192 x 8064 binary32 19.7 -> 13.7.
 Schedule schedule(int64_t M, int64_t N, int64_t K, int es) {
   const Schedule wider = schedule_wider(M, N, K, es);
   const int64_t tiles = (N + kBN - 1) / kBN * (K / 64), steps = M / kStepM;
   if (N < 128 || tiles > 768 || wider.bk == 64) return wider;
-  const double limit = call_microseconds(wider, M, es) * (wider.bn == Wide::kBN ? 0.90 : 0.96);
+  const double limit = call_microseconds(wider, M, es) * (wider.bn == Wide::kBN || es == 4 ? 0.90 : 0.96);
   const int64_t room = daf_unpack_matmul_workspace_size(M, N, K);
   Schedule best = wider, sc = wider;
   sc.bn = kBN;

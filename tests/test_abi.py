@@ -151,7 +151,9 @@ def test_calls_with_another_number_of_looks_check_their_arguments_too(lib):
     (512, 1088, 11008, 2, (256, 128)),
     # one tile of n: never; enough of them for the wider general tile
     (4096, 256, 4096, 2, (256, 128)), (2048, 256, 65536, 1, (256, 256)), (4096, 128, 65536, 2, (256, 256)),
-    (4096, 4096, 4096, 0, (256, 256)), (256, 256, 192, 2, (256, 64)), (512, 1024, 1024, 1, (256, 64))])
+    (4096, 4096, 4096, 0, (256, 256)), (256, 256, 192, 2, (256, 64)), (512, 1024, 1024, 1, (256, 64)),
+    # the narrow tile 8 to 10 % ahead by the model, which is too little in binary32
+    (1920, 256, 1152, 0, (256, 128)), (1280, 192, 1920, 0, (256, 128)), (3008, 576, 384, 2, (256, 64))])
 def test_weight_gradient_tile(lib, m, n, k, dtype, tile):
     import paper_2507_07149_amd as daf
     import torch
