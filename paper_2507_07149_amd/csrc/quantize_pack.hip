@@ -381,7 +381,8 @@ hipError_t launch_batch_bits(const Batch& batch, int32_t uniform_bits, hipStream
   do {                                                                                                                    \
     auto kernel = any_short ? k_quantize_pack_tile_batch<DT, LPG_LOG2, BITS, true>                                        \
                             : k_quantize_pack_tile_batch<DT, LPG_LOG2, BITS, false>;                                      \
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), (tile_extra_lds<DT, LPG_LOG2>(tiles)), stream, batch);       \
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), (BITS > 1 ? tile_extra_lds<DT, LPG_LOG2>(tiles) : 0u),       \
+                       stream, batch);                                                                                    \
   } while (0)
   switch (uniform_bits) {
     case 0: DAF_LAUNCH(0); break;

@@ -712,12 +712,14 @@ constexpr int tile_max_waves() {
 // binary16 tiles are bound by HBM, and more waves than four scatter their streams, the more so the fewer instructions a wave has (2 bits
 // took 2 to 6 % longer than before the codes became bytes).  Shorter ones want the waves.  Six / four, quantize alone: 25 M elements, groups of
 // 128, four widths 14.0 / 15.1 us, 50 M 23.9 / 24.5, 72 M 32.2 / 32.6, 100 M 44.0 / 43.7, 2 bits 40.9 / 39.6; 200 M, groups of 1024, 2 bits 77.8 /
-// 71.8, four widths 84.4 / 79.9; lists of 400 M elements, groups of 128, 2 bits 159 / 152, four widths 175 / 169.  (Groups of 32 and the sums of
-// metrics are bound by their instructions; the other formats' registers leave no more than six and four waves.)
-constexpr int64_t kManyTiles = 5 << 12;                    // 84 M elements
-template <int DT, int LPG_LOG2, bool METRICS = false>
+// 71.8, four widths 84.4 / 79.9; lists of 400 M elements, 2 bits, groups of 64 to 4096 2 to 8 % faster, 4 and 8
+// bits the same; not those of 1 bit or several widths, from 5 % faster to 4 % slower by group size.  (Groups of 32 and the sums of
+// metrics are bound by their instructions; with relu's output stored as well the same within 1 %, four widths in groups of 64 2 % slower: 119 M 103.1 /
+// 105.7; the other formats' registers leave no more than six and four waves.)
+constexpr int64_t kManyTiles = 6 << 12;                    // 101 M elements
+template <int DT, int LPG_LOG2, bool METRICS = false, bool RELU = false>
 unsigned tile_extra_lds(int64_t tiles) {
-  if constexpr (DT == kF16 && LPG_LOG2 > 2 && !METRICS) {
+  if constexpr (DT == kF16 && LPG_LOG2 > 2 && !METRICS && !RELU) {
     constexpr unsigned kExtra = 12u << 10, kAll = kWavesPerBlock * sizeof(WaveLds<DT, LPG_LOG2, tile_div<DT, LPG_LOG2>()>) + kExtra;
     static_assert(4u * kAll <= (160u << 10) && 5u * kAll > (160u << 10), "four workgroups on a compute unit");
     return tiles > kManyTiles ? kExtra : 0u;
@@ -827,7 +829,7 @@ hipError_t launch_tile(const daf_plan_t* p, const void* x, int64_t n_tiles, uint
   do {                                                                                                     \
     auto kernel = k_quantize_pack_tile<DT, LPG_LOG2, BITS, false, METRICS, RELU, tile_div<DT, LPG_LOG2>()>; \
     const unsigned blocks = (unsigned)((n_tiles + kWavesPerBlock - 1) / kWavesPerBlock) + (short_len > 0);   \
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), (tile_extra_lds<DT, LPG_LOG2, METRICS>(n_tiles)),  \
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), (tile_extra_lds<DT, LPG_LOG2, METRICS, RELU>(n_tiles)), \
                        stream, static_cast<const u32x4*>(x), n_tiles, p->d_bits, p->d_off, seed_lo, seed_hi,  \
                        out_words, out_min, out_scale,                                                      \
                        nullptr, (int64_t)1, out_metrics, static_cast<u32x4*>(out_y), short_len);           \
