@@ -376,37 +376,62 @@ __device__ __forceinline__ int batch_entry_of(const uint32_t (&ends)[kBatchSlots
 }
 
 // Philox4x32-10 (Salmon et al., SC'11): ten rounds of two 32x32->64 multiplies and two
-// three-way xors; the key advances by the Weyl constants between rounds.
-__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+// three-way xors; the key advances by the Weyl constants between rounds.  The key is the same in all lanes and stays in
+// scalar registers: as vector operands the twenty round keys took a move and a register each.
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t key) {
   uint32_t r;
-  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x96" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x96" : "=v"(r) : "v"(a), "v"(b), "s"(key));
   return r;
 }
-__device__ __forceinline__ uint32_t not_xor3(uint32_t a, uint32_t b, uint32_t c) {
+__device__ __forceinline__ uint32_t not_xor3(uint32_t a, uint32_t b, uint32_t key) {
   uint32_t r;
-  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x69" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x69" : "=v"(r) : "v"(a), "v"(b), "s"(key));
   return r;
 }
 
-// The 16 random bytes of Philox block `blk` under `seed`: byte s serves element 16*blk + s.  COMPLEMENT: every bit inverted, as the
-// element map wants them (code_bytes).  (Round keys in scalar registers and the first rounds' products with the counter's
-// zeros left out took 0.994 to 1.007 of the time over sixteen cases of all formats and routes: not worth their code.)
+// The 16 random bytes of Philox block hi : lo under the seed: byte s serves element 16 * block + s.  The counter's upper half
+// is 0, so the first round has one product instead of two, and where `hi` is the same in all lanes the second round's product
+// of it, and what the third takes from that, are scalar.  COMPLEMENT: every bit inverted, as the element map
+// wants them (code_bytes).
 template <bool COMPLEMENT = false>
-__device__ __forceinline__ uint4 philox_block(uint64_t blk, uint32_t seed_lo, uint32_t seed_hi) {
-  uint32_t c0 = (uint32_t)blk, c1 = (uint32_t)(blk >> 32), c2 = 0u, c3 = 0u, k0 = seed_lo, k1 = seed_hi;
+__device__ __forceinline__ uint4 philox_block(uint32_t lo, uint32_t hi, uint32_t seed_lo, uint32_t seed_hi) {
+  constexpr uint32_t kMul0 = 0xD2511F53u, kMul1 = 0xCD9E8D57u, kWeyl0 = 0x9E3779B9u, kWeyl1 = 0xBB67AE85u;
+  uint32_t k0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)seed_lo), k1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)seed_hi);
+  uint64_t p0 = (uint64_t)kMul0 * lo, p1;
+  uint32_t c0 = hi ^ k0, c1, c2 = (uint32_t)(p0 >> 32) ^ k1, c3 = (uint32_t)p0;
+  k0 += kWeyl0;
+  k1 += kWeyl1;
+  p0 = (uint64_t)kMul0 * c0;
+  p1 = (uint64_t)kMul1 * c2;
+  c0 = (uint32_t)(p1 >> 32) ^ k0;
+  c2 = ((uint32_t)(p0 >> 32) ^ k1) ^ c3;
+  c1 = (uint32_t)p1;
+  c3 = (uint32_t)p0;
+  k0 += kWeyl0;
+  k1 += kWeyl1;
+  p0 = (uint64_t)kMul0 * c0;
+  p1 = (uint64_t)kMul1 * c2;
+  c0 = xor3((uint32_t)(p1 >> 32), c1, k0);
+  c2 = (uint32_t)(p0 >> 32) ^ (c3 ^ k1);
+  c1 = (uint32_t)p1;
+  c3 = (uint32_t)p0;
 #pragma unroll
-  for (int round = 0; round < 10; ++round) {
-    const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
-    const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
+  for (int round = 3; round < 10; ++round) {
+    k0 += kWeyl0;
+    k1 += kWeyl1;
+    p0 = (uint64_t)kMul0 * c0;
+    p1 = (uint64_t)kMul1 * c2;
     const bool invert = COMPLEMENT && round == 9;
     c0 = invert ? not_xor3((uint32_t)(p1 >> 32), c1, k0) : xor3((uint32_t)(p1 >> 32), c1, k0);
     c2 = invert ? not_xor3((uint32_t)(p0 >> 32), c3, k1) : xor3((uint32_t)(p0 >> 32), c3, k1);
     c1 = (uint32_t)p1;
     c3 = (uint32_t)p0;
-    k0 += 0x9E3779B9u;
-    k1 += 0xBB67AE85u;
   }
   return COMPLEMENT ? make_uint4(c0, ~c1, c2, ~c3) : make_uint4(c0, c1, c2, c3);
+}
+template <bool COMPLEMENT = false>
+__device__ __forceinline__ uint4 philox_block(uint64_t blk, uint32_t seed_lo, uint32_t seed_hi) {
+  return philox_block<COMPLEMENT>((uint32_t)blk, (uint32_t)(blk >> 32), seed_lo, seed_hi);
 }
 
 // floor(x + 1/2) as a signed integer in one instruction (round to nearest, ties upward).

@@ -484,11 +484,13 @@ __device__ __forceinline__ void quantize_pack_tile_body(
 
     // 2. random bytes of the tile, complemented (independent of the data; overlaps the loads' latency)
     {
-      const uint64_t blk0 = (uint64_t)tile * (S::kElems / kElemsPerPhilox);
+      constexpr int kBlocks = S::kElems / kElemsPerPhilox;
+      static_assert((kBlocks & (kBlocks - 1)) == 0, "a tile's block numbers agree in their upper halves");
+      const uint64_t blk0 = (uint64_t)tile * kBlocks;
       uint4* dst = reinterpret_cast<uint4*>(lds.rand_bytes);
 #pragma unroll
       for (int m = 0; m < S::kPhilox; ++m)
-        dst[m * kWave + lane] = philox_block<true>(blk0 + (uint64_t)(m * kWave + lane), seed_lo, seed_hi);
+        dst[m * kWave + lane] = philox_block<true>((uint32_t)blk0 + (uint32_t)(m * kWave + lane), (uint32_t)(blk0 >> 32), seed_lo, seed_hi);
     }
 
     // 3. per-group min/max: in-lane over the chunk, then across the group's lanes.
