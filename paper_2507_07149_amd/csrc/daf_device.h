@@ -392,7 +392,8 @@ __device__ __forceinline__ uint32_t not_xor3(uint32_t a, uint32_t b, uint32_t ke
 // The 16 random bytes of Philox block hi : lo under the seed: byte s serves element 16 * block + s.  The counter's upper half
 // is 0, so the first round has one product instead of two, and where `hi` is the same in all lanes the second round's product
 // of it, and what the third takes from that, are scalar.  COMPLEMENT: every bit inverted, as the element map
-// wants them (code_bytes).
+// wants them (code_bytes).  By themselves scalar keys and the short first rounds are worth 1 to 2 % of quantize with metrics (25 M elements, groups
+// of 256, 2 bits, binary16 19.2 -> 18.8 us, bfloat16 18.3 -> 18.0; over 96 such forms 1.3 %) and nothing elsewhere.
 template <bool COMPLEMENT = false>
 __device__ __forceinline__ uint4 philox_block(uint32_t lo, uint32_t hi, uint32_t seed_lo, uint32_t seed_hi) {
   constexpr uint32_t kMul0 = 0xD2511F53u, kMul1 = 0xCD9E8D57u, kWeyl0 = 0x9E3779B9u, kWeyl1 = 0xBB67AE85u;
