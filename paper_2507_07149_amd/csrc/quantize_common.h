@@ -60,7 +60,7 @@ __device__ __forceinline__ int neg_code(float x, float mn, float invs, uint32_t 
 // code = -((t + r) >> 8) = (r' - t) >> 8, which is byte 1 of the 16-bit value r' - t (t >= -255 * 256): two such values go to
 // the halves of one register by the instruction that subtracts them anyway, and a byte permutation brings four codes
 // together.  Shifting each out and into an accumulator took two instructions per element.  With the bytes packed by dot products
-// and stored without branches (store_by_width) a binary16 tile of 4096 elements with four widths takes 807 vector instructions
+// and stored without branches (store_by_width) a binary16 tile of 4096 elements with four widths takes 784 vector instructions
 // a wave instead of 956: 25 M elements both directions 27.0 -> 26.0 us, rows of 768 and 3072 73.2 -> 70.4, 361 M
 // bfloat16 elements with metrics, selection and plan 280.5 -> 268.9.  (A register that
 // an instruction has written in part is read two instructions later at the earliest: one wait state.)
