@@ -242,9 +242,9 @@ def test_list_left_over_chunks(env, dtype, bits, gs):
 @pytest.mark.timeout(400)
 @pytest.mark.parametrize("gs,bits", [(64, "mixed"), (256, 2)])
 def test_binary16_list_above_the_limit_for_four_waves(env, gs, bits):
-    """Two tensors of 5 << 11 tiles, one of them with a short one behind, and a third."""
+    """Two tensors of 6 << 11 tiles, one of them with a short one behind, and a third."""
     daf, orc = env
-    _roundtrip(daf, orc, F16, [(4096 * (5 << 11), gs, bits), (4096 * (5 << 11) + 2 * gs + 9, gs, bits), (4096 * 3, gs, bits)])
+    _roundtrip(daf, orc, F16, [(4096 * (6 << 11), gs, bits), (4096 * (6 << 11) + 2 * gs + 9, gs, bits), (4096 * 3, gs, bits)])
 
 
 def test_list_of_more_tensors_than_a_launch_takes(env):

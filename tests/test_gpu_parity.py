@@ -143,7 +143,7 @@ def test_many_tiles_full_parity(H, dtype, gs, bits, n_tiles):
 
 
 @pytest.mark.timeout(400)
-@pytest.mark.parametrize("gs,bits,n", [(64, 2, 4096 * (5 << 12)), (128, "mixed", 4096 * ((5 << 12) + 1) + 77), (4096, 1, 4096 * ((5 << 12) + 1))])
+@pytest.mark.parametrize("gs,bits,n", [(64, 2, 4096 * (6 << 12)), (128, "mixed", 4096 * ((6 << 12) + 1) + 77), (4096, 1, 4096 * ((6 << 12) + 1))])
 def test_binary16_launches_either_side_of_the_limit_for_four_waves(H, gs, bits, n):
     w = _workload(F16, n, gs, bits, seed=78, rng_seed=gs)
     print("case", w.name, flush=True)
